@@ -323,3 +323,225 @@ def tolerance(case):
     if case.get("dtype") == "f16":
         return {"rel": 1.2e-3, "max": 0.02}
     return {"rel": 1e-2, "max": 0.25}
+
+
+# --------------------------------------------------------------------------- the same in 64 bits
+
+
+def spread(v):
+    """Bits of v moved to every third place (the Z-order code of one axis)."""
+    r = torch.zeros_like(v)
+    for b in range(21):
+        r |= ((v >> b) & 1) << (3 * b)
+    return r
+
+
+def zorder(v):
+    return spread(v[..., 0]) | (spread(v[..., 1]) << 1) | (spread(v[..., 2]) << 2)
+
+
+def voxels(xyz, voxel):
+    """Voxel coordinates relative to the minimum over the last but one axis; subtraction and product in 32 bits."""
+    inv = torch.tensor(float(np.float32(1.0) / np.float32(voxel)), dtype=torch.float32, device=xyz.device)
+    return ((xyz - xyz.amin(dim=-2, keepdim=True)) * inv).floor().clamp(0, (1 << 21) - 1).to(torch.int64)
+
+
+def ranks(key):
+    """For every element of the last axis: how many earlier ones have the same key."""
+    order = key.argsort(dim=-1, stable=True)
+    s = key.gather(-1, order)
+    i = torch.arange(key.shape[-1], device=key.device).expand_as(s)
+    new = torch.ones_like(s, dtype=torch.bool)
+    new[..., 1:] = s[..., 1:] != s[..., :-1]
+    start = torch.where(new, i, torch.zeros_like(i)).cummax(dim=-1).values
+    return torch.empty_like(i).scatter_(-1, order, i - start)
+
+
+def scan_rows(xyz, voxel, size):
+    """Bucket-major row of every point of one scan: the direct Z-order hash, six axis probes, then the slots left over;
+    points are served in input order inside every step."""
+    n, dev = xyz.shape[0], xyz.device
+    k = -(-n // size)
+    v = voxels(xyz, voxel)
+    vmax = v.amax(dim=0)
+    div = int(zorder(vmax)) // k + 1
+    step = 1 << ((div.bit_length() + 2) // 3)
+    free = torch.full((k,), size, device=dev, dtype=torch.int64)
+    free[k - 1] = n - (k - 1) * size
+    used = torch.zeros_like(free)
+    row = torch.full((n,), -1, device=dev, dtype=torch.int64)
+    left = torch.arange(n, device=dev)
+    moves = [(0, 0, 0), (1, 0, 0), (-1, 0, 0), (0, 1, 0), (0, -1, 0), (0, 0, 1), (0, 0, -1)]
+    for move in moves:
+        w = v[left] + step * torch.tensor(move, device=dev)
+        h = (zorder(torch.minimum(w.clamp(min=0), vmax)) // div).clamp(max=k - 1)
+        rank = ranks(h)
+        ok = rank < free[h]
+        row[left[ok]] = h[ok] * size + used[h[ok]] + rank[ok]
+        got = torch.bincount(h[ok], minlength=k)
+        used, free, left = used + got, free - got, left[~ok]
+    slot = torch.arange(k * size, device=dev).reshape(k, size)
+    open_ = (slot - (torch.arange(k, device=dev) * size)[:, None] >= used[:, None]) & (slot < n)
+    row[left] = slot[open_]
+    return row
+
+
+def exact_perm(case, coords):
+    """perm: the input row of every bucket-major row."""
+    perm, at = torch.empty(case["points"], dtype=torch.int64, device=coords.device), 0
+    for n in scan_sizes(case):
+        perm[at + scan_rows(coords[at:at + n], case["voxel"], case["scope"] // SCOPE_BUCKETS)] = at + torch.arange(n, device=coords.device)
+        at += n
+    return perm
+
+
+def scope_rows(case, mode, device):
+    """The bucket-major rows of every scope, scopes of one size together: tensors [scopes, rows]."""
+    s, m, at, by_len = case["scope"] // SCOPE_BUCKETS, SCOPE_BUCKETS, 0, {}
+    for n in scan_sizes(case):
+        groups = {}
+        for j in range(-(-n // s)):
+            g = (j + m - 2) // m if mode == "shift" else (j // (2 * m)) * 2 + j % 2 if mode == "stride" else j // m
+            groups.setdefault(g, []).append(j)
+        for g in groups.values():
+            r = np.concatenate([np.arange(at + j * s, at + min((j + 1) * s, n)) for j in g])
+            by_len.setdefault(len(r), []).append(r)
+        at += n
+    return [torch.from_numpy(np.stack(v)).to(device) for v in by_len.values()]
+
+
+def exact_attention(case, mode, q, k, v, dout=None):
+    """Bucket-major rows in 64 bits in, output and log-sum-exp out, and the three gradients with dout."""
+    h, d = case["heads"], case["head_dim"]
+    n = q.shape[0]
+    res = [torch.empty(n, h * d, dtype=torch.float64, device=q.device), torch.empty(n, h, dtype=torch.float64, device=q.device)]
+    res += [torch.empty_like(q) for _ in range(3)] if dout is not None else []
+    scale = d ** -0.5
+    for rows in scope_rows(case, mode, q.device):
+        length = rows.shape[1]
+        for r in rows.split(max(1, (1 << 27) // (length * length * h))):
+            def heads(x):
+                return x[r].reshape(r.shape[0], length, h, d).transpose(1, 2).reshape(-1, length, d).contiguous()
+
+            def put(to, x):
+                to[r] = x.reshape(r.shape[0], h, length, -1).transpose(1, 2).reshape(r.shape[0], length, -1)
+
+            a, b, c = heads(q), heads(k), heads(v)
+            p = torch.bmm(a, b.transpose(1, 2).contiguous()) * scale
+            lse = p.logsumexp(dim=2, keepdim=True)
+            p = (p - lse).exp_()
+            o = torch.bmm(p, c)
+            put(res[0], o)
+            put(res[1], lse)
+            if dout is not None:
+                g = heads(dout)
+                put(res[4], torch.bmm(p.transpose(1, 2).contiguous(), g))
+                ds = p * (torch.bmm(g, c.transpose(1, 2).contiguous()) - (g * o).sum(dim=2, keepdim=True))
+                put(res[2], torch.bmm(ds, b) * scale)
+                put(res[3], torch.bmm(ds.transpose(1, 2).contiguous(), a) * scale)
+    return res
+
+
+def tile_subs(xyz, voxel, rho):
+    """Sub-bucket of every point of tiles [t, n, 3] of n points each: hashed ones, then new ones, then the nearest with room."""
+    t, n, dev = xyz.shape[0], xyz.shape[1], xyz.device
+    m = -(-n // rho)
+    v = voxels(xyz, voxel)
+    h = (zorder(v) // (zorder(v.amax(dim=1)) // m + 1)[:, None]).clamp(max=m - 1)
+    rank = ranks(h)
+    order = (rank == 0).cumsum(dim=1)                       # ids by first point
+    of_hash = torch.zeros(t, m, dtype=torch.int64, device=dev).scatter_add_(1, h, torch.where(rank == 0, order - 1, 0))
+    sub = torch.where(rank < rho, of_hash.gather(1, h), -1)
+    count = order[:, -1:]
+    late = sub < 0
+    opened = count + late.cumsum(dim=1) - 1
+    own = late & (opened < m)
+    sub = torch.where(own, opened, sub)
+    starts = own | (rank == 0)
+    at, row = starts.nonzero(as_tuple=True)
+    first = torch.zeros(t, m, dtype=torch.int64, device=dev)
+    first[at, sub[at, row]] = row
+    heads = xyz.gather(1, first[..., None].expand(-1, -1, 3))
+    at, row = (sub >= 0).nonzero(as_tuple=True)
+    room = torch.full((t, m), rho, dtype=torch.int64, device=dev)
+    room.view(-1).sub_(torch.bincount(at * m + sub[at, row], minlength=t * m))
+    live = (sub < 0).any(dim=1).nonzero().flatten()
+    while live.numel():
+        still = []
+        for part in live.split(max(1, (1 << 27) // (n * m))):
+            wait = sub[part] < 0
+            most = int(wait.sum(dim=1).max())
+            row = wait.to(torch.int8).argsort(dim=1, descending=True, stable=True)[:, :most]     # the waiting rows, in order
+            ok = wait.gather(1, row)
+            p = xyz[part].gather(1, row[..., None].expand(-1, -1, 3))
+            e = [(p[:, :, None, a] - heads[part][:, None, :, a]) ** 2 for a in range(3)]
+            dist = ((e[0] + e[1]) + e[2]).masked_fill_((room[part] <= 0)[:, None, :], math.inf)
+            near = dist == dist.amin(dim=2, keepdim=True)
+            pick = torch.where(near, torch.arange(m, device=dev), m).amin(dim=2)
+            pick = torch.where(ok, pick, m + torch.arange(most, device=dev))       # the filling of shorter lists meets nobody
+            join = ok & (ranks(pick) < room[part].gather(1, pick.clamp(max=m - 1)))
+            i, j = join.nonzero(as_tuple=True)
+            sub[part[i], row[i, j]] = pick[i, j]
+            room.view(-1).sub_(torch.bincount(part[i] * m + pick[i, j], minlength=t * m))
+            still.append(part[(sub[part] < 0).any(dim=1)])
+        live = torch.cat(still)
+    return sub
+
+
+def exact_pool(case, st):
+    n, tile, rho = case["points"], case["tile"], case["rho"]
+    dev = st["coords"].device
+    xyz = st["coords"][exact_perm(case, st["coords"])]
+    at, base, offsets, jobs = 0, 0, [0], {}
+    for size in scan_sizes(case):
+        for a in range(0, size, tile):
+            b = min(tile, size - a)
+            jobs.setdefault(b, []).append((at + a, base))
+            base += -(-b // rho)
+        at += size
+        offsets.append(base)
+    sub = torch.empty(n, dtype=torch.int64, device=dev)
+    for b, tiles in jobs.items():
+        rows = torch.tensor([x for x, _ in tiles], device=dev)[:, None] + torch.arange(b, device=dev)
+        sub[rows] = tile_subs(xyz[rows], 0.1, rho) + torch.tensor([y for _, y in tiles], device=dev)[:, None]
+
+    def reduce(x, op, like):
+        out = torch.zeros(like.shape, dtype=torch.float64, device=dev)
+        how = {"mean": "mean", "sum": "sum", "max": "amax"}[op]
+        return out.scatter_reduce_(0, sub[:, None].expand_as(x), x, how, include_self=False)
+
+    return {"feat": reduce(st["feat"].double(), case["op"], st["pooled"].feat), "coords": reduce(xyz.double(), "mean", st["pooled"].coords),
+            "sub_of": None, "pooled_offsets": None}
+
+
+def exact(case, seed):
+    if case["kind"] == "bucketize":
+        return None                     # whole numbers
+    st = prepare(case, seed)
+    if case["kind"] == "project":
+        x, c, perm = st["x"].double(), case["channels"], st["perm"].long()
+        x = (x - x.mean(dim=1, keepdim=True)) / (x.var(dim=1, unbiased=False, keepdim=True) + 1e-5).sqrt() * st["gamma"].double() + st["beta"].double()
+        qkv = (x[perm] @ st["w_qkv"].double().t() + st["b_qkv"].double()).reshape(-1, 3, c)
+        y = st["x"].double()
+        y[perm] += st["attn"].double() @ st["w_out"].double().t() + st["b_out"].double()
+        return {"q": qkv[:, 0].contiguous(), "k": qkv[:, 1].contiguous(), "v": qkv[:, 2].contiguous(), "y": y}
+    if case["kind"] == "pool":
+        return exact_pool(case, st)
+    res = {"perm": None, "inv_perm": None, "bucket_offsets": None, "scan_bucket_start": None, "placed": None}
+    perm = exact_perm(case, st["coords"])
+    gather = not case["bucket_major"]
+    q, k, v = ((st[x][perm] if gather else st[x]).double() for x in "qkv")
+
+    def in_input_order(x):
+        return torch.empty_like(x).index_copy_(0, perm, x)
+
+    modes = case["passes"].split(",")
+    if case["kind"] == "train":
+        out, lse, dq, dk, dv = exact_attention(case, modes[0], q, k, v, st["dout"].double())
+        if gather:
+            dq, dk, dv = map(in_input_order, (dq, dk, dv))
+        return {**res, "out": out, "lse": lse, "dq": dq, "dk": dk, "dv": dv}
+    for i, mode in enumerate(modes):
+        out = exact_attention(case, mode, q, k, v)[0]
+        res["out%d" % i] = in_input_order(out) if i + 1 == len(modes) else out
+    return res
