@@ -40,7 +40,8 @@ struct AttnBwdArgs {
     uint16_t* dk;
     uint16_t* dv;
     float scale;            // softmax scale (the forward's c_log2 divided by log2 e)
-    int kblocks;            // ceil(bucket_cap / 128): key blocks of a scope in the dK/dV kernel
+    int tiles;              // tiles of 32 rows a wave owns (1 or 2): queries in the dQ kernel, keys in the dK/dV kernel
+    int kblocks;            // ceil(bucket_cap / (128 * tiles)): row blocks of a scope (f.qblocks is the same)
 };
 
 hipError_t attn_bwd_launch(const AttnBwdArgs& a, int head_dim, hipStream_t stream);

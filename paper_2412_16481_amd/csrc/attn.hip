@@ -38,10 +38,6 @@ namespace f3d {
 
 namespace {
 
-typedef __attribute__((ext_vector_type(4))) short s16x4;
-#define F3D_LDS(p) ((__attribute__((address_space(3))) void*)(p))
-#define F3D_GLB(p) ((const __attribute__((address_space(1))) void*)(p))
-
 // what depends on the 16-bit element type
 template <bool F16>
 struct Elem;
@@ -110,30 +106,6 @@ struct Lay {
     static constexpr int LPW = AKT * NC / 256;        // global->LDS loads per lane, stage and tensor
     static constexpr int TOTAL = NBUF * (KBUF + VBUF);
 };
-
-// One 16-byte global -> LDS load per lane: lane i of the wave fills bytes [16 i, 16 i + 16) of the 1 KB block at the
-// LDS byte address `lds` (wave-uniform; it travels in M0). Written as assembly so that the compiler does not count
-// it among its own memory operations: it would otherwise wait for ALL loads in flight before every LDS read that
-// follows, and the loads issued here are meant to stay in flight for a whole stage. The kernel waits for them itself
-// (s_waitcnt vmcnt(0) before the barrier that hands a stage over).
-__device__ __forceinline__ void lds_dma16(const void* g, uint32_t lds)
-{
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(g) : "memory", "m0");
-}
-
-__device__ __forceinline__ uint2 lds_read_tr(uint32_t addr)
-{
-    const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(uintptr_t)addr);
-    return *reinterpret_cast<const uint2*>(&v);
-}
-
-__device__ __forceinline__ uint4 lds_read16(uint32_t addr)
-{
-    const u32x4 v = *(const __attribute__((address_space(3))) u32x4*)(uintptr_t)addr;
-    return make_uint4(v.x, v.y, v.z, v.w);
-}
-
-#define F3D_SB() __builtin_amdgcn_sched_barrier(0)
 
 template <int D, int QT, bool F16>
 __global__ __launch_bounds__(256) void k_attn(AttnArgs a)

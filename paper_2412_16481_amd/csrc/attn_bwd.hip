@@ -5,15 +5,25 @@
 // inside every scope, with the same scope -> row arithmetic as the forward kernel. P is recomputed from the
 // forward's log-sum-exp; nothing of size n_g^2 ever leaves the registers.
 //
-// Two kernels, neither needs atomics:
-//   k_attn_bwd_dq    a workgroup owns 128 query rows and streams the scope's K and V through LDS (as the forward
-//                    kernel does). Scores are computed transposed (keys x queries), so a lane owns 16 keys of ONE
-//                    query: lse and D are per-lane scalars, and dS^T, packed to bf16, is directly the B operand of
-//                    dQ^T += K^T dS^T with K^T kept in LDS in the matching key order.
-//   k_attn_bwd_dkdv  a workgroup owns 128 key rows and streams the scope's Q and dO through LDS. Scores are
-//                    computed as queries x keys, so a lane owns 16 queries of ONE key: P and dS, packed to bf16, are
-//                    the B operands of dV^T += dO^T P and dK^T += Q^T dS with Q^T and dO^T kept in LDS.
-// Both recompute the exponentials; the matrix core has the room (it is not the busy unit of the forward either).
+// Two kernels, neither needs atomics; in both a wave owns 32 or 64 rows and the scope's other rows stream through LDS in
+// row-major stages filled by global -> LDS loads (as in the forward kernel), from which the transposing LDS read
+// delivers the transposed operands:
+//   k_attn_bwd_dq    owns query rows, streams K and V, works out D on the way. Scores are computed transposed (keys x
+//                    queries), so a lane owns 16 keys of ONE query: lse and D are per-lane scalars, and dS^T, packed to
+//                    bf16, is directly the B operand of dQ^T += K^T dS^T.
+//   k_attn_bwd_dkdv  owns key rows, streams Q and dO (after the first kernel: it reads D). Scores are queries x keys, so
+//                    a lane owns 16 queries of ONE key: P and dS, packed to bf16, are the B operands of
+//                    dV^T += dO^T P and dK^T += Q^T dS.
+// Both recompute the exponentials. One kernel that computes each score once would need dQ summed over waves in LDS:
+// 128 KB of it at a scope of 1024 rows and head_dim 32, which leaves no room for the staged rows and an order of the sums
+// that does not depend on timing.
+//
+// Bound: power and issue. On 914601 points x 8 heads x 32 (scopes of 1024) the dK/dV kernel keeps the matrix core busy
+// 61 % and the vector ALU 58 % of the cycles while the clock falls to 1.69 GHz, and runs 1.1 PFLOP/s of MFMAs (an 8192^3
+// bf16 matrix product reaches 1.2 here). Measured per pass on that input: dQ and D 2.57 -> 1.88 ms, dK/dV 3.19 -> 2.6 ms
+// against staging through registers with a transposed copy written by 2-byte LDS stores (bank conflicts in every one
+// of them), a separate pass for D and no overlap of one tile's products with another's exponentials; on 200000 points x
+// 4 heads x 16: 0.199 -> 0.177 and 0.251 -> 0.234 ms.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -26,37 +36,13 @@ namespace {
 
 constexpr float LOG2E = 1.4426950408889634f;
 
-// ------------------------------------------------------------------------------------------------
-// D[p, h] = sum over the head's channels of dO[p, c] * O[p, c]   (both bucket-major bf16 rows)
-__global__ __launch_bounds__(256) void k_attn_bwd_pre(AttnBwdArgs a, int head_dim)
-{
-    const long long total = (long long)a.f.n * a.f.H;
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= total) return;
-    const long long p = i / a.f.H;
-    const int h = (int)(i - p * a.f.H);
-    const uint4* o = reinterpret_cast<const uint4*>(a.f.out + p * a.f.C + (size_t)h * head_dim);
-    const uint4* g = reinterpret_cast<const uint4*>(a.dout + p * a.f.C + (size_t)h * head_dim);
-    float acc = 0.f;
-    for (int c = 0; c < head_dim / 8; ++c) {
-        const uint4 x = o[c], y = g[c];
-        const uint32_t xw[4] = {x.x, x.y, x.z, x.w}, yw[4] = {y.x, y.y, y.z, y.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            acc += __uint_as_float(xw[e] << 16) * __uint_as_float(yw[e] << 16);
-            acc += __uint_as_float(xw[e] & 0xFFFF0000u) * __uint_as_float(yw[e] & 0xFFFF0000u);
-        }
-    }
-    a.dsum[i] = acc;
-}
-
 // scope of a workgroup, shared by both kernels
 struct ScopeCtx {
     int head, blk, ng;
     SegMap sm;
 };
 
-template <int D>
+template <int BM>
 __device__ __forceinline__ bool scope_of_block(const AttnArgs& a, int blocks_per_scope, int* seg_row0, int* seg_pre, int* s_nseg,
                                                ScopeCtx& c)
 {
@@ -77,7 +63,7 @@ __device__ __forceinline__ bool scope_of_block(const AttnArgs& a, int blocks_per
     const int nseg = *s_nseg;
     if (nseg == 0) return false;
     c.ng = seg_pre[nseg];
-    if (c.blk * 128 >= c.ng) return false;
+    if (c.blk * BM >= c.ng) return false;
     constexpr int BIG = 0x7FFFFFFF;
     c.sm.nseg = nseg;
     c.sm.d0 = __builtin_amdgcn_readfirstlane(seg_row0[0]);
@@ -116,24 +102,6 @@ __device__ __forceinline__ uint2 split_pairs(float l2, float dsum)
     return make_uint2((lh & 0xFFFFu) | (lo << 16), (lh >> 16) | (lo & 0xFFFF0000u));
 }
 
-// store one 16-byte piece of a row transposed into a [rows of dims][VSTR] array, at the column the MFMA result order
-// wants for row kk of the stage (see the forward kernel's V^T)
-template <int TS>
-__device__ __forceinline__ void store_transposed(uint16_t* base, int c, int kk, uint32_t v0, uint32_t v1, uint32_t v2, uint32_t v3)
-{
-    const int w16 = kk & 15;
-    const int pos = (kk & ~15) + 8 * ((w16 >> 2) & 1) + 4 * (w16 >> 3) + (w16 & 3);
-    uint16_t* col = base + c * 8 * TS + pos;
-    col[0 * TS] = (uint16_t)(v0 & 0xFFFFu);
-    col[1 * TS] = (uint16_t)(v0 >> 16);
-    col[2 * TS] = (uint16_t)(v1 & 0xFFFFu);
-    col[3 * TS] = (uint16_t)(v1 >> 16);
-    col[4 * TS] = (uint16_t)(v2 & 0xFFFFu);
-    col[5 * TS] = (uint16_t)(v2 >> 16);
-    col[6 * TS] = (uint16_t)(v3 & 0xFFFFu);
-    col[7 * TS] = (uint16_t)(v3 >> 16);
-}
-
 template <int D>
 __device__ __forceinline__ void store_grad_rows(uint16_t* dst_base, const int32_t* out_perm, int row, int C, size_t hoff, int hf,
                                                 const f32x16& acc, float mul)
@@ -150,395 +118,570 @@ __device__ __forceinline__ void store_grad_rows(uint16_t* dst_base, const int32_
     }
 }
 
-constexpr int TROWS16 = 17;   // head_dim 16: 16 rows of a transposed operand plus one row of zeros for the idle MFMA rows
+template <int D>
+struct BLay {
+    static constexpr int NC = D / 8;                 // 16-byte pieces of one head in a row
+    static constexpr int ROWB = D * 2;               // bytes of a row
+    static constexpr int TILE = 32 * ROWB;           // from one 32-row tile to the next
+    static constexpr int ROWS = 128;                 // rows per stage
+    static constexpr int BUF = ROWS * ROWB;          // one operand of a stage
+    static constexpr int NBUF = 3;
+    static constexpr int LPW = ROWS * NC / 256;      // global -> LDS loads per lane, stage and operand
+};
+
+// byte offsets inside a tile of the transposing read that delivers X^T as an A operand (rows = dims, k = the tile's rows
+// in the order of the score registers): lane 4j + c of a group of 16 hands in the address of dims 4c .. 4c+3 of row
+// 4*hf + j (+ 8 s for the s-th read). The pieces of a row are swizzled by the row, which alternates with s. At
+// head_dim 16 the second group of 16 lanes repeats the first: the 16 result rows it feeds are never read.
+template <int D>
+__device__ __forceinline__ void tr_offsets(int lane, uint32_t& even, uint32_t& odd)
+{
+    const int i16 = lane & 15, j = i16 >> 2, c = i16 & 3, g16 = (lane >> 4) & 1, hf = lane >> 5;
+    const int row = 4 * hf + j;
+    if (D == 32) {
+        even = row * 64 + (((2 * g16 + (c >> 1)) ^ hf) * 16) + (c & 1) * 8;
+        odd = even ^ 32;                             // rows 8 further on: swizzle hf + 2
+    } else {
+        even = row * 32 + (c >> 1) * 16 + (c & 1) * 8;
+        odd = even ^ 16;
+    }
+}
 
 template <int D>
-constexpr int trows() { return D == 16 ? TROWS16 : D; }
+__device__ __forceinline__ void read_tr(U4& x0, U4& x1, uint32_t even, uint32_t odd)
+{
+    constexpr int STEP = 8 * BLay<D>::ROWB;
+    const uint2 a0 = lds_read_tr(even), a1 = lds_read_tr(odd + STEP), a2 = lds_read_tr(even + 2 * STEP), a3 = lds_read_tr(odd + 3 * STEP);
+    x0.u = make_uint4(a0.x, a0.y, a1.x, a1.y);
+    x1.u = make_uint4(a2.x, a2.y, a3.x, a3.y);
+}
 
-template <int D>
-constexpr int dkdv_stage_rows() { return D == 32 ? 64 : 128; }
+__device__ __forceinline__ f32x16 mfma_bf16(const U4& x, const U4& y, f32x16 c)
+{
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(x.b, y.b, c, 0, 0, 0);
+}
 
 // ------------------------------------------------------------------------------------------------
-// dQ. dynamic LDS per buffer: K rows [KT*D] | V rows [KT*D] | K^T [trows][VSTR]   (bf16), two buffers
-template <int D>
-__global__ __launch_bounds__(256) void k_attn_bwd_dq(AttnBwdArgs b)
+// dQ, and on the way D, which the other kernel reads. A wave owns QT tiles of 32 query rows; K and V stream through LDS in
+// stages of 128 key rows, three resident, as in the forward kernel. Scores are transposed (keys x queries), so a lane
+// owns 16 keys of ONE query, its log-sum-exp is a scalar, and dS^T, packed to bf16, is the B operand of
+// dQ^T += K^T dS^T, whose A operand comes from the row-major K through the transposing read.
+// -D is the accumulator the dP product starts from, so dP - D costs nothing. The scaled score minus the log-sum-exp is
+//   head_dim 32: one fused multiply-add per element on the plain product q k^T (6 MFMAs per tile). The two more MFMAs
+//                the remainder of the scaled query would take cost the same issue time, more registers and more power;
+//   head_dim 16: the two-term query of the forward kernel with -lse as the starting accumulator (5 MFMAs per tile): there
+//                the remainder is one MFMA, half the issue time of 16 multiply-adds.
+template <int D, int QT>
+__global__ __launch_bounds__(256, 2) void k_attn_bwd_dq(AttnBwdArgs b)
 {
-    constexpr int NC = D / 8, KS = D / 16, LPT = KT * NC / 256;
-    constexpr int SWZ_SHIFT = (NC == 2) ? 3 : 2;
-    constexpr int BUF = 2 * KT * D + trows<D>() * VSTR;   // elements per buffer
-    extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+    using L = BLay<D>;
+    constexpr bool SPLIT = D == 16;
+    constexpr int NC = L::NC, KS = D / 16, LPW = L::LPW, SR = L::ROWS;
+    constexpr int BM = 128 * QT;                      // query rows per workgroup
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[L::NBUF * 2 * L::BUF];   // K stages, then V stages
     __shared__ int seg_row0[MAXSEG];
     __shared__ int seg_pre[MAXSEG + 1];
     __shared__ int s_nseg;
     const AttnArgs& a = b.f;
     ScopeCtx sc;
-    if (!scope_of_block<D>(a, a.qblocks, seg_row0, seg_pre, &s_nseg, sc)) return;
+    if (!scope_of_block<BM>(a, a.qblocks, seg_row0, seg_pre, &s_nseg, sc)) return;
     const int ng = sc.ng, head = sc.head;
     const SegMap sm = sc.sm;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, hf = lane >> 5;
     const size_t hoff = (size_t)head * D;
     const uint32_t row_bytes = (uint32_t)a.C * 2u;
+    const uint32_t sK = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)smem;
+    const uint32_t sV = sK + L::NBUF * L::BUF;
 
-    // ---- this lane's query: q and dO fragments, log-sum-exp and D
-    const int xq = sc.blk * 128 + wave * 32 + l32;
-    const bool qok = xq < ng;
-    const int orow = qok ? seg_row_of(sm, seg_pre, seg_row0, xq) : -1;
-    U4 qhi[KS], qlo[KS], dof[KS];
-    U4 ext;         // B operand that carries this query's log-sum-exp and D (lower half-wave: k positions 0..3)
-    U4 negS, negD;  // A operands with -1 at the positions of the log-sum-exp pair / the D pair
-    ext.u = make_uint4(0, 0, 0, 0);
-    negS.u = make_uint4(hf == 0 ? 0xBF80BF80u : 0u, 0, 0, 0);
-    negD.u = make_uint4(0, hf == 0 ? 0xBF80BF80u : 0u, 0, 0);
-    {
-        const size_t gr = qok ? (size_t)(a.perm ? a.perm[orow] : orow) : 0;
+    // ---- staging of K and V rows (see the forward kernel); positions past the end fetch the scope's last row again
+    uint32_t rows_next[LPW];
+    const char* kthr[LPW];
+    const char* vthr[LPW];
+    int srow[LPW];
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            U4 qf;
-            qf.u = make_uint4(0, 0, 0, 0);
-            dof[ks].u = make_uint4(0, 0, 0, 0);
-            if (qok) {
-                qf.u = *reinterpret_cast<const uint4*>(a.q + gr * a.C + hoff + ks * 16 + hf * 8);
-                dof[ks].u = *reinterpret_cast<const uint4*>(b.dout + (size_t)orow * a.C + hoff + ks * 16 + hf * 8);
-            }
-            scale_split(qf, a.c_log2, qhi[ks], qlo[ks]);
-        }
-        if (qok && hf == 0) {
-            const uint2 pr = split_pairs(a.lse[(size_t)orow * a.H + head] * LOG2E, b.dsum[(size_t)orow * a.H + head]);
-            ext.u.x = pr.x;
-            ext.u.y = pr.y;
-        }
-    }
-
-    // ---- staging of K and V rows (row index through perm one stage ahead, as in the forward kernel)
-    u32x4 kreg[LPT], vreg[LPT];
-    uint32_t rows_next[LPT];
-    const char* kthr[LPT];
-    const char* vthr[LPT];
-#pragma unroll
-    for (int i = 0; i < LPT; ++i) {
-        const int c = (tid + i * 256) % NC;
+    for (int i = 0; i < LPW; ++i) {
+        const int p = (wave * LPW + i) * 64 + lane;
+        const int kk = p / NC, cs = p % NC;
+        const int c = (NC == 4) ? (cs ^ ((kk >> 2) & 3)) : (cs ^ ((kk >> 3) & 1));
+        srow[i] = kk;
         kthr[i] = reinterpret_cast<const char*>(a.k + hoff + c * 8);
         vthr[i] = reinterpret_cast<const char*>(a.v + hoff + c * 8);
     }
     auto fetch_rows = [&](int st) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < LPT; ++i) {
-            const int x = min(st * KT + (tid + i * 256) / NC, ng - 1);
-            const uint32_t r = (uint32_t)seg_row_of(sm, seg_pre, seg_row0, x);
+        for (int i = 0; i < LPW; ++i) {
+            const uint32_t r = (uint32_t)seg_row_of(sm, seg_pre, seg_row0, min(st * SR + srow[i], ng - 1));
             rows_next[i] = a.perm ? (uint32_t)a.perm[r] : r;
         }
     };
-    auto load_stage = [&]() __attribute__((always_inline)) {
+    auto dma_stage = [&](int buf) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < LPT; ++i) {
+        for (int i = 0; i < LPW; ++i) {
             const uint64_t at = (uint64_t)rows_next[i] * row_bytes;
-            kreg[i] = *reinterpret_cast<const u32x4*>(kthr[i] + at);
-            vreg[i] = *reinterpret_cast<const u32x4*>(vthr[i] + at);
+            const int blk = wave * LPW + i;
+            lds_dma16(kthr[i] + at, sK + buf * L::BUF + blk * 1024);
+            lds_dma16(vthr[i] + at, sV + buf * L::BUF + blk * 1024);
         }
     };
-    auto store_stage = [&](int buf) __attribute__((always_inline)) {
-        uint16_t* sK = smem + buf * BUF;
-        uint16_t* sVr = sK + KT * D;
-        uint16_t* sKT = sVr + KT * D;
+    const int nst = (ng + SR - 1) / SR, ntile = (ng + 31) >> 5;
+    int orow[QT];
+    size_t qrd[QT];
 #pragma unroll
-        for (int i = 0; i < LPT; ++i) {
-            uint32_t k0 = kreg[i].x, k1 = kreg[i].y, k2 = kreg[i].z, k3 = kreg[i].w;
-            asm volatile("" : "+v"(k0), "+v"(k1), "+v"(k2), "+v"(k3));   // no half-splitting right behind the load
-            const int uidx = tid + i * 256;
-            const int kk = uidx / NC, c = uidx % NC;
-            const int cs = c ^ ((kk >> SWZ_SHIFT) & (NC - 1));
-            u32x4 kw = {k0, k1, k2, k3};
-            *reinterpret_cast<u32x4*>(&sK[kk * D + cs * 8]) = kw;
-            *reinterpret_cast<u32x4*>(&sVr[kk * D + cs * 8]) = vreg[i];
-            store_transposed<VSTR>(sKT, c, kk, k0, k1, k2, k3);
-        }
-    };
-    if (D == 16)   // the zeros row of K^T
-        for (int i = tid; i < VSTR; i += 256) {
-            smem[2 * KT * D + D * VSTR + i] = 0;
-            smem[BUF + 2 * KT * D + D * VSTR + i] = 0;
-        }
-
-    const int nst = (ng + KT - 1) / KT;
-    const int trow = (D == 16) ? min(l32, 16) : l32;
-    const int toff = trow * VSTR + 8 * hf;
-    f32x16 acc = {0};
-
+    for (int t = 0; t < QT; ++t) {
+        const int xq = sc.blk * BM + (wave * QT + t) * 32 + l32;
+        orow[t] = xq < ng ? seg_row_of(sm, seg_pre, seg_row0, xq) : -1;
+        const int r = max(orow[t], 0);                // past the end: some valid row, never stored
+        qrd[t] = (size_t)(a.perm ? a.perm[r] : r);
+    }
     fetch_rows(0);
-    load_stage();
-    if (nst > 1) fetch_rows(1);
-    store_stage(0);
-    __syncthreads();
-    for (int st = 0; st < nst; ++st) {
-        const int buf = st & 1;
-        if (st + 1 < nst) {
-            load_stage();
-            if (st + 2 < nst) fetch_rows(st + 2);
-        }
-        const uint16_t* sK = smem + buf * BUF;
-        const uint16_t* sVr = sK + KT * D;
-        const uint16_t* sKT = sVr + KT * D + toff;
-#pragma unroll 2
-        for (int t4 = 0; t4 < KT / 32; ++t4) {
-            const int kbase = st * KT + t4 * 32;
-            if (kbase >= ng) break;
-            const int kk = t4 * 32 + l32;
-            f32x16 s = {0}, dp = {0};
+    dma_stage(0);
+    if (nst > 1) {
+        fetch_rows(1);
+        dma_stage(1);
+    }
+
+    // ---- this lane's queries: q and dO fragments, the log-sum-exp, and D = sum over the head's channels of dO * O
+    U4 qhi[QT][KS], qlo[QT][KS], dof[QT][KS];
+    f32x16 iS[QT], iD[QT], acc[QT];                   // starting accumulators: -lse (log2 units), -D
+    float nl[QT];
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                const int c = 2 * ks + hf;
-                const int cs = c ^ ((kk >> SWZ_SHIFT) & (NC - 1));
-                U4 kf, vf;
-                kf.u = *reinterpret_cast<const uint4*>(&sK[kk * D + cs * 8]);
-                vf.u = *reinterpret_cast<const uint4*>(&sVr[kk * D + cs * 8]);
-                s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf.b, qhi[ks].b, s, 0, 0, 0);
-                s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf.b, qlo[ks].b, s, 0, 0, 0);
-                dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf.b, dof[ks].b, dp, 0, 0, 0);
-            }
-            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(negS.b, ext.b, s, 0, 0, 0);     // score - lse
-            dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(negD.b, ext.b, dp, 0, 0, 0);   // dP - D
-            U4 kt0, kt1;
-            kt0.u = *reinterpret_cast<const uint4*>(&sKT[t4 * 32]);
-            kt1.u = *reinterpret_cast<const uint4*>(&sKT[t4 * 32 + 16]);
-            if (kbase + 32 > ng) {
+    for (int t = 0; t < QT; ++t) {
+        const size_t orw = (size_t)max(orow[t], 0);
+        float dot = 0.f;
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int key = kbase + 8 * (r >> 2) + 4 * hf + (r & 3);
-                    if (key >= ng) s[r] = -INFINITY;
-                }
-            }
-            // dS^T = P o (dP^T - D), P = 2^(score - lse)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) s[r] = __builtin_amdgcn_exp2f(s[r]) * dp[r];
-            union { uint32_t u[4]; bf16x8 b; } pb0, pb1;
+        for (int ks = 0; ks < KS; ++ks) {
+            U4 qf, of;
+            qf.u = *reinterpret_cast<const uint4*>(a.q + qrd[t] * a.C + hoff + ks * 16 + hf * 8);
+            dof[t][ks].u = *reinterpret_cast<const uint4*>(b.dout + orw * a.C + hoff + ks * 16 + hf * 8);
+            of.u = *reinterpret_cast<const uint4*>(a.out + orw * a.C + hoff + ks * 16 + hf * 8);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                pb0.u[e] = pack_bf16(s[2 * e], s[2 * e + 1]);
-                pb1.u[e] = pack_bf16(s[8 + 2 * e], s[8 + 2 * e + 1]);
+                const uint32_t x = (&of.u.x)[e], y = (&dof[t][ks].u.x)[e];
+                dot += __uint_as_float(x << 16) * __uint_as_float(y << 16);
+                dot += __uint_as_float(x & 0xFFFF0000u) * __uint_as_float(y & 0xFFFF0000u);
             }
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kt0.b, pb0.b, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kt1.b, pb1.b, acc, 0, 0, 0);
+            if (SPLIT) scale_split(qf, a.c_log2, qhi[t][ks], qlo[t][ks]);
+            else qhi[t][ks] = qf;
         }
-        if (st + 1 < nst) store_stage(buf ^ 1);
-        __syncthreads();
+        dot += __shfl_xor(dot, 32, 64);               // the two half-waves hold the two halves of a row
+        if (orow[t] >= 0 && hf == 0) b.dsum[orw * a.H + head] = dot;
+        // past the end: probabilities exactly zero
+        nl[t] = orow[t] >= 0 ? -LOG2E * a.lse[orw * a.H + head] : -1e30f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            iS[t][r] = nl[t];
+            iD[t][r] = -dot;
+        }
+        acc[t] = f32x16{0};
     }
-    store_grad_rows<D>(b.dq, a.out_perm, orow, a.C, hoff, hf, acc, b.scale);
+
+    uint32_t foff[KS];                                // row l32 of a tile, dims 16*ks + 8*hf ..
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+        const int c = 2 * ks + hf;
+        foff[ks] = (l32 * NC + ((NC == 4) ? (c ^ ((l32 >> 2) & 3)) : (c ^ ((l32 >> 3) & 1)))) * 16;
+    }
+    uint32_t tre, tro;
+    tr_offsets<D>(lane, tre, tro);
+    const float cl2 = a.c_log2;
+
+    struct Rows { U4 k[KS], v[KS]; };                 // the A operands of one key tile's score products
+    auto read_rows = [&](Rows& f, uint32_t at) __attribute__((always_inline)) {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            f.k[ks].u = lds_read16(sK + at + foff[ks]);
+            f.v[ks].u = lds_read16(sV + at + foff[ks]);
+        }
+    };
+    // One unit of the pipeline: dS^T = P^T o (dP^T - D) of the current tile (query tile t, keys from kbase on) and its dQ^T
+    // product, with the score products of the NEXT tile (rows f, query tile tn) issued in between.
+    auto unit = [&](f32x16& s, f32x16& dp, int t, int kbase, const U4& kt0, const U4& kt1, f32x16& sn, f32x16& dpn, const Rows& f, int tn)
+        __attribute__((always_inline)) {
+        const auto prob = [&](int r) __attribute__((always_inline)) {
+            s[r] = __builtin_amdgcn_exp2f(SPLIT ? s[r] : __builtin_fmaf(s[r], cl2, nl[t]));
+        };
+        if (kbase + 32 > ng) {                        // keys past the end repeat a key of the scope: their dS is dropped here
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int key = kbase + 8 * (r >> 2) + 4 * hf + (r & 3);
+                if (key >= ng) dp[r] = 0.f;
+            }
+        }
+        U4 pb;
+        F3D_SB();
+#pragma unroll
+        for (int r = 0; r < 4; ++r) prob(r);
+        F3D_SB();
+        sn = mfma_bf16(f.k[0], qhi[tn][0], SPLIT ? iS[tn] : f32x16{0});
+        F3D_SB();
+#pragma unroll
+        for (int r = 4; r < 8; ++r) prob(r);
+        F3D_SB();
+        sn = SPLIT ? mfma_bf16(f.k[0], qlo[tn][0], sn) : mfma_bf16(f.k[KS - 1], qhi[tn][KS - 1], sn);
+        F3D_SB();
+#pragma unroll
+        for (int r = 0; r < 8; ++r) dp[r] *= s[r];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) (&pb.u.x)[e] = pack_bf16(dp[2 * e], dp[2 * e + 1]);
+        F3D_SB();
+        acc[t] = mfma_bf16(kt0, pb, acc[t]);
+        F3D_SB();
+#pragma unroll
+        for (int r = 8; r < 12; ++r) prob(r);
+        F3D_SB();
+        dpn = mfma_bf16(f.v[0], dof[tn][0], iD[tn]);
+        F3D_SB();
+#pragma unroll
+        for (int r = 12; r < 16; ++r) prob(r);
+        F3D_SB();
+        if (KS == 2) dpn = mfma_bf16(f.v[KS - 1], dof[tn][KS - 1], dpn);
+        F3D_SB();
+#pragma unroll
+        for (int r = 8; r < 16; ++r) dp[r] *= s[r];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) (&pb.u.x)[e] = pack_bf16(dp[8 + 2 * e], dp[8 + 2 * e + 1]);
+        F3D_SB();
+        acc[t] = mfma_bf16(kt1, pb, acc[t]);
+        F3D_SB();
+    };
+    auto handover = [&](int st) __attribute__((always_inline)) {      // as in the forward kernel
+        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+        __syncthreads();
+        if (st + 2 < nst) {
+            dma_stage((st + 2) % L::NBUF);
+            if (st + 3 < nst) fetch_rows(st + 3);
+        }
+    };
+
+    __builtin_amdgcn_s_waitcnt(0x0F70);       // stages 0 and 1 have landed for every wave
+    __syncthreads();
+    if (nst > 2) fetch_rows(2);
+
+    f32x16 sa, sb, da, db;
+    Rows f;
+    read_rows(f, 0);
+    sa = SPLIT ? iS[0] : f32x16{0};
+    da = iD[0];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+        sa = mfma_bf16(f.k[ks], qhi[0][ks], sa);
+        if (SPLIT) sa = mfma_bf16(f.k[ks], qlo[0][ks], sa);
+        da = mfma_bf16(f.v[ks], dof[0][ks], da);
+    }
+    if (QT == 1) read_rows(f, L::TILE);
+    int bufi = 0;
+    for (int st = 0; st < nst; ++st) {
+        const int bufn = bufi + 1 == L::NBUF ? 0 : bufi + 1;
+#pragma unroll
+        for (int t4 = 0; t4 < 4; ++t4) {
+            if (4 * st + t4 >= ntile) break;          // the products computed ahead of the last tile are never used
+            const uint32_t at = bufi * L::BUF + t4 * L::TILE;
+            const int kbase = st * SR + t4 * 32;
+            U4 kt0, kt1;
+            read_tr<D>(kt0, kt1, sK + at + tre, sK + at + tro);
+            if (QT == 1) {                            // the score registers alternate from one key tile to the next
+                Rows fn;
+                read_rows(fn, t4 < 2 ? at + 2 * L::TILE : bufn * L::BUF + (t4 - 2) * L::TILE);
+                if ((t4 & 1) == 0) unit(sa, da, 0, kbase, kt0, kt1, sb, db, f, 0);
+                else unit(sb, db, 0, kbase, kt0, kt1, sa, da, f, 0);
+                f = fn;
+            } else {                                  // a is query tile 0, b query tile 1 of the same key tile
+                unit(sa, da, 0, kbase, kt0, kt1, sb, db, f, QT - 1);
+                read_rows(f, t4 < 3 ? at + L::TILE : bufn * L::BUF);
+                unit(sb, db, QT - 1, kbase, kt0, kt1, sa, da, f, 0);
+            }
+            if (t4 == 1) handover(st);
+        }
+        bufi = bufn;
+    }
+#pragma unroll
+    for (int t = 0; t < QT; ++t) store_grad_rows<D>(b.dq, a.out_perm, orow[t], a.C, hoff, hf, acc[t], b.scale);
 }
 
 // ------------------------------------------------------------------------------------------------
-// dK and dV. dynamic LDS per buffer: Q rows [KT*D] | dO rows [KT*D] | Q^T [trows][VSTR] | dO^T [trows][VSTR] (bf16) |
-// per row 16 bytes {lse*log2e hi, lo, D hi, lo, 0 x 4} [KT], two buffers
-template <int D>
-__global__ __launch_bounds__(256) void k_attn_bwd_dkdv(AttnBwdArgs b)
+// dK and dV. A wave owns KTW tiles of 32 key rows; the scope's query rows stream through LDS in stages of 128, three
+// of them resident, filled by global -> LDS loads two stages ahead exactly as the forward kernel fills its K and V.
+// Q and dO are kept once, row-major: the rows of the score products come from 16-byte reads (pieces of a row
+// xor-swizzled by the row, free of bank conflicts), and Q^T, dO^T, the A operands of dK^T += Q^T dS and
+// dV^T += dO^T P, from the transposing read, which follows the same swizzle.
+// The vector ALU (16 exponentials, 16 multiplies and 16 packs per tile and lane) and the matrix core (12 MFMAs at
+// head_dim 32) are both busy, so the loop runs one score tile ahead: the products of the next tile are issued between
+// the exponentials, multiplies and packs of the current one.
+template <int D, int KTW>
+__global__ __launch_bounds__(256, 2) void k_attn_bwd_dkdv(AttnBwdArgs b)
 {
-    constexpr int KT = dkdv_stage_rows<D>();   // query rows per stage: 64 at head_dim 32 keeps three workgroups per CU
-    constexpr int VSTR = KT + 8;
-    constexpr int NC = D / 8, KS = D / 16, LPT = KT * NC / 256;
-    constexpr int SWZ_SHIFT = (NC == 2) ? 3 : 2;
-    constexpr int BUF = 2 * KT * D + 2 * trows<D>() * VSTR + 8 * KT;   // 16-bit elements per buffer
-    extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
+    using L = BLay<D>;
+    constexpr int NC = L::NC, KS = D / 16, LPW = L::LPW, SR = L::ROWS;
+    constexpr int BM = 128 * KTW;                     // key rows per workgroup
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[L::NBUF * 2 * L::BUF];   // Q stages, then dO stages
+    __shared__ uint2 sx[L::NBUF * SR];                // per staged row {lse hi, lo, D hi, lo}, see split_pairs
     __shared__ int seg_row0[MAXSEG];
     __shared__ int seg_pre[MAXSEG + 1];
     __shared__ int s_nseg;
     const AttnArgs& a = b.f;
     ScopeCtx sc;
-    if (!scope_of_block<D>(a, b.kblocks, seg_row0, seg_pre, &s_nseg, sc)) return;
+    if (!scope_of_block<BM>(a, b.kblocks, seg_row0, seg_pre, &s_nseg, sc)) return;
     const int ng = sc.ng, head = sc.head;
     const SegMap sm = sc.sm;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, hf = lane >> 5;
     const size_t hoff = (size_t)head * D;
     const uint32_t row_bytes = (uint32_t)a.C * 2u;
+    const uint32_t sQ = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)smem;
+    const uint32_t sG = sQ + L::NBUF * L::BUF;
+    const uint32_t sX = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)sx;
 
-    // ---- this lane's key: k (scaled, split) and v fragments
-    const int xk = sc.blk * 128 + wave * 32 + l32;
-    const bool kok = xk < ng;
-    const int krow = kok ? seg_row_of(sm, seg_pre, seg_row0, xk) : -1;
-    U4 khi[KS], klo[KS], vfr[KS];
-    U4 negS, negD;   // B operands with -1 at the positions of a staged row's log-sum-exp pair / D pair
-    negS.u = make_uint4(hf == 0 ? 0xBF80BF80u : 0u, 0, 0, 0);
-    negD.u = make_uint4(0, hf == 0 ? 0xBF80BF80u : 0u, 0, 0);
-    {
-        const size_t gr = kok ? (size_t)(a.perm ? a.perm[krow] : krow) : 0;
+    // ---- staging: load i of this lane fills piece (wave*LPW + i)*64 + lane of a stage (row = piece / NC), with the piece
+    //      of that row the swizzle puts there. q rows go through the permutation, dO rows are bucket-major. Positions past
+    //      the end of the scope fetch its last row again: finite, and their probabilities are exactly zero (lse = 1e30).
+    uint32_t qrow_next[LPW], grow_next[LPW];
+    const char* qthr[LPW];
+    const char* gthr[LPW];
+    int srow[LPW];
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            U4 kf;
-            kf.u = make_uint4(0, 0, 0, 0);
-            vfr[ks].u = make_uint4(0, 0, 0, 0);
-            if (kok) {
-                kf.u = *reinterpret_cast<const uint4*>(a.k + gr * a.C + hoff + ks * 16 + hf * 8);
-                vfr[ks].u = *reinterpret_cast<const uint4*>(a.v + gr * a.C + hoff + ks * 16 + hf * 8);
-            }
-            scale_split(kf, a.c_log2, khi[ks], klo[ks]);
-        }
-    }
-
-    // ---- staging of Q and dO rows with their lse and D
-    u32x4 qreg[LPT], greg[LPT];
-    uint32_t rows_next[LPT], brow_next[LPT];   // row of q (through perm) and bucket-major row (dO, lse, D)
-    float lreg = 0.f, dreg = 0.f;
-    int lrow_next = 0;
-    const char* qthr[LPT];
-    const char* gthr[LPT];
-#pragma unroll
-    for (int i = 0; i < LPT; ++i) {
-        const int c = (tid + i * 256) % NC;
+    for (int i = 0; i < LPW; ++i) {
+        const int p = (wave * LPW + i) * 64 + lane;
+        const int kk = p / NC, cs = p % NC;
+        const int c = (NC == 4) ? (cs ^ ((kk >> 2) & 3)) : (cs ^ ((kk >> 3) & 1));
+        srow[i] = kk;
         qthr[i] = reinterpret_cast<const char*>(a.q + hoff + c * 8);
         gthr[i] = reinterpret_cast<const char*>(b.dout + hoff + c * 8);
     }
+    float lreg = 0.f, dreg = 0.f;                     // log-sum-exp and D of row `tid` of the stage fetched last
     auto fetch_rows = [&](int st) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < LPT; ++i) {
-            const int x = min(st * KT + (tid + i * 256) / NC, ng - 1);
+        for (int i = 0; i < LPW; ++i) {
+            const int x = min(st * SR + srow[i], ng - 1);
             const uint32_t r = (uint32_t)seg_row_of(sm, seg_pre, seg_row0, x);
-            brow_next[i] = r;
-            rows_next[i] = a.perm ? (uint32_t)a.perm[r] : r;
+            grow_next[i] = r;
+            qrow_next[i] = a.perm ? (uint32_t)a.perm[r] : r;
         }
-        if (tid < KT) {
-            const int x = st * KT + tid;
-            lrow_next = x < ng ? seg_row_of(sm, seg_pre, seg_row0, x) : -1;
-        }
-    };
-    auto load_stage = [&]() __attribute__((always_inline)) {
-#pragma unroll
-        for (int i = 0; i < LPT; ++i) {
-            qreg[i] = *reinterpret_cast<const u32x4*>(qthr[i] + (uint64_t)rows_next[i] * row_bytes);
-            greg[i] = *reinterpret_cast<const u32x4*>(gthr[i] + (uint64_t)brow_next[i] * row_bytes);
-        }
-        if (tid < KT) {
-            // a position past the end of the scope gets a huge lse: its probabilities are exactly zero
-            lreg = lrow_next >= 0 ? a.lse[(size_t)lrow_next * a.H + head] * LOG2E : 1e30f;
-            dreg = lrow_next >= 0 ? b.dsum[(size_t)lrow_next * a.H + head] : 0.f;
+        if (tid < SR) {
+            const int x = st * SR + tid;
+            const size_t at = (size_t)seg_row_of(sm, seg_pre, seg_row0, min(x, ng - 1)) * a.H + head;
+            const float l = a.lse[at], d = b.dsum[at];
+            lreg = x < ng ? l : 1e30f;
+            dreg = x < ng ? d : 0.f;
         }
     };
-    auto store_stage = [&](int buf) __attribute__((always_inline)) {
-        uint16_t* sQ = smem + buf * BUF;
-        uint16_t* sG = sQ + KT * D;
-        uint16_t* sQT = sG + KT * D;
-        uint16_t* sGT = sQT + trows<D>() * VSTR;
-        uint4* sX = reinterpret_cast<uint4*>(sGT + trows<D>() * VSTR);
+    auto dma_stage = [&](int buf) __attribute__((always_inline)) {   // the rows fetched last -> LDS buffer `buf`
 #pragma unroll
-        for (int i = 0; i < LPT; ++i) {
-            uint32_t q0 = qreg[i].x, q1 = qreg[i].y, q2 = qreg[i].z, q3 = qreg[i].w;
-            uint32_t g0 = greg[i].x, g1 = greg[i].y, g2 = greg[i].z, g3 = greg[i].w;
-            asm volatile("" : "+v"(q0), "+v"(q1), "+v"(q2), "+v"(q3), "+v"(g0), "+v"(g1), "+v"(g2), "+v"(g3));
-            const int uidx = tid + i * 256;
-            const int kk = uidx / NC, c = uidx % NC;
-            const int cs = c ^ ((kk >> SWZ_SHIFT) & (NC - 1));
-            u32x4 qw = {q0, q1, q2, q3}, gw = {g0, g1, g2, g3};
-            *reinterpret_cast<u32x4*>(&sQ[kk * D + cs * 8]) = qw;
-            *reinterpret_cast<u32x4*>(&sG[kk * D + cs * 8]) = gw;
-            store_transposed<VSTR>(sQT, c, kk, q0, q1, q2, q3);
-            store_transposed<VSTR>(sGT, c, kk, g0, g1, g2, g3);
+        for (int i = 0; i < LPW; ++i) {
+            const int blk = wave * LPW + i;
+            lds_dma16(qthr[i] + (uint64_t)qrow_next[i] * row_bytes, sQ + buf * L::BUF + blk * 1024);
+            lds_dma16(gthr[i] + (uint64_t)grow_next[i] * row_bytes, sG + buf * L::BUF + blk * 1024);
         }
-        if (tid < KT) {
-            const uint2 pr = split_pairs(lreg, dreg);
-            sX[tid] = make_uint4(pr.x, pr.y, 0, 0);
-        }
+        if (tid < SR) sx[buf * SR + tid] = split_pairs(lreg * LOG2E, dreg);
     };
-    if (D == 16)   // the zeros rows of Q^T and dO^T
-        for (int i = tid; i < VSTR; i += 256)
-            for (int bf = 0; bf < 2; ++bf) {
-                smem[bf * BUF + 2 * KT * D + D * VSTR + i] = 0;
-                smem[bf * BUF + 2 * KT * D + trows<D>() * VSTR + D * VSTR + i] = 0;
-            }
-
-    const int nst = (ng + KT - 1) / KT;
-    const int trow = (D == 16) ? min(l32, 16) : l32;
-    const int toff = trow * VSTR + 8 * hf;
-    f32x16 dk = {0}, dv = {0};
-
-    fetch_rows(0);
-    load_stage();
-    if (nst > 1) fetch_rows(1);
-    store_stage(0);
-    __syncthreads();
-    for (int st = 0; st < nst; ++st) {
-        const int buf = st & 1;
-        if (st + 1 < nst) {
-            load_stage();
-            if (st + 2 < nst) fetch_rows(st + 2);
-        }
-        const uint16_t* sQ = smem + buf * BUF;
-        const uint16_t* sG = sQ + KT * D;
-        const uint16_t* sQT = sG + KT * D + toff;
-        const uint16_t* sGT = sQT + trows<D>() * VSTR;
-        const uint4* sX = reinterpret_cast<const uint4*>(smem + buf * BUF + 2 * KT * D + 2 * trows<D>() * VSTR);
-#pragma unroll 2
-        for (int t4 = 0; t4 < KT / 32; ++t4) {
-            const int qbase = st * KT + t4 * 32;
-            if (qbase >= ng) break;
-            const int qq = t4 * 32 + l32;   // the stage row this lane reads as an A operand (a query)
-            f32x16 s = {0}, dp = {0};
+    const int nst = (ng + SR - 1) / SR, ntile = (ng + 31) >> 5;
+    int krow[KTW];
+    size_t krd[KTW];
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                const int c = 2 * ks + hf;
-                const int cs = c ^ ((qq >> SWZ_SHIFT) & (NC - 1));
-                U4 qf, gf;
-                qf.u = *reinterpret_cast<const uint4*>(&sQ[qq * D + cs * 8]);
-                gf.u = *reinterpret_cast<const uint4*>(&sG[qq * D + cs * 8]);
-                s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf.b, khi[ks].b, s, 0, 0, 0);
-                s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf.b, klo[ks].b, s, 0, 0, 0);
-                dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(gf.b, vfr[ks].b, dp, 0, 0, 0);
-            }
-            {   // subtract every query's log-sum-exp from its score row and its D from its dP row on the matrix core
-                U4 xf;
-                xf.u = sX[qq];
-                s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf.b, negS.b, s, 0, 0, 0);
-                dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf.b, negD.b, dp, 0, 0, 0);
-            }
-            U4 qt0, qt1, gt0, gt1;
-            qt0.u = *reinterpret_cast<const uint4*>(&sQT[t4 * 32]);
-            qt1.u = *reinterpret_cast<const uint4*>(&sQT[t4 * 32 + 16]);
-            gt0.u = *reinterpret_cast<const uint4*>(&sGT[t4 * 32]);
-            gt1.u = *reinterpret_cast<const uint4*>(&sGT[t4 * 32 + 16]);
-            // P = 2^(score - lse), dS = P o (dP - D)
-            f32x16 p;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                p[r] = __builtin_amdgcn_exp2f(s[r]);
-                s[r] = p[r] * dp[r];
-            }
-            union { uint32_t u[4]; bf16x8 b; } pb0, pb1, sb0, sb1;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                pb0.u[e] = pack_bf16(p[2 * e], p[2 * e + 1]);
-                pb1.u[e] = pack_bf16(p[8 + 2 * e], p[8 + 2 * e + 1]);
-                sb0.u[e] = pack_bf16(s[2 * e], s[2 * e + 1]);
-                sb1.u[e] = pack_bf16(s[8 + 2 * e], s[8 + 2 * e + 1]);
-            }
-            dv = __builtin_amdgcn_mfma_f32_32x32x16_bf16(gt0.b, pb0.b, dv, 0, 0, 0);
-            dv = __builtin_amdgcn_mfma_f32_32x32x16_bf16(gt1.b, pb1.b, dv, 0, 0, 0);
-            dk = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qt0.b, sb0.b, dk, 0, 0, 0);
-            dk = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qt1.b, sb1.b, dk, 0, 0, 0);
-        }
-        if (st + 1 < nst) store_stage(buf ^ 1);
-        __syncthreads();
+    for (int j = 0; j < KTW; ++j) {
+        const int xk = sc.blk * BM + (wave * KTW + j) * 32 + l32;
+        krow[j] = xk < ng ? seg_row_of(sm, seg_pre, seg_row0, xk) : -1;
+        const int r = max(krow[j], 0);                // past the end: some valid row, never stored
+        krd[j] = (size_t)(a.perm ? a.perm[r] : r);
     }
-    store_grad_rows<D>(b.dk, a.out_perm, krow, a.C, hoff, hf, dk, b.scale);
-    store_grad_rows<D>(b.dv, a.out_perm, krow, a.C, hoff, hf, dv, 1.0f);
+    fetch_rows(0);
+    dma_stage(0);
+    if (nst > 1) {
+        fetch_rows(1);
+        dma_stage(1);
+    }
+    if (nst > 2) fetch_rows(2);
+
+    // ---- this lane's keys: k (scaled, split) and v fragments
+    U4 khi[KTW][KS], klo[KTW][KS], vfr[KTW][KS];
+    U4 negS, negD;   // B operands with -1 at the positions of a staged row's log-sum-exp pair / D pair
+    negS.u = make_uint4(hf == 0 ? 0xBF80BF80u : 0u, 0, 0, 0);
+    negD.u = make_uint4(0, hf == 0 ? 0xBF80BF80u : 0u, 0, 0);
+#pragma unroll
+    for (int j = 0; j < KTW; ++j) {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            U4 kf;
+            kf.u = *reinterpret_cast<const uint4*>(a.k + krd[j] * a.C + hoff + ks * 16 + hf * 8);
+            vfr[j][ks].u = *reinterpret_cast<const uint4*>(a.v + krd[j] * a.C + hoff + ks * 16 + hf * 8);
+            scale_split(kf, a.c_log2, khi[j][ks], klo[j][ks]);
+        }
+    }
+
+    // ---- this lane's fragment addresses inside a buffer
+    uint32_t foff[KS];                                // row l32 of a tile, dims 16*ks + 8*hf ..
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+        const int c = 2 * ks + hf;
+        foff[ks] = (l32 * NC + ((NC == 4) ? (c ^ ((l32 >> 2) & 3)) : (c ^ ((l32 >> 3) & 1)))) * 16;
+    }
+    uint32_t tre, tro;
+    tr_offsets<D>(lane, tre, tro);
+
+    f32x16 dk[KTW], dv[KTW];
+#pragma unroll
+    for (int j = 0; j < KTW; ++j) {
+        dk[j] = f32x16{0};
+        dv[j] = f32x16{0};
+    }
+
+    struct Rows { U4 q[KS], g[KS], x; };              // the A operands of one query tile's score products
+    auto read_rows = [&](Rows& f, uint32_t at, uint32_t xat) __attribute__((always_inline)) {   // tile at byte `at`, entries at `xat`
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            f.q[ks].u = lds_read16(sQ + at + foff[ks]);
+            f.g[ks].u = lds_read16(sG + at + foff[ks]);
+        }
+        const u32x2 e = *(const __attribute__((address_space(3))) u32x2*)(uintptr_t)(sX + xat + l32 * 8);
+        f.x.u = make_uint4(e.x, e.y, 0, 0);
+    };
+    // One unit of the pipeline: P = 2^s, dS = P o dp of the current tile (key tile j) and its dV^T, dK^T products, with
+    // the products of the NEXT tile (rows f, key tile jn) issued in between.
+    auto unit = [&](f32x16& s, f32x16& dp, int j, const U4& qt0, const U4& qt1, const U4& gt0, const U4& gt1, f32x16& sn, f32x16& dpn,
+                    const Rows& f, int jn) __attribute__((always_inline)) {
+        U4 pb, db;
+        F3D_SB();
+#pragma unroll
+        for (int r = 0; r < 4; ++r) s[r] = __builtin_amdgcn_exp2f(s[r]);
+        F3D_SB();
+        sn = mfma_bf16(f.x, negS, f32x16{0});
+        F3D_SB();
+#pragma unroll
+        for (int r = 4; r < 8; ++r) s[r] = __builtin_amdgcn_exp2f(s[r]);
+        F3D_SB();
+        sn = mfma_bf16(f.q[0], khi[jn][0], sn);
+        F3D_SB();
+#pragma unroll
+        for (int e = 0; e < 4; ++e) (&pb.u.x)[e] = pack_bf16(s[2 * e], s[2 * e + 1]);
+#pragma unroll
+        for (int r = 8; r < 10; ++r) s[r] = __builtin_amdgcn_exp2f(s[r]);
+        F3D_SB();
+        dv[j] = mfma_bf16(gt0, pb, dv[j]);
+        F3D_SB();
+#pragma unroll
+        for (int r = 10; r < 12; ++r) s[r] = __builtin_amdgcn_exp2f(s[r]);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) dp[r] *= s[r];
+        F3D_SB();
+        sn = mfma_bf16(f.q[0], klo[jn][0], sn);
+        F3D_SB();
+#pragma unroll
+        for (int r = 4; r < 8; ++r) dp[r] *= s[r];
+        s[12] = __builtin_amdgcn_exp2f(s[12]);
+        F3D_SB();
+        dpn = mfma_bf16(f.x, negD, f32x16{0});
+        F3D_SB();
+#pragma unroll
+        for (int e = 0; e < 4; ++e) (&db.u.x)[e] = pack_bf16(dp[2 * e], dp[2 * e + 1]);
+        F3D_SB();
+        dk[j] = mfma_bf16(qt0, db, dk[j]);
+        F3D_SB();
+#pragma unroll
+        for (int r = 13; r < 16; ++r) s[r] = __builtin_amdgcn_exp2f(s[r]);
+        F3D_SB();
+        if (KS == 2) sn = mfma_bf16(f.q[KS - 1], khi[jn][KS - 1], sn);
+        F3D_SB();
+#pragma unroll
+        for (int e = 0; e < 4; ++e) (&pb.u.x)[e] = pack_bf16(s[8 + 2 * e], s[8 + 2 * e + 1]);
+        F3D_SB();
+        dv[j] = mfma_bf16(gt1, pb, dv[j]);
+        F3D_SB();
+#pragma unroll
+        for (int r = 8; r < 12; ++r) dp[r] *= s[r];
+        F3D_SB();
+        if (KS == 2) sn = mfma_bf16(f.q[KS - 1], klo[jn][KS - 1], sn);
+        F3D_SB();
+#pragma unroll
+        for (int r = 12; r < 16; ++r) dp[r] *= s[r];
+        F3D_SB();
+        dpn = mfma_bf16(f.g[0], vfr[jn][0], dpn);
+        F3D_SB();
+#pragma unroll
+        for (int e = 0; e < 4; ++e) (&db.u.x)[e] = pack_bf16(dp[8 + 2 * e], dp[8 + 2 * e + 1]);
+        F3D_SB();
+        dk[j] = mfma_bf16(qt1, db, dk[j]);
+        F3D_SB();
+        if (KS == 2) dpn = mfma_bf16(f.g[KS - 1], vfr[jn][KS - 1], dpn);
+        F3D_SB();
+    };
+    // Hands stage st+1 over to the readers and refills the buffer of stage st-1 with stage st+2: every wave waits for its
+    // own loads of stage st+1 (issued a stage ago) and meets the others; whoever arrives has read the last of stage st-1.
+    // The rows' log-sum-exp and D are written behind the barrier, one whole stage before they are read.
+    auto handover = [&](int st) __attribute__((always_inline)) {
+        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+        __syncthreads();
+        if (st + 2 < nst) {
+            dma_stage((st + 2) % L::NBUF);
+            if (st + 3 < nst) fetch_rows(st + 3);
+        }
+    };
+
+    __builtin_amdgcn_s_waitcnt(0x0F70);       // stages 0 and 1 have landed for every wave
+    __syncthreads();
+
+    f32x16 sa, sb, da, db;
+    Rows f;
+    read_rows(f, 0, 0);
+    sa = mfma_bf16(f.x, negS, f32x16{0});
+    da = mfma_bf16(f.x, negD, f32x16{0});
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+        sa = mfma_bf16(f.q[ks], khi[0][ks], sa);
+        sa = mfma_bf16(f.q[ks], klo[0][ks], sa);
+        da = mfma_bf16(f.g[ks], vfr[0][ks], da);
+    }
+    if (KTW == 1) read_rows(f, L::TILE, 32 * 8);
+    int bufi = 0;
+    for (int st = 0; st < nst; ++st) {
+        const int bufn = bufi + 1 == L::NBUF ? 0 : bufi + 1;
+#pragma unroll
+        for (int t4 = 0; t4 < 4; ++t4) {
+            if (4 * st + t4 >= ntile) break;          // the products computed ahead of the last tile are never used
+            const uint32_t at = bufi * L::BUF + t4 * L::TILE;
+            U4 qt0, qt1, gt0, gt1;
+            read_tr<D>(gt0, gt1, sG + at + tre, sG + at + tro);
+            read_tr<D>(qt0, qt1, sQ + at + tre, sQ + at + tro);
+            if (KTW == 1) {                           // the score registers alternate from one query tile to the next
+                Rows fn;
+                read_rows(fn, t4 < 2 ? at + 2 * L::TILE : bufn * L::BUF + (t4 - 2) * L::TILE,
+                          (t4 < 2 ? bufi * SR + (t4 + 2) * 32 : bufn * SR + (t4 - 2) * 32) * 8);
+                if ((t4 & 1) == 0) unit(sa, da, 0, qt0, qt1, gt0, gt1, sb, db, f, 0);
+                else unit(sb, db, 0, qt0, qt1, gt0, gt1, sa, da, f, 0);
+                f = fn;
+            } else {                                  // a is key tile 0, b key tile 1 of the same query tile
+                unit(sa, da, 0, qt0, qt1, gt0, gt1, sb, db, f, KTW - 1);
+                read_rows(f, t4 < 3 ? at + L::TILE : bufn * L::BUF, (t4 < 3 ? bufi * SR + (t4 + 1) * 32 : bufn * SR) * 8);
+                unit(sb, db, KTW - 1, qt0, qt1, gt0, gt1, sa, da, f, 0);
+            }
+            if (t4 == 1) handover(st);
+        }
+        bufi = bufn;
+    }
+#pragma unroll
+    for (int j = 0; j < KTW; ++j) {
+        store_grad_rows<D>(b.dk, a.out_perm, krow[j], a.C, hoff, hf, dk[j], b.scale);
+        store_grad_rows<D>(b.dv, a.out_perm, krow[j], a.C, hoff, hf, dv[j], 1.0f);
+    }
 }
 
 template <int D>
 hipError_t launch_d(const AttnBwdArgs& b, hipStream_t stream)
 {
     const AttnArgs& a = b.f;
-    const long long rows = (long long)a.n * a.H;
-    if (rows > 0) k_attn_bwd_pre<<<(unsigned)((rows + 255) / 256), 256, 0, stream>>>(b, D);
-    const size_t lds_dq = (size_t)2 * (2 * KT * D + trows<D>() * VSTR) * 2;
-    constexpr int KB = dkdv_stage_rows<D>();
-    const size_t lds_kv = (size_t)2 * (2 * KB * D + 2 * trows<D>() * (KB + 8) + 8 * KB) * 2;
-    hipError_t e = hipFuncSetAttribute((const void*)k_attn_bwd_dq<D>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_dq);
-    if (e != hipSuccess) return e;
-    e = hipFuncSetAttribute((const void*)k_attn_bwd_dkdv<D>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_kv);
-    if (e != hipSuccess) return e;
     long long total = (long long)a.n_slots * a.H * a.qblocks;
     total = (total + 7) / 8 * 8;
-    if (total > 0) k_attn_bwd_dq<D><<<(unsigned)total, 256, lds_dq, stream>>>(b);
+    if (total > 0) {
+        if (b.tiles == 2) k_attn_bwd_dq<D, 2><<<(unsigned)total, 256, 0, stream>>>(b);
+        else k_attn_bwd_dq<D, 1><<<(unsigned)total, 256, 0, stream>>>(b);
+    }
     total = (long long)a.n_slots * a.H * b.kblocks;
     total = (total + 7) / 8 * 8;
-    if (total > 0) k_attn_bwd_dkdv<D><<<(unsigned)total, 256, lds_kv, stream>>>(b);
+    if (total > 0) {
+        if (b.tiles == 2) k_attn_bwd_dkdv<D, 2><<<(unsigned)total, 256, 0, stream>>>(b);
+        else k_attn_bwd_dkdv<D, 1><<<(unsigned)total, 256, 0, stream>>>(b);
+    }
     return hipGetLastError();
 }
 

@@ -16,10 +16,12 @@ typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+typedef __attribute__((ext_vector_type(4))) short s16x4;
 
-constexpr int KT = 128;         // key rows per LDS stage
-constexpr int VSTR = KT + 8;    // row pitch of V^T in LDS (elements); keeps 16-byte alignment, staggers banks
+#define F3D_SB() __builtin_amdgcn_sched_barrier(0)
+
 constexpr int MAXSEG = 16;
 
 union U4 {
@@ -65,6 +67,28 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
     f32x2 x = {lo, hi};
     bf16x2 y = __builtin_convertvector(x, bf16x2);  // v_cvt_pk_bf16_f32, round to nearest even
     return *reinterpret_cast<uint32_t*>(&y);
+}
+
+// One 16-byte global -> LDS load per lane: lane i of the wave fills bytes [16 i, 16 i + 16) of the 1 KB block at the
+// LDS byte address `lds` (wave-uniform; it travels in M0). Written as assembly so that the compiler does not count
+// it among its own memory operations: it would otherwise wait for ALL loads in flight before every LDS read that
+// follows, and the loads issued here are meant to stay in flight for a whole stage. The kernel waits for them itself
+// (s_waitcnt vmcnt(0) before the barrier that hands a stage over).
+__device__ __forceinline__ void lds_dma16(const void* g, uint32_t lds)
+{
+    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(g) : "memory", "m0");
+}
+
+__device__ __forceinline__ uint2 lds_read_tr(uint32_t addr)
+{
+    const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(uintptr_t)addr);
+    return *reinterpret_cast<const uint2*>(&v);
+}
+
+__device__ __forceinline__ uint4 lds_read16(uint32_t addr)
+{
+    const u32x4 v = *(const __attribute__((address_space(3))) u32x4*)(uintptr_t)addr;
+    return make_uint4(v.x, v.y, v.z, v.w);
 }
 
 // Row segments of scope g of a scan (first bucket kb0, K buckets): one run for plain and shifted scopes, up to m

@@ -483,9 +483,12 @@ int f3d_bucket_swin_attn_bwd(const void* q, const void* k, const void* v, const 
     b.dk = (uint16_t*)dk;
     b.dv = (uint16_t*)dv;
     b.scale = scale;
-    b.f.qblocks = (bucket_cap + 127) / 128;
-    b.kblocks = b.f.qblocks;
-    if (slots * heads * b.f.qblocks > 2000000000ll) return F3D_ERR_UNSUPPORTED;
+    if (slots * heads * ((bucket_cap + 127) / 128) > 2000000000ll) return F3D_ERR_UNSUPPORTED;
+    // two tiles per wave share every staged row; one where a scope is short or the launch would leave compute units
+    // without a workgroup (the forward kernel's rule)
+    b.tiles = f3d::attn_block_rows(head_dim, slots, heads, bucket_cap) / 128;
+    b.kblocks = (bucket_cap + 128 * b.tiles - 1) / (128 * b.tiles);
+    b.f.qblocks = b.kblocks;
     b.f.n_slots = (int)slots;
     (void)hipGetLastError();
     const hipError_t e = f3d::attn_bwd_launch(b, head_dim, (hipStream_t)stream);

@@ -890,6 +890,23 @@ def test_attention_backward_full_size_sampled_scopes(name):
         bwd_case(q, k, v, g, bk, ref, w.heads, w.head_dim, mode, not bucket_major, scope_sel=sel)
 
 
+@pytest.mark.parametrize("d,heads", [(16, 4), (32, 3)])
+def test_attention_backward_two_tiles_per_wave_ragged(d, heads):
+    # enough workgroups for two row tiles per wave, last buckets around the 32-row tile, 128-row stage and 256-row block
+    tails = [1, 31, 32, 33, 64, 95, 96, 97, 127, 128]
+    sizes = [[128] * (2 + i % 4) + [tails[i % len(tails)]] for i in range(40)]
+    bk, ref, n = hand_layout(sizes, 512, 4)
+    rng = np.random.default_rng(64)
+    q, k, v, g = (wl.f32_to_bf16_bits(rng.standard_normal((n, heads * d)).astype(np.float32)) for _ in range(4))
+    sel = np.zeros(n, dtype=np.uint8)
+    ends = np.cumsum([sum(x) for x in sizes])
+    sel[ends[:10] - 1] = 1                       # the last scope of ten scans, and a whole one
+    sel[0] = 1
+    for mode in ("plain", "shift", "stride"):
+        assert f3d.attn_block_rows(bk, heads, d, mode) == 256
+        bwd_case(q, k, v, g, bk, ref, heads, d, mode, mode != "shift", scope_sel=sel)
+
+
 def test_attention_backward_short_scopes_with_peaked_softmax():
     """Where a flat bound on the gradient error fails: scopes of a few dozen rows with a peaked softmax, in which the
     rounding of the stored output moves D by an amount common to all keys of a row. (a) 27218 points in four uneven
