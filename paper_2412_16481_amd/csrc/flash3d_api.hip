@@ -278,6 +278,8 @@ static int bucketize_on(const Plan& pl, char* ws, const float* coords, const int
     const bool fast_ok = f3d::psh_fast_eligible(pl.max_scan_points, pl.kcap);
     int schedule = p->schedule;
     if (schedule == F3D_SCHEDULE_SCANS && !pl.scans) return F3D_ERR_UNSUPPORTED;
+    // scans whose points fit the registers of a workgroup (see psh_small.hip)
+    const bool small = schedule == F3D_SCHEDULE_AUTO && f3d::psh_small_eligible(n, pl.max_scan_points, pl.kcap);
     if (pl.scans) schedule = F3D_SCHEDULE_SCANS;
     if (schedule == F3D_SCHEDULE_AUTO) schedule = fast_ok ? F3D_SCHEDULE_STEPS : F3D_SCHEDULE_GENERAL;
     if (schedule == F3D_SCHEDULE_STEPS && !fast_ok) return F3D_ERR_UNSUPPORTED;
@@ -304,7 +306,9 @@ static int bucketize_on(const Plan& pl, char* ws, const float* coords, const int
         a.inv_perm = (int32_t*)(ws + pl.o_inv);
     }
     hipError_t e;
-    if (schedule == F3D_SCHEDULE_SCANS)
+    if (small)
+        e = f3d::psh_small_launch(a, (hipStream_t)stream);
+    else if (schedule == F3D_SCHEDULE_SCANS)
         e = f3d::psh_scan_launch(a, (int32_t*)(ws + pl.o_lidx0), (int32_t*)(ws + pl.o_lidx1), (unsigned long long*)(ws + pl.o_lvox0),
                                  (unsigned long long*)(ws + pl.o_lvox1), (hipStream_t)stream);
     else

@@ -59,6 +59,8 @@ hipError_t psh_launch(const PshArgs& args, hipStream_t stream);       // any siz
 hipError_t psh_fast_launch(const PshArgs& args, hipStream_t stream);  // small count matrix
 hipError_t psh_scan_launch(const PshArgs& args, int32_t* lidx0, int32_t* lidx1, unsigned long long* lvox0,
                            unsigned long long* lvox1, hipStream_t stream);    // one workgroup per scan: batches of many scans
+hipError_t psh_small_launch(const PshArgs& args, hipStream_t stream); // one workgroup per scan, points in registers
+bool psh_small_eligible(long long n, long long max_scan_points, int kcap);
 bool psh_scan_eligible(int kcap);
 bool psh_fast_eligible(long long max_scan_points, int kcap);
 size_t psh_fast_matrix_bytes(long long n, int n_scans, int kcap);

@@ -214,14 +214,14 @@ __device__ __forceinline__ unsigned long long udiv63_small(unsigned long long z,
     return (q2 << 42) + (q1 << 21) + q0;
 }
 
-// hash setting of scan b from its bounding box (ordered-int encoding: min xyz at [0..2], max xyz at [4..6])
-// and the scan tables
-__device__ inline void compute_cfg(const PshArgs& a, int b, const uint32_t* box, ScanCfg& c)
+// hash setting of a scan (first point, points, first bucket, buckets) from its bounding box (ordered-int encoding:
+// min xyz at [0..2], max xyz at [4..6])
+__device__ inline void compute_cfg_of(const PshArgs& a, int p0, int nb, int kb0, int nk, const uint32_t* box, ScanCfg& c)
 {
-    c.p0 = a.scan_p0[b];
-    c.nb = a.scan_p0[b + 1] - c.p0;
-    c.kb0 = a.sbs[b];
-    c.K = a.sbs[b + 1] - c.kb0;
+    c.p0 = p0;
+    c.nb = nb;
+    c.kb0 = kb0;
+    c.K = nk;
     c.lastcap = c.nb - (c.K - 1) * a.S;
     int vm = 0;
     for (int ax = 0; ax < 3; ++ax) {
@@ -247,6 +247,13 @@ __device__ inline void compute_cfg(const PshArgs& a, int b, const uint32_t* box,
     if (a.hash == 3) step = 1ll << ((bit_width64(D) + 2) / 3);
     if (a.step > 0) step = a.step;
     c.step = (int)step;
+}
+
+// the same for scan b of the scan tables
+__device__ inline void compute_cfg(const PshArgs& a, int b, const uint32_t* box, ScanCfg& c)
+{
+    const int p0 = a.scan_p0[b], kb0 = a.sbs[b];
+    compute_cfg_of(a, p0, a.scan_p0[b + 1] - p0, kb0, a.sbs[b + 1] - kb0, box, c);
 }
 
 __device__ __forceinline__ int wave_incl_scan(int v, int lane)

@@ -138,6 +138,22 @@ def test_bucketize_one_workgroup_per_scan_is_refused_above_1024_buckets_per_scan
     assert e.value.code == f3d.ERR_UNSUPPORTED
 
 
+@pytest.mark.parametrize("hash", HASHES)
+def test_bucketize_small_scans_in_registers(hash):
+    # scans that fit one workgroup's registers: around a wave, a workgroup, and one past the last (another path); clustered
+    # points (most are left over) and uniform ones (closed up early); single scans (one launch) and batches with empty
+    # and one-point scans
+    rng = np.random.default_rng(31)
+    for n in (1, 63, 64, 65, 1023, 1024, 1025, 2049, 4095, 4096, 4097):
+        c = clustered_cloud(rng, n)
+        check_bucketize(c, None, 0.05, 64 if n != 4095 else 192, 4, hash, n_probes=(n % 7))
+        check_bucketize((rng.random((n, 3)) * 4.0).astype(np.float32), None, 0.02, 128, 4, hash)
+    bo = np.array([0, 0, 1, 4097, 4097, 7000, 9049, 9050, 9050], dtype=np.int32)
+    c = np.concatenate([clustered_cloud(rng, int(k), float(i)) for i, k in enumerate(np.diff(bo)) if k])
+    for order, probe_mode in (("index", "axes"), ("canonical", "seeded")):
+        check_bucketize(c, bo, 0.05, 128, 4, hash, max_scan_points=4096, order=order, probe_mode=probe_mode, probe_seed=5)
+
+
 @pytest.mark.parametrize("schedule", ["general", "steps", "scans"])
 def test_bucketize_probe_offsets_at_the_limits_of_int32(schedule):
     """A probe step or a table offset of any size is legal: the moved voxel is clamped to the scan's voxel box."""
