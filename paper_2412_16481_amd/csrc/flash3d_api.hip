@@ -64,7 +64,7 @@ struct Plan {
     // offsets (bytes) of the workspace arrays
     size_t o_status, o_p0, o_c0, o_mm, o_cnt, o_cnt2, o_hist, o_key, o_left, o_leftpre, o_freepre, o_inv, o_rc, o_cfg, o_done, o_ci, o_mmpart;
     // canonical order only
-    size_t o_obox, o_owords, o_oidx0, o_oidx1, o_ohist, o_ocoords, o_operm;
+    size_t o_obox, o_okeys, o_oidx0, o_oidx1, o_ocoords, o_operm;
     // one workgroup per scan only: the two lists of points still unplaced (index, packed voxel)
     bool scans;
     size_t o_lidx0, o_lidx1, o_lvox0, o_lvox1;
@@ -144,10 +144,9 @@ void make_plan(int64_t n, int32_t n_scans, const f3d_params* p, Plan* pl)
     pl->o_inv = take((size_t)n * 4);
     if (p->order == F3D_ORDER_CANONICAL) {
         pl->o_obox = take((size_t)n_scans * 16);
-        pl->o_owords = take((size_t)n * 24);
+        pl->o_okeys = take((size_t)n * 24);
         pl->o_oidx0 = take((size_t)n * 4);
         pl->o_oidx1 = take((size_t)n * 4);
-        pl->o_ohist = take(f3d::order_hist_bytes(n));
         pl->o_ocoords = take((size_t)n * 12);
         pl->o_operm = take((size_t)n * 4);
     }
@@ -294,10 +293,9 @@ static int bucketize_on(const Plan& pl, char* ws, const float* coords, const int
         o.n_scans = n_scans;
         o.inv_voxel = a.inv_voxel;
         o.box = (uint32_t*)(ws + pl.o_obox);
-        o.words = (uint32_t*)(ws + pl.o_owords);
+        o.keys = (unsigned long long*)(ws + pl.o_okeys);
         o.idx[0] = (int32_t*)(ws + pl.o_oidx0);
         o.idx[1] = (int32_t*)(ws + pl.o_oidx1);
-        o.hist = (uint32_t*)(ws + pl.o_ohist);
         o.coords_sorted = (float*)(ws + pl.o_ocoords);
         const hipError_t eo = f3d::order_launch(o, &order, (hipStream_t)stream);
         if (eo != hipSuccess) return hip_fail(eo);

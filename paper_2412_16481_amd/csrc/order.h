@@ -14,13 +14,10 @@ struct OrderArgs {
     float inv_voxel;
     // workspace
     uint32_t* box;      // [n_scans][4] per-scan minimum as ordered ints (word 3 unused)
-    uint32_t* words;    // [6][n] key words: z, y, x (ordered ints), Z-order code low and high word, scan
+    unsigned long long* keys;  // [n][3] sort keys
     int32_t* idx[2];    // [n] each: ping-pong buffers of the sort
-    uint32_t* hist;     // [tiles][256]
     float* coords_sorted;  // [n,3] (out)
 };
-
-size_t order_hist_bytes(long long n);
 
 // Sorts the points by (scan, Z-order code of the voxel, x, y, z, input index) and writes the coordinates in that
 // order. Returns in *order_out the buffer (one of idx[0], idx[1]) that holds the input index of every sorted position.

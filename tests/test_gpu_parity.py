@@ -64,6 +64,18 @@ def test_bucketize_matches_oracle_on_workloads(name, hash):
     check_bucketize(w.coords, w.batch_offsets, w.voxel_size, w.bucket_cap, w.scope_buckets, hash)
 
 
+@pytest.mark.parametrize("n", [1, 2, 2047, 2048, 2049, 4096, 4097, 6145, 8193, 12289])
+def test_bucketize_canonical_order_at_sort_tile_edges(n):
+    # sizes around the sort's tiles and runs (an odd run without a partner among them), a lattice with many equal points
+    # (ties by index), signed coordinates, and one voxel for everything (the coordinates decide)
+    rng = np.random.default_rng(32)
+    lattice = rng.integers(-3, 4, (n, 3)).astype(np.float32) * np.float32(0.25)
+    check_bucketize(lattice, None, 0.5, 128, 4, "zorder_div", order="canonical")
+    check_bucketize((rng.random((n, 3)) - 0.5).astype(np.float32), None, 16.0, 256, 4, "xor_mod", order="canonical")
+    bo = np.array([0, n // 3, n // 3, n], dtype=np.int32)
+    check_bucketize(clustered_cloud(rng, n), bo, 0.05, 128, 4, "zorder_mod", order="canonical")
+
+
 @pytest.mark.parametrize("schedule", ["general", "steps", "scans"])
 @pytest.mark.parametrize("name,hash", [("tiny", "xor_mod"), ("indoor", "zorder_div"), ("indoor", "xor_div"), ("lidar4", "zorder_mod")])
 def test_bucketize_every_schedule_gives_the_oracle_result(name, hash, schedule):
