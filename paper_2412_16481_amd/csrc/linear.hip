@@ -7,145 +7,147 @@
 //
 // One workgroup = 4 waves = 128 rows; a wave owns 32 rows and keeps them in registers for the whole kernel, in the
 // layout of the B operand of v_mfma_f32_32x32x16_bf16 (a lane holds half of one row), normalised there and rounded
-// to bf16. The weight matrix (resident in L2) streams through LDS in double-buffered tiles of 16 KB, loaded with whole
-// rows per wave (coalesced) once per workgroup, and is the A operand of the TRANSPOSED product Y^T = W X^T: a lane
-// then owns one row of Y and, with the rows of W stored in a suitable order, 16 consecutive columns of it: 16-byte
-// stores, no shuffles.
+// to bf16. The weight matrix (resident in L2) streams through LDS in double-buffered tiles of 16 KB filled by
+// global -> LDS loads a tile ahead, and is the A operand of the TRANSPOSED product Y^T = W X^T: a lane then owns one row of Y and, with
+// the rows of W fetched in a suitable order, 16 consecutive columns of it: 16-byte stores, no shuffles. The bias is the
+// accumulator the product starts from.
+//
+// No wait inside the tile loop may drain the stores: the memory counter retires in order, so the one wait per tile (for
+// the next tile's loads, and the next residual) allows the stores issued behind them to stay in flight.
+//
+// Bound: HBM, mostly the writes. The workgroups of an XCD keep more output rows open (6 MB at 256 channels) than its L2
+// holds, so a line that is written in two halves a tile apart leaves L2 half full: pairs of 32-column blocks are stored
+// together, whole lines per instruction (914601 rows, 256 -> 3 x 256: WRITE_SIZE 1.60 -> 1.37 GB = what there is to write).
+// Measured at 900000 rows, LayerNorm + q, k, v map / output map with residual: 256 channels 649 -> 541 / 296 -> 250 us, 128
+// 261 -> 216 / 134 -> 116, 64 128 -> 91 / 46 -> 47. A third resident tile and 256 rows per workgroup were no faster.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "attn_common.h"
 #include "linear.h"
 
 namespace f3d {
 
 namespace {
 
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(2))) float f32x2;
-
-union F8 {
-    uint4 u;
-    bf16x8 b;
-};
-
-__device__ __forceinline__ uint32_t pack2(float lo, float hi)
-{
-    f32x2 x = {lo, hi};
-    bf16x2 y = __builtin_convertvector(x, bf16x2);
-    return *reinterpret_cast<uint32_t*>(&y);
-}
 __device__ __forceinline__ float lo16(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float hi16(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
+
+// lds_dma16 with a scalar base and a 32-bit byte offset per lane
+__device__ __forceinline__ void lds_dma16_from(const void* base, uint32_t off, uint32_t lds)
+{
+    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory", "m0");
+}
+
+// s_waitcnt operand that waits for the memory counter alone
+constexpr int vmcnt_imm(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }
 
 constexpr int LNW = 4;          // waves per workgroup; a wave owns 32 rows
 constexpr int LTH = LNW * 64;
 constexpr int LBM = LNW * 32;   // rows per workgroup
 
-// W tiles in LDS: 32 * TCB output columns x CI inputs, TCB chosen so that a tile is 1024 16-byte pieces (16 KB) and a
-// wave runs 16 MFMAs per tile and barrier whatever the width.
+// W tiles in LDS: 32 * TCB output columns x CI inputs: 16 KB and 16 MFMAs per wave and barrier at 128 and 256 inputs, 8 KB at
+// 64 (c_out is a multiple of 64, so every tile is whole). Row-major, the pieces of a row xor-swizzled so that 16
+// consecutive rows read at one column fall on different banks.
 template <int CI>
 struct Tile {
-    static constexpr int TCB = 256 / CI;            // 32-column blocks per tile
+    static constexpr int TCB = CI == 256 ? 1 : 2;   // 32-column blocks per tile
     static constexpr int TROWS = 32 * TCB;          // rows of W (output columns) per tile
-    static constexpr int PITCH = CI + 8;            // elements; the 16-byte pad staggers the banks of consecutive rows
-    static constexpr size_t LDS_BYTES = (size_t)2 * TROWS * PITCH * 2;
+    static constexpr int CPR = CI / 8;              // 16-byte pieces per row of W
+    static constexpr int BYTES = TROWS * CI * 2;
+    static constexpr int PPT = TROWS * CPR / LTH;   // pieces per thread and tile
+    static_assert(TROWS * CPR % LTH == 0 && BYTES % 1024 == 0, "a W tile is a whole number of pieces per thread");
+    static __device__ __forceinline__ int swizzle(int row) { return CPR >= 16 ? (row & 15) : ((row >> 1) & 7); }
 };
 
-template <int CI>
+// LN: LayerNorm in front of the map; RES: a residual is added behind it
+template <int CI, bool LN, bool RES>
 __global__ __launch_bounds__(LTH, 3) void k_ln_linear(LinearArgs a)
 {
+    using T = Tile<CI>;
     constexpr int KS = CI / 16;                     // MFMA k-steps
-    constexpr int TCB = Tile<CI>::TCB, TROWS = Tile<CI>::TROWS, PITCH = Tile<CI>::PITCH;
-    constexpr int CPR = CI / 8;                     // 16-byte pieces per row of W
-    constexpr int PPT = TROWS * CPR / LTH;          // pieces per thread and tile (4)
-    static_assert(TROWS * CPR % LTH == 0, "a W tile is a whole number of pieces per thread");
-    extern __shared__ __attribute__((aligned(16))) uint16_t sw[];   // [2][TROWS][PITCH], then binary32 bias [c_out], scale [CI], shift [CI]
-    float* sbias = reinterpret_cast<float*>(sw + 2 * TROWS * PITCH);   // [c_out], zeros without a bias
-    float* sgamma = sbias + a.c_out;                                  // [CI] LayerNorm scale
-    float* sbeta = sgamma + CI;                                       // [CI] LayerNorm shift, zeros without one
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    constexpr int TCB = T::TCB, TROWS = T::TROWS, CPR = T::CPR, PPT = T::PPT;
+    __shared__ __attribute__((aligned(1024))) unsigned char sw[2 * T::BYTES];
+    __shared__ uint4 sy[LNW][256];                  // 32 x 64 results per wave, on their way from one row per lane to whole lines
+    float* sgamma = reinterpret_cast<float*>(sy);   // first: LayerNorm scale and shift
+    float* sbeta = sgamma + CI;
+    extern __shared__ __attribute__((aligned(16))) float sbias[];   // [c_out], zeros without a bias; then the column table
+    // where the 16 columns from 16 g on go: their output tensor's address advanced to the first of them
+    uint16_t** stab = reinterpret_cast<uint16_t**>(sbias + a.c_out);
+    const uint32_t lds_w = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)sw;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, hf = lane >> 5;
     const long long p = (long long)blockIdx.x * LBM + wave * 32 + l32;   // this lane's row of Y
     const bool ok = p < a.n;
-    const int n_cb = a.c_out >> 5;                  // 32-column blocks of the output
-    const int n_tiles = (n_cb + TCB - 1) / TCB;
+    const bool stores = (long long)blockIdx.x * LBM + wave * 32 + 24 < a.n;   // every store instruction of this wave has a row
+    const int n_tiles = (a.c_out >> 5) / TCB;
+    // few rows: the columns are split over the grid's second dimension
+    constexpr int UT = 2 / TCB;                     // tiles of a pair of blocks, which is stored together
+    const int units = n_tiles / UT;
+    const int t_begin = units * (int)blockIdx.y / (int)gridDim.y * UT, t_end = units * ((int)blockIdx.y + 1) / (int)gridDim.y * UT;
 
-    // ---- staging of W tiles: global -> registers (coalesced: whole rows of W) -> LDS. Row j of a 32-row block is
-    //      stored at slot 8*((j>>2)&3) + 4*(j>>4) + (j&3), so that MFMA row i holds output column
-    //      16*((i>>2)&1) + 4*(i>>3) + (i&3) of the block: with this order the 16 accumulator registers of a lane are 16
-    //      CONSECUTIVE columns of its row (two 16-byte stores; the two half-waves of a row write 64 contiguous bytes).
-    struct WTile { uint4 v[PPT]; } wreg;   // handled by value: a lambda that captures an array by reference can put it in scratch
-    const auto load_tile = [=](int t) __attribute__((always_inline)) -> WTile {
-        WTile r;
+    // ---- staging of W tiles. Load i of this lane fills piece (wave*PPT + i)*64 + lane of the tile: slot = piece / CPR, with
+    //      the piece of its row the swizzle puts there. Slot i of a 32-row block holds output column
+    //      16*((i>>2)&1) + 4*(i>>3) + (i&3): with this order the 16 accumulator registers of a lane are 16 CONSECUTIVE
+    //      columns of its row (two 16-byte stores; the two half-waves of a row write 64 contiguous bytes).
+    uint32_t woff[PPT];               // bytes from the first row of a tile
 #pragma unroll
-        for (int i = 0; i < PPT; ++i) {
-            const int q = tid + i * LTH;
-            const int j = q / CPR, c = q % CPR;
-            const int col = min(t * TROWS + j, a.c_out - 1);   // past the last column: some valid row, never used
-            r.v[i] = *reinterpret_cast<const uint4*>(a.w + (size_t)col * CI + 8 * c);
-        }
-        return r;
-    };
-    const auto store_tile = [=](int buf, const WTile r) __attribute__((always_inline)) {
-#pragma unroll
-        for (int i = 0; i < PPT; ++i) {
-            const int q = tid + i * LTH;
-            const int j = q / CPR, c = q % CPR;
-            const int jr = j & 31;
-            const int slot = (j & ~31) + 8 * ((jr >> 2) & 3) + 4 * (jr >> 4) + (jr & 3);
-            *reinterpret_cast<uint4*>(&sw[(size_t)buf * TROWS * PITCH + slot * PITCH + 8 * c]) = r.v[i];
-        }
-    };
-    // Everything the prologue reads from memory is requested before anything waits: the row index (the row loads depend
-    // on it), the first W tile, the per-column vectors, then the rows themselves.
-    const size_t src = ok ? (size_t)(a.row_in ? a.row_in[p] : p) : 0;
-    wreg = load_tile(0);
-    // the output tensors' addresses are kept in LDS: indexing the argument block inside the loop is a dependent load
-    // from memory per tile, in front of the tile's stores
-    __shared__ uint16_t* s_outs[LIN_MAX_OUTS];
-    if (tid == 0) {
-        s_outs[0] = a.outs[0];
-        s_outs[1] = a.outs[1];
-        s_outs[2] = a.outs[2];
-        s_outs[3] = a.outs[3];
+    for (int i = 0; i < PPT; ++i) {
+        const int q = (wave * PPT + i) * 64 + lane;
+        const int slot = q / CPR, c = (q % CPR) ^ T::swizzle(slot);
+        const int s32 = slot & 31;
+        const int col = (slot & ~31) + 16 * ((s32 >> 2) & 1) + 4 * (s32 >> 3) + (s32 & 3);
+        woff[i] = (uint32_t)(col * CI * 2 + c * 16);
     }
-    // The per-column vectors are read by every wave (the bias for every tile): they are kept in LDS, off the vector
-    // memory path, so that neither the LayerNorm nor an epilogue waits for a trip to memory. Loads in batches of four
-    // without per-element predicates (an index past the end re-reads the last element and is not written).
+    auto dma_tile = [&](int t, int buf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < PPT; ++i) {
+            lds_dma16_from(a.w, (uint32_t)(t * T::BYTES) + woff[i], lds_w + buf * T::BYTES + (wave * PPT + i) * 1024);
+        }
+    };
+    // Everything the prologue reads from memory is requested before anything waits.
+    const size_t src = ok ? (size_t)(a.row_in ? a.row_in[p] : p) : 0;
+    const size_t drow = ok ? (size_t)(a.row_out ? a.row_out[p] : p) : 0;   // a valid row also past the end
+    dma_tile(t_begin, 0);
     float gv = 0.f, bev = 0.f;
-    if (a.gamma) {
+    if (LN) {
         gv = a.gamma[min(tid, CI - 1)];
         if (a.beta) bev = a.beta[min(tid, CI - 1)];
     }
-    if (a.bias) {
-        for (int i0 = tid; i0 < a.c_out; i0 += 4 * LTH) {
-            float v[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = a.bias[min(i0 + u * LTH, a.c_out - 1)];
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (i0 + u * LTH < a.c_out) sbias[i0 + u * LTH] = v[u];
-        }
-    } else {
-        for (int i = tid; i < a.c_out; i += LTH) sbias[i] = 0.f;
-    }
-
-    // ---- this lane's part of its row: elements 16*ks + 8*hf .. +7 for every k-step, i.e. the B operand of the MFMAs.
-    //      The row stays in registers for the whole kernel.
-    F8 xf[KS];
+    // this lane's part of its row: elements 16*ks + 8*hf .. +7 for every k-step, i.e. the B operand of the MFMAs
+    U4 xf[KS];
     {
         const uint16_t* xr = a.x + src * CI + 8 * hf;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) xf[ks].u = *reinterpret_cast<const uint4*>(xr + 16 * ks);   // rows past the end read row 0 and are never stored
     }
-    if (a.gamma && tid < CI) {
+    const int per_out = a.c_out / a.n_outs;
+    // the results in LDS: eight 16-byte pieces per row, xor-swizzled by the row; of a pair of blocks this lane puts pieces
+    // 4 (block & 1) + 2 hf and + 1 of row l32, and stores piece lane & 7 of rows 8 k + (lane >> 3)
+    const int yput = l32 * 8 + ((2 * hf) ^ (l32 & 7)), yget = (lane >> 3) * 8 + ((lane & 7) ^ (lane >> 3));
+    int yrow[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) yrow[k] = __shfl(ok ? (int)drow : -1, 8 * k + (lane >> 3), 64);
+    for (int i = tid; i < a.c_out; i += LTH) sbias[i] = a.bias ? a.bias[i] : 0.f;
+    for (int g = tid; g < a.c_out / 16; g += LTH) {
+        const int to = 16 * g / per_out;
+        uint16_t* const o = to == 0 ? a.outs[0] : to == 1 ? a.outs[1] : to == 2 ? a.outs[2] : a.outs[3];
+        stab[g] = o + (16 * g - to * per_out);
+    }
+    if (LN && tid < CI) {
         sgamma[tid] = gv;
         sbeta[tid] = bev;
     }
-    __syncthreads();   // the vectors are in LDS (the row loads stay in flight across the barrier)
-    if (a.gamma) {   // LayerNorm: the two half-waves hold the two halves of a row
+    uint4 rn[2] = {make_uint4(0, 0, 0, 0), make_uint4(0, 0, 0, 0)};   // residual of the next 32-column block
+    auto fetch_residual = [&](int block) __attribute__((always_inline)) {
+        const uint4* rp = reinterpret_cast<const uint4*>(a.residual + drow * a.c_out + min(block * 32 + 16 * hf, a.c_out - 16));
+        rn[0] = rp[0];
+        rn[1] = rp[1];
+    };
+    if (RES) fetch_residual(t_begin * TCB);
+    __syncthreads();   // the vectors are in LDS
+    if (LN) {   // the two half-waves hold the two halves of a row
         // Between the three passes the packed words are made opaque, so that each pass unpacks them again instead of
         // keeping the whole row alive as binary32 values.
         const auto opaque = [&]() __attribute__((always_inline)) {
@@ -187,106 +189,116 @@ __global__ __launch_bounds__(LTH, 3) void k_ln_linear(LinearArgs a)
             uint32_t o[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                o[e] = pack2((lo16(w4[e]) - mu) * rstd * gg[2 * e] + bt[2 * e], (hi16(w4[e]) - mu) * rstd * gg[2 * e + 1] + bt[2 * e + 1]);
+                o[e] = pack_bf16((lo16(w4[e]) - mu) * rstd * gg[2 * e] + bt[2 * e], (hi16(w4[e]) - mu) * rstd * gg[2 * e + 1] + bt[2 * e + 1]);
             xf[ks].u = make_uint4(o[0], o[1], o[2], o[3]);
-            if ((ks & 1) == 1) asm volatile("" ::: "memory");   // at most two k-steps of scale/shift reads in flight
+            // the step's result is wanted here (its inputs would otherwise be kept until the product), and at most two steps
+            // of scale/shift reads are in flight
+            asm volatile("" : "+v"(xf[ks].u.x), "+v"(xf[ks].u.y), "+v"(xf[ks].u.z), "+v"(xf[ks].u.w));
+            if ((ks & 1) == 1) asm volatile("" ::: "memory");
         }
     }
-    store_tile(0, wreg);
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // the rows, the first W tiles and the first residual are here
     __syncthreads();
 
     // ---- Y^T = W X^T tile by tile: the A operand (32 rows of W) comes from LDS, the B operand is the wave's rows
-    const size_t drow = ok ? (size_t)(a.row_out ? a.row_out[p] : p) : 0;
-    const int per_out = a.c_out / a.n_outs;
-
-    for (int t = 0; t < n_tiles; ++t) {
-        const int buf = t & 1;
-        if (t + 1 < n_tiles) wreg = load_tile(t + 1);
-        const uint16_t* wt = &sw[(size_t)buf * TROWS * PITCH + l32 * PITCH + 8 * hf];
-        // The next tile goes to LDS in the middle of this iteration: behind enough MFMAs to cover the latency of its
-        // loads, and in front of the stores of the epilogues that follow (the memory counter retires in order, so a
-        // wait placed behind those stores would also wait for them). The other buffer is free: every wave passed the
-        // barrier at the end of the last iteration, after its last read of it.
-        bool staged = t + 1 >= n_tiles;
+    // piece hf of slot l32, swizzled; piece 2 ks + hf is a flip of the bits 32 ks away (slots 32 further on have the same
+    // swizzle, pieces 16 further on lie 256 bytes on)
+    const uint32_t foff = lds_w + l32 * (CI * 2) + ((hf ^ T::swizzle(l32)) << 4);
+    int buf = 0;
+    for (int t = t_begin; t < t_end; ++t) {
+        // the other buffer is free: every wave passed the barrier at the end of the last iteration, after its last read of it
+        if (t + 1 < t_end) dma_tile(t + 1, buf ^ 1);
 #pragma unroll
         for (int cb = 0; cb < TCB; ++cb) {
             const int col0 = (t * TCB + cb) << 5;
-            if (col0 >= a.c_out) break;
-            f32x16 acc = {0};
-            // what the epilogue needs from LDS is requested before the MFMAs, not behind them
+            const uint4 rv[2] = {rn[0], rn[1]};
+            if (RES) fetch_residual(t * TCB + cb + 1);
             const int col = col0 + 16 * hf;                      // first of this lane's 16 columns
-            const int to = col / per_out, lc = col - to * per_out;
-            uint16_t* const ob = s_outs[to];
-            float4 bv[4];
+            f32x16 acc;
 #pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) bv[q4] = *reinterpret_cast<const float4*>(sbias + col + 4 * q4);
-            uint4 rv[2] = {make_uint4(0, 0, 0, 0), make_uint4(0, 0, 0, 0)};   // the residual's 16 columns (bf16 zeros without one)
-            if (a.residual) {
-                const uint4* rp = reinterpret_cast<const uint4*>(a.residual + drow * a.c_out + col);   // drow is a valid row also past the end
-                rv[0] = rp[0];
-                rv[1] = rp[1];
+            for (int q4 = 0; q4 < 4; ++q4) {
+                const float4 bv = *reinterpret_cast<const float4*>(sbias + col + 4 * q4);
+                acc[4 * q4] = bv.x;
+                acc[4 * q4 + 1] = bv.y;
+                acc[4 * q4 + 2] = bv.z;
+                acc[4 * q4 + 3] = bv.w;
             }
-            // W fragments four k-steps at a time, one group ahead of the MFMAs that use them
+            // W fragments some k-steps at a time, one group ahead of the MFMAs that use them
             constexpr int G = 4, NG = KS / G;
-            F8 wf[2][G];
+            U4 wf[2][G];
+            const uint32_t wt = foff + buf * T::BYTES + cb * 32 * CI * 2;
+            const auto read_w = [&](int ks) __attribute__((always_inline)) { return lds_read16((wt ^ (32 * (ks & 7))) + (ks >> 3) * 256); };
 #pragma unroll
-            for (int i = 0; i < G; ++i) wf[0][i].u = *reinterpret_cast<const uint4*>(wt + cb * 32 * PITCH + 16 * i);
+            for (int i = 0; i < G; ++i) wf[0][i].u = read_w(i);
 #pragma unroll
             for (int g = 0; g < NG; ++g) {
                 if (g + 1 < NG) {
 #pragma unroll
-                    for (int i = 0; i < G; ++i)
-                        wf[(g + 1) & 1][i].u = *reinterpret_cast<const uint4*>(wt + cb * 32 * PITCH + 16 * ((g + 1) * G + i));
+                    for (int i = 0; i < G; ++i) wf[(g + 1) & 1][i].u = read_w((g + 1) * G + i);
                 }
 #pragma unroll
                 for (int i = 0; i < G; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[g & 1][i].b, xf[g * G + i].b, acc, 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
+                F3D_SB();
             }
-            if (cb == TCB / 2 && !staged) {
-                store_tile(buf ^ 1, wreg);
-                staged = true;
-            }
-            if (ok) {
-                float y[16];
-#pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4) {
-                    y[4 * q4] = acc[4 * q4] + bv[q4].x;
-                    y[4 * q4 + 1] = acc[4 * q4 + 1] + bv[q4].y;
-                    y[4 * q4 + 2] = acc[4 * q4 + 2] + bv[q4].z;
-                    y[4 * q4 + 3] = acc[4 * q4 + 3] + bv[q4].w;
-                }
+            if (RES) {
 #pragma unroll
                 for (int h8 = 0; h8 < 2; ++h8) {
                     const uint32_t w4[4] = {rv[h8].x, rv[h8].y, rv[h8].z, rv[h8].w};
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        y[8 * h8 + 2 * e] += lo16(w4[e]);
-                        y[8 * h8 + 2 * e + 1] += hi16(w4[e]);
+                        acc[8 * h8 + 2 * e] += lo16(w4[e]);
+                        acc[8 * h8 + 2 * e + 1] += hi16(w4[e]);
                     }
                 }
-                uint4* op = reinterpret_cast<uint4*>(ob + drow * per_out + lc);
+            }
+            // A lane holds 16 columns of its row. Stored from here, an instruction would write 16 bytes here and there in
+            // every row, and lines would leave L2 half written: the workgroups' open rows do not fit there. Through LDS
+            // eight lanes write 128 bytes, a whole line, of one row.
+            const int odd = (t * TCB + cb) & 1;
 #pragma unroll
-                for (int h8 = 0; h8 < 2; ++h8)
-                    op[h8] = make_uint4(pack2(y[8 * h8], y[8 * h8 + 1]), pack2(y[8 * h8 + 2], y[8 * h8 + 3]),
-                                        pack2(y[8 * h8 + 4], y[8 * h8 + 5]), pack2(y[8 * h8 + 6], y[8 * h8 + 7]));
+            for (int h8 = 0; h8 < 2; ++h8)
+                sy[wave][(yput ^ h8) ^ (4 * odd)] = make_uint4(pack_bf16(acc[8 * h8], acc[8 * h8 + 1]), pack_bf16(acc[8 * h8 + 2], acc[8 * h8 + 3]),
+                                                               pack_bf16(acc[8 * h8 + 4], acc[8 * h8 + 5]), pack_bf16(acc[8 * h8 + 6], acc[8 * h8 + 7]));
+            if (odd) {
+                uint16_t* const ob = stab[(col0 >> 4) - 2 + ((lane & 7) >> 1)] + (lane & 1) * 8;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const uint4 y = sy[wave][yget + 64 * k];
+                    if (yrow[k] >= 0) *reinterpret_cast<uint4*>(ob + (size_t)yrow[k] * per_out) = y;
+                }
             }
         }
-        if (!staged) store_tile(buf ^ 1, wreg);   // a last, partial tile ended before the staging point
+        // The next tile has landed for this wave once only memory operations younger than its loads are outstanding: the
+        // tile's own stores (with residual loads between them: the last four), or the residual loads of a tile that stores
+        // nothing yet. A wave with rows missing leaves out stores.
+        if (TCB == 1 && !(t & 1)) __builtin_amdgcn_s_waitcnt(vmcnt_imm(RES ? 2 : 0));
+        else if (stores) __builtin_amdgcn_s_waitcnt(vmcnt_imm(RES || TCB == 1 ? 4 : 2 * TCB));
+        else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+        buf ^= 1;
         __syncthreads();
     }
+}
+
+template <int CI, bool LN, bool RES>
+hipError_t launch_one(const LinearArgs& a, hipStream_t stream)
+{
+    const unsigned blocks = (unsigned)((a.n + LBM - 1) / LBM);
+    if (blocks == 0) return hipSuccess;
+    // Few rows leave compute units idle while a workgroup walks all of W alone: then the columns are split until there are
+    // about two workgroups per compute unit (every part reads and normalises its rows again): 1500 rows, 256 -> 3 x 256:
+    // 28 -> 17 us, from 512 workgroups on one part.
+    const unsigned units = (unsigned)(a.c_out / 64);
+    const unsigned split = blocks >= 512 ? 1u : (512u / blocks < units ? 512u / blocks : units);
+    const size_t lds = (size_t)a.c_out * 4 + (size_t)a.c_out / 16 * sizeof(uint16_t*);
+    k_ln_linear<CI, LN, RES><<<dim3(blocks, split), LTH, lds, stream>>>(a);
+    return hipGetLastError();
 }
 
 template <int CI>
 hipError_t launch_ci(const LinearArgs& a, hipStream_t stream)
 {
-    const unsigned blocks = (unsigned)((a.n + LBM - 1) / LBM);
-    const size_t lds = Tile<CI>::LDS_BYTES + (size_t)a.c_out * 4 + (size_t)2 * CI * 4;
-    if (lds > 60000) {
-        const hipError_t e = hipFuncSetAttribute((const void*)k_ln_linear<CI>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-    }
-    if (blocks > 0) k_ln_linear<CI><<<blocks, LTH, lds, stream>>>(a);
-    return hipGetLastError();
+    if (a.gamma) return a.residual ? launch_one<CI, true, true>(a, stream) : launch_one<CI, true, false>(a, stream);
+    return a.residual ? launch_one<CI, false, true>(a, stream) : launch_one<CI, false, false>(a, stream);
 }
 
 }  // namespace

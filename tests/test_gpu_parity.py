@@ -1233,6 +1233,17 @@ def test_ln_linear_matches_oracle(c_in, c_out, n_outs):
     check_ln_linear(129, c_in, c_out, n_outs, rng, ln=True, with_bias=False, with_res=True, gather=True, scatter=True)
 
 
+@pytest.mark.parametrize("c_in,c_out,n_outs", [(64, 64, 4), (64, 192, 4), (128, 64, 1), (128, 384, 3), (256, 768, 3), (256, 320, 4)])
+def test_ln_linear_row_and_column_splits(c_in, c_out, n_outs):
+    # rows: last waves with 1, 24, 25 and 32 rows (stores left out or not), waves without rows; columns split over the
+    # grid (few rows) and not (512 workgroups and more); output tensors of 16, 48, 64 and 80 columns
+    rng = np.random.default_rng(82)
+    for n in (1, 24, 25, 33, 97, 121, 152, 2049):
+        check_ln_linear(n, c_in, c_out, n_outs, rng, ln=True, gather=True)
+        check_ln_linear(n, c_in, c_out, n_outs, rng, ln=False, with_res=True, scatter=True)
+    check_ln_linear(65536 + 25, c_in, c_out, n_outs, rng, ln=True, with_res=True, gather=True, scatter=True)
+
+
 def test_ln_linear_edge_sizes_and_block_composition():
     rng = np.random.default_rng(81)
     for n in (1, 127, 128, 129, 4096):
