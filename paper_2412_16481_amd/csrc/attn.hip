@@ -108,12 +108,13 @@ struct Lay {
 };
 
 template <int D, int QT, bool F16>
-__global__ __launch_bounds__(256) void k_attn(AttnArgs a)
+__global__ __launch_bounds__(256, 3) void k_attn(AttnArgs a)
 {
     using E = Elem<F16>;
     using L = Lay<D>;
     constexpr int NC = L::NC;
     constexpr int KS = D / 16;             // MFMA k-steps for Q K^T
+    constexpr bool SPLIT = D == 16;        // the scale is folded into the query as two 16-bit terms (see below)
     constexpr int LPW = L::LPW;
     constexpr int BM = 128 * QT;           // query rows per workgroup
 
@@ -247,30 +248,33 @@ __global__ __launch_bounds__(256) void k_attn(AttnArgs a)
         }
     }
 
-    // The query fragment is pre-multiplied by softmax_scale*log2(e) and split into a 16-bit head and a 16-bit
-    // remainder (q*c = hi + lo up to 2^-17 relative), so the MFMA delivers the scaled score directly. The
-    // vector ALU is the busy unit of this kernel, the matrix core is not: one more MFMA per tile is cheaper
-    // than 16 multiplies. (binary16: the product is kept inside the finite range of the format.)
+    // Where softmax_scale*log2(e) enters.
+    //   head_dim 16: the query fragment is multiplied by it and split into a 16-bit head and a 16-bit remainder (q*c =
+    //   hi + lo up to 2^-17 relative), so the MFMA delivers the scaled score: one more MFMA per tile against 16
+    //   multiplies (200000 points x 16 heads: 4.95 against 5.03 ms for three passes). binary16: the product is kept inside
+    //   the finite range of the format.
+    //   head_dim 32: the remainder takes two MFMAs, and their power and registers cost more than the 16 multiplies: with the
+    //   plain query and the scale multiplied onto the score (exactly, in binary32) the kernel needs 168 instead of 194
+    //   registers and runs three waves per SIMD (914601 points x 8 heads, a pass: 1.58 -> 1.38 ms).
     U4 qhi[QT][KS], qlo[QT][KS];
-    {
-        const float cl2 = a.c_log2;
 #pragma unroll
-        for (int t = 0; t < QT; ++t) {
+    for (int t = 0; t < QT; ++t) {
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
+        for (int ks = 0; ks < KS; ++ks) {
+            qhi[t][ks] = qf[t][ks];
+            if (!SPLIT) continue;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const uint32_t w2 = (&qf[t][ks].u.x)[e];
-                    float x0 = E::lo(w2) * cl2, x1 = E::hi(w2) * cl2;
-                    if (F16) {
-                        x0 = fminf(fmaxf(x0, -65000.f), 65000.f);
-                        x1 = fminf(fmaxf(x1, -65000.f), 65000.f);
-                    }
-                    const uint32_t h = E::pack(x0, x1);
-                    const float r0 = x0 - E::lo(h), r1 = x1 - E::hi(h);
-                    (&qhi[t][ks].u.x)[e] = h;
-                    (&qlo[t][ks].u.x)[e] = E::pack(r0, r1);
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t w2 = (&qf[t][ks].u.x)[e];
+                float x0 = E::lo(w2) * a.c_log2, x1 = E::hi(w2) * a.c_log2;
+                if (F16) {
+                    x0 = fminf(fmaxf(x0, -65000.f), 65000.f);
+                    x1 = fminf(fmaxf(x1, -65000.f), 65000.f);
                 }
+                const uint32_t h = E::pack(x0, x1);
+                const float r0 = x0 - E::lo(h), r1 = x1 - E::hi(h);
+                (&qhi[t][ks].u.x)[e] = h;
+                (&qlo[t][ks].u.x)[e] = E::pack(r0, r1);
             }
         }
     }
@@ -320,6 +324,7 @@ __global__ __launch_bounds__(256) void k_attn(AttnArgs a)
             request_first_stages();
         }
         const int ntile = (ng + 31) >> 5;
+        const float post = SPLIT ? 1.0f : a.c_log2;   // multiplied onto the scores (positive)
 
         // One unit of the pipeline: the softmax of the score tile `s` (query tile t, keys from kbase on; scores in log2
         // units) and O^T += V^T P^T, with the MFMAs that produce the NEXT score tile (`sn` = kfn * q[tn]^T) issued in
@@ -336,6 +341,10 @@ __global__ __launch_bounds__(256) void k_attn(AttnArgs a)
                 }
             }
             if (ROBUST) {
+                if (!SPLIT) {
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) s[r] *= post;
+                }
                 float mx = fmaxf(fmaxf(s[0], s[1]), s[2]);
 #pragma unroll
                 for (int r = 3; r < 15; r += 2) mx = fmaxf(fmaxf(mx, s[r]), s[r + 1]);
@@ -361,26 +370,23 @@ __global__ __launch_bounds__(256) void k_attn(AttnArgs a)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) s[r] -= m_ref[t];
             }
+            const auto prob = [&](float x) __attribute__((always_inline)) { return __builtin_amdgcn_exp2f((SPLIT || ROBUST) ? x : x * post); };
             F3D_SB();
 #pragma unroll
-            for (int r = 0; r < 4; ++r) s[r] = __builtin_amdgcn_exp2f(s[r]);
+            for (int r = 0; r < 4; ++r) s[r] = prob(s[r]);
             F3D_SB();
             if (MORE) sn = E::mfma(kfn[0], qhi[tn][0], f32x16{0});
             F3D_SB();
 #pragma unroll
-            for (int r = 4; r < 8; ++r) s[r] = __builtin_amdgcn_exp2f(s[r]);
+            for (int r = 4; r < 8; ++r) s[r] = prob(s[r]);
             F3D_SB();
-            if (MORE && KS == 2) sn = E::mfma(kfn[0], qlo[tn][0], sn);
-            F3D_SB();
-#pragma unroll
-            for (int r = 8; r < 12; ++r) s[r] = __builtin_amdgcn_exp2f(s[r]);
-            F3D_SB();
-            if (MORE) sn = (KS == 2) ? E::mfma(kfn[KS - 1], qhi[tn][KS - 1], sn) : E::mfma(kfn[0], qlo[tn][0], sn);
+            if (MORE) sn = SPLIT ? E::mfma(kfn[0], qlo[tn][0], sn) : E::mfma(kfn[KS - 1], qhi[tn][KS - 1], sn);
             F3D_SB();
 #pragma unroll
-            for (int r = 12; r < 16; ++r) s[r] = __builtin_amdgcn_exp2f(s[r]);
+            for (int r = 8; r < 12; ++r) s[r] = prob(s[r]);
             F3D_SB();
-            if (MORE && KS == 2) sn = E::mfma(kfn[KS - 1], qlo[tn][KS - 1], sn);
+#pragma unroll
+            for (int r = 12; r < 16; ++r) s[r] = prob(s[r]);
             F3D_SB();
             U4 pb0, pb1;
 #pragma unroll
@@ -418,7 +424,7 @@ __global__ __launch_bounds__(256) void k_attn(AttnArgs a)
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
                 s = E::mfma(kf[ks], qhi[t][ks], s);
-                s = E::mfma(kf[ks], qlo[t][ks], s);
+                if (SPLIT) s = E::mfma(kf[ks], qlo[t][ks], s);
             }
         };
         // Hands stage st+1 over to the readers and refills the buffer of stage st-1 with stage st+2: every wave waits
