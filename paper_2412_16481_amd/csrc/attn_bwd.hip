@@ -18,12 +18,13 @@
 // 128 KB of it at a scope of 1024 rows and head_dim 32, which leaves no room for the staged rows and an order of the sums
 // that does not depend on timing.
 //
-// Bound: power and issue. On 914601 points x 8 heads x 32 (scopes of 1024) the dK/dV kernel keeps the matrix core busy
-// 61 % and the vector ALU 58 % of the cycles while the clock falls to 1.69 GHz, and runs 1.1 PFLOP/s of MFMAs (an 8192^3
-// bf16 matrix product reaches 1.2 here). Measured per pass on that input: dQ and D 2.57 -> 1.88 ms, dK/dV 3.19 -> 2.6 ms
-// against staging through registers with a transposed copy written by 2-byte LDS stores (bank conflicts in every one
-// of them), a separate pass for D and no overlap of one tile's products with another's exponentials; on 200000 points x
-// 4 heads x 16: 0.199 -> 0.177 and 0.251 -> 0.234 ms.
+// Bound: power and issue. On 914601 points x 8 heads x 32 (scopes of 1024) the dK/dV kernel kept the matrix core busy
+// 61 % and the vector ALU 58 % of the cycles while the clock fell to 1.69 GHz, and ran 1.1 PFLOP/s of MFMAs (an 8192^3
+// bf16 matrix product reaches 1.2 here); two MFMAs fewer per tile for 16 multiplies more then took it from 2.6 to 2.5 ms.
+// Measured per pass on that input: dQ and D 2.57 -> 1.87 ms, dK/dV 3.19 -> 2.51 ms against staging through registers with
+// a transposed copy written by 2-byte LDS stores (bank conflicts in every one of them), a separate pass for D and no
+// overlap of one tile's products with another's exponentials; on 200000 points x 4 heads x 16: 0.199 -> 0.175 and
+// 0.251 -> 0.232 ms. One row tile per wave at three waves per SIMD (dQ 2.06, dK/dV 3.30 ms) is slower.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -90,7 +91,19 @@ __device__ __forceinline__ void scale_split(const U4& x, float c, U4& hi, U4& lo
     }
 }
 
-// A row's log-sum-exp (in log2 units) and D as bf16 head + remainder pairs: {L_hi, L_lo}, {D_hi, D_lo}. One more MFMA
+// bf16 fragment times a power of two: exact
+__device__ __forceinline__ U4 scale_pow2(const U4& x, float p2)
+{
+    U4 y;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const uint32_t w2 = (&x.u.x)[e];
+        (&y.u.x)[e] = pack_bf16(__uint_as_float(w2 << 16) * p2, __uint_as_float(w2 & 0xFFFF0000u) * p2);
+    }
+    return y;
+}
+
+// A row's log-sum-exp (in the units of the staged scores) and D as bf16 head + remainder pairs: {L_hi, L_lo}, {D_hi, D_lo}. One more MFMA
 // whose other operand holds -1 at the matching two positions subtracts them from a whole score tile (error 2^-17
 // relative), which is cheaper than 16 subtractions per lane and tile on the vector ALU.
 __device__ __forceinline__ uint2 split_pairs(float l2, float dsum)
@@ -406,13 +419,14 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_dq(AttnBwdArgs b)
 // Q and dO are kept once, row-major: the rows of the score products come from 16-byte reads (pieces of a row
 // xor-swizzled by the row, free of bank conflicts), and Q^T, dO^T, the A operands of dK^T += Q^T dS and
 // dV^T += dO^T P, from the transposing read, which follows the same swizzle.
-// The vector ALU (16 exponentials, 16 multiplies and 16 packs per tile and lane) and the matrix core (12 MFMAs at
+// The vector ALU (16 exponentials, 16 or 32 multiplies and 16 packs per tile and lane) and the matrix core (10 MFMAs at
 // head_dim 32) are both busy, so the loop runs one score tile ahead: the products of the next tile are issued between
 // the exponentials, multiplies and packs of the current one.
 template <int D, int KTW>
 __global__ __launch_bounds__(256, 2) void k_attn_bwd_dkdv(AttnBwdArgs b)
 {
     using L = BLay<D>;
+    constexpr bool SPLIT = D == 16;
     constexpr int NC = L::NC, KS = D / 16, LPW = L::LPW, SR = L::ROWS;
     constexpr int BM = 128 * KTW;                     // key rows per workgroup
     __shared__ __attribute__((aligned(1024))) unsigned char smem[L::NBUF * 2 * L::BUF];   // Q stages, then dO stages
@@ -450,6 +464,9 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_dkdv(AttnBwdArgs b)
         qthr[i] = reinterpret_cast<const char*>(a.q + hoff + c * 8);
         gthr[i] = reinterpret_cast<const char*>(b.dout + hoff + c * 8);
     }
+    int cexp = 0;
+    const float cres = SPLIT ? 1.0f : 2.0f * frexpf(a.c_log2, &cexp);   // c_log2 = cres * 2^(cexp - 1), 1 <= |cres| < 2
+    const float cpow = SPLIT ? 1.0f : ldexpf(1.0f, cexp - 1), lmul = LOG2E / cres;
     float lreg = 0.f, dreg = 0.f;                     // log-sum-exp and D of row `tid` of the stage fetched last
     auto fetch_rows = [&](int st) __attribute__((always_inline)) {
 #pragma unroll
@@ -474,7 +491,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_dkdv(AttnBwdArgs b)
             lds_dma16(qthr[i] + (uint64_t)qrow_next[i] * row_bytes, sQ + buf * L::BUF + blk * 1024);
             lds_dma16(gthr[i] + (uint64_t)grow_next[i] * row_bytes, sG + buf * L::BUF + blk * 1024);
         }
-        if (tid < SR) sx[buf * SR + tid] = split_pairs(lreg * LOG2E, dreg);
+        if (tid < SR) sx[buf * SR + tid] = split_pairs(lreg * lmul, dreg);
     };
     const int nst = (ng + SR - 1) / SR, ntile = (ng + 31) >> 5;
     int krow[KTW];
@@ -495,6 +512,8 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_dkdv(AttnBwdArgs b)
     if (nst > 2) fetch_rows(2);
 
     // ---- this lane's keys: k (scaled, split) and v fragments
+    // head_dim 32: k times the power of two below the factor (exact), and what is left of the factor, 1 <= cres < 2, is a
+    // multiply behind the product; the staged log-sum-exp is divided by it
     U4 khi[KTW][KS], klo[KTW][KS], vfr[KTW][KS];
     U4 negS, negD;   // B operands with -1 at the positions of a staged row's log-sum-exp pair / D pair
     negS.u = make_uint4(hf == 0 ? 0xBF80BF80u : 0u, 0, 0, 0);
@@ -506,7 +525,8 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_dkdv(AttnBwdArgs b)
             U4 kf;
             kf.u = *reinterpret_cast<const uint4*>(a.k + krd[j] * a.C + hoff + ks * 16 + hf * 8);
             vfr[j][ks].u = *reinterpret_cast<const uint4*>(a.v + krd[j] * a.C + hoff + ks * 16 + hf * 8);
-            scale_split(kf, a.c_log2, khi[j][ks], klo[j][ks]);
+            if (SPLIT) scale_split(kf, a.c_log2, khi[j][ks], klo[j][ks]);
+            else khi[j][ks] = scale_pow2(kf, cpow);
         }
     }
 
@@ -542,34 +562,36 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_dkdv(AttnBwdArgs b)
     auto unit = [&](f32x16& s, f32x16& dp, int j, const U4& qt0, const U4& qt1, const U4& gt0, const U4& gt1, f32x16& sn, f32x16& dpn,
                     const Rows& f, int jn) __attribute__((always_inline)) {
         U4 pb, db;
+        const auto prob = [&](int r) __attribute__((always_inline)) { s[r] = __builtin_amdgcn_exp2f(SPLIT ? s[r] : s[r] * cres); };
         F3D_SB();
 #pragma unroll
-        for (int r = 0; r < 4; ++r) s[r] = __builtin_amdgcn_exp2f(s[r]);
+        for (int r = 0; r < 4; ++r) prob(r);
         F3D_SB();
         sn = mfma_bf16(f.x, negS, f32x16{0});
         F3D_SB();
 #pragma unroll
-        for (int r = 4; r < 8; ++r) s[r] = __builtin_amdgcn_exp2f(s[r]);
+        for (int r = 4; r < 8; ++r) prob(r);
         F3D_SB();
         sn = mfma_bf16(f.q[0], khi[jn][0], sn);
         F3D_SB();
 #pragma unroll
         for (int e = 0; e < 4; ++e) (&pb.u.x)[e] = pack_bf16(s[2 * e], s[2 * e + 1]);
 #pragma unroll
-        for (int r = 8; r < 10; ++r) s[r] = __builtin_amdgcn_exp2f(s[r]);
+        for (int r = 8; r < 10; ++r) prob(r);
         F3D_SB();
         dv[j] = mfma_bf16(gt0, pb, dv[j]);
         F3D_SB();
 #pragma unroll
-        for (int r = 10; r < 12; ++r) s[r] = __builtin_amdgcn_exp2f(s[r]);
+        for (int r = 10; r < 12; ++r) prob(r);
 #pragma unroll
         for (int r = 0; r < 4; ++r) dp[r] *= s[r];
         F3D_SB();
-        sn = mfma_bf16(f.q[0], klo[jn][0], sn);
+        if (SPLIT) sn = mfma_bf16(f.q[0], klo[jn][0], sn);
+        else sn = mfma_bf16(f.q[KS - 1], khi[jn][KS - 1], sn);
         F3D_SB();
 #pragma unroll
         for (int r = 4; r < 8; ++r) dp[r] *= s[r];
-        s[12] = __builtin_amdgcn_exp2f(s[12]);
+        prob(12);
         F3D_SB();
         dpn = mfma_bf16(f.x, negD, f32x16{0});
         F3D_SB();
@@ -579,9 +601,9 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_dkdv(AttnBwdArgs b)
         dk[j] = mfma_bf16(qt0, db, dk[j]);
         F3D_SB();
 #pragma unroll
-        for (int r = 13; r < 16; ++r) s[r] = __builtin_amdgcn_exp2f(s[r]);
+        for (int r = 13; r < 16; ++r) prob(r);
         F3D_SB();
-        if (KS == 2) sn = mfma_bf16(f.q[KS - 1], khi[jn][KS - 1], sn);
+        if (KS == 2) dpn = mfma_bf16(f.g[0], vfr[jn][0], dpn);
         F3D_SB();
 #pragma unroll
         for (int e = 0; e < 4; ++e) (&pb.u.x)[e] = pack_bf16(s[8 + 2 * e], s[8 + 2 * e + 1]);
@@ -591,19 +613,15 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_dkdv(AttnBwdArgs b)
 #pragma unroll
         for (int r = 8; r < 12; ++r) dp[r] *= s[r];
         F3D_SB();
-        if (KS == 2) sn = mfma_bf16(f.q[KS - 1], klo[jn][KS - 1], sn);
-        F3D_SB();
 #pragma unroll
         for (int r = 12; r < 16; ++r) dp[r] *= s[r];
         F3D_SB();
-        dpn = mfma_bf16(f.g[0], vfr[jn][0], dpn);
+        dpn = mfma_bf16(f.g[KS - 1], vfr[jn][KS - 1], dpn);
         F3D_SB();
 #pragma unroll
         for (int e = 0; e < 4; ++e) (&db.u.x)[e] = pack_bf16(dp[8 + 2 * e], dp[8 + 2 * e + 1]);
         F3D_SB();
         dk[j] = mfma_bf16(qt1, db, dk[j]);
-        F3D_SB();
-        if (KS == 2) dpn = mfma_bf16(f.g[KS - 1], vfr[jn][KS - 1], dpn);
         F3D_SB();
     };
     // Hands stage st+1 over to the readers and refills the buffer of stage st-1 with stage st+2: every wave waits for its
@@ -629,7 +647,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_dkdv(AttnBwdArgs b)
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
         sa = mfma_bf16(f.q[ks], khi[0][ks], sa);
-        sa = mfma_bf16(f.q[ks], klo[0][ks], sa);
+        if (SPLIT) sa = mfma_bf16(f.q[ks], klo[0][ks], sa);
         da = mfma_bf16(f.g[ks], vfr[0][ks], da);
     }
     if (KTW == 1) read_rows(f, L::TILE, 32 * 8);
