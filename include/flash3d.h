@@ -196,7 +196,8 @@ int f3d_psh_bucketize_static(const float *coords, const int32_t *batch_offsets, 
  *   lse  (out)  NULL, or binary32 [n, heads], BUCKET-MAJOR rows (out_perm does not apply): natural logarithm of
  *               the sum of exponentials of the row's scaled scores; what f3d_bucket_swin_attn_bwd needs
  * Arithmetic: bf16 operands, fp32 accumulation and softmax, probabilities rounded to bf16 before P*V. The scale
- * is folded into q before the product (q*scale*log2(e) carried as two bf16 terms), so a scaled score is exact to
+ * is multiplied onto the score in binary32 at head_dim 32; at head_dim 16 it is folded into q before the product
+ * (q*scale*log2(e) carried as two bf16 terms), so there a scaled score is exact to
  * about 2^-17 of |q||k| scale (the product of the norms, not the score itself): far below the rounding of the
  * probabilities while |q||k| scale stays below a few hundred, and visible in `lse` as an absolute error of about
  * 4e-3 plus that amount. Where |q||k| scale reaches 10^4 and two top scores of a row lie within one unit of each

@@ -111,13 +111,9 @@ __device__ __forceinline__ uint64_t morton3_low(int x, int y, int z)
     return (uint64_t)lx | ((uint64_t)ly << 1) | ((uint64_t)lz << 2);
 }
 
-__device__ __forceinline__ int hash_bucket(int hash, int x, int y, int z, const ScanCfg& c)
+// bucket of a code (the Z-order code of the voxel, or the xor of its coordinates)
+__device__ __forceinline__ int hash_code(int hash, unsigned long long code, const ScanCfg& c)
 {
-    unsigned long long code;
-    if (hash == 0 || hash == 1)
-        code = (unsigned long long)((uint32_t)x ^ (uint32_t)y ^ (uint32_t)z);
-    else
-        code = c.wide ? morton3(x, y, z) : morton3_low(x, y, z);
     if (hash == 0 || hash == 2) {
         if (c.K < 2) return 0;
         // code = hi*2^32 + lo  =>  code mod K = ((hi mod K) * (2^32 mod K) + lo) mod K; K < 2^13 keeps the
@@ -140,6 +136,16 @@ __device__ __forceinline__ int hash_bucket(int hash, int x, int y, int z, const 
     if (r < 0) --q;
     else if ((unsigned long long)r >= c.D) ++q;
     return (int)(q < (long long)c.K ? q : (long long)(c.K - 1));
+}
+
+__device__ __forceinline__ int hash_bucket(int hash, int x, int y, int z, const ScanCfg& c)
+{
+    unsigned long long code;
+    if (hash == 0 || hash == 1)
+        code = (unsigned long long)((uint32_t)x ^ (uint32_t)y ^ (uint32_t)z);
+    else
+        code = c.wide ? morton3(x, y, z) : morton3_low(x, y, z);
+    return hash_code(hash, code, c);
 }
 
 // 32-bit mixer (xor-shift, odd multiply, xor-shift, odd multiply, xor-shift): a stateless generator for the seeded
@@ -186,6 +192,41 @@ __device__ __forceinline__ void probe_voxel(const PshArgs& a, int r, const ScanC
     x = min(max(x + dx, 0), c.vmax[0]);
     y = min(max(y + dy, 0), c.vmax[1]);
     z = min(max(z + dz, 0), c.vmax[2]);
+}
+
+// Probe r (1..6) along the axes as arithmetic on the Z-order code itself: one axis moves by +-step and is clamped to the
+// scan's voxel box, the bits of the other two stay. The bits of one axis, three apart, add and subtract like an integer
+// when the gaps are filled with ones (the carry runs through) or zeros (the borrow does), and compare in its order. About 15
+// instructions against 75 for taking the voxel apart, moving it and interleaving it again.
+struct ZProbe {
+    unsigned long long mask;    // the axis' bits
+    unsigned long long step;    // distance, limited to the largest coordinate (further is clamped to the same place)
+    unsigned long long lim;     // largest coordinate that does not leave the box by +step
+    unsigned long long vmax;    // largest coordinate
+    int minus;
+};
+
+__device__ __forceinline__ ZProbe zprobe_of(const ScanCfg& c, int r)
+{
+    const int ax = (r - 1) >> 1;
+    const int vm = ax == 0 ? c.vmax[0] : ax == 1 ? c.vmax[1] : c.vmax[2];
+    const int st = min(c.step, vm);
+    ZProbe z;
+    z.mask = 0x1249249249249249ull << ax;
+    z.step = morton3(st, 0, 0) << ax;
+    z.lim = morton3(vm - st, 0, 0) << ax;
+    z.vmax = morton3(vm, 0, 0) << ax;
+    z.minus = (r - 1) & 1;
+    return z;
+}
+
+__device__ __forceinline__ unsigned long long zprobe(unsigned long long code, const ZProbe& z)
+{
+    const unsigned long long a = code & z.mask;
+    unsigned long long to;
+    if (z.minus) to = a < z.step ? 0ull : (a - z.step) & z.mask;
+    else to = a > z.lim ? z.vmax : ((code | ~z.mask) + z.step) & z.mask;
+    return (code & ~z.mask) | to;
 }
 
 // largest b in [0, n_scans) with start[b] <= x, given start[0] <= x < start[n_scans]
