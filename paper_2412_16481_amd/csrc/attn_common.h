@@ -73,10 +73,11 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
 // LDS byte address `lds` (wave-uniform; it travels in M0). Written as assembly so that the compiler does not count
 // it among its own memory operations: it would otherwise wait for ALL loads in flight before every LDS read that
 // follows, and the loads issued here are meant to stay in flight for a whole stage. The kernel waits for them itself
-// (s_waitcnt vmcnt(0) before the barrier that hands a stage over).
+// (s_waitcnt vmcnt(0) before the barrier that hands a stage over). M0 written by the scalar unit is safe to read one wait
+// state later; the compiler does not look for such hazards inside assembly, so the s_nop is written out.
 __device__ __forceinline__ void lds_dma16(const void* g, uint32_t lds)
 {
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(g) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(g) : "memory", "m0");
 }
 
 __device__ __forceinline__ uint2 lds_read_tr(uint32_t addr)

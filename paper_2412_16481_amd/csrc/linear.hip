@@ -33,10 +33,10 @@ namespace {
 __device__ __forceinline__ float lo16(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float hi16(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
 
-// lds_dma16 with a scalar base and a 32-bit byte offset per lane
+// lds_dma16 (see there for the s_nop) with a scalar base and a 32-bit byte offset per lane
 __device__ __forceinline__ void lds_dma16_from(const void* base, uint32_t off, uint32_t lds)
 {
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory", "m0");
 }
 
 // s_waitcnt operand that waits for the memory counter alone

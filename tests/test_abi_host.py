@@ -3,6 +3,8 @@ refuses bad arguments before anything is launched."""
 import ctypes
 import os
 import re
+import shutil
+import subprocess
 
 import pytest
 
@@ -37,6 +39,26 @@ def test_microbenchmark_library_is_built_and_refuses_bad_arguments_on_the_host()
     assert mb.f3d_mb_run(0, 0, ctypes.byref(ms), ctypes.byref(work)) != 0
     assert mb.f3d_mb_run(0, 9, ctypes.byref(ms), ctypes.byref(work)) != 0
     assert mb.f3d_mb_run(0, 4, None, ctypes.byref(work)) != 0
+
+
+def test_every_load_into_lds_waits_for_the_write_of_m0(tmp_path):
+    # a load into LDS takes its address from M0, which needs one wait state behind a scalar write of it; the compiler does
+    # not insert that inside assembly statements, so the built code is looked through
+    objdump = "/opt/rocm/llvm/bin/llvm-objdump"
+    if not os.path.exists(objdump):
+        pytest.skip("no llvm-objdump here")
+    shutil.copy(f3d.LIB_PATH, tmp_path / "lib.so")
+    subprocess.run([objdump, "--offloading", "lib.so"], cwd=tmp_path, check=True, capture_output=True)
+    loads = 0
+    for part in tmp_path.glob("lib.so.*gfx950*"):
+        text = subprocess.run([objdump, "-d", part.name], cwd=tmp_path, check=True, capture_output=True, text=True).stdout
+        before = ""
+        for line in (x.split("//")[0].strip() for x in text.splitlines()):
+            if re.match(r"(global|scratch)_load_lds_|buffer_load_.*\blds\b", line):
+                loads += 1
+                assert not re.match(r"s_\w+ m0\b", before), f"{part.name}: {before}; {line}"
+            before = line or before
+    assert loads > 0
 
 
 def test_params_default_and_sizes():
