@@ -279,6 +279,17 @@ __global__ __launch_bounds__(LTH, 3) void k_ln_linear(LinearArgs a)
     }
 }
 
+// an output tensor shares memory with x
+bool in_place(const LinearArgs& a)
+{
+    const uintptr_t x0 = (uintptr_t)a.x, x1 = x0 + (size_t)a.n * a.c_in * 2;
+    for (int t = 0; t < a.n_outs; ++t) {
+        const uintptr_t o0 = (uintptr_t)a.outs[t], o1 = o0 + (size_t)a.n * (a.c_out / a.n_outs) * 2;
+        if (o0 < x1 && x0 < o1) return true;
+    }
+    return false;
+}
+
 template <int CI, bool LN, bool RES>
 hipError_t launch_one(const LinearArgs& a, hipStream_t stream)
 {
@@ -286,9 +297,10 @@ hipError_t launch_one(const LinearArgs& a, hipStream_t stream)
     if (blocks == 0) return hipSuccess;
     // Few rows leave compute units idle while a workgroup walks all of W alone: then the columns are split until there are
     // about two workgroups per compute unit (every part reads and normalises its rows again): 1500 rows, 256 -> 3 x 256:
-    // 28 -> 17 us, from 512 workgroups on one part.
+    // 28 -> 17 us, from 512 workgroups on one part. One part also where an output overwrites x: the workgroup that owns the
+    // rows holds them in registers before its first store, a second one would read what the first has stored.
     const unsigned units = (unsigned)(a.c_out / 64);
-    const unsigned split = blocks >= 512 ? 1u : (512u / blocks < units ? 512u / blocks : units);
+    const unsigned split = blocks >= 512 || in_place(a) ? 1u : (512u / blocks < units ? 512u / blocks : units);
     const size_t lds = (size_t)a.c_out * 4 + (size_t)a.c_out / 16 * sizeof(uint16_t*);
     k_ln_linear<CI, LN, RES><<<dim3(blocks, split), LTH, lds, stream>>>(a);
     return hipGetLastError();

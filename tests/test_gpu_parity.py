@@ -1246,6 +1246,28 @@ def test_ln_linear_row_and_column_splits(c_in, c_out, n_outs):
     check_ln_linear(65536 + 25, c_in, c_out, n_outs, rng, ln=False, with_res=True, gather=True, scatter=True)
 
 
+@pytest.mark.parametrize("c", [64, 128, 256])
+def test_ln_linear_in_place(c):
+    # x as output, with the residual too and through one row map: a row's whole input is read before any of it is
+    # overwritten, also at the sizes whose columns several workgroups would share
+    rng = np.random.default_rng(83)
+    w = dev(wl.f32_to_bf16_bits(rng.standard_normal((c, c)).astype(np.float32) / c ** 0.5), torch.bfloat16)
+    gamma = dev(1 + 0.1 * rng.standard_normal(c).astype(np.float32))
+    for n in (1, 129, 1500, 9000, 32768, 66000):
+        x = dev(wl.f32_to_bf16_bits(rng.standard_normal((n, c)).astype(np.float32)), torch.bfloat16)
+        rows = dev(rng.permutation(n).astype(np.int32))
+        for rmap in (None, rows):
+            for res in (None, x):
+                for g in (None, gamma):
+                    (want,) = f3d.ln_linear(x, w, None, g, None, 1e-5, rmap, res, rmap)
+                    y = x.clone()
+                    at, ptr = y.data_ptr(), lambda t: None if t is None else t.data_ptr()
+                    rc = f3d.lib().f3d_ln_linear(at, ptr(rmap), ptr(g), None, 1e-5, w.data_ptr(), None, None if res is None else at, n, c, c,
+                                                 (f3d.ctypes.c_void_p * 1)(at), 1, ptr(rmap), torch.cuda.current_stream().cuda_stream)
+                    assert rc == 0
+                    assert torch.equal(y, want), (n, rmap is None, res is None, g is None)
+
+
 def test_ln_linear_edge_sizes_and_block_composition():
     rng = np.random.default_rng(81)
     for n in (1, 127, 128, 129, 4096):
