@@ -302,6 +302,11 @@ hipError_t launch_one(const LinearArgs& a, hipStream_t stream)
     const unsigned units = (unsigned)(a.c_out / 64);
     const unsigned split = blocks >= 512 || in_place(a) ? 1u : (512u / blocks < units ? 512u / blocks : units);
     const size_t lds = (size_t)a.c_out * 4 + (size_t)a.c_out / 16 * sizeof(uint16_t*);
+    // tiles and results in static LDS, 32 or 48 KB: from 3000 columns or so on the sum passes what a kernel gets unasked
+    if (2 * Tile<CI>::BYTES + LNW * 4096 + lds > 60000) {
+        const hipError_t e = hipFuncSetAttribute((const void*)k_ln_linear<CI, LN, RES>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
     k_ln_linear<CI, LN, RES><<<dim3(blocks, split), LTH, lds, stream>>>(a);
     return hipGetLastError();
 }

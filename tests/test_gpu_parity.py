@@ -1246,6 +1246,15 @@ def test_ln_linear_row_and_column_splits(c_in, c_out, n_outs):
     check_ln_linear(65536 + 25, c_in, c_out, n_outs, rng, ln=False, with_res=True, gather=True, scatter=True)
 
 
+@pytest.mark.parametrize("c_out,n_outs", [(3648, 3), (4096, 1), (4096, 4)])
+@pytest.mark.parametrize("c_in", [64, 128, 256])
+def test_ln_linear_most_output_columns(c_in, c_out, n_outs):
+    # the bias and the column table take the workgroup's LDS past 64 KB at 128 and 256 inputs from 3648 columns on
+    rng = np.random.default_rng(84)
+    check_ln_linear(200, c_in, c_out, n_outs, rng, ln=True, gather=True)
+    check_ln_linear(33, c_in, c_out, n_outs, rng, ln=False, with_res=True, scatter=True)
+
+
 @pytest.mark.parametrize("c", [64, 128, 256])
 def test_ln_linear_in_place(c):
     # x as output, with the residual too and through one row map: a row's whole input is read before any of it is
