@@ -196,7 +196,7 @@ int f3d_psh_bucketize_static(const float *coords, const int32_t *batch_offsets, 
  *   lse  (out)  NULL, or binary32 [n, heads], BUCKET-MAJOR rows (out_perm does not apply): natural logarithm of
  *               the sum of exponentials of the row's scaled scores; what f3d_bucket_swin_attn_bwd needs
  * Arithmetic: bf16 operands, fp32 accumulation and softmax, probabilities rounded to bf16 before P*V. The scale
- * is multiplied onto the score in binary32 at head_dim 32; at head_dim 16 it is folded into q before the product
+ * is multiplied onto the score in binary32 at head_dim 32 (the power of two in a factor below 1 onto q); at head_dim 16 it is folded into q before the product
  * (q*scale*log2(e) carried as two bf16 terms), so there a scaled score is exact to
  * about 2^-17 of |q||k| scale (the product of the norms, not the score itself): far below the rounding of the
  * probabilities while |q||k| scale stays below a few hundred, and visible in `lse` as an absolute error of about
@@ -219,8 +219,9 @@ int f3d_attn_block_rows(int64_t n_scans, int64_t max_buckets, int32_t bucket_cap
  * The same attention on IEEE binary16 ("FP16") tensors, the element type the Appendix "Bucket-Swin" names for the
  * point features: q, k, v and out are binary16 [n, heads*head_dim]; every other argument, the layout and the error
  * behaviour are those of f3d_bucket_swin_attn. Arithmetic: binary16 operands, fp32 accumulation and softmax,
- * probabilities rounded to binary16 (round to nearest even) before P*V. |q * softmax_scale * log2(e)| is
- * clamped to 65000 (finite in binary16); scores that large saturate the softmax anyway. Forward only.
+ * probabilities rounded to binary16 (round to nearest even) before P*V. At head_dim 16 |q * softmax_scale * log2(e)| is
+ * clamped to 65000 (finite in binary16); scores that large saturate the softmax anyway. At head_dim 32 the scale is
+ * multiplied onto the score, softmax_scale * log2(e) limited to 2^90: every score is finite. Forward only.
  */
 int f3d_bucket_swin_attn_f16(const void *q, const void *k, const void *v, const int32_t *perm, const int32_t *offsets,
                              const int32_t *scan_bucket_start, int64_t n, int32_t n_scans, int64_t max_buckets,

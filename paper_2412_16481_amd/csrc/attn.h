@@ -24,6 +24,8 @@ struct AttnArgs {
     int H;
     int C;        // row pitch in elements = heads * head_dim
     float c_log2; // softmax scale * log2(e)
+    float q_pow2; // head_dim 32, bfloat16: a power of two, at most 1, that goes into the query (exactly), and
+    float s_mul;  // head_dim 32: what is left of c_log2, multiplied onto the score
     int n_slots;  // scope slots over all scans (upper bound, surplus workgroups exit)
     int qblocks;  // query blocks per scope = ceil(bucket_cap / attn_block_rows(...))
     int extra;    // spare slots per scan: 2 (plain, shift) or stride + 1

@@ -255,13 +255,15 @@ __global__ __launch_bounds__(256, 3) void k_attn(AttnArgs a)
     //   the finite range of the format.
     //   head_dim 32: the remainder takes two MFMAs, and their power and registers cost more than the 16 multiplies: with the
     //   plain query and the scale multiplied onto the score (exactly, in binary32) the kernel needs 168 instead of 194
-    //   registers and runs three waves per SIMD (914601 points x 8 heads, a pass: 1.58 -> 1.38 ms).
+    //   registers and runs three waves per SIMD (914601 points x 8 heads, a pass: 1.58 -> 1.38 ms). The power of two in a
+    //   factor below one goes into the query all the same, exactly: a product q k^T may be too large for binary32 where
+    //   the scaled score is not. (binary16 products cannot be.)
     U4 qhi[QT][KS], qlo[QT][KS];
 #pragma unroll
     for (int t = 0; t < QT; ++t) {
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-            qhi[t][ks] = qf[t][ks];
+            qhi[t][ks] = SPLIT || F16 ? qf[t][ks] : scale_pow2(qf[t][ks], a.q_pow2);
             if (!SPLIT) continue;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
@@ -324,7 +326,7 @@ __global__ __launch_bounds__(256, 3) void k_attn(AttnArgs a)
             request_first_stages();
         }
         const int ntile = (ng + 31) >> 5;
-        const float post = SPLIT ? 1.0f : a.c_log2;   // multiplied onto the scores (positive)
+        const float post = SPLIT ? 1.0f : a.s_mul;   // multiplied onto the scores (positive)
 
         // One unit of the pipeline: the softmax of the score tile `s` (query tile t, keys from kbase on; scores in log2
         // units) and O^T += V^T P^T, with the MFMAs that produce the NEXT score tile (`sn` = kfn * q[tn]^T) issued in

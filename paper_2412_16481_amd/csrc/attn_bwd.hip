@@ -91,18 +91,6 @@ __device__ __forceinline__ void scale_split(const U4& x, float c, U4& hi, U4& lo
     }
 }
 
-// bf16 fragment times a power of two: exact
-__device__ __forceinline__ U4 scale_pow2(const U4& x, float p2)
-{
-    U4 y;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const uint32_t w2 = (&x.u.x)[e];
-        (&y.u.x)[e] = pack_bf16(__uint_as_float(w2 << 16) * p2, __uint_as_float(w2 & 0xFFFF0000u) * p2);
-    }
-    return y;
-}
-
 // A row's log-sum-exp (in the units of the staged scores) and D as bf16 head + remainder pairs: {L_hi, L_lo}, {D_hi, D_lo}. One more MFMA
 // whose other operand holds -1 at the matching two positions subtracts them from a whole score tile (error 2^-17
 // relative), which is cheaper than 16 subtractions per lane and tile on the vector ALU.
@@ -180,8 +168,9 @@ __device__ __forceinline__ f32x16 mfma_bf16(const U4& x, const U4& y, f32x16 c)
 // owns 16 keys of ONE query, its log-sum-exp is a scalar, and dS^T, packed to bf16, is the B operand of
 // dQ^T += K^T dS^T, whose A operand comes from the row-major K through the transposing read.
 // -D is the accumulator the dP product starts from, so dP - D costs nothing. The scaled score minus the log-sum-exp is
-//   head_dim 32: one fused multiply-add per element on the plain product q k^T (6 MFMAs per tile). The two more MFMAs
-//                the remainder of the scaled query would take cost the same issue time, more registers and more power;
+//   head_dim 32: one fused multiply-add per element on the product q k^T (6 MFMAs per tile), with as much of the factor in
+//                q as is a power of two. The two more MFMAs the remainder of the scaled query would take cost the same issue
+//                time, more registers and more power;
 //   head_dim 16: the two-term query of the forward kernel with -lse as the starting accumulator (5 MFMAs per tile): there
 //                the remainder is one MFMA, half the issue time of 16 multiply-adds.
 template <int D, int QT>
@@ -276,7 +265,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_dq(AttnBwdArgs b)
                 dot += __uint_as_float(x & 0xFFFF0000u) * __uint_as_float(y & 0xFFFF0000u);
             }
             if (SPLIT) scale_split(qf, a.c_log2, qhi[t][ks], qlo[t][ks]);
-            else qhi[t][ks] = qf;
+            else qhi[t][ks] = scale_pow2(qf, a.q_pow2);
         }
         dot += __shfl_xor(dot, 32, 64);               // the two half-waves hold the two halves of a row
         if (orow[t] >= 0 && hf == 0) b.dsum[orw * a.H + head] = dot;
@@ -298,7 +287,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_dq(AttnBwdArgs b)
     }
     uint32_t tre, tro;
     tr_offsets<D>(lane, tre, tro);
-    const float cl2 = a.c_log2;
+    const float smul = a.s_mul;
 
     struct Rows { U4 k[KS], v[KS]; };                 // the A operands of one key tile's score products
     auto read_rows = [&](Rows& f, uint32_t at) __attribute__((always_inline)) {
@@ -313,7 +302,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_dq(AttnBwdArgs b)
     auto unit = [&](f32x16& s, f32x16& dp, int t, int kbase, const U4& kt0, const U4& kt1, f32x16& sn, f32x16& dpn, const Rows& f, int tn)
         __attribute__((always_inline)) {
         const auto prob = [&](int r) __attribute__((always_inline)) {
-            s[r] = __builtin_amdgcn_exp2f(SPLIT ? s[r] : __builtin_fmaf(s[r], cl2, nl[t]));
+            s[r] = __builtin_amdgcn_exp2f(SPLIT ? s[r] : __builtin_fmaf(s[r], smul, nl[t]));
         };
         if (kbase + 32 > ng) {                        // keys past the end repeat a key of the scope: their dS is dropped here
 #pragma unroll

@@ -69,6 +69,18 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
     return *reinterpret_cast<uint32_t*>(&y);
 }
 
+// bf16 fragment times a power of two: exact
+__device__ __forceinline__ U4 scale_pow2(const U4& x, float p2)
+{
+    U4 y;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const uint32_t w2 = (&x.u.x)[e];
+        (&y.u.x)[e] = pack_bf16(__uint_as_float(w2 << 16) * p2, __uint_as_float(w2 & 0xFFFF0000u) * p2);
+    }
+    return y;
+}
+
 // One 16-byte global -> LDS load per lane: lane i of the wave fills bytes [16 i, 16 i + 16) of the 1 KB block at the
 // LDS byte address `lds` (wave-uniform; it travels in M0). Written as assembly so that the compiler does not count
 // it among its own memory operations: it would otherwise wait for ALL loads in flight before every LDS read that

@@ -385,6 +385,13 @@ static int fill_attn_args(f3d::AttnArgs& a, const void* q, const void* k, const 
     a.C = heads * head_dim;
     const float scale = softmax_scale > 0.0f ? softmax_scale : 1.0f / sqrtf((float)head_dim);
     a.c_log2 = scale * 1.44269504088896340736f;
+    a.q_pow2 = 1.0f;
+    a.s_mul = a.c_log2;
+    if (a.c_log2 < 1.0f) {   // c_log2 = q_pow2 * s_mul, 1 <= s_mul < 2
+        int e = 0;
+        a.s_mul = 2.0f * frexpf(a.c_log2, &e);
+        a.q_pow2 = ldexpf(1.0f, e - 1);
+    }
     a.extra = mode == F3D_STRIDE ? stride + 1 : 2;
     *scale_out = scale;
     *slots_out = max_buckets / scope_buckets + (long long)a.extra * n_scans + 1;
@@ -410,6 +417,9 @@ static int attn_forward(int f16, const void* q, const void* k, const void* v, co
     a.out_perm = out_perm;
     a.lse = lse;
     a.f16 = f16;
+    // binary16: 32 products of its largest values stay below 2^37, so a factor of 2^90 keeps every score finite; different
+    // scores are then so far apart that a larger factor changes no probability
+    if (f16) a.s_mul = fminf(a.c_log2, 0x1p90f);
     const int bm = f3d::attn_block_rows(head_dim, slots, heads, bucket_cap);
     a.qblocks = (bucket_cap + bm - 1) / bm;
     if (slots * heads * a.qblocks > 2000000000ll) return F3D_ERR_UNSUPPORTED;

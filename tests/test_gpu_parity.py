@@ -599,6 +599,42 @@ def test_attention_two_term_query_at_very_large_norms():
     assert lerr <= 4e-3 + 2.0 ** -15 * norm, f"lse error {lerr:.4g} at norm {norm:.4g}"
 
 
+@pytest.mark.parametrize("d", [16, 32])
+def test_attention_products_beyond_binary32_with_finite_scores(d):
+    """Only the scaled scores have to be finite. q and k times 2^63 and the scale times 2^-126 leave every score as it is,
+    while most products q k^T pass the largest binary32. All factors are powers of two: output, log-sum-exp and
+    gradients are those of the unscaled inputs, bit for bit up to the same powers of two."""
+    heads = 2
+    rng = np.random.default_rng(46)
+    for sizes in ([[64, 64, 64, 50, 64, 64, 9], [64, 3]], [[128] * 3 + [17]] * 60):     # one and two tiles per wave
+        bk, ref, n = hand_layout(sizes, 4 * max(max(s) for s in sizes), 4)
+        q, k, v, g = (dev(wl.f32_to_bf16_bits(rng.standard_normal((n, heads * d)).astype(np.float32)), torch.bfloat16) for _ in range(4))
+        assert float((q[:64].float() @ k[:64].float().t()).abs().max()) * 2.0 ** 126 > 2.0 ** 128
+        for mode in ("plain", "stride"):
+            got = []
+            for up, scale in ((1.0, 1.0), (2.0 ** 63, 2.0 ** -126)):
+                lse = torch.empty(n, heads, dtype=torch.float32, device=DEV)
+                out = f3d.bucket_swin_attn(q * up, k * up, v, bk, heads, d, mode, softmax_scale=scale, lse=lse)
+                dq, dk, dv = f3d.bucket_swin_attn_bwd(q * up, k * up, v, out, g, lse, bk, heads, d, mode, softmax_scale=scale)
+                got.append((out, lse, dq * up, dk * up, dv))
+            for a, b in zip(*got):
+                assert torch.isfinite(a).all() and torch.equal(a, b)
+
+
+@pytest.mark.parametrize("d", [16, 32])
+def test_attention_f16_finite_for_every_scale(d):
+    # a softmax that has long saturated: the value of the key with the largest score, whatever finite scale comes on top
+    bk, ref, n = hand_layout([[64, 64, 64, 50, 64, 64, 9], [64, 3]], 256, 4)
+    rng = np.random.default_rng(47)
+    q, k, v = (dev(rng.standard_normal((n, 2 * d)).astype(np.float16)) for _ in range(3))
+    for size in (1.0, 2000.0):
+        for mode in ("plain", "stride"):
+            out = [f3d.bucket_swin_attn(q * size, k * size, v, bk, 2, d, mode, softmax_scale=s) for s in (1e20, 1e30, 3e38)]
+            assert all(torch.isfinite(o).all() for o in out)
+            if d == 32:
+                assert torch.equal(out[0], out[1]) and torch.equal(out[0], out[2])
+
+
 def test_attention_large_values_meet_the_relative_bound():
     """Values of magnitude up to about 12 and a peaked softmax (scale 1): outputs are then near single V rows and the
     absolute 1e-2 no longer covers the bf16 rounding of the output itself (2^-9 |o|), nor that of the probabilities
