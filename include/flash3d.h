@@ -244,6 +244,7 @@ int f3d_bucket_swin_attn_f16(const void *q, const void *k, const void *v, const 
  *               gradients in the input order of the points)
  *   grad_perm   NULL or [n] int32, a permutation
  *   workspace   >= f3d_attn_bwd_workspace_bytes(n, heads), 256-byte aligned
+ * In place: one of dq, dk, dv may be out (which is then lost); they overlap nothing else.
  * Arithmetic: bf16 operands, fp32 accumulation; P and dS are rounded to bf16 before the second products.
  */
 int f3d_attn_bwd_workspace_bytes(int64_t n, int32_t heads, size_t *out_bytes);

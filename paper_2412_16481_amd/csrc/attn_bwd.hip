@@ -163,6 +163,30 @@ __device__ __forceinline__ f32x16 mfma_bf16(const U4& x, const U4& y, f32x16 c)
 }
 
 // ------------------------------------------------------------------------------------------------
+// D by itself, one row and head per thread, for calls whose dQ takes the place of the forward output and is stored at
+// permuted rows: there a workgroup of the dQ kernel would read output rows that another has overwritten.
+template <int D>
+__global__ __launch_bounds__(256) void k_attn_bwd_d(AttnBwdArgs b)
+{
+    const AttnArgs& a = b.f;
+    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (i >= (long long)a.n * a.H) return;
+    const size_t at = (size_t)(i / a.H) * a.C + (size_t)(i % a.H) * D;
+    float dot = 0.f;
+#pragma unroll
+    for (int c = 0; c < D; c += 8) {
+        const uint4 x = *reinterpret_cast<const uint4*>(a.out + at + c), y = *reinterpret_cast<const uint4*>(b.dout + at + c);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t p = (&x.x)[e], g = (&y.x)[e];
+            dot += __uint_as_float(p << 16) * __uint_as_float(g << 16);
+            dot += __uint_as_float(p & 0xFFFF0000u) * __uint_as_float(g & 0xFFFF0000u);
+        }
+    }
+    b.dsum[i] = dot;
+}
+
+// ------------------------------------------------------------------------------------------------
 // dQ, and on the way D, which the other kernel reads. A wave owns QT tiles of 32 query rows; K and V stream through LDS in
 // stages of 128 key rows, three resident, as in the forward kernel. Scores are transposed (keys x queries), so a lane
 // owns 16 keys of ONE query, its log-sum-exp is a scalar, and dS^T, packed to bf16, is the B operand of
@@ -257,7 +281,8 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_dq(AttnBwdArgs b)
             U4 qf, of;
             qf.u = *reinterpret_cast<const uint4*>(a.q + qrd[t] * a.C + hoff + ks * 16 + hf * 8);
             dof[t][ks].u = *reinterpret_cast<const uint4*>(b.dout + orw * a.C + hoff + ks * 16 + hf * 8);
-            of.u = *reinterpret_cast<const uint4*>(a.out + orw * a.C + hoff + ks * 16 + hf * 8);
+            of.u = make_uint4(0, 0, 0, 0);
+            if (!b.d_first) of.u = *reinterpret_cast<const uint4*>(a.out + orw * a.C + hoff + ks * 16 + hf * 8);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const uint32_t x = (&of.u.x)[e], y = (&dof[t][ks].u.x)[e];
@@ -268,7 +293,8 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_dq(AttnBwdArgs b)
             else qhi[t][ks] = scale_pow2(qf, a.q_pow2);
         }
         dot += __shfl_xor(dot, 32, 64);               // the two half-waves hold the two halves of a row
-        if (orow[t] >= 0 && hf == 0) b.dsum[orw * a.H + head] = dot;
+        if (b.d_first) dot = b.dsum[orw * a.H + head];
+        else if (orow[t] >= 0 && hf == 0) b.dsum[orw * a.H + head] = dot;
         // past the end: probabilities exactly zero
         nl[t] = orow[t] >= 0 ? -LOG2E * a.lse[orw * a.H + head] : -1e30f;
 #pragma unroll
@@ -677,6 +703,7 @@ template <int D>
 hipError_t launch_d(const AttnBwdArgs& b, hipStream_t stream)
 {
     const AttnArgs& a = b.f;
+    if (b.d_first) k_attn_bwd_d<D><<<(unsigned)(((long long)a.n * a.H + 255) / 256), 256, 0, stream>>>(b);
     long long total = (long long)a.n_slots * a.H * a.qblocks;
     total = (total + 7) / 8 * 8;
     if (total > 0) {

@@ -495,6 +495,8 @@ int f3d_bucket_swin_attn_bwd(const void* q, const void* k, const void* v, const 
     b.dk = (uint16_t*)dk;
     b.dv = (uint16_t*)dv;
     b.scale = scale;
+    const uintptr_t at = (uintptr_t)out, dq_at = (uintptr_t)dq, size = (uintptr_t)n * heads * head_dim * 2;
+    b.d_first = at < dq_at + size && dq_at < at + size && (at != dq_at || grad_perm);
     if (slots * heads * ((bucket_cap + 127) / 128) > 2000000000ll) return F3D_ERR_UNSUPPORTED;
     // two tiles per wave share every staged row; one where a scope is short or the launch would leave compute units
     // without a workgroup (the forward kernel's rule)

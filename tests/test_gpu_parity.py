@@ -971,6 +971,33 @@ def test_attention_backward_two_tiles_per_wave_ragged(d, heads):
         bwd_case(q, k, v, g, bk, ref, heads, d, mode, mode != "shift", scope_sel=sel)
 
 
+@pytest.mark.parametrize("d", [16, 32])
+def test_attention_backward_gradient_in_place_of_the_output(d):
+    # any of the three gradients may take the forward output's place, bucket-major or at permuted rows
+    heads, rng = 3, np.random.default_rng(66)
+    bk, ref, n = hand_layout([[64] * 9 + [40], [64] * 30 + [1]], 256, 4)
+    q, k, v, g = (dev(wl.f32_to_bf16_bits(rng.standard_normal((n, heads * d)).astype(np.float32)), torch.bfloat16) for _ in range(4))
+    lse = torch.empty(n, heads, dtype=torch.float32, device=DEV)
+    out = f3d.bucket_swin_attn(q, k, v, bk, heads, d, "plain", lse=lse)
+    ws = torch.empty(n * heads * 4 + 256, dtype=torch.uint8, device=DEV)
+    for original_order in (False, True):
+        want = f3d.bucket_swin_attn_bwd(q, k, v, out, g, lse, bk, heads, d, "plain", original_order=original_order)
+        for which in range(3):
+            o = out.clone()
+            grads = [o if i == which else torch.empty_like(q) for i in range(3)]
+            perm = bk.perm.data_ptr()
+            rc = f3d.lib().f3d_bucket_swin_attn_bwd(
+                q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), g.data_ptr(), lse.data_ptr(), perm, bk.offsets.data_ptr(),
+                bk.scan_bucket_start.data_ptr(), n, bk.n_scans, bk.max_buckets, bk.bucket_cap, bk.scope_buckets, 0, 2, 2, heads, d, 0.0,
+                *(t.data_ptr() for t in grads), perm if original_order else None, ws.data_ptr(), ws.numel(),
+                torch.cuda.current_stream().cuda_stream)
+            assert rc == 0
+            for a, b in zip(grads, want):
+                # D may be summed in another order: binary32, far below the rounding of the gradients to bf16
+                assert float((a.float() - b.float()).abs().max()) <= 2.0 ** -6 * float(b.float().abs().max())
+                assert float((a != b).float().mean()) <= 0.01
+
+
 def test_attention_backward_short_scopes_with_peaked_softmax():
     """Where a flat bound on the gradient error fails: scopes of a few dozen rows with a peaked softmax, in which the
     rounding of the stored output moves D by an amount common to all keys of a row. (a) 27218 points in four uneven
