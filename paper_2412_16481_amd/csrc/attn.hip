@@ -343,6 +343,10 @@ __global__ __launch_bounds__(256, 3) void k_attn(AttnArgs a)
                 }
             }
             if (ROBUST) {
+                if (!SPLIT) {
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) s[r] *= post;
+                }
                 float mx = fmaxf(fmaxf(s[0], s[1]), s[2]);
 #pragma unroll
                 for (int r = 3; r < 15; r += 2) mx = fmaxf(fmaxf(mx, s[r]), s[r + 1]);
@@ -351,7 +355,6 @@ __global__ __launch_bounds__(256, 3) void k_attn(AttnArgs a)
                     const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_int(mx), __float_as_int(mx), false, false);
                     mx = fmaxf(__int_as_float(sw[0]), __int_as_float(sw[1]));
                 }
-                if (!SPLIT) mx *= post;
                 // the reference follows the maximum only when a score exceeds it by more than 2^8 (the first
                 // tile sets it): exponentials stay below 256 and O is rescaled rarely
                 if (first[t] || __builtin_amdgcn_ballot_w64(mx > m_ref[t] + 8.0f)) {
@@ -367,7 +370,7 @@ __global__ __launch_bounds__(256, 3) void k_attn(AttnArgs a)
                     if (D == 32) l_run[t] *= alpha;
                 }
 #pragma unroll
-                for (int r = 0; r < 16; ++r) s[r] = SPLIT ? s[r] - m_ref[t] : __builtin_fmaf(s[r], post, -m_ref[t]);
+                for (int r = 0; r < 16; ++r) s[r] -= m_ref[t];
             }
             const auto prob = [&](float x) __attribute__((always_inline)) { return __builtin_amdgcn_exp2f((SPLIT || ROBUST) ? x : x * post); };
             F3D_SB();
