@@ -141,7 +141,7 @@ __global__ __launch_bounds__(LTH, 3) void k_ln_linear(LinearArgs a)
     }
     uint4 rn[2] = {make_uint4(0, 0, 0, 0), make_uint4(0, 0, 0, 0)};   // residual of the next 32-column block
     auto fetch_residual = [&](int block) __attribute__((always_inline)) {
-        const uint4* rp = reinterpret_cast<const uint4*>(a.residual + drow * a.c_out + min(block * 32 + 16 * hf, a.c_out - 16));
+        const uint4* rp = reinterpret_cast<const uint4*>(a.residual + drow * a.c_out + block * 32 + 16 * hf);
         rn[0] = rp[0];
         rn[1] = rp[1];
     };
@@ -212,7 +212,7 @@ __global__ __launch_bounds__(LTH, 3) void k_ln_linear(LinearArgs a)
         for (int cb = 0; cb < TCB; ++cb) {
             const int col0 = (t * TCB + cb) << 5;
             const uint4 rv[2] = {rn[0], rn[1]};
-            if (RES) fetch_residual(t * TCB + cb + 1);
+            if (RES && (cb + 1 < TCB || t + 1 < t_end)) fetch_residual(t * TCB + cb + 1);
             const int col = col0 + 16 * hf;                      // first of this lane's 16 columns
             f32x16 acc;
 #pragma unroll
@@ -268,6 +268,7 @@ __global__ __launch_bounds__(LTH, 3) void k_ln_linear(LinearArgs a)
                 }
             }
         }
+        if (t + 1 == t_end) break;
         // The next tile has landed for this wave once only memory operations younger than its loads are outstanding: the
         // tile's own stores (with residual loads between them: the last four), or the residual loads of a tile that stores
         // nothing yet. A wave with rows missing leaves out stores.
