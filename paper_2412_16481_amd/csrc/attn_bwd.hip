@@ -197,7 +197,8 @@ __global__ __launch_bounds__(256) void k_attn_bwd_d(AttnBwdArgs b)
 //                time, more registers and more power;
 //   head_dim 16: the two-term query of the forward kernel with -lse as the starting accumulator (5 MFMAs per tile): there
 //                the remainder is one MFMA, half the issue time of 16 multiply-adds.
-template <int D, int QT>
+// DF: D is there already (k_attn_bwd_d)
+template <int D, int QT, bool DF>
 __global__ __launch_bounds__(256, 2) void k_attn_bwd_dq(AttnBwdArgs b)
 {
     using L = BLay<D>;
@@ -281,10 +282,9 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_dq(AttnBwdArgs b)
             U4 qf, of;
             qf.u = *reinterpret_cast<const uint4*>(a.q + qrd[t] * a.C + hoff + ks * 16 + hf * 8);
             dof[t][ks].u = *reinterpret_cast<const uint4*>(b.dout + orw * a.C + hoff + ks * 16 + hf * 8);
-            of.u = make_uint4(0, 0, 0, 0);
-            if (!b.d_first) of.u = *reinterpret_cast<const uint4*>(a.out + orw * a.C + hoff + ks * 16 + hf * 8);
+            if (!DF) of.u = *reinterpret_cast<const uint4*>(a.out + orw * a.C + hoff + ks * 16 + hf * 8);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
+            for (int e = 0; e < 4 && !DF; ++e) {
                 const uint32_t x = (&of.u.x)[e], y = (&dof[t][ks].u.x)[e];
                 dot += __uint_as_float(x << 16) * __uint_as_float(y << 16);
                 dot += __uint_as_float(x & 0xFFFF0000u) * __uint_as_float(y & 0xFFFF0000u);
@@ -293,7 +293,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_dq(AttnBwdArgs b)
             else qhi[t][ks] = scale_pow2(qf, a.q_pow2);
         }
         dot += __shfl_xor(dot, 32, 64);               // the two half-waves hold the two halves of a row
-        if (b.d_first) dot = b.dsum[orw * a.H + head];
+        if (DF) dot = b.dsum[orw * a.H + head];
         else if (orow[t] >= 0 && hf == 0) b.dsum[orw * a.H + head] = dot;
         // past the end: probabilities exactly zero
         nl[t] = orow[t] >= 0 ? -LOG2E * a.lse[orw * a.H + head] : -1e30f;
@@ -703,12 +703,15 @@ template <int D>
 hipError_t launch_d(const AttnBwdArgs& b, hipStream_t stream)
 {
     const AttnArgs& a = b.f;
-    if (b.d_first) k_attn_bwd_d<D><<<(unsigned)(((long long)a.n * a.H + 255) / 256), 256, 0, stream>>>(b);
     long long total = (long long)a.n_slots * a.H * a.qblocks;
     total = (total + 7) / 8 * 8;
-    if (total > 0) {
-        if (b.tiles == 2) k_attn_bwd_dq<D, 2><<<(unsigned)total, 256, 0, stream>>>(b);
-        else k_attn_bwd_dq<D, 1><<<(unsigned)total, 256, 0, stream>>>(b);
+    if (total > 0 && b.d_first) {
+        k_attn_bwd_d<D><<<(unsigned)(((long long)a.n * a.H + 255) / 256), 256, 0, stream>>>(b);
+        if (b.tiles == 2) k_attn_bwd_dq<D, 2, true><<<(unsigned)total, 256, 0, stream>>>(b);
+        else k_attn_bwd_dq<D, 1, true><<<(unsigned)total, 256, 0, stream>>>(b);
+    } else if (total > 0) {
+        if (b.tiles == 2) k_attn_bwd_dq<D, 2, false><<<(unsigned)total, 256, 0, stream>>>(b);
+        else k_attn_bwd_dq<D, 1, false><<<(unsigned)total, 256, 0, stream>>>(b);
     }
     total = (long long)a.n_slots * a.H * b.kblocks;
     total = (total + 7) / 8 * 8;
