@@ -43,6 +43,7 @@ struct AttnBwdArgs {
     uint16_t* dv;
     float scale;            // softmax scale (the forward's c_log2 divided by log2 e)
     int d_first;            // dq overwrites the forward output at other rows: D is summed by a kernel of its own, first
+    int ahead;              // the score products run a tile ahead (always with two tiles); 0: the form for short scopes
     int tiles;              // tiles of 32 rows a wave owns (1 or 2): queries in the dQ kernel, keys in the dK/dV kernel
     int kblocks;            // ceil(bucket_cap / (128 * tiles)): row blocks of a scope (f.qblocks is the same)
 };

@@ -24,7 +24,9 @@
 // Measured per pass on that input: dQ and D 2.57 -> 1.87 ms, dK/dV 3.19 -> 2.51 ms against staging through registers with
 // a transposed copy written by 2-byte LDS stores (bank conflicts in every one of them), a separate pass for D and no
 // overlap of one tile's products with another's exponentials; on 200000 points x 4 heads x 16: 0.199 -> 0.175 and
-// 0.251 -> 0.232 ms. One row tile per wave at three waves per SIMD (dQ 2.06, dK/dV 3.30 ms) is slower.
+// 0.251 -> 0.232 ms. One row tile per wave at three waves per SIMD (dQ 2.06, dK/dV 3.30 ms) is slower there. In scopes of a
+// few tiles latency is the bound instead, and a form of each kernel without the overlap, in fewer registers, puts three
+// workgroups on a compute unit (the rule and its figures: f3d_bucket_swin_attn_bwd).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -197,9 +199,9 @@ __global__ __launch_bounds__(256) void k_attn_bwd_d(AttnBwdArgs b)
 //                time, more registers and more power;
 //   head_dim 16: the two-term query of the forward kernel with -lse as the starting accumulator (5 MFMAs per tile): there
 //                the remainder is one MFMA, half the issue time of 16 multiply-adds.
-// DF: D is there already (k_attn_bwd_d)
-template <int D, int QT, bool DF>
-__global__ __launch_bounds__(256, 2) void k_attn_bwd_dq(AttnBwdArgs b)
+// DF: D is there already (k_attn_bwd_d). AHEAD: the score products run a tile ahead; without, the form for short scopes
+template <int D, int QT, bool DF, bool AHEAD>
+__global__ __launch_bounds__(256, AHEAD ? 2 : 3) void k_attn_bwd_dq(AttnBwdArgs b)
 {
     using L = BLay<D>;
     constexpr bool SPLIT = D == 16;
@@ -387,6 +389,44 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_dq(AttnBwdArgs b)
     __syncthreads();
     if (nst > 2) fetch_rows(2);
 
+    if (!AHEAD) {
+        static_assert(AHEAD || QT == 1, "one tile per wave");
+        for (int st = 0, buf = 0; st < nst; ++st, buf = buf + 1 == L::NBUF ? 0 : buf + 1) {
+#pragma unroll 1
+            for (int t4 = 0; t4 < 4 && 4 * st + t4 < ntile; ++t4) {
+                const uint32_t at = buf * L::BUF + t4 * L::TILE;
+                const int kbase = st * SR + t4 * 32;
+                Rows f;
+                read_rows(f, at);
+                U4 kt0, kt1, p0, p1;
+                read_tr<D>(kt0, kt1, sK + at + tre, sK + at + tro);
+                f32x16 s = SPLIT ? iS[0] : f32x16{0}, dp = iD[0];
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) {
+                    s = mfma_bf16(f.k[ks], qhi[0][ks], s);
+                    if (SPLIT) s = mfma_bf16(f.k[ks], qlo[0][ks], s);
+                    dp = mfma_bf16(f.v[ks], dof[0][ks], dp);
+                }
+                if (kbase + 32 > ng) {
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        if (kbase + 8 * (r >> 2) + 4 * hf + (r & 3) >= ng) dp[r] = 0.f;
+                }
+#pragma unroll
+                for (int r = 0; r < 16; ++r) dp[r] *= __builtin_amdgcn_exp2f(SPLIT ? s[r] : __builtin_fmaf(s[r], smul, nl[0]));
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    (&p0.u.x)[e] = pack_bf16(dp[2 * e], dp[2 * e + 1]);
+                    (&p1.u.x)[e] = pack_bf16(dp[8 + 2 * e], dp[8 + 2 * e + 1]);
+                }
+                acc[0] = mfma_bf16(kt0, p0, acc[0]);
+                acc[0] = mfma_bf16(kt1, p1, acc[0]);
+                if (t4 == 1) handover(st);
+            }
+        }
+        store_grad_rows<D>(b.dq, a.out_perm, orow[0], a.C, hoff, hf, acc[0], b.scale);
+        return;
+    }
     f32x16 sa, sb, da, db;
     Rows f;
     read_rows(f, 0);
@@ -437,8 +477,8 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_dq(AttnBwdArgs b)
 // The vector ALU (16 exponentials, 16 or 32 multiplies and 16 packs per tile and lane) and the matrix core (10 MFMAs at
 // head_dim 32) are both busy, so the loop runs one score tile ahead: the products of the next tile are issued between
 // the exponentials, multiplies and packs of the current one.
-template <int D, int KTW>
-__global__ __launch_bounds__(256, 2) void k_attn_bwd_dkdv(AttnBwdArgs b)
+template <int D, int KTW, bool AHEAD>
+__global__ __launch_bounds__(256, AHEAD ? 2 : 3) void k_attn_bwd_dkdv(AttnBwdArgs b)
 {
     using L = BLay<D>;
     constexpr bool SPLIT = D == 16;
@@ -654,6 +694,47 @@ __global__ __launch_bounds__(256, 2) void k_attn_bwd_dkdv(AttnBwdArgs b)
     __builtin_amdgcn_s_waitcnt(0x0F70);       // stages 0 and 1 have landed for every wave
     __syncthreads();
 
+    if (!AHEAD) {
+        static_assert(AHEAD || KTW == 1, "one tile per wave");
+        for (int st = 0, buf = 0; st < nst; ++st, buf = buf + 1 == L::NBUF ? 0 : buf + 1) {
+#pragma unroll 1
+            for (int t4 = 0; t4 < 4 && 4 * st + t4 < ntile; ++t4) {
+                const uint32_t at = buf * L::BUF + t4 * L::TILE;
+                Rows f;
+                read_rows(f, at, (buf * SR + t4 * 32) * 8);
+                U4 qt0, qt1, gt0, gt1, p0, p1, d0, d1;
+                f32x16 s = mfma_bf16(f.x, negS, f32x16{0}), dp = mfma_bf16(f.x, negD, f32x16{0});
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) {
+                    s = mfma_bf16(f.q[ks], khi[0][ks], s);
+                    if (SPLIT) s = mfma_bf16(f.q[ks], klo[0][ks], s);
+                    dp = mfma_bf16(f.g[ks], vfr[0][ks], dp);
+                }
+                read_tr<D>(gt0, gt1, sG + at + tre, sG + at + tro);
+                read_tr<D>(qt0, qt1, sQ + at + tre, sQ + at + tro);
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    s[r] = __builtin_amdgcn_exp2f(SPLIT ? s[r] : s[r] * cres);
+                    dp[r] *= s[r];
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    (&p0.u.x)[e] = pack_bf16(s[2 * e], s[2 * e + 1]);
+                    (&p1.u.x)[e] = pack_bf16(s[8 + 2 * e], s[8 + 2 * e + 1]);
+                    (&d0.u.x)[e] = pack_bf16(dp[2 * e], dp[2 * e + 1]);
+                    (&d1.u.x)[e] = pack_bf16(dp[8 + 2 * e], dp[8 + 2 * e + 1]);
+                }
+                dv[0] = mfma_bf16(gt0, p0, dv[0]);
+                dv[0] = mfma_bf16(gt1, p1, dv[0]);
+                dk[0] = mfma_bf16(qt0, d0, dk[0]);
+                dk[0] = mfma_bf16(qt1, d1, dk[0]);
+                if (t4 == 1) handover(st);
+            }
+        }
+        store_grad_rows<D>(b.dk, a.out_perm, krow[0], a.C, hoff, hf, dk[0], b.scale);
+        store_grad_rows<D>(b.dv, a.out_perm, krow[0], a.C, hoff, hf, dv[0], 1.0f);
+        return;
+    }
     f32x16 sa, sb, da, db;
     Rows f;
     read_rows(f, 0, 0);
@@ -707,17 +788,19 @@ hipError_t launch_d(const AttnBwdArgs& b, hipStream_t stream)
     total = (total + 7) / 8 * 8;
     if (total > 0 && b.d_first) {
         k_attn_bwd_d<D><<<(unsigned)(((long long)a.n * a.H + 255) / 256), 256, 0, stream>>>(b);
-        if (b.tiles == 2) k_attn_bwd_dq<D, 2, true><<<(unsigned)total, 256, 0, stream>>>(b);
-        else k_attn_bwd_dq<D, 1, true><<<(unsigned)total, 256, 0, stream>>>(b);
+        if (b.tiles == 2) k_attn_bwd_dq<D, 2, true, true><<<(unsigned)total, 256, 0, stream>>>(b);
+        else k_attn_bwd_dq<D, 1, true, true><<<(unsigned)total, 256, 0, stream>>>(b);
     } else if (total > 0) {
-        if (b.tiles == 2) k_attn_bwd_dq<D, 2, false><<<(unsigned)total, 256, 0, stream>>>(b);
-        else k_attn_bwd_dq<D, 1, false><<<(unsigned)total, 256, 0, stream>>>(b);
+        if (b.tiles == 2) k_attn_bwd_dq<D, 2, false, true><<<(unsigned)total, 256, 0, stream>>>(b);
+        else if (b.ahead) k_attn_bwd_dq<D, 1, false, true><<<(unsigned)total, 256, 0, stream>>>(b);
+        else k_attn_bwd_dq<D, 1, false, false><<<(unsigned)total, 256, 0, stream>>>(b);
     }
     total = (long long)a.n_slots * a.H * b.kblocks;
     total = (total + 7) / 8 * 8;
     if (total > 0) {
-        if (b.tiles == 2) k_attn_bwd_dkdv<D, 2><<<(unsigned)total, 256, 0, stream>>>(b);
-        else k_attn_bwd_dkdv<D, 1><<<(unsigned)total, 256, 0, stream>>>(b);
+        if (b.tiles == 2) k_attn_bwd_dkdv<D, 2, true><<<(unsigned)total, 256, 0, stream>>>(b);
+        else if (b.ahead) k_attn_bwd_dkdv<D, 1, true><<<(unsigned)total, 256, 0, stream>>>(b);
+        else k_attn_bwd_dkdv<D, 1, false><<<(unsigned)total, 256, 0, stream>>>(b);
     }
     return hipGetLastError();
 }

@@ -501,6 +501,20 @@ int f3d_bucket_swin_attn_bwd(const void* q, const void* k, const void* v, const 
     // two tiles per wave share every staged row; one where a scope is short or the launch would leave compute units
     // without a workgroup (the forward kernel's rule)
     b.tiles = f3d::attn_block_rows(head_dim, slots, heads, bucket_cap) / 128;
+    b.ahead = 1;
+    // rows of a scope in a scan of average size. Short scopes keep a workgroup for a few tiles only, most of it waiting for
+    // loads: there three workgroups per compute unit of the plain one-tile form are faster than two that overlap one tile's
+    // products with another's exponentials (100000 points, scope 128, 8 heads x 32 / x 16: 160 / 90 us against 189 / 109;
+    // 600 scans of 333 points 1029 / 770 against 1387 / 1148). Full scopes of 512 rows are past it (277 / 206 against 308 /
+    // 211); at head_dim 16, where the gain is smaller, half-filled blocks of 256 rows cost more than it gives (200 scans of
+    // 1000 points, scope 1024: 799 against 853).
+    const int64_t scan = (n + n_scans - 1) / n_scans, buckets = (scan * scope_buckets + bucket_cap - 1) / bucket_cap;
+    const int64_t round = (int64_t)scope_buckets * stride, rest = mode == F3D_STRIDE ? buckets % round : 0;
+    const int64_t scopes = mode == F3D_STRIDE ? buckets / round * stride + (rest < stride ? rest : stride) : (buckets + scope_buckets - 1) / scope_buckets;
+    if (scan / scopes < 448 || (b.tiles == 2 && head_dim == 16 && scan < 2 * (int64_t)bucket_cap)) {
+        b.ahead = 0;
+        b.tiles = 1;
+    }
     b.kblocks = (bucket_cap + 128 * b.tiles - 1) / (128 * b.tiles);
     b.f.qblocks = b.kblocks;
     b.f.n_slots = (int)slots;

@@ -604,10 +604,12 @@ def test_attention_products_beyond_binary32_with_finite_scores(d):
     """Only the scaled scores have to be finite. q and k times 2^63 and the scale times 2^-126 leave every score as it is,
     while most products q k^T pass the largest binary32. All factors are powers of two: output, log-sum-exp and
     gradients are those of the unscaled inputs, bit for bit up to the same powers of two."""
-    heads = 2
+    heads = 4
     rng = np.random.default_rng(46)
-    for sizes in ([[64, 64, 64, 50, 64, 64, 9], [64, 3]], [[128] * 3 + [17]] * 60):     # one and two tiles per wave
+    # short scopes, long ones with one and with two tiles per wave
+    for sizes, rows in (([[64, 64, 64, 50, 64, 64, 9], [64, 3]], 128), ([[128] * 8 + [33]], 128), ([[128] * 32 + [17]] * 10, 256)):
         bk, ref, n = hand_layout(sizes, 4 * max(max(s) for s in sizes), 4)
+        assert f3d.attn_block_rows(bk, heads, d) == rows
         q, k, v, g = (dev(wl.f32_to_bf16_bits(rng.standard_normal((n, heads * d)).astype(np.float32)), torch.bfloat16) for _ in range(4))
         assert float((q[:64].float() @ k[:64].float().t()).abs().max()) * 2.0 ** 126 > 2.0 ** 128
         for mode in ("plain", "stride"):
@@ -956,19 +958,36 @@ def test_attention_backward_full_size_sampled_scopes(name):
 
 @pytest.mark.parametrize("d,heads", [(16, 4), (32, 3)])
 def test_attention_backward_two_tiles_per_wave_ragged(d, heads):
-    # enough workgroups for two row tiles per wave, last buckets around the 32-row tile, 128-row stage and 256-row block
+    # enough workgroups for two row tiles per wave, last buckets around the 32-row tile, 128-row stage and 256-row block:
+    # scans of many scopes take two tiles, scans of one or two the form for short scopes
     tails = [1, 31, 32, 33, 64, 95, 96, 97, 127, 128]
-    sizes = [[128] * (2 + i % 4) + [tails[i % len(tails)]] for i in range(40)]
-    bk, ref, n = hand_layout(sizes, 512, 4)
-    rng = np.random.default_rng(64)
-    q, k, v, g = (wl.f32_to_bf16_bits(rng.standard_normal((n, heads * d)).astype(np.float32)) for _ in range(4))
-    sel = np.zeros(n, dtype=np.uint8)
-    ends = np.cumsum([sum(x) for x in sizes])
-    sel[ends[:10] - 1] = 1                       # the last scope of ten scans, and a whole one
-    sel[0] = 1
-    for mode in ("plain", "shift", "stride"):
-        assert f3d.attn_block_rows(bk, heads, d, mode) == 256
-        bwd_case(q, k, v, g, bk, ref, heads, d, mode, mode != "shift", scope_sel=sel)
+    for scan, scans in ((32, 10), (2, 40)):
+        sizes = [[128] * (scan + i % 4) + [tails[i % len(tails)]] for i in range(scans)]
+        bk, ref, n = hand_layout(sizes, 512, 4)
+        rng = np.random.default_rng(64)
+        q, k, v, g = (wl.f32_to_bf16_bits(rng.standard_normal((n, heads * d)).astype(np.float32)) for _ in range(4))
+        sel = np.zeros(n, dtype=np.uint8)
+        ends = np.cumsum([sum(x) for x in sizes])
+        sel[ends[:10] - 1] = 1                       # the last scope of ten scans, and a whole one
+        sel[0] = 1
+        for mode in ("plain", "shift", "stride"):
+            assert f3d.attn_block_rows(bk, heads, d, mode) == 256
+            bwd_case(q, k, v, g, bk, ref, heads, d, mode, mode != "shift", scope_sel=sel)
+
+
+@pytest.mark.parametrize("d,heads", [(16, 3), (32, 2)])
+def test_attention_backward_short_and_long_scopes_one_tile_per_wave(d, heads):
+    # the form for short scopes (an average below 448 rows) over one to four stages with last tiles of every kind, and
+    # scopes of 512 rows in a launch too small for two tiles
+    rng = np.random.default_rng(67)
+    rows = [1, 31, 32, 33, 127, 128, 129, 160, 255, 257, 384, 385, 440, 512]
+    scans = [[128] * (r // 128) + ([r % 128] if r % 128 else []) for r in rows]
+    for sizes in (scans, [[128] * 8 + [97]]):
+        bk, ref, n = hand_layout(sizes, 512, 4)
+        q, k, v, g = (wl.f32_to_bf16_bits(rng.standard_normal((n, heads * d)).astype(np.float32)) for _ in range(4))
+        for mode in ("plain", "shift", "stride"):
+            assert f3d.attn_block_rows(bk, heads, d, mode) == 128
+            bwd_case(q, k, v, g, bk, ref, heads, d, mode, mode != "shift")
 
 
 @pytest.mark.parametrize("d", [16, 32])
