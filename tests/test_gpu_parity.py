@@ -150,6 +150,21 @@ def test_bucketize_one_workgroup_per_scan_is_refused_above_1024_buckets_per_scan
     assert e.value.code == f3d.ERR_UNSUPPORTED
 
 
+@pytest.mark.parametrize("hash", ["zorder_div", "zorder_mod"])
+def test_bucketize_scan_path_axis_probes_with_wide_voxels(hash):
+    # voxel coordinates below and above 2^11 and up to the saturation at 2^21 - 1, an axis on which the scan is flat, probe
+    # steps from one voxel to beyond the box: the workgroup that walks a scan moves the Z-order code itself
+    rng = np.random.default_rng(33)
+    c = np.concatenate([clustered_cloud(rng, 3000), (rng.random((3000, 3)) * 6.0).astype(np.float32)])
+    flat = c.copy()
+    flat[:, 1] = 2.5
+    bo = np.array([0, 2900, 2900, 6000], dtype=np.int32)
+    for cloud in (c, flat):
+        for voxel in (0.02, 0.0015, 1e-6):
+            for step in (0, 1, 700, 1 << 22):
+                check_bucketize(cloud, bo, voxel, 128, 4, hash, schedule="scans", probe_step=step)
+
+
 @pytest.mark.parametrize("hash", HASHES)
 def test_bucketize_small_scans_in_registers(hash):
     # scans that fit one workgroup's registers: around a wave, a workgroup, and one past the last (another path); clustered
@@ -566,16 +581,20 @@ def test_attention_running_maximum_sweep_on_two_query_tiles_per_wave(d):
                   atol=max(ATOL_F16, 1.25 * 2.0 ** -11 * vmax))
 
 
-def test_attention_two_term_query_at_very_large_norms():
-    """The scale is folded into q as two bf16 terms, so a scaled score is exact to about 2^-16 of sum_c |q_c k_c| scale
-    (not of the score). The header states the size of the effect: with |q||k| scale near 10^4 single outputs move by a
+@pytest.mark.parametrize("d", [16, 32])
+def test_attention_two_term_query_at_very_large_norms(d):
+    """At head_dim 16 the scale is folded into q as two bf16 terms, so a scaled score is exact to about 2^-16 of
+    sum_c |q_c k_c| scale (not of the score). The header states the size of the effect: with |q||k| scale near 10^4 single outputs move by a
     few 10^-2 where two top scores lie within a unit of each other, and the log-sum-exp by up to about 0.1. This pins
     that statement: outputs finite, within 0.06 of the oracle everywhere, within 1e-2 for all but a small share of the
     elements, lse within 2^-15 of sum_c |q_c||k_c| scale maximised over the scope, plus the 4e-3 of the probabilities'
-    rounding."""
+    rounding; and the lse does leave the 4e-3, so the case shows the effect. At head_dim 32 the scale is a binary32
+    multiply on the score: what is left is the binary32 accumulation of 32 products and that multiply, each rounding at
+    most 2^-24 of the norm, 33 * 2^-24 norm < 2^-18.9 norm in lse in the worst case, and outputs are as close as
+    everywhere (1e-2) up to a tenth for scores wrong by what such roundings add up to, about 2^-22 of the norm."""
     bk, ref, n = hand_layout([[64, 64, 64, 64, 64, 64, 64, 40]], 256, 4)
     rng = np.random.default_rng(45)
-    heads, d = 2, 32
+    heads = 2
     # common offsets make |q||k| large while the score differences stay moderate: q = 40 + N(0,1), k = 8 + N(0, 0.02)
     q = wl.f32_to_bf16_bits((40.0 + rng.standard_normal((n, heads * d))).astype(np.float32))
     k = wl.f32_to_bf16_bits((8.0 + 0.02 * rng.standard_normal((n, heads * d))).astype(np.float32))
@@ -593,10 +612,15 @@ def test_attention_two_term_query_at_very_large_norms():
     ref_b = oracle.attn_bwd(q, k, v, v, ref["perm"], ref["offsets"], ref["scan_bucket_start"], 4, "plain", heads, d, 2, 2, scale)
     err = np.abs(got - want)
     assert np.isfinite(got).all()
-    assert err.max() <= 0.06, f"max-abs {err.max():.4g}"
-    assert (err > 1e-2).mean() <= 0.02, f"share above 1e-2: {(err > 1e-2).mean():.4g}"
     lerr = np.abs(lse.cpu().numpy().astype(np.float64) - ref_b["lse"]).max()
-    assert lerr <= 4e-3 + 2.0 ** -15 * norm, f"lse error {lerr:.4g} at norm {norm:.4g}"
+    print(f"d {d} norm {norm:.5g}: max-abs {err.max():.4g}, lse error {lerr:.4g} = 2^{np.log2(lerr / norm):.1f} of the norm")
+    if d == 16:
+        assert err.max() <= 0.06, f"max-abs {err.max():.4g}"
+        assert (err > 1e-2).mean() <= 0.02, f"share above 1e-2: {(err > 1e-2).mean():.4g}"
+        assert 4e-3 < lerr <= 4e-3 + 2.0 ** -15 * norm, f"lse error {lerr:.4g} at norm {norm:.4g}"
+    else:
+        assert err.max() <= 1.1e-2, f"max-abs {err.max():.4g}"
+        assert lerr <= 4e-3 + 2.0 ** -18.9 * norm, f"lse error {lerr:.4g} at norm {norm:.4g}"
 
 
 @pytest.mark.parametrize("d", [16, 32])
@@ -1266,13 +1290,15 @@ def test_pool_after_attention_end_to_end():
 # ----------------------------------------------------------------------------- LayerNorm + linear (block glue)
 
 
-def check_ln_linear(n, c_in, c_out, n_outs, rng, ln=True, with_bias=True, with_res=False, gather=False, scatter=False):
+def check_ln_linear(n, c_in, c_out, n_outs, rng, ln=True, with_bias=True, with_res=False, gather=False, scatter=False,
+                    statistical=True):
     """GPU against the binary64 oracle, which is the plain definition with no intermediate rounding. Bound per element:
     2^-8 |y| for the final bf16 rounding, plus what the kernel's own arithmetic adds before it.
     With LayerNorm the kernel rounds the normalised row to bf16 (the matrix core's operand): c_in terms of size
     |ln_c w_c| with independent relative errors of up to 2^-9 give a standard deviation of about 2^-9 |ln| |w| / sqrt(3)
     ~ 1.4e-3 for rows of norm 1.2 sqrt(c_in) and weight rows of norm 1 as generated here; 0.012 allows eight of those
-    (a statistical allowance: the worst case, 2^-8 sum |ln_c w_c| ~ 0.04, is also asserted).
+    (a statistical allowance, left out with statistical=False where tens of millions of elements would hold rows of larger
+    norm; the worst case, 2^-8 sum |ln_c w_c| ~ 0.04, is always asserted).
     Without LayerNorm the operands are the stored bf16 values themselves, so only the binary32 accumulation is left:
     c_in 2^-24 sum |x_c w_c| in the worst case."""
     x = wl.f32_to_bf16_bits((rng.standard_normal((n, c_in)) * 2 + 0.5).astype(np.float32))
@@ -1299,7 +1325,7 @@ def check_ln_linear(n, c_in, c_out, n_outs, rng, ln=True, with_bias=True, with_r
         full = np.zeros_like(mag); full[row_out] = mag; mag = full
     err = np.abs(got - want)
     if ln:
-        assert (err <= 2.0 ** -8 * np.abs(want) + 0.012).all(), f"max excess {(err - 2.0 ** -8 * np.abs(want) - 0.012).max():.4g}"
+        assert not statistical or (err <= 2.0 ** -8 * np.abs(want) + 0.012).all(), f"max excess {(err - 2.0 ** -8 * np.abs(want) - 0.012).max():.4g}"
         worst = 2.0 ** -8 * np.abs(want) * 1.01 + (2.0 ** -8 + c_in * 2.0 ** -23) * mag + 1e-6
     else:
         worst = 2.0 ** -8 * np.abs(want) * 1.01 + c_in * 2.0 ** -23 * mag + 1e-6
@@ -1323,9 +1349,8 @@ def test_ln_linear_row_and_column_splits(c_in, c_out, n_outs):
     for n in (1, 24, 25, 33, 97, 121, 152, 2049):
         check_ln_linear(n, c_in, c_out, n_outs, rng, ln=True, gather=True)
         check_ln_linear(n, c_in, c_out, n_outs, rng, ln=False, with_res=True, scatter=True)
-    # without LayerNorm: its check allows eight standard deviations of the rounded operand's error for a row of average
-    # norm, which 12 million elements at 64 channels exceed by 4e-5 (the worst-case bound of the form below is exact)
     check_ln_linear(65536 + 25, c_in, c_out, n_outs, rng, ln=False, with_res=True, gather=True, scatter=True)
+    check_ln_linear(65536 + 25, c_in, c_out, n_outs, rng, ln=True, gather=True, statistical=False)
 
 
 @pytest.mark.parametrize("c_out,n_outs", [(3648, 3), (4096, 1), (4096, 4)])
