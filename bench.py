@@ -82,8 +82,8 @@ def measured_ceilings(head_dim: int) -> dict:
     """What this GPU sustains on the attention kernel's instruction mix with no memory traffic (register-only
     loops, random operand bits), best over 1..8 waves per SIMD, as score elements (1024 per 32x32 tile) per second
     and as nanoseconds per tile and SIMD: the matrix core alone, the softmax's vector work alone, the tile loops
-    written serially and software-pipelined as the kernel issues them, and the vector and matrix streams of a
-    head_dim-32 tile with no data dependence between them."""
+    written serially and software-pipelined as the kernel issues them, and a vector stream (16 exponentials, 8 packs,
+    8 dot2) and six MFMAs per tile alone and together with no data dependence between them."""
     import ctypes
 
     import torch  # noqa: F401  (the HIP runtime that is already loaded)

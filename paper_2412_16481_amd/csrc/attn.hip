@@ -254,8 +254,13 @@ __global__ __launch_bounds__(256, 3) void k_attn(AttnArgs a)
     //   multiplies (200000 points x 16 heads: 4.95 against 5.03 ms for three passes). binary16: the product is kept inside
     //   the finite range of the format.
     //   head_dim 32: the remainder takes two MFMAs, and their power and registers cost more than the 16 multiplies: with the
-    //   plain query and the scale multiplied onto the score (exactly, in binary32) the kernel needs 168 instead of 194
-    //   registers and runs three waves per SIMD (914601 points x 8 heads, a pass: 1.58 -> 1.38 ms). The power of two in a
+    //   plain query and the scale multiplied onto the score (exactly, in binary32) the kernel needs 178 instead of 194
+    //   registers and is held to 168 for three waves per SIMD (914601 points x 8 heads, a pass: 1.58 -> 1.38 ms). What that
+    //   spills, about 100 bytes a lane, lies in the general last stage and around the running-maximum sweep, which gain all
+    //   the same (401111 points, every workgroup sweeping twice: 1.44 -> 1.27 ms; 200 ragged scans 373 -> 348 us). Launches
+    //   of at most a workgroup or two per compute unit, where one wave's issue is what counts, are 3 to 5 % slower (3000
+    //   points, scope 1024, 8 heads: 16.4 -> 17.1 us); a choice by launch size would make a row's bits depend on how many
+    //   rows are in the call. The power of two in a
     //   factor below one goes into the query all the same, exactly: a product q k^T may be too large for binary32 where
     //   the scaled score is not. (binary16 products cannot be.)
     U4 qhi[QT][KS], qlo[QT][KS];

@@ -5,11 +5,12 @@
 //   kind 2: tile loop        the head_dim-16 tile of Bucket-Swin attention (Section 4.2) in registers: two MFMAs
 //                            for the scaled scores (bf16 head + remainder of q), 16 exponentials, 8 packs, two
 //                            MFMAs for P V
-//   kind 3: pipelined tile, head_dim 32   the tile loop as the attention kernel issues it: the four score MFMAs of
-//                            the NEXT tile between groups of four exponentials of the current one, then packs,
-//                            8 dot2 (softmax denominator) and the two P V MFMAs; order pinned by scheduling barriers
-//   kind 4: pipelined tile, head_dim 16   the same with two score MFMAs and no dot2
-//   kind 5: vector part only of kind 3 (16 exp, 8 packs, 8 dot2)
+//   kind 3: pipelined tile, head_dim 32   the tile loop as the attention kernel issues it: the two score MFMAs of
+//                            the NEXT tile between groups of four multiplies by the scale and exponentials of the current
+//                            one, then packs, 8 dot2 (softmax denominator) and the two P V MFMAs; order pinned by
+//                            scheduling barriers
+//   kind 4: pipelined tile, head_dim 16   the same with the two score MFMAs of a two-term query, no multiplies, no dot2
+//   kind 5: a vector stream of 16 exp, 8 packs, 8 dot2 per tile
 //   kind 6: six accumulating MFMAs per tile on three independent accumulators, nothing else
 //   kind 7: kinds 5 and 6 in one loop, with no data dependence between the vector and the matrix work: what the two
 //           units cost each other when nothing but issue and register ports couple them
@@ -93,28 +94,25 @@ __global__ __launch_bounds__(256) void k_ceiling(const uint32_t* __restrict__ se
         f32x16 sa = {0}, sb = {0};
         float l2 = 0.f;
         sa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(K.b, Q.b, sa, 0, 0, 0);
+        const auto prob = [&](float x) __attribute__((always_inline)) { return __builtin_amdgcn_exp2f(D32 ? x * mul : x); };
         auto unit = [&](f32x16& s, f32x16& sn, int it) __attribute__((always_inline)) {
             K.u[0] ^= (uint32_t)it & 0x00010001u;
             MB_SB();
 #pragma unroll
-            for (int r = 0; r < 4; ++r) s[r] = __builtin_amdgcn_exp2f(s[r]);
+            for (int r = 0; r < 4; ++r) s[r] = prob(s[r]);
             MB_SB();
             sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(K.b, Q.b, f32x16{0}, 0, 0, 0);
             MB_SB();
 #pragma unroll
-            for (int r = 4; r < 8; ++r) s[r] = __builtin_amdgcn_exp2f(s[r]);
+            for (int r = 4; r < 8; ++r) s[r] = prob(s[r]);
             MB_SB();
-            if (D32) sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(K.b, Q2.b, sn, 0, 0, 0);
-            MB_SB();
-#pragma unroll
-            for (int r = 8; r < 12; ++r) s[r] = __builtin_amdgcn_exp2f(s[r]);
-            MB_SB();
-            sn = D32 ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(V0.b, Q.b, sn, 0, 0, 0) : __builtin_amdgcn_mfma_f32_32x32x16_bf16(K.b, Q2.b, sn, 0, 0, 0);
+            sn = D32 ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(V0.b, Q2.b, sn, 0, 0, 0) : __builtin_amdgcn_mfma_f32_32x32x16_bf16(K.b, Q2.b, sn, 0, 0, 0);
             MB_SB();
 #pragma unroll
-            for (int r = 12; r < 16; ++r) s[r] = __builtin_amdgcn_exp2f(s[r]);
+            for (int r = 8; r < 12; ++r) s[r] = prob(s[r]);
             MB_SB();
-            if (D32) sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(V0.b, Q2.b, sn, 0, 0, 0);
+#pragma unroll
+            for (int r = 12; r < 16; ++r) s[r] = prob(s[r]);
             MB_SB();
             Frag p0, p1;
 #pragma unroll

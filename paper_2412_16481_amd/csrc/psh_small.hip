@@ -1,7 +1,7 @@
 // PSH bucketing, small scans: ONE workgroup per scan with every point of the scan in registers.
 //
 // Same schedule and same results as the other paths (lock step, contenders served by input index). A scan of at most
-// 16384 points fits a workgroup of 1024 threads with its points' packed voxels in registers for all steps, so a step is
+// 4096 points (four per thread) fits a workgroup of 1024 threads with its points' packed voxels in registers for all steps, so a step is
 // a hash, a rank and an accept without a read or write of global memory and without a launch boundary; the one
 // read of the coordinates also gives the bounding box, and with a single scan the tables and bucket offsets are written
 // here too, so that the whole bucketing is one launch.
@@ -16,8 +16,9 @@
 // (about 300 instructions per visit of 64 points), not memory. That is also where the line to the other paths
 // lies: at 4096 points a scan takes 33-43 us here (buckets of 256 and 32 rows) against 77-82 us with one launch per step
 // and 49-55 us in psh_scan.hip, 1500 points 26-29 against 70-75 and 40-42, 600 scans of 4096 points 106-136 against
-// 295-323 and 141-160; with 8192 points in registers and most of them left to the recycle step, where nothing is
-// closed up, it took 82-96 us against 80-84 with one launch per step.
+// 295-323 and 141-160. The crossing with one launch per step lies beyond: with eight points per thread and most of them left to
+// the recycle step, where nothing is closed up, 8192 points took 82-96 us against 80-84. The sizes between are not
+// served here.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
