@@ -18,8 +18,8 @@
 // Bound: HBM, mostly the writes. The workgroups of an XCD keep more output rows open (6 MB at 256 channels) than its L2
 // holds, so a line that is written in two halves a tile apart leaves L2 half full: pairs of 32-column blocks are stored
 // together, whole lines per instruction (914601 rows, 256 -> 3 x 256: WRITE_SIZE 1.60 -> 1.37 GB = what there is to write).
-// Measured at 900000 rows, LayerNorm + q, k, v map / output map with residual: 256 channels 649 -> 541 / 296 -> 250 us, 128
-// 261 -> 216 / 134 -> 116, 64 128 -> 91 / 46 -> 47. A third resident tile and 256 rows per workgroup were no faster.
+// Measured at 900000 rows, LayerNorm + q, k, v map / output map with residual: 256 channels 636 -> 530 / 292 -> 242 us, 128
+// 253 -> 213 / 133 -> 111, 64 128 -> 89 / 46 -> 43. A third resident tile and 256 rows per workgroup were no faster.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
