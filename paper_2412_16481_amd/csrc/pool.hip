@@ -116,7 +116,7 @@ __device__ __forceinline__ int block_rank_by_key(int key, bool active, int keybi
     for (int w = tid; w < PW * kp / 2; w += PT) reinterpret_cast<uint32_t*>(wcnt)[w] = 0u;
     __syncthreads();
     const unsigned long long m = match_key(key, active, keybits);
-    const int before = __popcll(m & ((1ull << lane) - 1ull));
+    const int before = bits_below(m);
     if (active && before == 0) wcnt[wave * kp + key] = (uint16_t)__popcll(m);
     __syncthreads();
     for (int k = tid; k < nkeys; k += PT) {   // exclusive prefix over the waves

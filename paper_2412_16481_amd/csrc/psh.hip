@@ -209,17 +209,11 @@ __global__ __launch_bounds__(PSH_THREADS) void k_psh_step(PshArgs a, int r)
             if (r > 0) probe_voxel(a, r, cfg, x, y, z);
             h = hash_bucket(a.hash, x, y, z, cfg);
         }
-        // lanes of this wave that contend for the same bucket, by ballots over the key bits
-        unsigned long long m = __ballot(active);
-        for (int bit = 0; bit < keybits; ++bit) {
-            const bool one = (h >> bit) & 1;
-            const unsigned long long bal = __ballot(active && one);
-            m &= one ? bal : ~bal;
-        }
+        const unsigned long long m = match_key(h, active, keybits);
         int old = 0;
         if (active) {
             const int leader = __ffsll((long long)m) - 1;
-            const int before = __popcll(m & ((1ull << lane) - 1ull));
+            const int before = bits_below(m);
             if (lane == leader) {
                 const int sh = (h & 1) * 16;
                 const uint32_t o = atomicAdd(&wh[wave * kwords + (h >> 1)], (uint32_t)__popcll(m) << sh);

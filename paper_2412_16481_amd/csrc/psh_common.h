@@ -327,20 +327,28 @@ __device__ inline int block_excl_scan(int v, int* total, int* lds /*[17]*/)
     return res;
 }
 
-// lanes of the wave whose key equals this lane's key (ballots over the key bits); 0 for inactive lanes
+// Lanes of the wave whose key equals this lane's key (ballots over the key bits); only active lanes are in it, and what an
+// inactive lane receives means nothing. Four vector instructions per key bit: the bit spread over a word, the compare that
+// writes the lane mask, and m & ~(mask ^ bit) as one three-input operation per half (with selects between the mask and its
+// complement it was eight). The bucketing of 128 scans of 131072 points took 1174 us with those and 1107 with these,
+// that of one scan of 4096 points 41 and 39.
 __device__ __forceinline__ unsigned long long match_key(int key, bool active, int keybits)
 {
-    // Inactive lanes take key 0 and are never in the starting mask, so a ballot needs no "and active": the compare
-    // writes the lane mask directly (the compiler builtin takes the predicate as it is; __ballot() goes through an
-    // integer and back).
-    unsigned long long m = __builtin_amdgcn_ballot_w64(active);
-    const int k = active ? key : 0;
+    const unsigned long long a = __builtin_amdgcn_ballot_w64(active);
+    uint32_t lo = (uint32_t)a, hi = (uint32_t)(a >> 32);
     for (int bit = 0; bit < keybits; ++bit) {
-        const bool one = (k >> bit) & 1;
-        const unsigned long long bal = __builtin_amdgcn_ballot_w64(one);
-        m &= one ? bal : ~bal;
+        const int t = __builtin_amdgcn_sbfe(key, bit, 1);
+        const unsigned long long bal = __builtin_amdgcn_ballot_w64(t != 0);
+        lo &= ~((uint32_t)bal ^ (uint32_t)t);
+        hi &= ~((uint32_t)(bal >> 32) ^ (uint32_t)t);
     }
-    return active ? m : 0ull;
+    return ((unsigned long long)hi << 32) | lo;
+}
+
+// set bits of m below this lane
+__device__ __forceinline__ int bits_below(unsigned long long m)
+{
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
 }  // namespace f3d

@@ -401,7 +401,7 @@ __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32
         int old = 0;
         if (active) {
             const int leader = __ffsll((long long)m) - 1;
-            const int before = __popcll(m & ((1ull << lane) - 1ull));
+            const int before = bits_below(m);
             if (lane == leader) {
                 const int sh = (h & 1) * 16;
                 const uint32_t o = atomicAdd(&wh[wave * kwp + (h >> 1)], (uint32_t)__popcll(m) << sh);

@@ -207,7 +207,7 @@ __global__ __launch_bounds__(STH, WPE) void k_pshs_scan(PshArgs a, int32_t* __re
                 int old = 0;
                 if (act[s]) {
                     const int leader = __ffsll((long long)m) - 1;
-                    const int before = __popcll(m & ((1ull << lane) - 1ull));
+                    const int before = bits_below(m);
                     if (lane == leader) {
                         const int sh = (h & 1) * 16;
                         const uint32_t o = atomicAdd(&wh[wave * kw + (h >> 1)], (uint32_t)__popcll(m) << sh);
@@ -277,13 +277,12 @@ __global__ __launch_bounds__(STH, WPE) void k_pshs_scan(PshArgs a, int32_t* __re
             }
             {
                 const unsigned long long b0 = __ballot(pass[0]), b1 = __ballot(pass[1]);
-                const unsigned long long lt = (1ull << lane) - 1ull;
                 const int c0 = __popcll(b0);
                 if (lane == 0) wcount[it & 1][wave] = c0 + __popcll(b1);
                 pend[0] = pass[0];
                 pend[1] = pass[1];
-                pend_pos[0] = __popcll(b0 & lt);
-                pend_pos[1] = c0 + __popcll(b1 & lt);
+                pend_pos[0] = bits_below(b0);
+                pend_pos[1] = c0 + bits_below(b1);
 #pragma unroll
                 for (int s = 0; s < SPPT; ++s) { pend_idx[s] = idx[s]; pend_vox[s] = vox[s]; }
             }

@@ -159,7 +159,7 @@ __global__ __launch_bounds__(MTH) void k_pshs_small(PshArgs a)
                     const int sh = (h & 1) * 16;
                     old = (int)((atomicAdd(&mine[h >> 1], (uint32_t)__popcll(m) << sh) >> sh) & 0xFFFFu);
                 }
-                old = __shfl(old, leader, 64) + __popcll(m & ((1ull << lane) - 1ull));
+                old = __shfl(old, leader, 64) + bits_below(m);
                 hk[s] = h | (old << 16);
             }
         }
@@ -228,7 +228,7 @@ __global__ __launch_bounds__(MTH) void k_pshs_small(PshArgs a)
                 const bool act = (left >> s) & 1u;
                 const unsigned long long m = __builtin_amdgcn_ballot_w64(act);
                 if (act) {
-                    const int e = before + __popcll(m & ((1ull << lane) - 1ull));
+                    const int e = before + bits_below(m);
                     list[e] = (uint32_t)idx[s];
                     list[MTH * PPT + e] = vlo[s];
                     list[2 * MTH * PPT + e] = vhi[s];
@@ -270,7 +270,7 @@ __global__ __launch_bounds__(MTH) void k_pshs_small(PshArgs a)
             const bool act = (left >> s) & 1u;
             const unsigned long long m = __builtin_amdgcn_ballot_w64(act);
             if (act) {
-                const int j = at + __popcll(m & ((1ull << lane) - 1ull));
+                const int j = at + bits_below(m);
                 int lo = 0, hi = K;                   // largest k with freepre[k] <= j
                 while (hi - lo > 1) {
                     const int mid = (lo + hi) >> 1;
