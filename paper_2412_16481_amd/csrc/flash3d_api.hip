@@ -93,10 +93,11 @@ int check_params(int64_t n, int32_t n_scans, const f3d_params* p)
     return F3D_OK;
 }
 
-// One workgroup per scan pays when the scans themselves fill the GPU. Measured on an MI355X: that path needs about
-// 10.4 ns per point of the LARGEST scan and per round of 256 scans (a workgroup walks its scan alone; with more scans
-// than compute units two workgroups share one and a round is about 15 % shorter than this), the paths that spread a
-// scan over the GPU about 0.13 ms plus 0.125 ns per point of the whole batch.
+// One workgroup per scan pays when the scans themselves fill the GPU. The line was drawn when that path needed 10.4 ns per
+// point of the LARGEST scan and per round of 256 scans (a workgroup walks its scan alone), and the paths that spread a
+// scan over the GPU about 0.13 ms plus 0.125 ns per point of the whole batch. It needs 3 to 9 ns now; the line stays all the
+// same, because the lists of that path are part of the workspace: moved, calls would need more of it than before, and
+// some that fit the static scratch would be refused.
 bool wants_scans(int64_t n, int32_t n_scans, const f3d_params* p, long long max_scan_points, int kcap)
 {
     if (!f3d::psh_scan_eligible(kcap)) return false;

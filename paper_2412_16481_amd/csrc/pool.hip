@@ -151,6 +151,7 @@ __device__ inline void tile_hash_cfg(int hash, int M, const int* vmax, ScanCfg& 
     c.D = D;
     c.invD = 1.0 / (double)D;
     c.invDf = (float)c.invD;
+    c.qeps = (float)(K + 2) * 2.4e-7f + 1e-6f;   // 2^-22 = 2.384e-7, and what the comparison itself rounds
     c.wide = vm >= 2048;
     c.m32 = umod52(4294967296ull, K, c.invK);
     c.step = 1;

@@ -57,8 +57,8 @@ struct PshArgs {
 
 hipError_t psh_launch(const PshArgs& args, hipStream_t stream);       // any size
 hipError_t psh_fast_launch(const PshArgs& args, hipStream_t stream);  // small count matrix
-hipError_t psh_scan_launch(const PshArgs& args, int32_t* lidx0, int32_t* lidx1, unsigned long long* lvox0,
-                           unsigned long long* lvox1, hipStream_t stream);    // one workgroup per scan: batches of many scans
+hipError_t psh_scan_launch(const PshArgs& args, int32_t* left_idx, int32_t* surv_pos, unsigned long long* voxels,
+                           unsigned long long* surv_hash, hipStream_t stream);    // one workgroup per scan: batches of many scans
 hipError_t psh_small_launch(const PshArgs& args, hipStream_t stream); // one workgroup per scan, points in registers
 bool psh_small_eligible(long long n, long long max_scan_points, int kcap);
 bool psh_scan_eligible(int kcap);

@@ -66,6 +66,7 @@ struct ScanCfg {
     int kb0;                // first bucket (global index)
     int lastcap;            // capacity of the scan's last bucket
     float invDf;            // 1/D in binary32: quotient estimate of the *_DIV hashes (the result is clamped below 2^13)
+    float qeps;             // no estimate below K + 1 is further than this from the quotient
     int wide;               // some voxel coordinate of the scan needs more than 11 bits
 };
 
@@ -123,19 +124,24 @@ __device__ __forceinline__ int hash_code(int hash, unsigned long long code, cons
         return (int)umod_q32(t, c.K, c.invK);
     }
     // code / D clamped to K-1, K < 2^13 + 1. A binary32 estimate (code, 1/D and their product each rounded once more
-    // than exactly: relative error below 2^-22) is within 0.002 of the true quotient wherever it is below K + 1, so its
-    // integer part is within one of the true one and one correction step with the exact remainder settles it; at K + 1
-    // and above the true quotient is certainly >= K. With K >= 2 the divisor is at most 2^62 + 1 and the product below
-    // stays inside 64 bits.
+    // than exactly: relative error below 2^-22) is within qeps = (K + 2) 2^-22 of the true quotient wherever it is below
+    // K + 1, so its integer part is the quotient's unless the estimate is that close to an integer. Only then the
+    // exact remainder decides (a wave in sixty at 512 buckets, so the 64-bit product is nearly always branched over); at
+    // K + 1 and above the true quotient is certainly >= K. With K >= 2 the divisor is at most 2^62 + 1 and the product
+    // below stays inside 64 bits.
     if (c.K < 2) return 0;
     const float cf = __fmaf_rn(__uint2float_rn((unsigned int)(code >> 32)), 4294967296.0f, __uint2float_rn((unsigned int)code));
     const float qf = cf * c.invDf;
-    if (qf >= (float)(c.K + 1)) return c.K - 1;
-    long long q = (long long)__float2uint_rz(qf);
-    const long long r = (long long)(code - (unsigned long long)(unsigned int)q * c.D);
-    if (r < 0) --q;
-    else if ((unsigned long long)r >= c.D) ++q;
-    return (int)(q < (long long)c.K ? q : (long long)(c.K - 1));
+    const float below = floorf(qf), frac = qf - below;
+    int q = qf >= (float)c.K ? c.K - 1 : (int)below;
+    if (fabsf(frac - 0.5f) > 0.5f - c.qeps && qf < (float)(c.K + 1)) {
+        q = (int)below;
+        const long long r = (long long)(code - (unsigned long long)(unsigned int)q * c.D);
+        if (r < 0) --q;
+        else if ((unsigned long long)r >= c.D) ++q;
+        q = min(q, c.K - 1);
+    }
+    return q;
 }
 
 __device__ __forceinline__ int hash_bucket(int hash, int x, int y, int z, const ScanCfg& c)
@@ -229,6 +235,31 @@ __device__ __forceinline__ unsigned long long zprobe(unsigned long long code, co
     return (code & ~z.mask) | to;
 }
 
+// The same two operations when no coordinate of the scan needs more than 10 bits: the code fits 30 bits, so the low words of
+// the probe's fields do. About 16 instructions for both, against 35.
+__device__ __forceinline__ uint32_t zprobe30(uint32_t code, uint32_t mask, uint32_t step, uint32_t lim, uint32_t vmax, bool minus)
+{
+    const uint32_t a = code & mask;
+    uint32_t to;
+    if (minus) to = a < step ? 0u : a - step;
+    else to = a > lim ? vmax : (code | ~mask) + step;
+    return (code & ~mask) | (to & mask);
+}
+
+__device__ __forceinline__ int zdiv30(uint32_t code, const ScanCfg& c)
+{
+    if (c.K < 2) return 0;
+    const float qf = __uint2float_rn(code) * c.invDf;     // see hash_code
+    const float below = floorf(qf), frac = qf - below;
+    uint32_t q = __float2uint_rz(below);
+    if (fabsf(frac - 0.5f) > 0.5f - c.qeps && qf < (float)(c.K + 1)) {
+        const int r = (int)(code - q * (uint32_t)c.D);    // an estimate is off by one at most: |r| < 2 D < 2^31
+        if (r < 0) --q;
+        else if ((uint32_t)r >= (uint32_t)c.D) ++q;
+    }
+    return (int)min(q, (uint32_t)(c.K - 1));
+}
+
 // largest b in [0, n_scans) with start[b] <= x, given start[0] <= x < start[n_scans]
 __device__ __forceinline__ int find_scan(const int* start, int n_scans, int x)
 {
@@ -281,6 +312,7 @@ __device__ inline void compute_cfg_of(const PshArgs& a, int p0, int nb, int kb0,
     c.D = D;
     c.invD = 1.0 / (double)D;
     c.invDf = (float)c.invD;
+    c.qeps = (float)(K + 2) * 2.4e-7f + 1e-6f;   // 2^-22 = 2.384e-7, and what the comparison itself rounds
     c.wide = vm >= 2048;
     c.m32 = umod52(4294967296ull, K, c.invK);
     long long step = 1;

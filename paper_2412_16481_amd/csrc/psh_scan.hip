@@ -2,17 +2,30 @@
 //
 // Same schedule and same results as psh.hip and psh_fast.hip (lock step, contenders served by input index). Those
 // two spread a scan over many workgroups and need a grid-wide boundary per step; with many scans in a batch the
-// scans themselves are the parallel work, and a workgroup that walks its scan in index order knows the rank of a
-// contender the moment it sees it (contenders so far + rank inside the 2048 points at hand), so a point is accepted
-// or passed on immediately: no count matrix, no launch boundary per step, and the points still unplaced are kept
-// as a compacted list (index, packed voxel) that shrinks from step to step, so later steps read only what is left.
+// scans themselves are the parallel work, and a step boundary is a workgroup barrier.
 //
-// Per iteration of 2048 list entries (two per thread): ranks inside a wave from ballots over the key bits, per-wave
-// counters packed two per LDS word, an exclusive prefix over the waves per bucket, then accept / pass on. Two
-// workgroup barriers per iteration; the list entries that are passed on are written one iteration late, after the
-// barrier that makes every wave's count visible.
+// A step is a count pass (the wave's contenders per bucket, one LDS add each), a prefix over the waves per bucket, and a
+// pass that ranks (ballots over the key bits for the 64 points at hand, the wave's running counter for those before) and
+// accepts; inside a pass the waves run freely. The direct step takes the scan in blocks of 8192 points, a run of 512 per
+// wave, with buckets and voxels in registers between the two passes. (The block is what keeps the writes to `perm` together:
+// its points fill about half a line of every bucket. With one run per wave over the whole scan, 16 lines of every bucket were
+// being filled at any time, sixteen scans to an XCD evicted them from its L2 half written, and the pass took 190 us
+// instead of 70 where the stores were left out.)
+//
+// Only a point whose probe hits a bucket that still has room can change anything, and room only shrinks. So after the
+// direct step all six probes of every point left are hashed at once and looked up in the room the buckets have THEN; a point
+// that finds none is done with (it waits for the recycle step), the others go on a list with their six buckets, ten bits each
+// (a full bucket standing in for the probes that found none). The probe steps walk that list, 0 to 30 % of the points on
+// most inputs and hashes, instead of all points left (45 % after the direct step on uniform cubes, 90 % on sensor sweeps).
+//
+// Bound: instruction issue on one compute unit per scan, then the waits for the survivors' list in the probe steps (it is read
+// twice per step). us per call before (every point left walked in every step) and now: 128 scans of 131 072 points in
+// buckets of 256, 1170 and 497; 300 of 40 000 in buckets of 128, 629 and 339; 64 sensor sweeps of 30 000 in buckets of 64,
+// 484 and 252; 100 of 60 000, Z-order-mod, 334 and 210; 200 of 20 000, XOR-div, 138 and 88.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "psh_common.h"
 
@@ -22,71 +35,130 @@ namespace {
 
 constexpr int STH = 1024;          // threads per workgroup
 constexpr int SNW = STH / 64;      // waves
-constexpr int SPPT = 2;            // list entries per thread and iteration
-constexpr int SIT = STH * SPPT;    // list entries per iteration
-constexpr int SKMAX = 1024;        // most buckets per scan on this path (LDS: 76 bytes per bucket)
+constexpr int SKMAX = 1024;        // most buckets per scan on this path (ten bits in a list entry; LDS: 76 bytes per bucket)
+constexpr int NPROBE = 6;          // most probe steps (six bucket numbers of ten bits fit a list entry)
 
 __device__ __forceinline__ unsigned long long pack_voxel(int x, int y, int z)
 {
     return (unsigned long long)(uint32_t)x | ((unsigned long long)(uint32_t)y << 21) | ((unsigned long long)(uint32_t)z << 42);
 }
 
-// dynamic LDS, in 32-bit words: fill[K] run[2][K] wh[SNW][kw] wbase[SNW][kw] with kw = (K + 1) / 2.
+struct Point3 {
+    float x, y, z;
+};
+
+// For U groups of 64, in order: the rank of every active lane among the wave's contenders of its bucket, counted on from
+// `mine` (the wave's own row of counters), which is advanced. The first lane of every bucket writes for all. Inactive lanes
+// hold a valid bucket too.
+template <int U>
+__device__ __forceinline__ void wave_ranks(const int (&h)[U], const bool (&act)[U], int keybits, uint32_t* mine, int (&rank)[U])
+{
+    uint32_t lo[U], hi[U];
+#pragma unroll
+    for (int s = 0; s < U; ++s) {
+        const unsigned long long m = __builtin_amdgcn_ballot_w64(act[s]);
+        lo[s] = (uint32_t)m;
+        hi[s] = (uint32_t)(m >> 32);
+    }
+    for (int bit = 0; bit < keybits; ++bit) {             // as match_key, the groups together
+#pragma unroll
+        for (int s = 0; s < U; ++s) {
+            const int t = __builtin_amdgcn_sbfe(h[s], bit, 1);
+            const unsigned long long bal = __builtin_amdgcn_ballot_w64(t != 0);
+            lo[s] &= ~((uint32_t)bal ^ (uint32_t)t);
+            hi[s] &= ~((uint32_t)(bal >> 32) ^ (uint32_t)t);
+        }
+    }
+#pragma unroll
+    for (int s = 0; s < U; ++s) {
+        const unsigned long long m = ((unsigned long long)hi[s] << 32) | lo[s];
+        const int below = bits_below(m);
+        rank[s] = (int)mine[h[s]] + below;
+        __builtin_amdgcn_wave_barrier();
+        if (act[s] && below == 0) mine[h[s]] = (uint32_t)(rank[s] + __popcll(m));
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+// The waves' counts become the rank of each wave's first contender. TO_ROOM: ranks count from 0, `from` is the room before the
+// step and `to` the room after it. Otherwise both are the contenders so far. By all threads, between two barriers.
+template <bool TO_ROOM>
+__device__ __forceinline__ void join_waves(int tid, int K, uint32_t* cnt, const int* from, int* to)
+{
+    for (int k = tid; k < K; k += STH) {
+        uint32_t run = TO_ROOM ? 0u : (uint32_t)from[k], t[SNW];
+#pragma unroll
+        for (int v = 0; v < SNW; ++v) t[v] = cnt[v * K + k];
+#pragma unroll
+        for (int v = 0; v < SNW; ++v) {
+            cnt[v * K + k] = run;
+            run += t[v];
+        }
+        to[k] = TO_ROOM ? max(from[k] - (int)run, 0) : (int)run;
+    }
+}
+
+// dynamic LDS, in 32-bit words: cnt[SNW][K] room[2][K] spare[K]
 // The hash function is a template parameter: the kernel holds many scan-wide values in scalar registers, and the
 // branches between four hash functions cost enough of them to spill.
 // WPE = waves per SIMD the kernel is compiled for: 4 (128 registers, one workgroup per compute unit) or 8 (64
-// registers at the price of a few spills, two workgroups per compute unit: taken when there are more scans than
-// compute units, where the second workgroup fills the issue slots the first leaves at its barriers).
+// registers, two workgroups per compute unit: taken when there are more scans than compute units, where the second
+// workgroup fills the issue slots the first leaves at its barriers).
 template <int HASH, int WPE>
-__global__ __launch_bounds__(STH, WPE) void k_pshs_scan(PshArgs a, int32_t* __restrict__ lidx0, int32_t* __restrict__ lidx1,
-                                                   unsigned long long* __restrict__ lvox0, unsigned long long* __restrict__ lvox1)
+__global__ __launch_bounds__(STH, WPE) void k_pshs_scan(PshArgs a, int32_t* left_idx, int32_t* surv_pos, unsigned long long* voxels,
+                                                   unsigned long long* surv_hash)
 {
+    // Groups of 64 a wave handles per iteration, all their loads in flight together: stores and loads are waited for in order,
+    // so a load an iteration ahead would wait for the stores of this one all the same; more work per wait hides it.
+    constexpr int SU = WPE == 4 ? 4 : 2;
+    constexpr int DG = WPE == 4 ? 8 : 4;   // groups of 64 in a wave's run of a block of the direct step (twice as many spill: 300 scans 339 -> 360 us)
     extern __shared__ int smem[];
     __shared__ ScanCfg cfg;
-    __shared__ ZProbe zps[6];
+    __shared__ ZProbe zps[NPROBE];
     __shared__ uint32_t red[8];
-    __shared__ int wcount[2][SNW];
-    __shared__ int s_placed;
+    __shared__ int wleft[SNW];   // points a block of the direct step leaves, by wave
+    __shared__ int s_round[8];
+    __shared__ int s_full, s_surv;
     __shared__ int lds17[17];
     if (a.status[0]) return;   // inconsistent batch offsets: flagged by the set-up kernel, nothing to do
     const int b = blockIdx.x;
     const int p0 = a.scan_p0[b], nb = a.scan_p0[b + 1] - p0;
     const int kb0 = a.sbs[b], K = a.sbs[b + 1] - kb0;
     if (nb <= 0 || K <= 0) return;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int kw = (K + 1) >> 1;
-    int* fill = smem;
-    int* runb[2] = {smem + K, smem + 2 * K};
-    uint32_t* wh = reinterpret_cast<uint32_t*>(smem + 3 * K);
-    uint32_t* wbase = wh + SNW * kw;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    uint32_t* cnt = reinterpret_cast<uint32_t*>(smem);
+    uint32_t* mine = cnt + wave * K;
+    int* roomb[2] = {smem + SNW * K, smem + (SNW + 1) * K};
+    int* spare = smem + (SNW + 2) * K;
+    // The lists: points left by the direct step (number in the scan, voxel), and of those the survivors (position in the first
+    // list, number, buckets). Every list of a scan lies in the scan's own stretch of its array.
+    int32_t* const surv_idx = reinterpret_cast<int32_t*>(a.key) + p0;
+    left_idx += p0;
+    surv_pos += p0;
+    voxels += p0;
+    surv_hash += p0;
 
     // ---- first row of every bucket of the scan (buckets are full except the last), bounding box
     for (int j = tid; j < K; j += STH) a.offsets[kb0 + j] = p0 + min(j * a.S, nb);
+    const Point3* pts = reinterpret_cast<const Point3*>(a.coords) + p0;
     {
         uint32_t mn[3] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu}, mx[3] = {0u, 0u, 0u};
-        const float* src = a.coords + (size_t)p0 * 3;
-        const long long nf = (long long)nb * 3;
-        constexpr int UB = 6;   // loads in flight per thread; 6 * 1024 is a multiple of 3, so a slot keeps its axis
-        for (long long f0 = tid; f0 < nf; f0 += (long long)UB * STH) {
-            float v[UB];
+        constexpr int UB = 4;   // points in flight per thread
+        for (long long f0 = tid; f0 < nb; f0 += (long long)UB * STH) {
+            Point3 v[UB];
+#pragma unroll
+            for (int j = 0; j < UB; ++j) v[j] = pts[min(f0 + (long long)j * STH, (long long)nb - 1)];   // past the end: the last point again
 #pragma unroll
             for (int j = 0; j < UB; ++j) {
-                const long long f = f0 + (long long)j * STH;
-                v[j] = f < nf ? src[f] : 0.f;
-            }
+                const uint32_t o[3] = {f2ord(v[j].x), f2ord(v[j].y), f2ord(v[j].z)};
 #pragma unroll
-            for (int j = 0; j < UB; ++j) {
-                const long long f = f0 + (long long)j * STH;
-                if (f < nf) {
-                    const uint32_t o = f2ord(v[j]);
-                    const int ax = (tid + j) % 3;   // f mod 3: 1024 = 1 (mod 3), and f0 advances by a multiple of 3
-#pragma unroll
-                    for (int t = 0; t < 3; ++t)
-                        if (ax == t) { mn[t] = min(mn[t], o); mx[t] = max(mx[t], o); }
-                }
+                for (int t = 0; t < 3; ++t) { mn[t] = min(mn[t], o[t]); mx[t] = max(mx[t], o[t]); }
             }
         }
         if (tid < 3) { red[tid] = 0xFFFFFFFFu; red[4 + tid] = 0u; }
+        if (tid < 8) s_round[tid] = 0;
+        if (tid == 0) s_surv = 0;
         __syncthreads();
 #pragma unroll
         for (int t = 0; t < 3; ++t) {
@@ -100,289 +172,325 @@ __global__ __launch_bounds__(STH, WPE) void k_pshs_scan(PshArgs a, int32_t* __re
         __syncthreads();
         if (tid == 0) compute_cfg(a, b, red, cfg);
     }
-    for (int k = tid; k < K; k += STH) { fill[k] = 0; runb[0][k] = 0; }
-    for (int w = tid; w < SNW * kw; w += STH) wh[w] = 0u;
+    for (int w = tid; w < SNW * K; w += STH) cnt[w] = 0u;
     __syncthreads();
+    for (int k = tid; k < K; k += STH) roomb[0][k] = 0;      // the contenders so far, in the direct step
 
     const int keybits = max(1, 32 - __clz(max(K - 1, 1)));
-    int n_in = nb;          // entries of the list this step reads (step 0: the scan itself)
-    // The lists hold the voxel as its Z-order code where the hash and the probes work on that, else packed. Only in the form
-    // with registers to spare (128 scans of 131072 points 1257 -> 1157 us, 64 of 5000 55.7 -> 53.8; in the 64-register form
-    // 300 scans took 2.62 ms instead of 2.20), and not for the modulus, which gained nothing.
-    constexpr bool ZC = HASH == 3 && WPE == 4;
-    const bool zc = ZC && a.probe_mode == 0;
-    if (ZC && tid < 6) zps[tid] = zprobe_of(cfg, tid + 1);   // read from step 1 on, behind step 0's barriers
-    int cur = 0;            // which run buffer holds the contenders seen so far in this step
-    for (int r = 0; r <= a.n_probes; ++r) {
-        const int32_t* in_idx = (r & 1) ? lidx0 : lidx1;     // step 0 reads the coordinates instead
-        const unsigned long long* in_vox = (r & 1) ? lvox0 : lvox1;
-        int32_t* out_idx = (r & 1) ? lidx1 : lidx0;
-        unsigned long long* out_vox = (r & 1) ? lvox1 : lvox0;
-        if (tid == 0) s_placed = 0;
-        const ZProbe zp = zps[r > 0 ? r - 1 : 0];     // not used in step 0
-        int out_base = 0, nplaced = 0;
-        // entries passed on by the previous iteration, written after the next barrier
-        int pend_idx[SPPT], pend_pos[SPPT];
-        unsigned long long pend_vox[SPPT];
-        bool pend[SPPT] = {false, false};
-        const int n_it = (n_in + SIT - 1) / SIT;
-        // The entries of an iteration are requested one iteration ahead (three words each: the coordinates in step 0,
-        // index and packed voxel afterwards), so that an iteration does not start by waiting for memory.
-        uint32_t nw0[SPPT], nw1[SPPT], nw2[SPPT];
+    // A point's voxel is kept as its Z-order code where the hash and the probes work on that, else packed.
+    const bool zc = HASH == 3 && a.probe_mode == 0;
+    if (HASH == 3 && tid < NPROBE) zps[tid] = zprobe_of(cfg, tid + 1);
+    const bool narrow = zc && max(max(cfg.vmax[0], cfg.vmax[1]), cfg.vmax[2]) < 1024;   // the code fits 30 bits
+
+    // ---- direct step, block by block
+    int total = 0;                          // points left so far
+    auto direct_step = [&](auto narrow_tag) __attribute__((always_inline)) {
+        constexpr bool NARROW = decltype(narrow_tag)::value;
+        for (int b0 = 0; b0 < nb; b0 += 64 * DG * SNW) {
+            const int i0 = b0 + wave * (64 * DG) + lane;      // at most 8192 beyond nb, which is 2^20 short of 2^31
+            int hh[DG];
+            unsigned long long vox[DG];
+            uint32_t pass = 0;                                // bit s: the point of group s is passed on
 #pragma unroll
-        for (int s = 0; s < SPPT; ++s) {
-            const int j = wave * (SIT / SNW) + s * 64 + lane;
-            nw0[s] = nw1[s] = nw2[s] = 0u;
-            if (j < n_in) {
-                if (r == 0) {
-                    const uint32_t* c = reinterpret_cast<const uint32_t*>(a.coords + (size_t)(p0 + j) * 3);
-                    nw0[s] = c[0]; nw1[s] = c[1]; nw2[s] = c[2];
-                } else {
-                    const unsigned long long v = in_vox[p0 + j];
-                    nw0[s] = (uint32_t)in_idx[p0 + j]; nw1[s] = (uint32_t)v; nw2[s] = (uint32_t)(v >> 32);
-                }
-            }
-        }
-        for (int it = 0; it < n_it; ++it) {
-            int idx[SPPT], hh[SPPT], wl[SPPT];
-            unsigned long long vox[SPPT];
-            bool act[SPPT];
-            uint32_t w0[SPPT], w1[SPPT], w2[SPPT];
+            for (int s0 = 0; s0 < DG; s0 += SU) {
+                Point3 c[SU];
 #pragma unroll
-            for (int s = 0; s < SPPT; ++s) { w0[s] = nw0[s]; w1[s] = nw1[s]; w2[s] = nw2[s]; }
-            if (it + 1 < n_it) {
+                for (int s = 0; s < SU; ++s) c[s] = pts[(uint32_t)min(i0 + (s0 + s) * 64, nb - 1)];
 #pragma unroll
-                for (int s = 0; s < SPPT; ++s) {
-                    const int j = (it + 1) * SIT + wave * (SIT / SNW) + s * 64 + lane;
-                    if (j < n_in) {
-                        if (r == 0) {
-                            const uint32_t* c = reinterpret_cast<const uint32_t*>(a.coords + (size_t)(p0 + j) * 3);
-                            nw0[s] = c[0]; nw1[s] = c[1]; nw2[s] = c[2];
-                        } else {
-                            const unsigned long long v = in_vox[p0 + j];
-                            nw0[s] = (uint32_t)in_idx[p0 + j]; nw1[s] = (uint32_t)v; nw2[s] = (uint32_t)(v >> 32);
-                        }
-                    }
-                }
-            }
-#pragma unroll
-            for (int s = 0; s < SPPT; ++s) {
-                const int j = it * SIT + wave * (SIT / SNW) + s * 64 + lane;
-                act[s] = j < n_in;
-                idx[s] = 0;
-                vox[s] = 0ull;
-                if (act[s]) {
-                    if (r == 0) {
-                        idx[s] = j;
-                        const int x = voxel_of(__uint_as_float(w0[s]), cfg.mn[0], a.inv_voxel),
-                                  y = voxel_of(__uint_as_float(w1[s]), cfg.mn[1], a.inv_voxel),
-                                  z = voxel_of(__uint_as_float(w2[s]), cfg.mn[2], a.inv_voxel);
-                        if (ZC && zc) vox[s] = cfg.wide ? morton3(x, y, z) : morton3_low(x, y, z);
-                        else vox[s] = pack_voxel(x, y, z);
+                for (int s = 0; s < SU; ++s) {
+                    const int x = voxel_of(c[s].x, cfg.mn[0], a.inv_voxel), y = voxel_of(c[s].y, cfg.mn[1], a.inv_voxel),
+                              z = voxel_of(c[s].z, cfg.mn[2], a.inv_voxel);
+                    int h;
+                    if (NARROW) {
+                        const uint32_t code = (uint32_t)morton3_low(x, y, z);
+                        vox[s0 + s] = code;
+                        h = zdiv30(code, cfg);
+                    } else if (zc) {
+                        vox[s0 + s] = cfg.wide ? morton3(x, y, z) : morton3_low(x, y, z);
+                        h = hash_code(HASH, vox[s0 + s], cfg);
                     } else {
-                        idx[s] = (int)w0[s];
-                        vox[s] = (unsigned long long)w1[s] | ((unsigned long long)w2[s] << 32);
-                    }
-                }
-            }
-#pragma unroll
-            for (int s = 0; s < SPPT; ++s) {
-                int h = 0;
-                if (act[s]) {
-                    if (ZC && zc) {
-                        h = hash_code(HASH, r > 0 ? zprobe(vox[s], zp) : vox[s], cfg);
-                    } else {
-                        int x = (int)(vox[s] & 0x1FFFFFull), y = (int)((vox[s] >> 21) & 0x1FFFFFull), z = (int)(vox[s] >> 42);
-                        if (r > 0) probe_voxel(a, r, cfg, x, y, z);
+                        vox[s0 + s] = pack_voxel(x, y, z);
                         h = hash_bucket(HASH, x, y, z, cfg);
                     }
+                    hh[s0 + s] = h;
+                    if (i0 + (s0 + s) * 64 < nb) atomicAdd(&mine[h], 1u);
                 }
-                hh[s] = h;
-            }
-            // ---- rank inside the wave, per-wave counters
-#pragma unroll
-            for (int s = 0; s < SPPT; ++s) {
-                const int h = hh[s];
-                const unsigned long long m = match_key(h, act[s], keybits);
-                int old = 0;
-                if (act[s]) {
-                    const int leader = __ffsll((long long)m) - 1;
-                    const int before = bits_below(m);
-                    if (lane == leader) {
-                        const int sh = (h & 1) * 16;
-                        const uint32_t o = atomicAdd(&wh[wave * kw + (h >> 1)], (uint32_t)__popcll(m) << sh);
-                        old = (int)((o >> sh) & 0xFFFFu);
-                    }
-                    old = __shfl(old, leader, 64) + before;
-                }
-                wl[s] = old;
             }
             __syncthreads();
-            // ---- entries the previous iteration passed on: every wave's count is visible now
-            {
-                const int pb = (it + 1) & 1;
-                int before = 0, total = 0;
-                if (it > 0) {
-#pragma unroll
-                    for (int v = 0; v < SNW; ++v) {
-                        const int c = wcount[pb][v];
-                        before += v < wave ? c : 0;
-                        total += c;
-                    }
-                }
-#pragma unroll
-                for (int s = 0; s < SPPT; ++s) {
-                    if (pend[s]) {
-                        out_idx[p0 + out_base + before + pend_pos[s]] = pend_idx[s];
-                        out_vox[p0 + out_base + before + pend_pos[s]] = pend_vox[s];
-                    }
-                }
-                out_base += total;
-            }
-            // ---- exclusive prefix over the waves per bucket; the counters are cleared for the next iteration
-            int* run_cur = runb[cur];
-            int* run_next = runb[cur ^ 1];
-            for (int w = tid; w < kw; w += STH) {
-                uint32_t run = 0;
-#pragma unroll
-                for (int v = 0; v < SNW; ++v) {
-                    const uint32_t t = wh[v * kw + w];
-                    wbase[v * kw + w] = run;
-                    wh[v * kw + w] = 0u;
-                    run += t;   // halves cannot carry into each other: an iteration has 2048 entries
-                }
-                run_next[2 * w] = run_cur[2 * w] + (int)(run & 0xFFFFu);
-                if (2 * w + 1 < K) run_next[2 * w + 1] = run_cur[2 * w + 1] + (int)(run >> 16);
-            }
+            join_waves<false>(tid, K, cnt, roomb[0], roomb[0]);
             __syncthreads();
-            // ---- accept while the bucket has room, pass on otherwise
-            bool pass[SPPT];
+            int nleft = 0;
 #pragma unroll
-            for (int s = 0; s < SPPT; ++s) {
-                pass[s] = false;
-                if (act[s]) {
-                    const int h = hh[s];
-                    const int rank = run_cur[h] + (int)((wbase[wave * kw + (h >> 1)] >> ((h & 1) * 16)) & 0xFFFFu) + wl[s];
-                    const int cap = (h == K - 1) ? cfg.lastcap : a.S;
-                    const int f = fill[h];
-                    if (rank < cap - f) {
-                        const int dst = p0 + h * a.S + f + rank;
-                        a.inv_perm[p0 + idx[s]] = dst;
-                        a.perm[dst] = p0 + idx[s];
-                        ++nplaced;
-                    } else {
-                        pass[s] = true;
+            for (int s0 = 0; s0 < DG; s0 += SU) {
+                int h[SU], rank[SU];
+                bool act[SU];
+#pragma unroll
+                for (int s = 0; s < SU; ++s) {
+                    h[s] = hh[s0 + s];
+                    act[s] = i0 + (s0 + s) * 64 < nb;
+                }
+                wave_ranks<SU>(h, act, keybits, mine, rank);
+#pragma unroll
+                for (int s = 0; s < SU; ++s) {
+                    const int i = i0 + (s0 + s) * 64;
+                    const bool fits = rank[s] < (h[s] == K - 1 ? cfg.lastcap : a.S);
+                    if (act[s] && fits) {
+                        const uint32_t dst = (uint32_t)(p0 + h[s] * a.S + rank[s]);
+                        a.inv_perm[(uint32_t)(p0 + i)] = (int)dst;
+                        a.perm[dst] = p0 + i;
+                    }
+                    const bool on = act[s] && !fits;
+                    pass |= on ? 1u << (s0 + s) : 0u;
+                    nleft += __popcll(__builtin_amdgcn_ballot_w64(on));
+                }
+            }
+            for (int k = lane; k < K; k += 64) mine[k] = 0u;
+            if (lane == 0) wleft[wave] = nleft;
+            __syncthreads();
+            int at = total;
+#pragma unroll
+            for (int v = 0; v < SNW; ++v) {
+                const int c = wleft[v];
+                at += v < wave ? c : 0;
+                total += c;
+            }
+            at = __builtin_amdgcn_readfirstlane(at);
+            total = __builtin_amdgcn_readfirstlane(total);
+#pragma unroll
+            for (int s = 0; s < DG; ++s) {
+                const bool on = (pass >> s) & 1u;
+                const unsigned long long m = __builtin_amdgcn_ballot_w64(on);
+                if (on) {
+                    const uint32_t e = (uint32_t)(at + bits_below(m));
+                    left_idx[e] = i0 + s * 64;
+                    if (NARROW) reinterpret_cast<uint32_t*>(voxels)[e] = (uint32_t)vox[s];   // four of the eight bytes an entry has
+                    else voxels[e] = vox[s];
+                }
+                at += __popcll(m);
+            }
+        }
+    };
+    if (HASH == 3 && narrow) direct_step(std::true_type{});
+    else direct_step(std::false_type{});
+    if (tid == 0) s_round[0] = nb - total;
+    for (int k = tid; k < K; k += STH) {    // a thread's own k, as in join_waves
+        const int room = max((k == K - 1 ? cfg.lastcap : a.S) - roomb[0][k], 0);
+        roomb[1][k] = room;
+        if (room == 0) s_full = k;          // some full bucket (there is one if a point was passed on); any will do
+    }
+    __threadfence_block();                  // the list is read by other threads of the workgroup from here on
+    __syncthreads();
+    int cur = 1;                            // roomb[cur]: the room the buckets have now
+    // wave w takes entries [l0, l1) of the points left, up to SU groups of 64 at a time
+    const int per = (total + SNW - 1) / SNW;
+    const int l0 = min(wave * per, total), l1 = min(l0 + per, total);
+
+    int nplaced = 0;
+    if (total > 0 && a.n_probes > 0) {
+        // ---- all probes of the points left, against the room after the direct step
+        int nsurv = 0;
+        const int full = s_full;
+        auto probe_all = [&](auto narrow_tag) __attribute__((always_inline)) {
+            constexpr bool NARROW = decltype(narrow_tag)::value;
+            const int* room = roomb[cur];
+            for (int pos0 = l0; pos0 < l1; pos0 += 64 * SU) {
+                const int entries = min(l1 - pos0, 64 * SU);
+                unsigned long long v[SU], hs[SU];
+                int i[SU];
+                bool any[SU];
+#pragma unroll
+                for (int s = 0; s < SU; ++s) {
+                    const uint32_t e = (uint32_t)(pos0 + min(s * 64 + lane, entries - 1));
+                    i[s] = left_idx[e];
+                    v[s] = NARROW ? reinterpret_cast<const uint32_t*>(voxels)[e] : voxels[e];
+                    hs[s] = 0ull;
+                    any[s] = false;
+                }
+#pragma unroll
+                for (int r = 1; r <= NPROBE; ++r) {
+                    if (r > a.n_probes) break;
+                    const ZProbe zp = zps[HASH == 3 ? r - 1 : 0];
+#pragma unroll
+                    for (int s = 0; s < SU; ++s) {
+                        int h;
+                        if (NARROW) {
+                            h = zdiv30(zprobe30((uint32_t)v[s], (uint32_t)zp.mask, (uint32_t)zp.step, (uint32_t)zp.lim, (uint32_t)zp.vmax, (r - 1) & 1), cfg);
+                        } else if (zc) {
+                            h = hash_code(HASH, zprobe(v[s], zp), cfg);
+                        } else {
+                            int x = (int)(v[s] & 0x1FFFFFull), y = (int)((v[s] >> 21) & 0x1FFFFFull), z = (int)(v[s] >> 42);
+                            probe_voxel(a, r, cfg, x, y, z);
+                            h = hash_bucket(HASH, x, y, z, cfg);
+                        }
+                        const bool open = room[h] > 0;
+                        any[s] |= open;
+                        hs[s] |= (unsigned long long)(unsigned int)(open ? h : full) << (10 * (r - 1));
                     }
                 }
-            }
-            {
-                const unsigned long long b0 = __ballot(pass[0]), b1 = __ballot(pass[1]);
-                const int c0 = __popcll(b0);
-                if (lane == 0) wcount[it & 1][wave] = c0 + __popcll(b1);
-                pend[0] = pass[0];
-                pend[1] = pass[1];
-                pend_pos[0] = bits_below(b0);
-                pend_pos[1] = c0 + bits_below(b1);
 #pragma unroll
-                for (int s = 0; s < SPPT; ++s) { pend_idx[s] = idx[s]; pend_vox[s] = vox[s]; }
-            }
-            cur ^= 1;
-        }
-        __syncthreads();
-        // ---- what the last iteration passed on; the list of the next step is complete after this
-        {
-            int before = 0, total = 0;
-            if (n_it > 0) {
-                const int pb = (n_it + 1) & 1;
-#pragma unroll
-                for (int v = 0; v < SNW; ++v) {
-                    const int c = wcount[pb][v];
-                    before += v < wave ? c : 0;
-                    total += c;
+                for (int s = 0; s < SU; ++s) {
+                    const bool go = any[s] && s * 64 + lane < entries;
+                    const unsigned long long m = __builtin_amdgcn_ballot_w64(go);
+                    if (go) {
+                        const uint32_t e = (uint32_t)(l0 + nsurv + bits_below(m));
+                        surv_pos[e] = pos0 + s * 64 + lane;
+                        surv_idx[e] = i[s];
+                        surv_hash[e] = hs[s];
+                    }
+                    nsurv += __popcll(m);
                 }
             }
+        };
+        if (HASH == 3 && narrow) probe_all(std::true_type{});
+        else probe_all(std::false_type{});
+        if (lane == 0 && nsurv) atomicAdd(&s_surv, nsurv);
+        __threadfence_block();   // a list entry is read by another lane of the wave that wrote it
+        __syncthreads();
+        // ---- the probe steps, on the survivors
+        if (s_surv > 0) {
+            const unsigned long long all_full = (unsigned long long)(unsigned int)full;
+            for (int r = 1; r <= a.n_probes; ++r) {
+                const int sh = 10 * (r - 1);
+                const int* room = roomb[cur];
+                for (int j0 = 0; j0 < nsurv; j0 += 64 * 2 * SU) {
+                    unsigned long long e[2 * SU];
 #pragma unroll
-            for (int s = 0; s < SPPT; ++s) {
-                if (pend[s]) {
-                    out_idx[p0 + out_base + before + pend_pos[s]] = pend_idx[s];
-                    out_vox[p0 + out_base + before + pend_pos[s]] = pend_vox[s];
+                    for (int s = 0; s < 2 * SU; ++s) e[s] = surv_hash[(uint32_t)(l0 + min(j0 + s * 64 + lane, nsurv - 1))];
+#pragma unroll
+                    for (int s = 0; s < 2 * SU; ++s) {
+                        const int h = (int)(e[s] >> sh) & 1023;
+                        if (j0 + s * 64 + lane < nsurv && room[h] > 0) atomicAdd(&mine[h], 1u);
+                    }
                 }
+                __syncthreads();
+                join_waves<true>(tid, K, cnt, room, roomb[cur ^ 1]);
+                __syncthreads();
+                int got = 0;
+                for (int j0 = 0; j0 < nsurv; j0 += 64 * SU) {
+                    unsigned long long e[SU];
+                    int pos[SU], idx[SU];
+#pragma unroll
+                    for (int s = 0; s < SU; ++s) {
+                        const uint32_t j = (uint32_t)(l0 + min(j0 + s * 64 + lane, nsurv - 1));
+                        e[s] = surv_hash[j];
+                        pos[s] = surv_pos[j];
+                        idx[s] = surv_idx[j];
+                    }
+#pragma unroll
+                    for (int s = 0; s < SU; ++s) {
+                        const int j = j0 + s * 64 + lane;
+                        const int h[1] = {(int)(e[s] >> sh) & 1023};
+                        const int f = room[h[0]];
+                        const bool act[1] = {j < nsurv && f > 0};
+                        if (__builtin_amdgcn_ballot_w64(act[0]) == 0ull) continue;
+                        int rank[1];
+                        wave_ranks<1>(h, act, keybits, mine, rank);
+                        const bool ok = act[0] && rank[0] < f;
+                        if (ok) {
+                            const int dst = p0 + h[0] * a.S + (h[0] == K - 1 ? cfg.lastcap : a.S) - f + rank[0];
+                            a.inv_perm[(uint32_t)(p0 + idx[s])] = dst;
+                            a.perm[(uint32_t)dst] = p0 + idx[s];
+                            left_idx[(uint32_t)pos[s]] = -1;
+                            // from now on it contends for a bucket without room
+                            unsigned long long gone = 0ull;
+                            for (int t = 0; t < NPROBE; ++t) gone |= all_full << (10 * t);
+                            surv_hash[(uint32_t)(l0 + j)] = gone;
+                        }
+                        got += __popcll(__builtin_amdgcn_ballot_w64(ok));
+                    }
+                }
+                for (int k = lane; k < K; k += 64) mine[k] = 0u;
+                if (lane == 0 && got) atomicAdd(&s_round[r], got);
+                nplaced += got;
+                cur ^= 1;
             }
-            n_in = out_base + total;
         }
-        for (int d = 32; d >= 1; d >>= 1) nplaced += __shfl_xor(nplaced, d, 64);
-        if (lane == 0 && nplaced) atomicAdd(&s_placed, nplaced);
-        // fill levels after this step; contenders are counted afresh in the next one
-        {
-            int* run_cur = runb[cur];
-            for (int k = tid; k < K; k += STH) {
-                const int cap = (k == K - 1) ? cfg.lastcap : a.S;
-                fill[k] = min(fill[k] + run_cur[k], cap);
-                run_cur[k] = 0;
-            }
-        }
-        // the list written in this step is read by other threads of the workgroup in the next one
-        __threadfence_block();
-        __syncthreads();
-        if (tid == 0 && s_placed) atomicAdd(&a.round_count[r], s_placed);
-        __syncthreads();
     }
 
     // ---- recycle: the j-th entry left takes the j-th free slot (buckets ascending, slots ascending)
-    if (n_in == 0) return;   // uniform
-    const int last = a.n_probes + 1;
-    const int32_t* in_idx = (last & 1) ? lidx0 : lidx1;
-    int* freepre = runb[0];   // both run buffers are free now
-    {
-        int carry = 0;
+    if (total > 0) {   // uniform
+        const int rest = l1 - l0 - nplaced;             // of this wave's entries
+        __threadfence_block();                          // entries marked as placed are read by other lanes below
+        __syncthreads();                                // everybody is done with the counters
+        // buckets with room, in order: slots before, bucket, first free row
+        int* slots_before = smem;                       // [K + 1] (the counters' place)
+        int* bucket_of = smem + (K + 1);                // [K]
+        const int* room = roomb[cur];
+        int carry = 0, ocarry = 0;
         for (int k0 = 0; k0 < K; k0 += STH) {
             const int k = k0 + tid;
-            int v = 0;
-            if (k < K) v = ((k == K - 1) ? cfg.lastcap : a.S) - fill[k];
-            int tot;
+            const int v = k < K ? room[k] : 0;
+            int tot, otot;
             const int pre = block_excl_scan(v, &tot, lds17);
-            if (k < K) freepre[k] = carry + pre;
+            const int opre = block_excl_scan(v > 0 ? 1 : 0, &otot, lds17);
+            if (v > 0) {
+                slots_before[ocarry + opre] = carry + pre;
+                bucket_of[ocarry + opre] = k;
+            }
             carry += tot;
+            ocarry += otot;
         }
+        if (tid == 0) slots_before[ocarry] = carry;
+        if (lane == 0) spare[wave] = rest;
+        __syncthreads();
+        int j0 = 0, left_total = 0;                     // entries left in earlier waves, in all
+        for (int v = 0; v < SNW; ++v) {
+            const int c = spare[v];
+            j0 += v < wave ? c : 0;
+            left_total += c;
+        }
+        int o = 0;                                      // last bucket whose slots begin at or before j0
+        {
+            int hi = ocarry;
+            while (hi - o > 1) {
+                const int mid = (o + hi) >> 1;
+                if (slots_before[mid] <= j0) o = mid; else hi = mid;
+            }
+        }
+        for (int pos0 = l0; pos0 < l1; pos0 += 64 * SU) {
+            const int entries = min(l1 - pos0, 64 * SU);
+            int i[SU];
+#pragma unroll
+            for (int s = 0; s < SU; ++s) i[s] = left_idx[(uint32_t)(pos0 + min(s * 64 + lane, entries - 1))];
+#pragma unroll
+            for (int s = 0; s < SU; ++s) {
+                const bool act = s * 64 + lane < entries && i[s] >= 0;
+                const unsigned long long m = __builtin_amdgcn_ballot_w64(act);
+                if (act) {
+                    const int j = j0 + bits_below(m);
+                    int q = o;
+                    while (q + 1 < ocarry && slots_before[q + 1] <= j) ++q;
+                    const int k = bucket_of[q];
+                    const int dst = p0 + k * a.S + (k == K - 1 ? cfg.lastcap : a.S) - room[k] + (j - slots_before[q]);
+                    if ((uint32_t)(dst - p0) < (uint32_t)nb) {   // always, while capacities add up to the scan size
+                        a.inv_perm[(uint32_t)(p0 + i[s])] = dst;
+                        a.perm[(uint32_t)dst] = p0 + i[s];
+                    }
+                }
+                j0 += __popcll(m);
+                while (o + 1 < ocarry && slots_before[o + 1] <= j0) ++o;
+            }
+        }
+        if (tid == 0) s_round[a.n_probes + 1] = left_total;
     }
     __syncthreads();
-    int placed = 0;
-    for (int j = tid; j < n_in; j += STH) {
-        const int i = in_idx[p0 + j];
-        int lo = 0, hi = K;   // largest k with freepre[k] <= j
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (freepre[mid] <= j) lo = mid; else hi = mid;
-        }
-        const int dst = p0 + lo * a.S + fill[lo] + (j - freepre[lo]);
-        if (dst < p0 || dst >= p0 + nb) continue;   // cannot happen while capacities add up to the scan size
-        a.inv_perm[p0 + i] = dst;
-        a.perm[dst] = p0 + i;
-        ++placed;
-    }
-    for (int d = 32; d >= 1; d >>= 1) placed += __shfl_xor(placed, d, 64);
-    if (tid == 0) s_placed = 0;   // the last step's count was read before that step's final barrier
-    __syncthreads();
-    if (lane == 0 && placed) atomicAdd(&s_placed, placed);
-    __syncthreads();
-    if (tid == 0 && s_placed) atomicAdd(&a.round_count[a.n_probes + 1], s_placed);
+    if (tid < 8 && s_round[tid]) atomicAdd(&a.round_count[tid], s_round[tid]);
 }
 
 }  // namespace
 
 bool psh_scan_eligible(int kcap) { return kcap <= SKMAX; }
 
-hipError_t psh_scan_launch(const PshArgs& args, int32_t* lidx0, int32_t* lidx1, unsigned long long* lvox0, unsigned long long* lvox1,
+hipError_t psh_scan_launch(const PshArgs& args, int32_t* left_idx, int32_t* surv_pos, unsigned long long* voxels, unsigned long long* surv_hash,
                            hipStream_t stream)
 {
     PshArgs a = args;
-    a.chunk = SIT;
+    a.chunk = 2 * STH;
     a.chunk_info = nullptr;
     a.meta_light = 1;   // the scan's own workgroup writes its bucket offsets
     k_psh_meta<<<1, 1024, 0, stream>>>(a);
     if (a.n == 0) return hipGetLastError();
-    const size_t kw = (size_t)(a.kcap + 1) / 2;
-    const size_t lds = ((size_t)3 * a.kcap + 2 * SNW * kw) * 4;
+    const size_t lds = ((size_t)(SNW + 2) * a.kcap + SNW) * 4;
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 0;
     const bool two = cus > 0 && a.n_scans > cus && 2 * lds <= 150 * 1024;
@@ -395,14 +503,14 @@ hipError_t psh_scan_launch(const PshArgs& args, int32_t* lidx0, int32_t* lidx1, 
         if (e != hipSuccess) return e;
     }
     switch (which) {
-        case 0: k_pshs_scan<0, 4><<<a.n_scans, STH, lds, stream>>>(a, lidx0, lidx1, lvox0, lvox1); break;
-        case 1: k_pshs_scan<1, 4><<<a.n_scans, STH, lds, stream>>>(a, lidx0, lidx1, lvox0, lvox1); break;
-        case 2: k_pshs_scan<2, 4><<<a.n_scans, STH, lds, stream>>>(a, lidx0, lidx1, lvox0, lvox1); break;
-        case 3: k_pshs_scan<3, 4><<<a.n_scans, STH, lds, stream>>>(a, lidx0, lidx1, lvox0, lvox1); break;
-        case 4: k_pshs_scan<0, 8><<<a.n_scans, STH, lds, stream>>>(a, lidx0, lidx1, lvox0, lvox1); break;
-        case 5: k_pshs_scan<1, 8><<<a.n_scans, STH, lds, stream>>>(a, lidx0, lidx1, lvox0, lvox1); break;
-        case 6: k_pshs_scan<2, 8><<<a.n_scans, STH, lds, stream>>>(a, lidx0, lidx1, lvox0, lvox1); break;
-        default: k_pshs_scan<3, 8><<<a.n_scans, STH, lds, stream>>>(a, lidx0, lidx1, lvox0, lvox1); break;
+        case 0: k_pshs_scan<0, 4><<<a.n_scans, STH, lds, stream>>>(a, left_idx, surv_pos, voxels, surv_hash); break;
+        case 1: k_pshs_scan<1, 4><<<a.n_scans, STH, lds, stream>>>(a, left_idx, surv_pos, voxels, surv_hash); break;
+        case 2: k_pshs_scan<2, 4><<<a.n_scans, STH, lds, stream>>>(a, left_idx, surv_pos, voxels, surv_hash); break;
+        case 3: k_pshs_scan<3, 4><<<a.n_scans, STH, lds, stream>>>(a, left_idx, surv_pos, voxels, surv_hash); break;
+        case 4: k_pshs_scan<0, 8><<<a.n_scans, STH, lds, stream>>>(a, left_idx, surv_pos, voxels, surv_hash); break;
+        case 5: k_pshs_scan<1, 8><<<a.n_scans, STH, lds, stream>>>(a, left_idx, surv_pos, voxels, surv_hash); break;
+        case 6: k_pshs_scan<2, 8><<<a.n_scans, STH, lds, stream>>>(a, left_idx, surv_pos, voxels, surv_hash); break;
+        default: k_pshs_scan<3, 8><<<a.n_scans, STH, lds, stream>>>(a, left_idx, surv_pos, voxels, surv_hash); break;
     }
     return hipGetLastError();
 }

@@ -166,6 +166,32 @@ def test_bucketize_scan_path_axis_probes_with_wide_voxels(hash):
 
 
 @pytest.mark.parametrize("hash", HASHES)
+def test_bucketize_scan_path_block_edges_in_unequal_scans(hash):
+    # the walk of a scan in blocks (8192 points, 4096 with more scans than compute units), its lists beside those of the other
+    # scans: sizes around a block, most points left over or hardly any, codes of up to and of more than 30 bits
+    rng = np.random.default_rng(34)
+    sizes = np.array([8191, 0, 8193, 4096, 16385, 1, 8192, 24577])
+    many = np.concatenate([sizes, rng.integers(0, 130, 292)])
+    for sz, voxels in ((sizes, (0.05, 0.0005)), (many, (0.05,))):
+        bo = np.concatenate([[0], np.cumsum(sz)]).astype(np.int32)
+        for voxel in voxels:
+            for cloud in (lambda k: clustered_cloud(rng, k), lambda k: rng.random((k, 3)) * 4.0):
+                c = np.concatenate([cloud(int(k)) for k in sz if k]).astype(np.float32)
+                check_bucketize(c, bo, voxel, 256, 4, hash, max_scan_points=int(sz.max()), schedule="scans")
+
+
+@pytest.mark.parametrize("schedule", ["auto", "general", "steps", "scans"])
+def test_bucketize_quotients_at_bucket_boundaries(schedule):
+    # every voxel of a 16^3, 32^3 and 64 x 64 x 16 lattice once, in mixed order: with the Z-order-div hash the codes run through
+    # all multiples of the divisor, where a quotient estimate must be settled by the exact remainder
+    rng = np.random.default_rng(35)
+    for shape, cap in (((16, 16, 16), 64), ((32, 32, 32), 128), ((32, 32, 32), 192), ((64, 64, 16), 256)):
+        g = np.stack(np.meshgrid(*(np.arange(k) for k in shape), indexing="ij"), axis=-1).reshape(-1, 3)
+        c = (rng.permutation(g) * 0.25 + 0.0625).astype(np.float32)     # exact in binary32, a quarter voxel from the faces
+        check_bucketize(c, None, 0.25, cap, 4, "zorder_div", schedule=schedule)
+
+
+@pytest.mark.parametrize("hash", HASHES)
 def test_bucketize_small_scans_in_registers(hash):
     # scans that fit one workgroup's registers: around a wave, a workgroup, and one past the last (another path); clustered
     # points (most are left over) and uniform ones (closed up early); single scans (one launch) and batches with empty
