@@ -61,6 +61,8 @@ __global__ __launch_bounds__(1024) void k_pool_meta(PoolArgs a)
 {
     __shared__ int lds[17];
     __shared__ int bad;
+    __shared__ int first_tile[1024];
+    __shared__ int3 scan_rows[1024];
     const int tid = threadIdx.x;
     if (tid == 0) {
         bad = 0;
@@ -91,11 +93,23 @@ __global__ __launch_bounds__(1024) void k_pool_meta(PoolArgs a)
         const int opre = block_excl_scan(rows, &otot, lds);
         if (b < a.n_scans) {
             a.pooled_offsets[b] = ocarry + opre;
-            for (int t = 0; t < tiles && tcarry + tpre + t < a.n_tiles_ub; ++t) {   // scans are spread over the threads
-                const int r0 = p0 + t * a.tile;
-                a.tile_info[tcarry + tpre + t] = make_int4(r0, min(a.tile, p0 + nb - r0), ocarry + opre + t * per_full, b);
-            }
         }
+        // Rows of the tile table: a thread takes every 1024th and finds its scan, so that a scan of hundreds of tiles is not
+        // one thread's loop (200 000 points in one scan: 20 -> 5 us).
+        first_tile[tid] = tpre;                          // at the threads without a scan: ttot
+        scan_rows[tid] = make_int3(p0, nb, ocarry + opre);
+        __syncthreads();
+        for (int t = tid; t < ttot && tcarry + t < a.n_tiles_ub; t += 1024) {
+            int lo = 0, hi = 1024;                       // the last scan that begins at or before t (those without tiles come first)
+            while (hi - lo > 1) {
+                const int mid = (lo + hi) >> 1;
+                if (first_tile[mid] <= t) lo = mid; else hi = mid;
+            }
+            const int3 sc = scan_rows[lo];
+            const int k = t - first_tile[lo], r0 = sc.x + k * a.tile;
+            a.tile_info[tcarry + t] = make_int4(r0, min(a.tile, sc.x + sc.y - r0), sc.z + k * per_full, base + lo);
+        }
+        __syncthreads();
         tcarry += ttot;
         ocarry += otot;
     }
@@ -225,21 +239,32 @@ __device__ __forceinline__ void wave_sort_keys(unsigned long long (&key)[NPL], i
     if constexpr (K < 64 * NPL) wave_sort_keys<NPL, K * 2>(key, lane);
 }
 
-// The same network on 32-bit keys, at less than half the instructions: a step is a minimum and a maximum. Runs that
-// are to end up descending are sorted ascending on complemented keys instead (the lanes of such a run flip their keys
-// when the phase begins), so no step depends on a direction except through the constant choice of the lower lane.
-template <int NPL, int K, int J>
-__device__ __forceinline__ void sort32_step(unsigned int (&key)[NPL], int lane)
+// The same network on 32-bit keys, at less than half the instructions. Runs that are to end up descending are sorted ascending
+// on complemented keys instead (the lanes of such a run flip their keys when the phase begins), so a step inside a lane is a
+// minimum and a maximum, and a step between lanes one move and one median: of (mine, other, 0) it is the smaller, of
+// (mine, other, ~0) the larger. bit[i] is all ones in the lanes whose number has bit i, else zero. Between rows of 16 lanes
+// and between the halves two keys travel in one swap, after which the pair lies in one lane.
+__device__ __forceinline__ unsigned int med3(unsigned int x, unsigned int y, unsigned int z)
 {
-    if constexpr (J >= NPL) {
-        constexpr int LJ = J / NPL;
-        const bool lower = (lane & LJ) == 0;
+    return max(min(x, y), min(max(x, y), z));   // v_med3_u32
+}
+template <int NPL, int K, int J>
+__device__ __forceinline__ void sort32_step(unsigned int (&key)[NPL], const unsigned int (&bit)[6], int lane)
+{
+    if constexpr (J >= 16 * NPL) {
 #pragma unroll
-        for (int r = 0; r < NPL; ++r) {
-            const unsigned int other = lane_xor<LJ>(key[r], lane);
-            const unsigned int lo = min(key[r], other), hi = max(key[r], other);
-            key[r] = lower ? lo : hi;
+        for (int r = 0; r < NPL; r += 2) {
+            const auto s = J == 32 * NPL ? __builtin_amdgcn_permlane32_swap(key[r], key[r + 1], false, false)
+                                         : __builtin_amdgcn_permlane16_swap(key[r], key[r + 1], false, false);
+            const unsigned int x = s[0], y = s[1], lo = min(x, y), hi = max(x, y);
+            const auto t = J == 32 * NPL ? __builtin_amdgcn_permlane32_swap(lo, hi, false, false) : __builtin_amdgcn_permlane16_swap(lo, hi, false, false);
+            key[r] = t[0];
+            key[r + 1] = t[1];
         }
+    } else if constexpr (J >= NPL) {
+        constexpr int LJ = J / NPL, B = LJ == 1 ? 0 : LJ == 2 ? 1 : LJ == 4 ? 2 : 3;
+#pragma unroll
+        for (int r = 0; r < NPL; ++r) key[r] = med3(key[r], lane_xor<LJ>(key[r], lane), bit[B]);
     } else {
 #pragma unroll
         for (int r = 0; r < NPL; ++r) {
@@ -250,20 +275,20 @@ __device__ __forceinline__ void sort32_step(unsigned int (&key)[NPL], int lane)
             key[r | J] = up ? hi : lo;
         }
     }
-    if constexpr (J > 1) sort32_step<NPL, K, J / 2>(key, lane);
+    if constexpr (J > 1) sort32_step<NPL, K, J / 2>(key, bit, lane);
 }
 template <int NPL, int K = 2>
-__device__ __forceinline__ void wave_sort32(unsigned int (&key)[NPL], int lane)
+__device__ __forceinline__ void wave_sort32(unsigned int (&key)[NPL], const unsigned int (&bit)[6], int lane)
 {
     if constexpr (K >= NPL) {
-        const bool up_now = K >= 64 * NPL ? true : (lane & (K / NPL)) == 0;
-        const bool up_before = K / 2 >= NPL ? (lane & (K / 2 / NPL)) == 0 : true;
-        const unsigned int flip = up_now != up_before ? 0xFFFFFFFFu : 0u;
+        constexpr int LK = K / NPL;                      // lanes in a run
+        constexpr int B = LK == 1 ? 0 : LK == 2 ? 1 : LK == 4 ? 2 : LK == 8 ? 3 : LK == 16 ? 4 : 5;
+        const unsigned int down_now = LK >= 64 ? 0u : bit[B], down_before = LK >= 2 ? bit[LK >= 64 ? 5 : B - (LK >= 2 ? 1 : 0)] : 0u;
 #pragma unroll
-        for (int r = 0; r < NPL; ++r) key[r] ^= flip;
+        for (int r = 0; r < NPL; ++r) key[r] ^= down_now ^ down_before;
     }
-    sort32_step<NPL, K, K / 2>(key, lane);
-    if constexpr (K < 64 * NPL) wave_sort32<NPL, K * 2>(key, lane);
+    sort32_step<NPL, K, K / 2>(key, bit, lane);
+    if constexpr (K < 64 * NPL) wave_sort32<NPL, K * 2>(key, bit, lane);
 }
 
 // Odd-even transposition sweeps over the wave's 64 * NPL keys (element lane * NPL + r) until a sweep swaps nothing;
@@ -302,41 +327,58 @@ __device__ __forceinline__ bool settle_order(unsigned long long (&key)[NPL], int
 // One wave writes, for each of the rows left it is given (every PW-th), the ids of the open sub-buckets in the
 // order in which the row would choose them: increasing squared distance to the sub-bucket's first row, the lower id
 // first on a tie, i.e. increasing (bits of the distance, position in the open list): a squared distance is a
-// non-negative binary32 number, whose bit patterns are ordered like the numbers. The sort runs on 32-bit keys (the
-// upper 23 bits of the distance's pattern, 9 bits of position: at most 512 sub-buckets are open when rows are
-// left); that orders all candidates except those whose distances agree in the bits kept, which the full 64-bit keys
-// then settle among neighbours (if that takes long, the full keys are sorted outright). `list` rows have `pitch`
-// entries (a multiple of 8, >= nopen).
+// non-negative binary32 number, whose bit patterns are ordered like the numbers. The sort runs on 32-bit keys of 23 bits for
+// the distance and 9 of position (at most 512 sub-buckets are open when rows are left). The 23 bits are those of the pattern
+// above `base`, without its last four: sixteen octaves below the largest distance the tile can have, in steps of 2^-19; what
+// lies below is one value. Only when two neighbours agree in those bits (one list in twenty on the measured layouts, with
+// 15 bits of mantissa it was most of them) are the full 64-bit keys worked out and settled among neighbours (if that takes
+// long, sorted outright). `list` rows have `pitch` entries (a multiple of 8, >= nopen).
+// Bound: the vector ALU (two workgroups per compute unit). Against a network of moves, minima, maxima and selects followed by
+// the full keys every time, candidates read eight words apart (all in the same banks): 914 601 points in 8 scans, rho 2,
+// 2264 -> 1654 us, 825 -> 594 million vector instructions; one room of 200 000 477 -> 360 (15 of them the tile table).
+constexpr unsigned int DIST_MAX = 0x7FFDFFu;   // distances beyond; the 512 prefixes above are for entries without a sub-bucket
 template <int NPL>
-__device__ __forceinline__ void sort_choices(int nleft, int nopen, int pitch, const uint16_t* left_list, const float* px,
+__device__ __forceinline__ void sort_choices(int nleft, int nopen, int pitch, unsigned int base, const uint16_t* left_list, const float* px,
                                              const float* py, const float* pz, const float4* o4, const uint16_t* open_list,
                                              uint16_t* list)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    unsigned int bit[6];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) bit[i] = (lane >> i) & 1 ? 0xFFFFFFFFu : 0u;
     for (int p = wave; p < nleft; p += PW) {
         const int id = left_list[p];
         const float qx = px[id], qy = py[id], qz = pz[id];
         unsigned int k32[NPL];
 #pragma unroll
         for (int r = 0; r < NPL; ++r) {   // the candidates' positions are read again for every row: registers are scarce
-            const int e = lane * NPL + r;
-            const float4 o = o4[min(e, nopen - 1)];
+            const unsigned int e = r * 64 + lane;        // neighbouring lanes, neighbouring words: no bank conflicts
+            const float4 o = o4[min((int)e, nopen - 1)];
             const float d2 = dist2(qx - o.x, qy - o.y, qz - o.z);
-            k32[r] = e < nopen ? ((__float_as_uint(d2) >> 8) << 9) | (unsigned int)e : 0xFFFFFFFFu;
+            const unsigned int d = min(__builtin_elementwise_sub_sat(__float_as_uint(d2), base) >> 4, DIST_MAX);
+            k32[r] = (((int)e < nopen ? d : DIST_MAX + 1 + e) << 9) | e;
         }
-        wave_sort32<NPL>(k32, lane);
-        unsigned long long key[NPL];
+        wave_sort32<NPL>(k32, bit, lane);
+        bool tie = false;
 #pragma unroll
-        for (int r = 0; r < NPL; ++r) {   // the full key of the candidate now at this place
-            const int e = min((int)(k32[r] & 511u), nopen - 1);
-            const float4 o = o4[e];
-            const float d2 = dist2(qx - o.x, qy - o.y, qz - o.z);
-            key[r] = k32[r] != 0xFFFFFFFFu ? ((unsigned long long)__float_as_uint(d2) << 32) | (unsigned int)e : ~0ull;
+        for (int r = 0; r + 1 < NPL; ++r) tie |= (k32[r] ^ k32[r + 1]) < 512u;
+        tie |= lane < 63 && (k32[NPL - 1] ^ (unsigned int)__shfl_down((int)k32[0], 1, 64)) < 512u;
+        if (__builtin_amdgcn_ballot_w64(tie)) {
+            unsigned long long key[NPL];
+#pragma unroll
+            for (int r = 0; r < NPL; ++r) {   // the full key of the candidate now at this place
+                const int e = (int)(k32[r] & 511u);
+                const float4 o = o4[min(e, nopen - 1)];
+                const float d2 = dist2(qx - o.x, qy - o.y, qz - o.z);
+                key[r] = e < nopen ? ((unsigned long long)__float_as_uint(d2) << 32) | (unsigned int)e : ~0ull;
+            }
+            if (!settle_order<NPL>(key, lane, 16)) wave_sort_keys<NPL>(key, lane);
+#pragma unroll
+            for (int r = 0; r < NPL; ++r) k32[r] = (unsigned int)key[r];
         }
-        if (!settle_order<NPL>(key, lane, 16)) wave_sort_keys<NPL>(key, lane);
-        unsigned int sid[NPL];   // padding entries (beyond nopen) become id 0: never chosen, but a valid index
+        unsigned int sid[NPL];   // entries beyond nopen become some valid id: they are never chosen
 #pragma unroll
-        for (int r = 0; r < NPL; ++r) sid[r] = key[r] == ~0ull ? 0u : (unsigned int)open_list[(unsigned int)key[r] & 511u];
+        for (int r = 0; r < NPL; ++r) sid[r] = (unsigned int)open_list[min((int)(k32[r] & 511u), nopen - 1)];
         if (lane * NPL < pitch) {
             uint16_t* dst = list + (size_t)p * pitch + lane * NPL;
             if (NPL == 8) {
@@ -430,7 +472,7 @@ __global__ __launch_bounds__(PT, WPE) void k_pool(PoolArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     __shared__ int lds[17];
-    __shared__ uint32_t red[8];
+    __shared__ uint32_t red[11];
     __shared__ ScanCfg cfg;
     __shared__ int next_tile;
     __shared__ int rows_left;
@@ -479,7 +521,7 @@ __global__ __launch_bounds__(PT, WPE) void k_pool(PoolArgs a)
         py[tid] = y;
         pz[tid] = z;
     }
-    if (tid < 3) { red[tid] = 0xFFFFFFFFu; red[4 + tid] = 0u; }
+    if (tid < 3) { red[tid] = 0xFFFFFFFFu; red[4 + tid] = 0u; red[8 + tid] = 0u; }
     for (int k = tid; k < kp; k += PT) {
         fill[k] = 0;
         first_idx[k] = 0;
@@ -492,9 +534,12 @@ __global__ __launch_bounds__(PT, WPE) void k_pool(PoolArgs a)
         uint32_t o[3] = {act ? f2ord(x) : 0xFFFFFFFFu, act ? f2ord(y) : 0xFFFFFFFFu, act ? f2ord(z) : 0xFFFFFFFFu};
 #pragma unroll
         for (int ax = 0; ax < 3; ++ax) {
-            uint32_t lo = o[ax];
-            for (int d = 32; d >= 1; d >>= 1) lo = min(lo, (uint32_t)__shfl_xor((int)lo, d, 64));
-            if (lane == 0) atomicMin(&red[ax], lo);
+            uint32_t lo = o[ax], hi = act ? o[ax] : 0u;
+            for (int d = 32; d >= 1; d >>= 1) {
+                lo = min(lo, (uint32_t)__shfl_xor((int)lo, d, 64));
+                hi = max(hi, (uint32_t)__shfl_xor((int)hi, d, 64));
+            }
+            if (lane == 0) { atomicMin(&red[ax], lo); atomicMax(&red[8 + ax], hi); }
         }
     }
     __syncthreads();
@@ -641,12 +686,15 @@ __global__ __launch_bounds__(PT, WPE) void k_pool(PoolArgs a)
     }
     const int pitch = (nopen + 7) & ~7;
     if (nleft > 0 && nopen > 0 && (long long)nleft * pitch <= (long long)a.list_cap) {
+        // the pattern of the tile's squared diagonal bounds that of every distance in it (rounding is monotone)
+        const unsigned int top = __float_as_uint(dist2(ord2f(red[8]) - mnx, ord2f(red[9]) - mny, ord2f(red[10]) - mnz));
+        const unsigned int base = __builtin_elementwise_sub_sat(top, DIST_MAX << 4);
         if (nopen <= 128)
-            sort_choices<2>(nleft, nopen, pitch, left_list, px, py, pz, o4, open_list, my_lists);
+            sort_choices<2>(nleft, nopen, pitch, base, left_list, px, py, pz, o4, open_list, my_lists);
         else if (nopen <= 256)
-            sort_choices<4>(nleft, nopen, pitch, left_list, px, py, pz, o4, open_list, my_lists);
+            sort_choices<4>(nleft, nopen, pitch, base, left_list, px, py, pz, o4, open_list, my_lists);
         else
-            sort_choices<8>(nleft, nopen, pitch, left_list, px, py, pz, o4, open_list, my_lists);
+            sort_choices<8>(nleft, nopen, pitch, base, left_list, px, py, pz, o4, open_list, my_lists);
         __threadfence_block();   // the lists are read by other waves of this workgroup
         __syncthreads();
         // Thread t now speaks for the t-th row left: row order is kept. It walks its list in chunks of eight entries

@@ -1288,6 +1288,27 @@ def test_pool_candidates_at_nearly_equal_distances(spread):
         assert ref["step_of"].max() >= 100   # the cluster's rows take the shell's sub-buckets one round at a time
 
 
+@pytest.mark.parametrize("octaves", [10, 30, 60])
+def test_pool_candidates_over_many_octaves_of_distance(octaves):
+    """As above with the shell's radii spread over a range of 2^octaves around the cluster: the shortened sort keys hold sixteen
+    octaves of squared distance, everything nearer is one value to them. Scans of one to many tiles."""
+    rng = np.random.default_rng(47)
+    sizes = [1024, 5000, 1, 0, 700, 2048]
+    parts = []
+    for n in sizes:
+        for t0 in range(0, n, 1024):
+            m = min(1024, n - t0)
+            shell = (3 * m) // 5
+            u = rng.normal(size=(shell, 3))
+            u /= np.linalg.norm(u, axis=1, keepdims=True) if shell else 1.0
+            parts.append(np.concatenate([u * 1000.0 * 2.0 ** (-0.5 * octaves * rng.random((shell, 1))), np.zeros((m - shell, 3))]))
+    c = np.concatenate(parts).astype(np.float32)
+    bo = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    feat = wl.f32_to_bf16_bits(rng.standard_normal((len(c), 16)).astype(np.float32))
+    for rho, voxel in ((2, 50.0), (3, 0.01)):
+        check_pool(c, None, feat, bo, 1024, rho, voxel, "zorder_div", "max")
+
+
 def test_pool_empty_input_and_bad_offsets():
     z = np.zeros((0, 3), np.float32)
     got = f3d.inbucket_pool(dev(z), None, dev(np.zeros((0, 8), np.uint16), torch.bfloat16), None, 1024, 2, 0.1)
