@@ -324,7 +324,43 @@ __device__ __forceinline__ bool settle_order(unsigned long long (&key)[NPL], int
     return false;
 }
 
-// One wave writes, for each of the rows left it is given (every PW-th), the ids of the open sub-buckets in the
+// Odd-even transposition of 64 * NPL 32-bit keys (element lane * NPL + r): two passes over neighbours at even and at odd
+// places. `next_lane` / `prev_lane`: the key of the lane beside (lanes 63 and 0 keep `self`).
+__device__ __forceinline__ unsigned int next_lane(unsigned int self, unsigned int x)
+{
+    return (unsigned int)__builtin_amdgcn_update_dpp((int)self, (int)x, 0x130, 0xF, 0xF, false);   // wave_shl:1
+}
+__device__ __forceinline__ unsigned int prev_lane(unsigned int self, unsigned int x)
+{
+    return (unsigned int)__builtin_amdgcn_update_dpp((int)self, (int)x, 0x138, 0xF, 0xF, false);   // wave_shr:1
+}
+template <int NPL>
+__device__ __forceinline__ void transpose32(unsigned int (&key)[NPL])
+{
+#pragma unroll
+    for (int r0 = 0; r0 < 2; ++r0) {
+#pragma unroll
+        for (int r = r0; r + 1 < NPL; r += 2) {
+            const unsigned int lo = min(key[r], key[r + 1]), hi = max(key[r], key[r + 1]);
+            key[r] = lo;
+            key[r + 1] = hi;
+        }
+    }
+    const unsigned int last = key[NPL - 1], first = key[0];   // the pair that straddles two lanes
+    key[NPL - 1] = min(last, next_lane(0xFFFFFFFFu, first));
+    key[0] = max(first, prev_lane(0u, last));
+}
+// lanes whose keys are not in order up to the next lane's first
+template <int NPL>
+__device__ __forceinline__ int lanes_out_of_order(const unsigned int (&key)[NPL])
+{
+    bool bad = key[NPL - 1] > next_lane(0xFFFFFFFFu, key[0]);
+#pragma unroll
+    for (int r = 0; r + 1 < NPL; ++r) bad |= key[r] > key[r + 1];
+    return __popcll(__builtin_amdgcn_ballot_w64(bad));
+}
+
+// One wave writes, for each of a run of the rows left, the ids of the open sub-buckets in the
 // order in which the row would choose them: increasing squared distance to the sub-bucket's first row, the lower id
 // first on a tie, i.e. increasing (bits of the distance, position in the open list): a squared distance is a
 // non-negative binary32 number, whose bit patterns are ordered like the numbers. The sort runs on 32-bit keys of 23 bits for
@@ -332,37 +368,60 @@ __device__ __forceinline__ bool settle_order(unsigned long long (&key)[NPL], int
 // above `base`, without its last four: sixteen octaves below the largest distance the tile can have, in steps of 2^-19; what
 // lies below is one value. Only when two neighbours agree in those bits (one list in twenty on the measured layouts, with
 // 15 bits of mantissa it was most of them) are the full 64-bit keys worked out and settled among neighbours (if that takes
-// long, sorted outright). `list` rows have `pitch` entries (a multiple of 8, >= nopen).
-// Bound: the vector ALU (two workgroups per compute unit). Against a network of moves, minima, maxima and selects followed by
-// the full keys every time, candidates read eight words apart (all in the same banks): 914 601 points in 8 scans, rho 2,
-// 2264 -> 1654 us, 825 -> 594 million vector instructions; one room of 200 000 477 -> 360 (15 of them the tile table).
+// long, sorted outright).
+// The rows left are those of dense clusters, and rows that follow each other lie close together: the list of one is nearly
+// that of the next (on sensor sweeps no candidate moves by more than 1 to 6 places at the median, 12 on average). So only the
+// first row of a run goes through the network; the others take the previous row's order with their own distances and
+// transpose neighbours until nothing is out of place. Where half of the lanes are out of order or twelve passes have not
+// sufficed the network sorts, and after two such rows it sorts every row but each eighth (in rooms, where what is left lies
+// scattered over the tile).
+// `list` rows have `pitch` entries (a multiple of 8, >= nopen), each four times an id.
+// Bound: the vector ALU. Pooling 914 601 points of sensor sweeps took 2254 us (825 million vector instructions) with a network
+// of moves, minima, maxima and selects, the full keys every time and candidates read eight words apart (all in the same
+// banks), 1654 (594) with the network as it is, and 1550 to 1300 (540 to 340) with the previous row's order to start from.
 constexpr unsigned int DIST_MAX = 0x7FFDFFu;   // distances beyond; the 512 prefixes above are for entries without a sub-bucket
 template <int NPL>
 __device__ __forceinline__ void sort_choices(int nleft, int nopen, int pitch, unsigned int base, const uint16_t* left_list, const float* px,
                                              const float* py, const float* pz, const float4* o4, const uint16_t* open_list,
                                              uint16_t* list)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    unsigned int bit[6];
-#pragma unroll
-    for (int i = 0; i < 6; ++i) bit[i] = (lane >> i) & 1 ? 0xFFFFFFFFu : 0u;
-    for (int p = wave; p < nleft; p += PW) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    unsigned int k32[NPL] = {};                          // the previous row's list, entries without a sub-bucket last
+    const int run = (nleft + PW - 1) / PW, p_begin = wave * run, p_end = min(p_begin + run, nleft);
+    int misses = 2;                                      // rows in a row whose list was not nearly the previous one's
+    for (int p = p_begin; p < p_end; ++p) {
+        const bool ordered = misses < 2 || (p != p_begin && (p & 7) == 0);
         const int id = left_list[p];
         const float qx = px[id], qy = py[id], qz = pz[id];
-        unsigned int k32[NPL];
 #pragma unroll
         for (int r = 0; r < NPL; ++r) {   // the candidates' positions are read again for every row: registers are scarce
-            const unsigned int e = r * 64 + lane;        // neighbouring lanes, neighbouring words: no bank conflicts
+            const unsigned int e = ordered ? k32[r] & 511u : (unsigned int)(r * 64 + lane);   // in index order: no bank conflicts
             const float4 o = o4[min((int)e, nopen - 1)];
             const float d2 = dist2(qx - o.x, qy - o.y, qz - o.z);
             const unsigned int d = min(__builtin_elementwise_sub_sat(__float_as_uint(d2), base) >> 4, DIST_MAX);
             k32[r] = (((int)e < nopen ? d : DIST_MAX + 1 + e) << 9) | e;
         }
-        wave_sort32<NPL>(k32, bit, lane);
-        bool tie = false;
+        bool sorted = false;
+        misses = ordered ? misses + 1 : misses;
+        if (ordered) {
+            for (int pass = 0; pass < 12; pass += 2) {
+                const int bad = lanes_out_of_order<NPL>(k32);
+                if (bad == 0) { sorted = true; misses = 0; break; }
+                if (bad > 30) break;                     // hardly the same list
+                transpose32<NPL>(k32);
+                transpose32<NPL>(k32);
+            }
+        }
+        if (!sorted) {
+            unsigned int bit[6];
+#pragma unroll
+            for (int i = 0; i < 6; ++i) bit[i] = (lane >> i) & 1 ? 0xFFFFFFFFu : 0u;
+            wave_sort32<NPL>(k32, bit, lane);
+            if (p == p_begin) misses = 0;
+        }
+        bool tie = lane < 63 && (k32[NPL - 1] ^ next_lane(0u, k32[0])) < 512u;
 #pragma unroll
         for (int r = 0; r + 1 < NPL; ++r) tie |= (k32[r] ^ k32[r + 1]) < 512u;
-        tie |= lane < 63 && (k32[NPL - 1] ^ (unsigned int)__shfl_down((int)k32[0], 1, 64)) < 512u;
         if (__builtin_amdgcn_ballot_w64(tie)) {
             unsigned long long key[NPL];
 #pragma unroll
@@ -370,15 +429,15 @@ __device__ __forceinline__ void sort_choices(int nleft, int nopen, int pitch, un
                 const int e = (int)(k32[r] & 511u);
                 const float4 o = o4[min(e, nopen - 1)];
                 const float d2 = dist2(qx - o.x, qy - o.y, qz - o.z);
-                key[r] = e < nopen ? ((unsigned long long)__float_as_uint(d2) << 32) | (unsigned int)e : ~0ull;
+                key[r] = ((unsigned long long)(e < nopen ? __float_as_uint(d2) : 0xFFFFFFFFu) << 32) | (unsigned int)e;
             }
             if (!settle_order<NPL>(key, lane, 16)) wave_sort_keys<NPL>(key, lane);
 #pragma unroll
             for (int r = 0; r < NPL; ++r) k32[r] = (unsigned int)key[r];
         }
-        unsigned int sid[NPL];   // entries beyond nopen become some valid id: they are never chosen
+        unsigned int sid[NPL];   // four times the id: the byte offset of the sub-bucket's fill level. Entries beyond nopen: open_list[nopen]
 #pragma unroll
-        for (int r = 0; r < NPL; ++r) sid[r] = (unsigned int)open_list[min((int)(k32[r] & 511u), nopen - 1)];
+        for (int r = 0; r < NPL; ++r) sid[r] = 4u * (unsigned int)open_list[min((int)(k32[r] & 511u), nopen)];
         if (lane * NPL < pitch) {
             uint16_t* dst = list + (size_t)p * pitch + lane * NPL;
             if (NPL == 8) {
@@ -455,6 +514,133 @@ __device__ __forceinline__ bool join_passes(bool contend, int c, int tid, int rh
         if (!again) break;
     }
     return joined;
+}
+
+// The rounds for rho = 2. An open sub-bucket holds one row and has room for one: whoever contends for it knows that it
+// is closed after this round, without waiting for the winner. The contenders themselves mark it (with the round's number, so
+// that a search of the same round still sees it open), and a round needs one barrier instead of two. stamp[c]: OPEN while
+// open, minus the round in which it closed, 1 if it was full before the rounds; open in round t means stamp[c] < 1 - t.
+// Thread t speaks for the t-th row still walking, so that the lowest thread is the lowest row. Rows leave one or two per
+// round: every 32 rounds they are closed up when fewer waves would hold them, and when one wave holds them all it goes on
+// alone, without barriers. A row looks up the eight entries of its chunk (16 bytes of its list) together: their reads overlap,
+// and the sign of stamp - threshold is shifted into a mask. (A chunk is read when it is entered; with the next one already on its
+// way to LDS the pooling of a room of 200 000 took 351 us instead of 333.)
+// Bound: the chain of LDS reads, one LDS minimum and a barrier per round. One room of
+// 200 000, a tile per compute unit: 360 us with all rows' waves kept to the end and shifts and selects for the mask, 333 now.
+constexpr int STAMP_OPEN = -(1 << 30);
+__device__ __forceinline__ void rounds_of_two(int nleft, int pitch, int kp, const uint16_t* lists, int* stamp, int* win, uint16_t* rsub,
+                                              uint32_t* moved, int* wave_rows, int* any3)
+{
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int chunks = pitch >> 3;
+    int orig = tid, idx = 0, at = 0;        // the row's place among those left at the start; next entry; chunk in `cur`
+    bool walking = tid < nleft;
+    uint4 cur = make_uint4(0, 0, 0, 0);
+    const uint4* mine = nullptr;
+    auto load_row = [&]() __attribute__((always_inline)) {
+        mine = reinterpret_cast<const uint4*>(lists + (size_t)orig * pitch);
+        at = idx >> 3;
+        cur = mine[at];
+    };
+    if (walking) load_row();
+    // The first sub-bucket of the row's list that has room in this round, as its byte offset.
+    auto search = [&](int thr, int& c) __attribute__((always_inline)) -> bool {
+        if (!walking) return false;
+        for (;;) {
+            const unsigned int w[4] = {cur.x, cur.y, cur.z, cur.w};
+            int level[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const unsigned int eo = (j & 1) ? w[j >> 1] >> 16 : w[j >> 1] & 0xFFFFu;
+                level[j] = *reinterpret_cast<const int*>(reinterpret_cast<const char*>(stamp) + eo);
+            }
+            __builtin_amdgcn_sched_barrier(0);   // all eight reads are under way before the first is waited for
+            unsigned int room = 0;
+#pragma unroll
+            for (int j = 7; j >= 0; --j) room = __builtin_amdgcn_alignbit(room, (unsigned int)(level[j] - thr), 31);
+            room &= 0xFFu << (idx & 7);          // entries before idx are behind
+            if (room) {
+                const int j = __builtin_ctz(room);
+                idx = (idx & ~7) + j;
+                c = chunk_entry(cur, j);
+                return true;
+            }
+            if (++at >= chunks) { walking = false; return false; }   // cannot happen: the rows left and the rooms are equally many
+            idx = at << 3;
+            cur = mine[at];
+        }
+    };
+    int round = 0, par = 0, r3 = 0, waves = (nleft + 63) >> 6;
+    bool done = false;
+    while (!done && waves > 1) {
+        for (int k = 0; k < 32; ++k, ++round) {
+            if (tid == 0) any3[r3 == 2 ? 0 : r3 + 1] = 0;
+            int c = 0;
+            const bool contend = search(1 - round, c);
+            int* const w = reinterpret_cast<int*>(reinterpret_cast<char*>(win + par * kp) + c);
+            if (contend) {
+                atomicMin(w, tid);
+                *reinterpret_cast<int*>(reinterpret_cast<char*>(stamp) + c) = -round;
+                any3[r3] = 1;
+            }
+            lds_barrier();
+            const int lowest = contend ? *w : -1;
+            const int seen = __builtin_amdgcn_readfirstlane(any3[r3]);   // did any row contend? (the same answer for every thread)
+            if (contend && lowest == tid) {
+                rsub[orig] = (uint16_t)(c >> 2);
+                walking = false;
+                *w = 0x7FFFFFFF;                  // next written two rounds from here, a barrier in between
+            }
+            par ^= 1;
+            r3 = r3 == 2 ? 0 : r3 + 1;
+            if (!seen) { done = true; break; }
+        }
+        if (done) break;
+        const unsigned long long m = __builtin_amdgcn_ballot_w64(walking);
+        if (lane == 0) wave_rows[wave] = __popcll(m);
+        __syncthreads();
+        int before = 0, total = 0;
+#pragma unroll
+        for (int v = 0; v < PW; ++v) {
+            const int n = wave_rows[v];
+            before += v < wave ? n : 0;
+            total += n;
+        }
+        total = __builtin_amdgcn_readfirstlane(total);
+        const int fewer = (total + 63) >> 6;
+        if (fewer < waves) {                      // the same for every thread
+            waves = fewer;
+            if (walking) moved[before + bits_below(m)] = (uint32_t)orig | ((uint32_t)idx << 16);
+            __syncthreads();
+            walking = tid < total;
+            if (walking) {
+                const uint32_t r = moved[tid];
+                orig = (int)(r & 0xFFFFu);
+                idx = (int)(r >> 16);
+                load_row();
+            }
+        }
+        __syncthreads();                          // wave_rows is written again
+    }
+    if (done || wave != 0) return;
+    for (;; ++round) {                            // one wave: its LDS operations are in order
+        int c = 0;
+        const bool contend = search(1 - round, c);
+        if (__builtin_amdgcn_ballot_w64(contend) == 0ull) break;
+        int* const w = reinterpret_cast<int*>(reinterpret_cast<char*>(win + par * kp) + c);
+        if (contend) atomicMin(w, tid);
+        __builtin_amdgcn_wave_barrier();
+        const int lowest = contend ? *reinterpret_cast<volatile int*>(w) : -1;
+        __builtin_amdgcn_wave_barrier();
+        if (contend) *reinterpret_cast<int*>(reinterpret_cast<char*>(stamp) + c) = -round;
+        if (contend && lowest == tid) {
+            rsub[orig] = (uint16_t)(c >> 2);
+            walking = false;
+            *w = 0x7FFFFFFF;
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
 }
 
 // dynamic LDS, kp = a.kp: px,py,pz [PT] floats | o4 [kp] float4 (x, y, z, -) | fill [kp] ints | win [2][kp] ints |
@@ -686,6 +872,8 @@ __global__ __launch_bounds__(PT, WPE) void k_pool(PoolArgs a)
     }
     const int pitch = (nopen + 7) & ~7;
     if (nleft > 0 && nopen > 0 && (long long)nleft * pitch <= (long long)a.list_cap) {
+        if (tid == 0 && nopen < kp) open_list[nopen] = (uint16_t)kp;   // what list entries beyond nopen name (none if nopen = kp)
+        __syncthreads();
         // the pattern of the tile's squared diagonal bounds that of every distance in it (rounding is monotone)
         const unsigned int top = __float_as_uint(dist2(ord2f(red[8]) - mnx, ord2f(red[9]) - mny, ord2f(red[10]) - mnz));
         const unsigned int base = __builtin_elementwise_sub_sat(top, DIST_MAX << 4);
@@ -697,95 +885,65 @@ __global__ __launch_bounds__(PT, WPE) void k_pool(PoolArgs a)
             sort_choices<8>(nleft, nopen, pitch, base, left_list, px, py, pz, o4, open_list, my_lists);
         __threadfence_block();   // the lists are read by other waves of this workgroup
         __syncthreads();
-        // Thread t now speaks for the t-th row left: row order is kept. It walks its list in chunks of eight entries
-        // (16 bytes), the chunk in use in registers. The lists were written by this compute unit a moment ago and
-        // come back from its caches; a ring of the next chunks in LDS, refilled by global->LDS loads a round ahead,
-        // measured no faster than reading a chunk when it is entered: the rounds are bound by the number of
-        // instructions a wave issues per round, not by this latency.
-        bool walking = tid < nleft;
-        const uint4* mine = reinterpret_cast<const uint4*>(my_lists + (size_t)tid * pitch);
-        uint4 cur = make_uint4(0, 0, 0, 0);
-        if (walking) cur = mine[0];
-        // With rho = 2 an open sub-bucket holds one row and has room for one: whoever contends for it knows that it
-        // is closed after this round, without waiting for the winner. The contenders themselves mark it (with the
-        // round's number, so that a search of the same round still sees it open), and a round needs one barrier
-        // instead of two. stamp[c]: very negative while open, minus the round in which it closed, 1 if it was full
-        // before the rounds; open in round t means stamp[c] < 1 - t. For other rho the fill level decides (< rho).
-        const bool two = rho == 2;
-        int* stamp = reinterpret_cast<int*>(o4);   // the candidates' positions are not needed after the sort
-        if (two) {
-            for (int k = tid; k < M; k += PT) stamp[k] = fill[k] < 2 ? (int)0x80000000 : 1;
+        if (rho == 2) {
+            int* stamp = reinterpret_cast<int*>(o4);   // [kp + 1]; the candidates' positions are not needed after the sort
+            for (int k = tid; k <= kp; k += PT) stamp[k] = k < M && fill[k] < 2 ? STAMP_OPEN : 1;   // stamp[kp] is what entries beyond nopen name
             __syncthreads();
-        }
-        const int* level_of = two ? stamp : fill;
-        int idx = 0, c = 0, rpar = 0, r3 = 0;
-        for (int round = 0; round <= PT + 1; ++round) {   // every round places at least one row; the bound is a safeguard
-            bool contend = false;
-            const int thr = two ? 1 - round : rho;
-            if (tid == 0) {
-                if (two) any3[r3 == 2 ? 0 : r3 + 1] = 0; else any[rpar ^ 1] = 0;
-            }
-            if (walking) {
-                for (;;) {   // the first sub-bucket of the sequence that still has room
-                    if (idx >= nopen) break;
-                    // all eight entries of the chunk are looked up together (their reads overlap, no branch per entry)
-                    const unsigned int w[4] = {cur.x, cur.y, cur.z, cur.w};
-                    unsigned int room = 0;
-                    int level[8];
+            rounds_of_two(nleft, pitch, kp, my_lists, stamp, win, rsub, reinterpret_cast<uint32_t*>(wcnt), lds, any3);
+            __syncthreads();
+            for (int k = tid; k < M; k += PT)          // the sub-buckets closed in the rounds are full
+                if (stamp[k] != STAMP_OPEN && stamp[k] <= 0) fill[k] = 2;
+            if (left) rslot[lpos] = 1;
+        } else {
+            // Thread t now speaks for the t-th row left: row order is kept. It walks its list in chunks of eight entries
+            // (16 bytes), the chunk in use in registers.
+            bool walking = tid < nleft;
+            const uint4* mine = reinterpret_cast<const uint4*>(my_lists + (size_t)tid * pitch);
+            uint4 cur = make_uint4(0, 0, 0, 0);
+            if (walking) cur = mine[0];
+            int idx = 0, c = 0, rpar = 0;
+            for (int round = 0; round <= PT + 1; ++round) {   // every round places at least one row; the bound is a safeguard
+                bool contend = false;
+                if (tid == 0) any[rpar ^ 1] = 0;
+                if (walking) {
+                    for (;;) {   // the first sub-bucket of the sequence that still has room
+                        if (idx >= nopen) break;
+                        // all eight entries of the chunk are looked up together (their reads overlap, no branch per entry)
+                        const unsigned int w[4] = {cur.x, cur.y, cur.z, cur.w};
+                        unsigned int room = 0;
+                        int level[8];
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        const unsigned int eo = (j & 1) ? (w[j >> 1] >> 14) & ~3u : (w[j >> 1] << 2) & 0x3FFFCu;   // 4 * id
-                        level[j] = *reinterpret_cast<const int*>(reinterpret_cast<const char*>(level_of) + eo);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);   // all eight reads are under way before the first is waited for
+                        for (int j = 0; j < 8; ++j) {
+                            const unsigned int eo = (j & 1) ? w[j >> 1] >> 16 : w[j >> 1] & 0xFFFFu;   // 4 * id
+                            level[j] = *reinterpret_cast<const int*>(reinterpret_cast<const char*>(fill) + eo);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);   // all eight reads are under way before the first is waited for
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) room |= (level[j] < thr ? 1u : 0u) << j;
-                    const int base = idx & ~7, lim = nopen - base;   // entries before idx are behind, those from nopen on are padding
-                    room &= 0xFFu << (idx & 7);
-                    if (lim < 8) room &= (1u << lim) - 1u;
-                    if (room) {
-                        const int j = __builtin_ctz(room);
-                        idx = base + j;
-                        c = chunk_entry(cur, j);
-                        contend = true;
-                        break;
+                        for (int j = 0; j < 8; ++j) room |= (level[j] < rho ? 1u : 0u) << j;
+                        const int base = idx & ~7, lim = nopen - base;   // entries before idx are behind, those from nopen on are padding
+                        room &= 0xFFu << (idx & 7);
+                        if (lim < 8) room &= (1u << lim) - 1u;
+                        if (room) {
+                            const int j = __builtin_ctz(room);
+                            idx = base + j;
+                            c = chunk_entry(cur, j) >> 2;
+                            contend = true;
+                            break;
+                        }
+                        idx = base + 8;
+                        if (idx < nopen) cur = mine[idx >> 3];
                     }
-                    idx = base + 8;
-                    if (idx < nopen) cur = mine[idx >> 3];
                 }
-            }
-            int seen = 0;   // did any row contend in this round? (the same answer for every thread)
-            if (two) {
-                if (contend) {
-                    atomicMin(&win[par * kp + c], tid);
-                    stamp[c] = -round;
-                    any3[r3] = 1;
-                }
-                lds_barrier();
-                const int w = contend ? win[par * kp + c] : -1;
-                seen = any3[r3];
-                if (contend && w == tid) {
-                    rsub[tid] = (uint16_t)c;
-                    rslot[tid] = (uint16_t)1;
-                    walking = false;
-                    win[par * kp + c] = 0x7FFFFFFF;   // next written two rounds from here, a barrier in between
-                }
-                par ^= 1;
-                r3 = r3 == 2 ? 0 : r3 + 1;
-            } else {
-                if (contend) {   // first step of the passes
+                int seen = 0;   // did any row contend in this round? (the same answer for every thread)
+                if (contend) {  // first step of the passes
                     atomicMin(&win[par * kp + c], tid);
                     any[rpar] = 1;
                 }
                 if (join_passes(contend, c, tid, rho, kp, win, fill, rsub, rslot, &rows_left, more, par, true, &any[rpar], &seen)) walking = false;
                 rpar ^= 1;
+                if (!seen) break;
             }
-            if (!seen) break;
-        }
-        __syncthreads();
-        if (two) {   // the sub-buckets closed in the rounds are full
-            for (int k = tid; k < M; k += PT)
-                if (stamp[k] != (int)0x80000000 && stamp[k] <= 0) fill[k] = 2;
+            __syncthreads();
         }
         if (left && rsub[lpos] != 0xFFFF) {
             sub = rsub[lpos];
