@@ -1,45 +1,45 @@
 // PSH bucketing, small scans: ONE workgroup per scan with every point of the scan in registers.
 //
 // Same schedule and same results as the other paths (lock step, contenders served by input index). A scan of at most
-// 4096 points (four per thread) fits a workgroup of 1024 threads with its points' packed voxels in registers for all steps, so a step is
-// a hash, a rank and an accept without a read or write of global memory and without a launch boundary; the one
-// read of the coordinates also gives the bounding box, and with a single scan the tables and bucket offsets are written
-// here too, so that the whole bucketing is one launch.
+// 8192 points (up to eight per thread) fits a workgroup of 1024 threads with its points in registers for all steps, so a
+// step needs no read or write of global memory but the placements and no launch boundary; the one read of the coordinates also
+// gives the bounding box, and with a single scan the tables and bucket offsets are written here too, so that the whole
+// bucketing is one launch.
 //
-// A wave owns up to 64*PPT consecutive points and visits them in index order, 64 at a time: rank inside the 64 from
-// ballots over the key bits, contenders before them in the wave from per-wave LDS counters (packed two per word),
-// contenders in earlier waves from a prefix over the waves per bucket. The counters and the fill levels are
-// double-buffered, the idle copy is cleared between two barriers of a step. When fewer groups of 64 would hold what a step
-// leaves, the points left are closed up through LDS in index order, so later steps visit only what is left.
+// A wave owns up to 64*PPT consecutive points. A step counts the wave's contenders per bucket, joins the waves (prefix per
+// bucket) and then ranks and accepts in index order (psh_block.h). After the direct step the probes of all points left are
+// looked up at once in the room the buckets have then, as in psh_scan.hip: a point that finds none waits for the recycle step,
+// the others carry their six bucket numbers (ten bits each) and are closed up inside the wave, so that the probe steps visit
+// nothing else.
 //
-// Bound: instruction issue and the chain of hash, ballots, LDS atomics and three barriers per step on ONE compute unit
-// (about 300 instructions per visit of 64 points), not memory. That is also where the line to the other paths
-// lies: at 4096 points a scan takes 33-43 us here (buckets of 256 and 32 rows) against 77-82 us with one launch per step
-// and 49-55 us in psh_scan.hip, 1500 points 26-29 against 70-75 and 40-42, 600 scans of 4096 points 106-136 against
-// 295-323 and 141-160. The crossing with one launch per step lies beyond: with eight points per thread and most of them left to
-// the recycle step, where nothing is closed up, 8192 points took 82-96 us against 80-84. The sizes between are not
-// served here.
+// Bound: instruction issue and two barriers per step on ONE compute unit, not memory: about 7 ns per point of a sensor sweep, 4 of
+// a cube. That is where the line to the other paths lies. One scan, us here against the launch-per-step path: 1500 points 23
+// (70-75), 4096 31-32 (77-82), 6000 45-79 (76-84), 8192 47-71 (78-84); 16 384 points took 159-198 against 87-109 and are not
+// served. Batches above 4096 points that the one-workgroup-per-scan path takes stay there (100 scans of 8000: 55 against 62,
+// 600 of them 140 against 178). Walking every point left in every step, 4096 points took 42-52, 600 scans of 4000 115 (96 now).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include "psh_common.h"
+#include "psh_block.h"
 
 namespace f3d {
 
 namespace {
 
-constexpr int MTH = 1024;          // threads per workgroup
-constexpr int MNW = MTH / 64;      // waves
-constexpr int PPT = 4;             // points per thread at most
+constexpr int MKMAX = 1024;        // most buckets per scan on this path (ten bits; one thread per bucket in the recycle step)
 
-// dynamic LDS, in 32-bit words: fill[2][K] wh[2][MNW][kw] list[3][MTH * PPT], with kw = (K + 1) / 2
-__global__ __launch_bounds__(MTH) void k_pshs_small(PshArgs a)
+// dynamic LDS, in 32-bit words: cnt[SNW][K] room[2][K] placed[PPT * STH / 32] list[PPT * STH]
+template <int PPT>
+__global__ __launch_bounds__(STH) void k_pshs_small(PshArgs a)
 {
+    constexpr int U = PPT < 4 ? PPT : 4;              // groups of 64 ranked together
     extern __shared__ int smem[];
     __shared__ ScanCfg cfg;
+    __shared__ ZProbe zps[NPROBE];
     __shared__ uint32_t red[8];
     __shared__ int s_round[8];
-    __shared__ int s_left[2][MNW];
+    __shared__ int s_left[SNW];
+    __shared__ int s_full, s_live;
     __shared__ int lds17[17];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -62,7 +62,7 @@ __global__ __launch_bounds__(MTH) void k_pshs_small(PshArgs a)
             if (tid < 8) a.round_count[tid] = 0;
             return;
         }
-        for (int j = tid; j <= a.max_buckets; j += MTH) a.offsets[j] = j < K ? j * a.S : a.n;
+        for (int j = tid; j <= a.max_buckets; j += STH) a.offsets[j] = j < K ? j * a.S : a.n;
     } else {
         if (a.status[0]) return;       // inconsistent batch offsets: flagged by the set-up kernel, nothing to do
         p0 = a.scan_p0[b];
@@ -70,36 +70,34 @@ __global__ __launch_bounds__(MTH) void k_pshs_small(PshArgs a)
         kb0 = a.sbs[b];
         K = a.sbs[b + 1] - kb0;
         if (nb <= 0 || K <= 0) return;
-        for (int j = tid; j < K; j += MTH) a.offsets[kb0 + j] = p0 + min(j * a.S, nb);
+        for (int j = tid; j < K; j += STH) a.offsets[kb0 + j] = p0 + min(j * a.S, nb);
     }
-    const int kw = (K + 1) >> 1;
-    int* fillb = smem;
-    uint32_t* whb = reinterpret_cast<uint32_t*>(smem + 2 * K);
-    uint32_t* list = whb + 2 * MNW * kw;              // index, voxel low, voxel high
+    uint32_t* cnt = reinterpret_cast<uint32_t*>(smem);
+    uint32_t* mine = cnt + wave * K;
+    int* roomb[2] = {smem + SNW * K, smem + (SNW + 1) * K};
+    uint32_t* placed = reinterpret_cast<uint32_t*>(smem + (SNW + 2) * K);
+    uint32_t* list = placed + PPT * STH / 32 + wave * (64 * PPT);   // the wave's own stretch
 
     // ---- the points, the bounding box. A wave owns 64*grp consecutive ones.
-    int grp = (nb + MTH - 1) / MTH;
+    const int grp = (nb + STH - 1) / STH;
     const int i0 = wave * (64 * grp) + lane;          // this lane's points: i0, i0 + 64, ..
-    float cx[PPT], cy[PPT], cz[PPT];
+    Point3 c[PPT];
 #pragma unroll
-    for (int s = 0; s < PPT; ++s) {
-        const float* c = a.coords + (size_t)(p0 + min(i0 + 64 * s, nb - 1)) * 3;   // past the end: the last point again
-        cx[s] = c[0];
-        cy[s] = c[1];
-        cz[s] = c[2];
-    }
+    for (int s = 0; s < PPT; ++s)                     // past the end: the last point again
+        c[s] = reinterpret_cast<const Point3*>(a.coords)[(uint32_t)(p0 + min(i0 + 64 * (s < grp ? s : 0), nb - 1))];
     if (tid < 8) {
         red[tid] = tid < 4 ? 0xFFFFFFFFu : 0u;
         s_round[tid] = 0;
     }
-    for (int k = tid; k < K; k += MTH) fillb[k] = 0;
-    for (int w = tid; w < MNW * kw; w += MTH) whb[w] = 0u;
+    if (tid == 0) s_live = 0;
+    for (int w = tid; w < SNW * K; w += STH) cnt[w] = 0u;
+    for (int w = tid; w < PPT * STH / 32; w += STH) placed[w] = 0u;
     __syncthreads();
     {
         uint32_t mn[3] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu}, mx[3] = {0u, 0u, 0u};
 #pragma unroll
         for (int s = 0; s < PPT; ++s) {
-            const uint32_t o[3] = {f2ord(cx[s]), f2ord(cy[s]), f2ord(cz[s])};
+            const uint32_t o[3] = {f2ord(c[s].x), f2ord(c[s].y), f2ord(c[s].z)};
 #pragma unroll
             for (int t = 0; t < 3; ++t) {
                 mn[t] = min(mn[t], o[t]);
@@ -121,170 +119,250 @@ __global__ __launch_bounds__(MTH) void k_pshs_small(PshArgs a)
     __syncthreads();
     if (tid == 0) compute_cfg_of(a, p0, nb, kb0, K, red, cfg);
     __syncthreads();
-
-    int idx[PPT];                                     // index inside the scan
-    uint32_t vlo[PPT], vhi[PPT];                      // packed voxel: x | y << 21 | z << 42
-    uint32_t left = 0;                                // bit s: point s is not placed yet
-#pragma unroll
-    for (int s = 0; s < PPT; ++s) {
-        const unsigned long long v = (unsigned long long)(uint32_t)voxel_of(cx[s], cfg.mn[0], a.inv_voxel) |
-                                     ((unsigned long long)(uint32_t)voxel_of(cy[s], cfg.mn[1], a.inv_voxel) << 21) |
-                                     ((unsigned long long)(uint32_t)voxel_of(cz[s], cfg.mn[2], a.inv_voxel) << 42);
-        vlo[s] = (uint32_t)v;
-        vhi[s] = (uint32_t)(v >> 32);
-        idx[s] = i0 + 64 * s;
-        if (s < grp && idx[s] < nb) left |= 1u << s;
-    }
+    for (int k = tid; k < K; k += STH) roomb[0][k] = k == K - 1 ? cfg.lastcap : a.S;
+    if (tid < NPROBE) zps[tid] = zprobe_of(cfg, tid + 1);
 
     const int keybits = max(1, 32 - __clz(max(K - 1, 1)));
-    int cur = 0, rest = nb;                           // rest: points not placed yet
-    for (int r = 0; r <= a.n_probes; ++r) {
-        uint32_t* wh = whb + cur * MNW * kw;
-        uint32_t* mine = wh + wave * kw;
-        int hk[PPT];                                  // bucket | rank among the wave's contenders << 16
+    // The voxel is kept as its Z-order code where the hash and the probes work on that, else packed.
+    const bool zc = a.hash == 3 && a.probe_mode == 0;
+    const bool narrow = zc && max(max(cfg.vmax[0], cfg.vmax[1]), cfg.vmax[2]) < 1024;   // the code fits 30 bits
+    unsigned long long vox[PPT];                      // behind the direct step: the bucket numbers of the probes
+    int hh[PPT];
+    uint32_t left = 0;                                // bit s: point s is not placed by the direct step
+    // ---- direct step
 #pragma unroll
-        for (int s = 0; s < PPT; ++s) {
-            const bool act = (left >> s) & 1u;
-            hk[s] = 0;
-            if (__builtin_amdgcn_ballot_w64(act) == 0ull) continue;
-            const unsigned long long v = (unsigned long long)vlo[s] | ((unsigned long long)vhi[s] << 32);
-            int x = (int)(v & 0x1FFFFFull), y = (int)((v >> 21) & 0x1FFFFFull), z = (int)(v >> 42);
-            if (r > 0) probe_voxel(a, r, cfg, x, y, z);
-            const int h = hash_bucket(a.hash, x, y, z, cfg);
-            const unsigned long long m = match_key(h, act, keybits);
-            if (act) {
-                const int leader = __ffsll((long long)m) - 1;
-                int old = 0;
-                if (lane == leader) {
-                    const int sh = (h & 1) * 16;
-                    old = (int)((atomicAdd(&mine[h >> 1], (uint32_t)__popcll(m) << sh) >> sh) & 0xFFFFu);
-                }
-                old = __shfl(old, leader, 64) + bits_below(m);
-                hk[s] = h | (old << 16);
+    for (int s = 0; s < PPT; ++s) {
+        hh[s] = 0;
+        vox[s] = 0ull;
+        if (s >= grp) continue;                       // uniform
+        const int x = voxel_of(c[s].x, cfg.mn[0], a.inv_voxel), y = voxel_of(c[s].y, cfg.mn[1], a.inv_voxel),
+                  z = voxel_of(c[s].z, cfg.mn[2], a.inv_voxel);
+        if (narrow) {
+            vox[s] = (uint32_t)morton3_low(x, y, z);
+            hh[s] = zdiv30((uint32_t)vox[s], cfg);
+        } else if (zc) {
+            vox[s] = cfg.wide ? morton3(x, y, z) : morton3_low(x, y, z);
+            hh[s] = hash_code(3, vox[s], cfg);
+        } else {
+            vox[s] = pack_voxel(x, y, z);
+            hh[s] = hash_bucket(a.hash, x, y, z, cfg);
+        }
+        if (i0 + 64 * s < nb) atomicAdd(&mine[hh[s]], 1u);
+    }
+    __syncthreads();
+    join_waves<true>(tid, K, cnt, roomb[0], roomb[1]);
+    __syncthreads();
+#pragma unroll
+    for (int s0 = 0; s0 < PPT; s0 += U) {
+        if (s0 >= grp) continue;
+        int h[U], rank[U];
+        bool act[U];
+#pragma unroll
+        for (int s = 0; s < U; ++s) {
+            h[s] = hh[s0 + s];
+            act[s] = s0 + s < grp && i0 + 64 * (s0 + s) < nb;
+        }
+        wave_ranks<U>(h, act, keybits, mine, rank);
+#pragma unroll
+        for (int s = 0; s < U; ++s) {
+            const bool fits = rank[s] < (h[s] == K - 1 ? cfg.lastcap : a.S);
+            if (act[s] && fits) {
+                const int i = p0 + i0 + 64 * (s0 + s), dst = p0 + h[s] * a.S + rank[s];
+                a.inv_perm[(uint32_t)i] = dst;
+                a.perm[(uint32_t)dst] = i;
             }
+            left |= act[s] && !fits ? 1u << (s0 + s) : 0u;
         }
-        __syncthreads();
-        // ---- contenders in earlier waves (in place), fill levels after this step; the other counters are cleared
-        const int* fill = fillb + cur * K;
-        int* fill_next = fillb + (cur ^ 1) * K;
-        uint32_t* wh_next = whb + (cur ^ 1) * MNW * kw;
-        for (int w = tid; w < kw; w += MTH) {
-            uint32_t run = 0;
+    }
+    for (int k = lane; k < K; k += 64) mine[k] = 0u;
+    int n_left = 0;                                   // points of this wave that are not placed
 #pragma unroll
-            for (int v = 0; v < MNW; ++v) {
-                const uint32_t t = wh[v * kw + w];
-                wh[v * kw + w] = run;
-                wh_next[v * kw + w] = 0u;
-                run += t;                             // halves cannot carry into each other: at most 4096 points
-            }
-            const int k0 = 2 * w, k1 = 2 * w + 1;
-            fill_next[k0] = min(fill[k0] + (int)(run & 0xFFFFu), k0 == K - 1 ? cfg.lastcap : a.S);
-            if (k1 < K) fill_next[k1] = min(fill[k1] + (int)(run >> 16), k1 == K - 1 ? cfg.lastcap : a.S);
-        }
-        __syncthreads();
-        // ---- accept while the bucket has room
-        int placed = 0;
+    for (int s = 0; s < PPT; ++s) n_left += __popcll(__builtin_amdgcn_ballot_w64((left >> s) & 1u));
+    if (lane == 0) s_left[wave] = n_left;
+    if (tid < K && roomb[1][tid] == 0) s_full = tid;  // some full bucket (there is one if a point is left); any will do
+    __syncthreads();
+    int rest = 0;                                     // points not placed
 #pragma unroll
-        for (int s = 0; s < PPT; ++s) {
-            const bool act = (left >> s) & 1u;
-            if (__builtin_amdgcn_ballot_w64(act) == 0ull) continue;
-            bool ok = false;
-            if (act) {
-                const int h = hk[s] & 0xFFFF;
-                const int rank = (int)((mine[h >> 1] >> ((h & 1) * 16)) & 0xFFFFu) + (hk[s] >> 16);
-                const int f = fill[h];
-                if (rank < (h == K - 1 ? cfg.lastcap : a.S) - f) {
-                    const int i = p0 + idx[s], dst = p0 + h * a.S + f + rank;
-                    a.inv_perm[i] = dst;
-                    a.perm[dst] = i;
-                    left &= ~(1u << s);
-                    ok = true;
-                }
-            }
-            placed += __popcll(__builtin_amdgcn_ballot_w64(ok));
-        }
-        int n_left = 0;
-#pragma unroll
-        for (int s = 0; s < PPT; ++s) n_left += __popcll(__builtin_amdgcn_ballot_w64((left >> s) & 1u));
-        if (lane == 0) {
-            s_left[r & 1][wave] = n_left;
-            if (placed) atomicAdd(&s_round[r], placed);
-        }
-        cur ^= 1;
-        __syncthreads();
-        int before = 0;
-        rest = 0;
-#pragma unroll
-        for (int w = 0; w < MNW; ++w) {
-            const int c = s_left[r & 1][w];
-            before += w < wave ? c : 0;
-            rest += c;
-        }
-        if (rest == 0) break;                         // uniform
-        if ((rest + MTH - 1) / MTH < grp) {           // fewer groups of 64 hold what is left: close the gaps, in index order
-            grp = (rest + MTH - 1) / MTH;
+    for (int w = 0; w < SNW; ++w) rest += s_left[w];
+    rest = __builtin_amdgcn_readfirstlane(rest);
+    if (tid == 0) s_round[0] = nb - rest;
+    int cur = 1;                                      // roomb[cur]: the room the buckets have now
+
+    if (rest > 0 && a.n_probes > 0) {
+        // ---- all probes of the points left, against the room after the direct step; closed up inside the wave
+        const int full = s_full;
+        int idx[PPT];                                 // index inside the scan
+        int nlive = 0;
+        uint32_t live = 0;
+        {
+            const int* room = roomb[cur];
 #pragma unroll
             for (int s = 0; s < PPT; ++s) {
                 const bool act = (left >> s) & 1u;
-                const unsigned long long m = __builtin_amdgcn_ballot_w64(act);
-                if (act) {
-                    const int e = before + bits_below(m);
-                    list[e] = (uint32_t)idx[s];
-                    list[MTH * PPT + e] = vlo[s];
-                    list[2 * MTH * PPT + e] = vhi[s];
+                if (__builtin_amdgcn_ballot_w64(act) == 0ull) continue;
+                const unsigned long long v = vox[s];
+                unsigned long long hs = 0ull;
+                bool any = false;
+#pragma unroll
+                for (int r = 1; r <= NPROBE; ++r) {
+                    if (r > a.n_probes) break;
+                    int h;
+                    if (narrow) {
+                        const ZProbe& z = zps[r - 1];
+                        h = zdiv30(zprobe30((uint32_t)v, (uint32_t)z.mask, (uint32_t)z.step, (uint32_t)z.lim, (uint32_t)z.vmax, (r - 1) & 1), cfg);
+                    } else if (zc) {
+                        h = hash_code(3, zprobe(v, zps[r - 1]), cfg);
+                    } else {
+                        int x = (int)(v & 0x1FFFFFull), y = (int)((v >> 21) & 0x1FFFFFull), z = (int)(v >> 42);
+                        probe_voxel(a, r, cfg, x, y, z);
+                        h = hash_bucket(a.hash, x, y, z, cfg);
+                    }
+                    const bool open = room[h] > 0;
+                    any |= open;
+                    hs |= (unsigned long long)(unsigned int)(open ? h : full) << (10 * (r - 1));
                 }
-                before += __popcll(m);
+                vox[s] = hs;
+                live |= any && act ? 1u << s : 0u;
+                nlive += __popcll(__builtin_amdgcn_ballot_w64(any && act));
             }
-            __syncthreads();
-            left = 0;
+        }
+        if (lane == 0 && nlive) atomicAdd(&s_live, nlive);
+        // one word of every entry at a time through the wave's stretch of LDS, in index order
+        auto close_up = [&](auto get, auto put) __attribute__((always_inline)) {
+            int at = 0;
 #pragma unroll
             for (int s = 0; s < PPT; ++s) {
-                const int e = wave * (64 * grp) + 64 * s + lane;
-                if (s < grp && e < rest) {
-                    left |= 1u << s;
-                    idx[s] = (int)list[e];
-                    vlo[s] = list[MTH * PPT + e];
-                    vhi[s] = list[2 * MTH * PPT + e];
+                const bool on = (live >> s) & 1u;
+                const unsigned long long m = __builtin_amdgcn_ballot_w64(on);
+                if (on) list[at + bits_below(m)] = get(s);
+                at += __popcll(m);
+            }
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int s = 0; s < PPT; ++s)
+                if (64 * s < nlive) put(s, list[min(64 * s + lane, nlive - 1)]);
+            __builtin_amdgcn_wave_barrier();
+        };
+        if (nlive) {
+            uint32_t lo[PPT];
+#pragma unroll
+            for (int s = 0; s < PPT; ++s) idx[s] = 0;
+            close_up([&](int s) { return (uint32_t)(i0 + 64 * s); }, [&](int s, uint32_t v) { idx[s] = (int)v; });
+#pragma unroll
+            for (int s = 0; s < PPT; ++s) lo[s] = 0u;
+            close_up([&](int s) { return (uint32_t)vox[s]; }, [&](int s, uint32_t v) { lo[s] = v; });
+            close_up([&](int s) { return (uint32_t)(vox[s] >> 32); }, [&](int s, uint32_t v) { hh[s] = (int)v; });
+#pragma unroll
+            for (int s = 0; s < PPT; ++s) vox[s] = ((unsigned long long)(uint32_t)hh[s] << 32) | lo[s];
+        }
+        live = 0;
+#pragma unroll
+        for (int s = 0; s < PPT; ++s) live |= 64 * s + lane < nlive ? 1u << s : 0u;
+        __syncthreads();
+        // ---- the probe steps, on the survivors
+        if (s_live > 0) {
+            for (int r = 1; r <= a.n_probes; ++r) {
+                const int sh = 10 * (r - 1);
+                const int* room = roomb[cur];
+#pragma unroll
+                for (int s = 0; s < PPT; ++s) {
+                    if (64 * s >= nlive) continue;    // uniform in the wave
+                    const int h = (int)(vox[s] >> sh) & 1023;
+                    if (((live >> s) & 1u) && room[h] > 0) atomicAdd(&mine[h], 1u);
                 }
+                __syncthreads();
+                join_waves<true>(tid, K, cnt, room, roomb[cur ^ 1]);
+                __syncthreads();
+                int got = 0;
+#pragma unroll
+                for (int s = 0; s < PPT; ++s) {
+                    if (64 * s >= nlive) continue;
+                    const int h[1] = {(int)(vox[s] >> sh) & 1023};
+                    const bool on = (live >> s) & 1u;
+                    const int f = room[on ? h[0] : 0];
+                    const bool act[1] = {on && f > 0};
+                    if (__builtin_amdgcn_ballot_w64(act[0]) == 0ull) continue;
+                    int rank[1];
+                    wave_ranks<1>(h, act, keybits, mine, rank);
+                    const bool ok = act[0] && rank[0] < f;
+                    if (ok) {
+                        const int i = p0 + idx[s], dst = p0 + h[0] * a.S + (h[0] == K - 1 ? cfg.lastcap : a.S) - f + rank[0];
+                        a.inv_perm[(uint32_t)i] = dst;
+                        a.perm[(uint32_t)dst] = i;
+                        atomicOr(&placed[idx[s] >> 5], 1u << (idx[s] & 31));
+                        live &= ~(1u << s);
+                    }
+                    got += __popcll(__builtin_amdgcn_ballot_w64(ok));
+                }
+                for (int k = lane; k < K; k += 64) mine[k] = 0u;
+                if (lane == 0 && got) atomicAdd(&s_round[r], got);
+                cur ^= 1;
             }
         }
     }
 
     // ---- recycle: the j-th point left (by index) takes the j-th free slot (buckets ascending, slots ascending)
     if (rest > 0) {
-        int n_left = 0;
+        __syncthreads();                              // the marks are in place, the counters are free
+        n_left = 0;
 #pragma unroll
-        for (int s = 0; s < PPT; ++s) n_left += __popcll(__builtin_amdgcn_ballot_w64((left >> s) & 1u));
-        if (lane == 0) s_left[(a.n_probes + 1) & 1][wave] = n_left;
-        const int* fill = fillb + cur * K;
-        int* freepre = fillb + (cur ^ 1) * K;         // last read before the barrier at the end of the last step
-        const int own = tid < K ? ((tid == K - 1) ? cfg.lastcap : a.S) - fill[tid] : 0;   // K <= 1024
-        int tot;
+        for (int s = 0; s < PPT; ++s) {
+            const int i = i0 + 64 * s;
+            if ((left >> s) & 1u) left &= ~(((placed[i >> 5] >> (i & 31)) & 1u) << s);
+            n_left += __popcll(__builtin_amdgcn_ballot_w64((left >> s) & 1u));
+        }
+        if (lane == 0) s_left[wave] = n_left;
+        // buckets with room, in order: slots before, bucket
+        int* slots_before = smem;                     // [K + 1]
+        int* bucket_of = smem + (K + 1);              // [K]
+        const int* room = roomb[cur];
+        const int own = tid < K ? room[tid] : 0;      // K <= 1024
+        int tot, open;
         const int pre = block_excl_scan(own, &tot, lds17);
-        if (tid < K) freepre[tid] = pre;
+        const int opre = block_excl_scan(own > 0 ? 1 : 0, &open, lds17);
+        if (own > 0) {
+            slots_before[opre] = pre;
+            bucket_of[opre] = tid;
+        }
+        if (tid == 0) slots_before[open] = tot;
         __syncthreads();
-        int at = 0;
-        for (int w = 0; w < wave; ++w) at += s_left[(a.n_probes + 1) & 1][w];
+        int j0 = 0, all = 0;                          // points left in earlier waves, in all
+#pragma unroll
+        for (int w = 0; w < SNW; ++w) {
+            const int n = s_left[w];
+            j0 += w < wave ? n : 0;
+            all += n;
+        }
+        j0 = __builtin_amdgcn_readfirstlane(j0);
+        int o = 0;                                    // last bucket whose slots begin at or before j0
+        {
+            int hi = open;
+            while (hi - o > 1) {
+                const int mid = (o + hi) >> 1;
+                if (__builtin_amdgcn_readfirstlane(slots_before[mid]) <= j0) o = mid; else hi = mid;
+            }
+        }
 #pragma unroll
         for (int s = 0; s < PPT; ++s) {
             const bool act = (left >> s) & 1u;
             const unsigned long long m = __builtin_amdgcn_ballot_w64(act);
+            if (m == 0ull) continue;
             if (act) {
-                const int j = at + bits_below(m);
-                int lo = 0, hi = K;                   // largest k with freepre[k] <= j
-                while (hi - lo > 1) {
-                    const int mid = (lo + hi) >> 1;
-                    if (freepre[mid] <= j) lo = mid; else hi = mid;
-                }
-                const int dst = p0 + lo * a.S + fill[lo] + (j - freepre[lo]);
-                if (dst < p0 + nb) {                  // always, while capacities add up to the scan size
-                    a.inv_perm[p0 + idx[s]] = dst;
-                    a.perm[dst] = p0 + idx[s];
+                const int j = j0 + bits_below(m);
+                int q = o;
+                while (q + 1 < open && slots_before[q + 1] <= j) ++q;
+                const int k = bucket_of[q];
+                const int dst = k * a.S + (k == K - 1 ? cfg.lastcap : a.S) - room[k] + (j - slots_before[q]);
+                if ((uint32_t)dst < (uint32_t)nb) {   // always, while capacities add up to the scan size
+                    const int i = p0 + i0 + 64 * s;
+                    a.inv_perm[(uint32_t)i] = p0 + dst;
+                    a.perm[(uint32_t)(p0 + dst)] = i;
                 }
             }
-            at += __popcll(m);
+            j0 += __popcll(m);
+            while (o + 1 < open && __builtin_amdgcn_readfirstlane(slots_before[o + 1]) <= j0) ++o;
         }
-        if (tid == 0) s_round[a.n_probes + 1] = rest;
+        if (tid == 0) s_round[a.n_probes + 1] = all;
     }
     __syncthreads();
     if (tid < 8) {
@@ -293,27 +371,34 @@ __global__ __launch_bounds__(MTH) void k_pshs_small(PshArgs a)
     }
 }
 
+template <int PPT>
+hipError_t launch_small(const PshArgs& a, hipStream_t stream)
+{
+    const size_t lds = ((size_t)(SNW + 2) * a.kcap + (size_t)PPT * STH / 32 + (size_t)PPT * STH) * 4;
+    const hipError_t e = hipFuncSetAttribute((const void*)k_pshs_small<PPT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    k_pshs_small<PPT><<<a.n_scans, STH, lds, stream>>>(a);
+    return hipGetLastError();
+}
+
 }  // namespace
 
-bool psh_small_eligible(long long n, long long max_scan_points, int kcap)
+bool psh_small_eligible(long long n, long long max_scan_points, int kcap, bool scans)
 {
-    return n > 0 && max_scan_points <= MTH * PPT && kcap <= MTH;
+    return n > 0 && max_scan_points <= (scans ? 4 : 8) * STH && kcap <= MKMAX;
 }
 
 hipError_t psh_small_launch(const PshArgs& args, hipStream_t stream)
 {
     PshArgs a = args;
     if (a.n_scans > 1) {
-        a.chunk = MTH * PPT;
+        a.chunk = 8 * STH;
         a.chunk_info = nullptr;
         a.meta_light = 1;   // the scan's own workgroup writes its bucket offsets
         k_psh_meta<<<1, 1024, 0, stream>>>(a);
     }
-    const size_t lds = ((size_t)2 * a.kcap + (size_t)2 * MNW * ((a.kcap + 1) / 2) + (size_t)3 * MTH * PPT) * 4;
-    const hipError_t e = hipFuncSetAttribute((const void*)k_pshs_small, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    k_pshs_small<<<a.n_scans, MTH, lds, stream>>>(a);
-    return hipGetLastError();
+    if (a.max_scan_points <= 4 * STH) return launch_small<4>(a, stream);
+    return launch_small<8>(a, stream);
 }
 
 }  // namespace f3d

@@ -166,6 +166,20 @@ def test_bucketize_scan_path_axis_probes_with_wide_voxels(hash):
 
 
 @pytest.mark.parametrize("hash", HASHES)
+def test_bucketize_small_scans_eight_points_per_thread(hash):
+    # more than four points per thread: around the last of them and one past it (another path), few and many survivors, most
+    # buckets the path takes, every number of probes, a batch whose scans end inside and at the end of a wave's run
+    rng = np.random.default_rng(36)
+    for n in (4097, 5000, 8191, 8192, 8193):
+        check_bucketize(clustered_cloud(rng, n), None, 0.05, 64 if n <= 8192 else 128, 4, hash, n_probes=(n % 7))
+        check_bucketize((rng.random((n, 3)) * 4.0).astype(np.float32), None, 0.0005, 256, 4, hash, probe_mode="seeded", probe_seed=3)
+    check_bucketize((rng.random((8192, 3)) * 4.0).astype(np.float32), None, 0.05, 32, 2, hash)    # buckets of 16 rows, 512 of them
+    bo = np.array([0, 8192, 8192, 8193, 12289, 20000, 25121], dtype=np.int32)
+    c = np.concatenate([clustered_cloud(rng, int(k), float(i)) for i, k in enumerate(np.diff(bo)) if k])
+    check_bucketize(c, bo, 0.05, 128, 4, hash, max_scan_points=8192)
+
+
+@pytest.mark.parametrize("hash", HASHES)
 def test_bucketize_scan_path_block_edges_in_unequal_scans(hash):
     # the walk of a scan in blocks (8192 points, 4096 with more scans than compute units), its lists beside those of the other
     # scans: sizes around a block, most points left over or hardly any, codes of up to and of more than 30 bits
