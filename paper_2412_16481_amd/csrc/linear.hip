@@ -18,7 +18,11 @@
 // Bound: HBM, mostly the writes. The workgroups of an XCD keep more output rows open (6 MB at 256 channels) than its L2
 // holds, so a line that is written in two halves a tile apart leaves L2 half full: pairs of 32-column blocks are stored
 // together, whole lines per instruction (914601 rows, 256 -> 3 x 256: WRITE_SIZE 1.60 -> 1.37 GB = what there is to write).
-// Measured at 900000 rows, LayerNorm + q, k, v map / output map with residual: 256 channels 636 -> 530 / 292 -> 242 us, 128
+// The stores are non-temporal: nothing here reads a result again, and kept in L2 the lines only push out x, W and the residual
+// (both maps of a layer, us: 100000 rows of 128 channels 53.5 -> 41.0, 400000 of 64 77.5 -> 62.5, 200000 of 256 214 -> 194, 914601 of
+// 256 847 -> 820; with an attention pass between them, which reads the results, 0 to 7 % less in all). Loads of x or the
+// residual marked the same way cost 14 and 8 % more: both are read 16 bytes of a line at a time.
+// Measured at 900000 rows with ordinary stores, LayerNorm + q, k, v map / output map with residual: 256 channels 636 -> 530 / 292 -> 242 us, 128
 // 253 -> 213 / 133 -> 111, 64 128 -> 89 / 46 -> 43. A third resident tile and 256 rows per workgroup were no faster.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -264,7 +268,8 @@ __global__ __launch_bounds__(LTH, 3) void k_ln_linear(LinearArgs a)
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     const uint4 y = sy[wave][yget + 64 * k];
-                    if (yrow[k] >= 0) *reinterpret_cast<uint4*>(ob + (size_t)yrow[k] * per_out) = y;
+                    const u32x4 yv = {y.x, y.y, y.z, y.w};
+                    if (yrow[k] >= 0) __builtin_nontemporal_store(yv, reinterpret_cast<u32x4*>(ob + (size_t)yrow[k] * per_out));
                 }
             }
         }
