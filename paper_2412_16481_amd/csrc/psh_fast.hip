@@ -24,7 +24,6 @@ constexpr int FTH = 512;     // threads per workgroup
 constexpr int FW = FTH / 64; // waves
 constexpr int FPPT = FCH / FTH;
 constexpr int FKMAX = 2048;           // most buckets per scan on this path
-constexpr int KPT = FKMAX / FTH;      // buckets per thread when a row is walked linearly
 constexpr long long FMATMAX = 131072; // most (chunks of a scan) x (buckets of a scan)
 constexpr int CFGW = (int)(sizeof(ScanCfg) / 4);
 static_assert(sizeof(ScanCfg) <= 128 && sizeof(ScanCfg) % 4 == 0, "the workspace reserves 128 bytes per scan");
@@ -215,14 +214,19 @@ __global__ __launch_bounds__(FTH) void k_pshf_setup(PshArgs a)
 // dynamic LDS: tot[kcap] + pre[kcap] ints + NW x kwp words of packed 16-bit counters.
 // TH threads rank the 2048 points of a chunk: 512 (four points each, two workgroups per CU) when the grid is
 // larger than the GPU, 1024 (two points each: every phase of the step is half as long) when it is not.
-template <int TH>
+// LAST (r = n_probes + 1) settles the last probe and recycles in the same launch: the r-th leftover of a scan takes the r-th
+// free slot (buckets ascending, slots ascending). The count rows that settle a step also say how many of the earlier
+// chunks' contenders it turns away, so nobody has to count leftovers in a launch of their own (a pass over one room of 200000
+// points 333 -> 322 us, the canonical order of 457295 points 249 -> 239).
+template <int TH, bool LAST>
 __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32_t* __restrict__ mat_prev,
                                                    uint32_t* __restrict__ mat_cur)
 {
     constexpr int NW = TH / 64, PPT = FCH / TH, KPT_ = FKMAX / TH;
     extern __shared__ int smem[];
     __shared__ ScanCfg cfg;
-    __shared__ int placed_ct;
+    __shared__ int placed_ct, recycled_ct, left_before;
+    __shared__ int lds17[17];
     const int chunk = blockIdx.x;
     const ChunkInfo ci = load_chunk(a, chunk);
     if (ci.b < 0 || a.status[0]) return;
@@ -232,7 +236,6 @@ __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32
     int* tot = smem;                                // [kcap] contenders of step r-1 per bucket, all chunks
     int* pre = smem + a.kcap;                       // [kcap] ... of earlier chunks; then rebased fill level
     uint32_t* wh = (uint32_t*)(smem + 2 * a.kcap);  // [NW][kwp]
-    const bool last_step = (r == a.n_probes + 1);
 
     // ---- every global load of this kernel is issued here, before anything waits
     uint32_t box[8];
@@ -271,7 +274,7 @@ __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32
         cx[s] = cy[s] = cz[s] = 0.f;
         if (i < ci.end) {
             kwv[s] = r > 0 ? a.key[i] : 0u;
-            if (!last_step) {
+            if (!LAST) {
                 const float* c = a.coords + (size_t)i * 3;
                 cx[s] = c[0]; cy[s] = c[1]; cz[s] = c[2];
             }
@@ -318,7 +321,7 @@ __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32
     for (int w = tid; w < NW * kwp; w += TH) wh[w] = 0u;
     if (r > 0)
         for (int k = tid; k < 2 * a.kcap; k += TH) smem[k] = 0;
-    if (tid == 0) placed_ct = 0;
+    if (tid == 0) placed_ct = recycled_ct = left_before = 0;
     if (r == 0) {
         if (tid == 0) {
             compute_cfg(a, ci.b, box, cfg);   // a hundred-odd instructions on one lane
@@ -347,14 +350,99 @@ __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32
             const int k = tid + j * TH;
             if (k < K) {
                 const int base = cntv[j];
-                if (lc == 0) a.cnt_next[kb0 + k] = min(base + tot[k], k == K - 1 ? cfg.lastcap : a.S);
-                pre[k] += base;
+                if (!LAST && lc == 0) a.cnt_next[kb0 + k] = min(base + tot[k], k == K - 1 ? cfg.lastcap : a.S);
+                if (!LAST) pre[k] += base;
             }
         }
         __syncthreads();
     }
 
-    const int keybits = last_step ? 0 : max(1, 32 - __clz(max(K - 1, 1)));
+    if constexpr (LAST) {
+        // per bucket: the fill level when the probes are through, the free slots before it in the scan; and the contenders of
+        // earlier chunks that found no room
+        int* const fill = reinterpret_cast<int*>(wh);
+        int* const freepre = tot;
+        int carry = 0, turned = 0;
+#pragma unroll
+        for (int j = 0; j < KPT_; ++j) {
+            if (j * TH < K) {
+                const int k = tid + j * TH;
+                int v = 0;
+                if (k < K) {
+                    const int room = (k == K - 1 ? cfg.lastcap : a.S) - cntv[j];
+                    const int taken = min(tot[k], room);
+                    v = room - taken;
+                    fill[k] = cntv[j] + taken;
+                    turned += max(pre[k] - room, 0);
+                    pre[k] += cntv[j];
+                }
+                int t2;
+                const int before = block_excl_scan(v, &t2, lds17);
+                if (k < K) freepre[k] = carry + before;
+                carry += t2;
+            }
+        }
+        for (int d = 32; d >= 1; d >>= 1) turned += __shfl_xor(turned, d, 64);
+        if (lane == 0 && turned) atomicAdd(&left_before, turned);
+        __syncthreads();
+        unsigned long long rest[PPT];
+        int nplaced = 0, nrest = 0;
+#pragma unroll
+        for (int s = 0; s < PPT; ++s) {
+            const int i = ci.begin + wave * (FCH / NW) + s * 64 + lane;
+            bool left = i < ci.end && kwv[s] != KEY_PLACED;
+            if (left) {
+                const int hp = (int)(kwv[s] >> LR_BITS);
+                const int rank = pre[hp] + (int)(kwv[s] & ((1u << LR_BITS) - 1));
+                if (rank < (hp == K - 1 ? cfg.lastcap : a.S)) {
+                    const int dst = cfg.p0 + hp * a.S + rank;
+                    a.inv_perm[i] = dst;
+                    a.perm[dst] = i;
+                    left = false;
+                    ++nplaced;
+                }
+            }
+            rest[s] = __builtin_amdgcn_ballot_w64(left);
+            nrest += __popcll(rest[s]);
+        }
+        if (lane == 0) lds17[wave] = nrest;
+        __syncthreads();
+        int at = left_before;
+        for (int v = 0; v < wave; ++v) at += lds17[v];
+        int nrec = 0;
+#pragma unroll
+        for (int s = 0; s < PPT; ++s) {
+            const int i = ci.begin + wave * (FCH / NW) + s * 64 + lane;
+            if ((rest[s] >> lane) & 1ull) {
+                const int rank = at + bits_below(rest[s]);
+                int lo = 0, hi = K;  // largest j with freepre[j] <= rank
+                while (hi - lo > 1) {
+                    const int mid = (lo + hi) >> 1;
+                    if (freepre[mid] <= rank) lo = mid; else hi = mid;
+                }
+                const int off = lo * a.S + fill[lo] + (rank - freepre[lo]);
+                if (off >= 0 && off < cfg.nb) {   // always, while capacities add up to the scan size
+                    a.inv_perm[i] = cfg.p0 + off;
+                    a.perm[cfg.p0 + off] = i;
+                    ++nrec;
+                }
+            }
+            at += __popcll(rest[s]);
+        }
+        // one atomic per workgroup: hundreds of waves adding to the same counter queue up behind each other
+        for (int d = 32; d >= 1; d >>= 1) {
+            nplaced += __shfl_xor(nplaced, d, 64);
+            nrec += __shfl_xor(nrec, d, 64);
+        }
+        if (lane == 0 && nplaced) atomicAdd(&placed_ct, nplaced);
+        if (lane == 0 && nrec) atomicAdd(&recycled_ct, nrec);
+        __syncthreads();
+        if (tid == 0 && placed_ct) atomicAdd(&a.round_count[r - 1], placed_ct);
+        if (tid == 0 && recycled_ct) atomicAdd(&a.round_count[r], recycled_ct);
+        return;
+    }
+
+    const int keybits = max(1, 32 - __clz(max(K - 1, 1)));
     int hh[PPT], wl[PPT];
     bool act[PPT];
     int nplaced = 0;
@@ -382,7 +470,7 @@ __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32
                 }
             }
         }
-        if (active && !last_step) {
+        if (active) {
             int x = voxel_of(cx[s], cfg.mn[0], a.inv_voxel);
             int y = voxel_of(cy[s], cfg.mn[1], a.inv_voxel);
             int z = voxel_of(cz[s], cfg.mn[2], a.inv_voxel);
@@ -414,27 +502,17 @@ __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32
     }
     __syncthreads();
     // join the waves: exclusive prefix over the waves per bucket; the total is this chunk's row
-    if (!last_step) {
-        for (int w = tid; w < kwp; w += TH) {
-            uint32_t run = 0;
-            if (2 * w < K) {
-#pragma unroll
-                for (int v = 0; v < NW; ++v) {
-                    const uint32_t t = wh[v * kwp + w];
-                    wh[v * kwp + w] = run;
-                    run += t;  // halves cannot carry into each other: a chunk has 2048 points
-                }
-            }
-            mat_cur[(size_t)chunk * kwp + w] = run;   // padding words of the row are written as zero
-        }
-    } else if (tid == 0) {
+    for (int w = tid; w < kwp; w += TH) {
         uint32_t run = 0;
-        for (int v = 0; v < NW; ++v) {
-            const uint32_t t = wh[v * kwp];
-            wh[v * kwp] = run;
-            run += t;
+        if (2 * w < K) {
+#pragma unroll
+            for (int v = 0; v < NW; ++v) {
+                const uint32_t t = wh[v * kwp + w];
+                wh[v * kwp + w] = run;
+                run += t;  // halves cannot carry into each other: a chunk has 2048 points
+            }
         }
-        a.left[chunk] = (int)(run & 0xFFFFu);
+        mat_cur[(size_t)chunk * kwp + w] = run;   // padding words of the row are written as zero
     }
     __syncthreads();
 #pragma unroll
@@ -452,87 +530,6 @@ __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32
         __syncthreads();
         if (tid == 0 && placed_ct) atomicAdd(&a.round_count[r - 1], placed_ct);
     }
-}
-
-// ------------------------------------------------------------------------------------------------
-// recycle: the r-th leftover of a scan takes the r-th free slot (buckets ascending, slots ascending)
-// dynamic LDS: freepre[kcap] + fill[kcap] ints
-__global__ __launch_bounds__(FTH) void k_pshf_recycle(PshArgs a)
-{
-    extern __shared__ int smem[];
-    __shared__ int lds[17];
-    __shared__ int s_base;
-    const int chunk = blockIdx.x;
-    const ChunkInfo ci = load_chunk(a, chunk);
-    if (ci.b < 0 || a.status[0]) return;
-    const int tid = threadIdx.x;
-    const int K = ci.K, kb0 = ci.kb0, lc = ci.lc;
-    int* freepre = smem;
-    int* fill = smem + a.kcap;
-    // ---- all loads first
-    const int my_left = a.left[chunk];
-    int mine = 0;
-    for (int c = tid; c < lc; c += FTH) mine += a.left[ci.c0 + c];
-    int cntv[KPT];
-#pragma unroll
-    for (int j = 0; j < KPT; ++j) cntv[j] = (tid + j * FTH < K) ? a.cnt[kb0 + tid + j * FTH] : 0;
-    uint32_t kv[FPPT];
-#pragma unroll
-    for (int s = 0; s < FPPT; ++s) {
-        const int i = ci.begin + tid + s * FTH;
-        kv[s] = i < ci.end ? a.key[i] : KEY_PLACED;
-    }
-    const int p0 = ci.begin - lc * FCH;
-    const int nb = a.scan_p0[ci.b + 1] - p0;
-    if (my_left == 0) return;   // uniform: nothing of this chunk is left over
-    // leftovers of earlier chunks
-    int tot;
-    block_excl_scan(mine, &tot, lds);
-    if (tid == 0) s_base = tot;
-    // free slots per bucket, exclusive prefix
-    int carry = 0;
-#pragma unroll
-    for (int j = 0; j < KPT; ++j) {
-        if (j * FTH < K) {
-            const int k = tid + j * FTH;
-            int v = 0;
-            if (k < K) {
-                v = ((k == K - 1) ? nb - (K - 1) * a.S : a.S) - cntv[j];
-                fill[k] = cntv[j];
-            }
-            int t2;
-            const int pre = block_excl_scan(v, &t2, lds);
-            if (k < K) freepre[k] = carry + pre;
-            carry += t2;
-        }
-    }
-    __syncthreads();
-    const int base = s_base;
-    int placed = 0;
-#pragma unroll
-    for (int s = 0; s < FPPT; ++s) {
-        const int i = ci.begin + tid + s * FTH;
-        if (kv[s] == KEY_PLACED) continue;
-        const int rank = base + (int)(kv[s] & ((1u << LR_BITS) - 1));
-        int lo = 0, hi = K;  // largest j with freepre[j] <= rank
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (freepre[mid] <= rank) lo = mid; else hi = mid;
-        }
-        const int dst = p0 + lo * a.S + fill[lo] + (rank - freepre[lo]);
-        if (dst < p0 || dst >= p0 + nb) continue;  // cannot happen while capacities add up to the scan size
-        a.inv_perm[i] = dst;
-        a.perm[dst] = i;
-        ++placed;
-    }
-    // one atomic per workgroup: hundreds of waves adding to the same counter queue up behind each other
-    for (int d = 32; d >= 1; d >>= 1) placed += __shfl_xor(placed, d, 64);
-    __syncthreads();              // everybody is done with s_base
-    if (tid == 0) s_base = 0;
-    __syncthreads();
-    if ((tid & 63) == 0 && placed) atomicAdd(&s_base, placed);
-    __syncthreads();
-    if (tid == 0 && s_base) atomicAdd(&a.round_count[a.n_probes + 1], s_base);
 }
 
 }  // namespace
@@ -569,22 +566,27 @@ hipError_t psh_fast_launch(const PshArgs& args, hipStream_t stream)
     const int nw = wide ? 16 : 8;
     const size_t lds = (size_t)a.kcap * 8 + (size_t)nw * kwp * 4;
     if (lds > 60000) {
-        const hipError_t e = wide ? hipFuncSetAttribute((const void*)k_pshf_step<1024>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)
-                                  : hipFuncSetAttribute((const void*)k_pshf_step<512>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
+        const void* fn[4] = {(const void*)k_pshf_step<512, false>, (const void*)k_pshf_step<512, true>,
+                             (const void*)k_pshf_step<1024, false>, (const void*)k_pshf_step<1024, true>};
+        for (int last = 0; last < 2; ++last) {
+            const hipError_t e = hipFuncSetAttribute(fn[2 * (wide ? 1 : 0) + last], hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            if (e != hipSuccess) return e;
+        }
     }
     uint32_t* mat[2] = {reinterpret_cast<uint32_t*>(a.hist), reinterpret_cast<uint32_t*>(a.hist) + (size_t)chunks * kwp};
     int32_t* c0 = a.cnt;
     int32_t* c1 = a.cnt_next;
-    for (int r = 0; r <= a.n_probes + 1; ++r) {
+    for (int r = 0; r <= a.n_probes; ++r) {
         a.cnt = c0;
         a.cnt_next = c1;
-        if (wide) k_pshf_step<1024><<<chunks, 1024, lds, stream>>>(a, r, mat[(r + 1) & 1], mat[r & 1]);
-        else k_pshf_step<512><<<chunks, 512, lds, stream>>>(a, r, mat[(r + 1) & 1], mat[r & 1]);
+        if (wide) k_pshf_step<1024, false><<<chunks, 1024, lds, stream>>>(a, r, mat[(r + 1) & 1], mat[r & 1]);
+        else k_pshf_step<512, false><<<chunks, 512, lds, stream>>>(a, r, mat[(r + 1) & 1], mat[r & 1]);
         if (r > 0) { int32_t* t = c0; c0 = c1; c1 = t; }  // step r wrote the fill levels after step r-1
     }
     a.cnt = c0;
-    k_pshf_recycle<<<chunks, FTH, (size_t)a.kcap * 8, stream>>>(a);
+    const int r = a.n_probes + 1;
+    if (wide) k_pshf_step<1024, true><<<chunks, 1024, lds, stream>>>(a, r, mat[(r + 1) & 1], nullptr);
+    else k_pshf_step<512, true><<<chunks, 512, lds, stream>>>(a, r, mat[(r + 1) & 1], nullptr);
     return hipGetLastError();
 }
 
