@@ -120,6 +120,7 @@ void make_plan(int64_t n, int32_t n_scans, const f3d_params* p, Plan* pl)
     pl->kcap = (int)kcap;
     pl->max_buckets = n / pl->S + n_scans;
     pl->chunks = n / f3d::PSH_CHUNK + n_scans;
+    const long long fast_chunks = n / f3d::psh_fast_chunk(n, n_scans, msp, pl->kcap) + n_scans;
     size_t at = 0;
     auto take = [&](size_t bytes) { size_t o = at; at = align_up(at + bytes, 256); return o; };
     pl->o_status = take(16);
@@ -129,8 +130,8 @@ void make_plan(int64_t n, int32_t n_scans, const f3d_params* p, Plan* pl)
     pl->o_mm = take((size_t)n_scans * 8 * 4);
     pl->o_cfg = take((size_t)n_scans * 128);
     pl->o_done = take((size_t)n_scans * 4);
-    pl->o_ci = take((size_t)(n / 2048 + n_scans) * 32);
-    pl->o_mmpart = take((size_t)(n / 2048 + n_scans) * 32);
+    pl->o_ci = take((size_t)fast_chunks * 32);
+    pl->o_mmpart = take((size_t)fast_chunks * 32);
     pl->o_cnt = take((size_t)(pl->max_buckets + 1) * 4);
     pl->o_cnt2 = take((size_t)(pl->max_buckets + 1) * 4);
     pl->o_freepre = take((size_t)(pl->max_buckets + 1) * 4);
@@ -138,7 +139,7 @@ void make_plan(int64_t n, int32_t n_scans, const f3d_params* p, Plan* pl)
     pl->o_leftpre = take((size_t)pl->chunks * 4);
     {
         size_t hb = (size_t)pl->chunks * pl->kcap * 4;
-        const size_t fb = f3d::psh_fast_matrix_bytes(n, n_scans, pl->kcap);
+        const size_t fb = f3d::psh_fast_matrix_bytes(fast_chunks, pl->kcap);
         pl->o_hist = take(hb > fb ? hb : fb);
     }
     pl->o_key = take((size_t)n * 4);

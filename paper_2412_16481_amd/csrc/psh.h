@@ -63,7 +63,8 @@ hipError_t psh_small_launch(const PshArgs& args, hipStream_t stream); // one wor
 bool psh_small_eligible(long long n, long long max_scan_points, int kcap, bool scans);   // scans: psh_scan_launch would be taken else
 bool psh_scan_eligible(int kcap);
 bool psh_fast_eligible(long long max_scan_points, int kcap);
-size_t psh_fast_matrix_bytes(long long n, int n_scans, int kcap);
+int psh_fast_chunk(long long n, int n_scans, long long max_scan_points, int kcap);   // points per workgroup
+size_t psh_fast_matrix_bytes(long long chunks, int kcap);
 __global__ void k_psh_meta(PshArgs a);
 
 }  // namespace f3d

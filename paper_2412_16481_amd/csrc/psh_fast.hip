@@ -2,7 +2,7 @@
 // paper's operating range: ~1e5 points per scan, a few hundred buckets).
 //
 // Same schedule and same results as psh.hip (Algorithms 1 and 2 in lock step, index-ordered), but one
-// launch per step instead of two: a workgroup ranks a chunk of 2048 points, writes one row of 16-bit
+// launch per step instead of two: a workgroup ranks a chunk of 2048 (1024) points, writes one row of 16-bit
 // counts, and in the NEXT launch every workgroup sums the rows it needs by itself (rows of earlier
 // chunks rebase its local ranks, all rows give the new fill levels), so no separate scan kernel and no
 // second round trip through the launch queue.
@@ -19,12 +19,14 @@ namespace f3d {
 
 namespace {
 
-constexpr int FCH = 2048;    // points per workgroup
-constexpr int FTH = 512;     // threads per workgroup
+// Points per workgroup, CH in the kernels below: FCH, and SCH for batches that are small in every way (psh_fast_chunk).
+constexpr int FCH = 2048;
+constexpr int SCH = 1024;
+constexpr int FTH = 512;     // threads per workgroup of the set-up kernels
 constexpr int FW = FTH / 64; // waves
-constexpr int FPPT = FCH / FTH;
 constexpr int FKMAX = 2048;           // most buckets per scan on this path
 constexpr long long FMATMAX = 131072; // most (chunks of a scan) x (buckets of a scan)
+constexpr int SCHUNKS = 256;          // most chunks of SCH points
 constexpr int CFGW = (int)(sizeof(ScanCfg) / 4);
 static_assert(sizeof(ScanCfg) <= 128 && sizeof(ScanCfg) % 4 == 0, "the workspace reserves 128 bytes per scan");
 
@@ -48,6 +50,7 @@ __host__ __device__ inline int group_pitch(int kcap) { return ((((kcap + 7) >> 3
 // per-scan bounding box
 __global__ __launch_bounds__(FTH) void k_pshf_minmax(PshArgs a)
 {
+    constexpr int FPPT = FCH / FTH;
     const ChunkInfo ci = load_chunk(a, blockIdx.x);
     if (ci.b < 0 || a.status[0]) return;
     const int b = ci.b;
@@ -98,8 +101,10 @@ __global__ __launch_bounds__(FTH) void k_pshf_minmax(PshArgs a)
 // the later kernels read.
 constexpr int SETUP_MAX_SCANS = 64;
 
+template <int CH>
 __global__ __launch_bounds__(FTH) void k_pshf_setup(PshArgs a)
 {
+    constexpr int FPPT = CH / FTH;
     __shared__ int s_p0[SETUP_MAX_SCANS + 1], s_kb0[SETUP_MAX_SCANS + 1], s_c0[SETUP_MAX_SCANS + 1];
     __shared__ int s_bad;
     __shared__ uint32_t red[8];
@@ -117,7 +122,7 @@ __global__ __launch_bounds__(FTH) void k_pshf_setup(PshArgs a)
             if (lane == ns - 1 && p1 != a.n) ok = false;
             if (ok) {
                 K = (int)((nb + a.S - 1) / a.S);
-                c = (int)((nb + FCH - 1) / FCH);
+                c = (int)((nb + CH - 1) / CH);
             }
         }
         const bool bad = __builtin_amdgcn_ballot_w64(!ok) != 0ull;
@@ -170,7 +175,7 @@ __global__ __launch_bounds__(FTH) void k_pshf_setup(PshArgs a)
     // the chunk's scan: the last one that starts at or before it (scans without points have no chunks)
     const int b = __popcll(__builtin_amdgcn_ballot_w64(lane < ns && s_c0[lane] <= chunk)) - 1;
     const int p0 = s_p0[b], p1 = s_p0[b + 1], c0 = s_c0[b], lc = chunk - c0;
-    const int begin = p0 + lc * FCH, end = min(begin + FCH, p1);
+    const int begin = p0 + lc * CH, end = min(begin + CH, p1);
     if (tid == 0) {
         a.chunk_info[2 * chunk] = make_int4(b, lc, s_c0[b + 1] - c0, begin);
         a.chunk_info[2 * chunk + 1] = make_int4(end, s_kb0[b], s_kb0[b + 1] - s_kb0[b], c0);
@@ -216,17 +221,18 @@ __global__ __launch_bounds__(FTH) void k_pshf_setup(PshArgs a)
 // ------------------------------------------------------------------------------------------------
 // step r: settle step r-1 from the count rows of that step, then rank the contenders of step r
 // dynamic LDS: tot[8][gp] + pre[8][gp] ints + NW x kwp words of packed 16-bit counters.
-// TH threads rank the 2048 points of a chunk: 512 (four points each, two workgroups per CU) when the grid is
-// larger than the GPU, 1024 (two points each: every phase of the step is half as long) when it is not.
+// TH threads rank the CH points of a chunk: 512 and 2048 (four points each, two workgroups per CU) when the grid is
+// larger than the GPU, 1024 threads (two points each: every phase of the step is half as long) when it is not, 1024 and 1024
+// (one point each) when the count rows stay few enough.
 // LAST (r = n_probes + 1) settles the last probe and recycles in the same launch: the r-th leftover of a scan takes the r-th
 // free slot (buckets ascending, slots ascending). The count rows that settle a step also say how many of the earlier
 // chunks' contenders it turns away, so nobody has to count leftovers in a launch of their own (a pass over one room of 200000
 // points 333 -> 322 us, the canonical order of 457295 points 249 -> 239).
-template <int TH, bool LAST>
+template <int CH, int TH, bool LAST>
 __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32_t* __restrict__ mat_prev,
                                                    uint32_t* __restrict__ mat_cur)
 {
-    constexpr int NW = TH / 64, PPT = FCH / TH, KPT_ = FKMAX / TH;
+    constexpr int NW = TH / 64, PPT = CH / TH, KPT_ = FKMAX / TH;
     extern __shared__ int smem[];
     __shared__ ScanCfg cfg;
     __shared__ int placed_ct, recycled_ct, left_before;
@@ -275,7 +281,7 @@ __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32
     float cx[PPT], cy[PPT], cz[PPT];
 #pragma unroll
     for (int s = 0; s < PPT; ++s) {
-        const int i = ci.begin + wave * (FCH / NW) + s * 64 + lane;
+        const int i = ci.begin + wave * (CH / NW) + s * 64 + lane;
         kwv[s] = KEY_PLACED;
         cx[s] = cy[s] = cz[s] = 0.f;
         if (i < ci.end) {
@@ -301,7 +307,7 @@ __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32
             const int pitch4 = kwp >> 2;
             constexpr int LB = 12;   // loads in flight per thread: a row fetch costs a trip to HBM-side cache
             for (int c = seg; c < nc; c += LB * nseg) {
-                static_assert(LB * FCH < 65536, "sums of packed counts");
+                static_assert(LB * CH < 65536, "sums of packed counts");
                 uint4 v[LB];
                 uint32_t t2[4] = {0u, 0u, 0u, 0u}, p2[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
@@ -400,7 +406,7 @@ __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32
         int nplaced = 0, nrest = 0;
 #pragma unroll
         for (int s = 0; s < PPT; ++s) {
-            const int i = ci.begin + wave * (FCH / NW) + s * 64 + lane;
+            const int i = ci.begin + wave * (CH / NW) + s * 64 + lane;
             bool left = i < ci.end && kwv[s] != KEY_PLACED;
             if (left) {
                 const int hp = (int)(kwv[s] >> LR_BITS);
@@ -423,7 +429,7 @@ __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32
         int nrec = 0;
 #pragma unroll
         for (int s = 0; s < PPT; ++s) {
-            const int i = ci.begin + wave * (FCH / NW) + s * 64 + lane;
+            const int i = ci.begin + wave * (CH / NW) + s * 64 + lane;
             if ((rest[s] >> lane) & 1ull) {
                 const int rank = at + bits_below(rest[s]);
                 int lo = 0, hi = K;  // largest j with freepre[j] <= rank
@@ -460,7 +466,7 @@ __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32
     // accept what fits from step r-1, hash what is left for step r
 #pragma unroll
     for (int s = 0; s < PPT; ++s) {
-        const int i = ci.begin + wave * (FCH / NW) + s * 64 + lane;
+        const int i = ci.begin + wave * (CH / NW) + s * 64 + lane;
         bool active = i < ci.end;
         int h = 0;
         if (active && r > 0) {
@@ -521,7 +527,7 @@ __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32
 #pragma unroll
             for (int v = 0; v < NW; ++v) {
                 wh[v * kwp + w] = run;
-                run += t[v];  // halves cannot carry into each other: a chunk has 2048 points
+                run += t[v];  // halves cannot carry into each other: a chunk has at most 2048 points
             }
         }
         mat_cur[(size_t)chunk * kwp + w] = run;   // padding words of the row are written as zero
@@ -529,7 +535,7 @@ __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32
     __syncthreads();
 #pragma unroll
     for (int s = 0; s < PPT; ++s) {
-        const int i = ci.begin + wave * (FCH / NW) + s * 64 + lane;
+        const int i = ci.begin + wave * (CH / NW) + s * 64 + lane;
         if (hh[s] >= 0) {
             const int h = hh[s];
             const int base = (int)((wh[wave * kwp + (h >> 1)] >> ((h & 1) * 16)) & 0xFFFFu);
@@ -552,36 +558,32 @@ bool psh_fast_eligible(long long max_scan_points, int kcap)
     return kcap <= FKMAX && nc * kcap <= FMATMAX;
 }
 
-size_t psh_fast_matrix_bytes(long long n, int n_scans, int kcap)
+// A step of a small batch is instruction issue on the workgroups there are and two round trips to memory: with half the points per
+// workgroup the hash, the rank and the accept of a step take half as long, while the GPU has compute units to spare.
+// Against that every workgroup sums twice as many count rows, hence the limit on rows times buckets. us per bucketing with 2048 /
+// 1024 points: 9000 points 76 / 63, 60000 84 / 72, 130000 (64000 counts) 87 / 78, 2 x 100000 87 / 76; 100000 points in buckets
+// of 64 (153000 counts) 98 / 97, 200000 points (153000 counts) 94 / 100, 4 x 114000 (448 chunks) 91 / 99.
+int psh_fast_chunk(long long n, int n_scans, long long max_scan_points, int kcap)
 {
-    return (size_t)2 * (size_t)(n / FCH + n_scans) * row_pitch(kcap) * 4;
+    const long long nc = (max_scan_points + SCH - 1) / SCH;
+    return kcap <= FKMAX && n_scans <= SETUP_MAX_SCANS && n / SCH + n_scans <= SCHUNKS && nc * kcap <= FMATMAX ? SCH : FCH;
 }
 
-hipError_t psh_fast_launch(const PshArgs& args, hipStream_t stream)
+size_t psh_fast_matrix_bytes(long long chunks, int kcap)
 {
-    PshArgs a = args;
-    a.chunk = FCH;
-    const int chunks = (int)(a.n / FCH) + a.n_scans;  // upper bound, surplus workgroups exit
-    a.n_chunks_ub = chunks;
-    if (a.n_scans <= SETUP_MAX_SCANS && a.n > 0) {
-        k_pshf_setup<<<chunks, FTH, 0, stream>>>(a);
-    } else {
-        a.mmpart = nullptr;
-        k_psh_meta<<<1, 1024, 0, stream>>>(a);
-        if (a.n == 0) return hipGetLastError();
-        k_pshf_minmax<<<chunks, FTH, 0, stream>>>(a);
-    }
+    return (size_t)2 * (size_t)chunks * row_pitch(kcap) * 4;
+}
+
+namespace {
+
+template <int CH, int TH>
+hipError_t launch_steps(PshArgs a, int chunks, hipStream_t stream)
+{
     const int kwp = row_pitch(a.kcap);
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 0;
-    const bool wide = chunks <= cus;   // one workgroup per CU at most: take the 1024-thread form
-    const int nw = wide ? 16 : 8;
-    const size_t lds = (size_t)group_pitch(a.kcap) * 64 + (size_t)nw * kwp * 4;
+    const size_t lds = (size_t)group_pitch(a.kcap) * 64 + (size_t)(TH / 64) * kwp * 4;
     if (lds > 60000) {
-        const void* fn[4] = {(const void*)k_pshf_step<512, false>, (const void*)k_pshf_step<512, true>,
-                             (const void*)k_pshf_step<1024, false>, (const void*)k_pshf_step<1024, true>};
-        for (int last = 0; last < 2; ++last) {
-            const hipError_t e = hipFuncSetAttribute(fn[2 * (wide ? 1 : 0) + last], hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        for (const void* fn : {(const void*)k_pshf_step<CH, TH, false>, (const void*)k_pshf_step<CH, TH, true>}) {
+            const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
             if (e != hipSuccess) return e;
         }
     }
@@ -591,15 +593,37 @@ hipError_t psh_fast_launch(const PshArgs& args, hipStream_t stream)
     for (int r = 0; r <= a.n_probes; ++r) {
         a.cnt = c0;
         a.cnt_next = c1;
-        if (wide) k_pshf_step<1024, false><<<chunks, 1024, lds, stream>>>(a, r, mat[(r + 1) & 1], mat[r & 1]);
-        else k_pshf_step<512, false><<<chunks, 512, lds, stream>>>(a, r, mat[(r + 1) & 1], mat[r & 1]);
+        k_pshf_step<CH, TH, false><<<chunks, TH, lds, stream>>>(a, r, mat[(r + 1) & 1], mat[r & 1]);
         if (r > 0) { int32_t* t = c0; c0 = c1; c1 = t; }  // step r wrote the fill levels after step r-1
     }
     a.cnt = c0;
     const int r = a.n_probes + 1;
-    if (wide) k_pshf_step<1024, true><<<chunks, 1024, lds, stream>>>(a, r, mat[(r + 1) & 1], nullptr);
-    else k_pshf_step<512, true><<<chunks, 512, lds, stream>>>(a, r, mat[(r + 1) & 1], nullptr);
+    k_pshf_step<CH, TH, true><<<chunks, TH, lds, stream>>>(a, r, mat[(r + 1) & 1], nullptr);
     return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t psh_fast_launch(const PshArgs& args, hipStream_t stream)
+{
+    PshArgs a = args;
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 0;
+    a.chunk = psh_fast_chunk(a.n, a.n_scans, a.max_scan_points, a.kcap);
+    if (a.chunk == SCH && a.n / SCH + a.n_scans > cus) a.chunk = FCH;
+    const int chunks = (int)(a.n / a.chunk) + a.n_scans;  // upper bound, surplus workgroups exit
+    a.n_chunks_ub = chunks;
+    if (a.n_scans <= SETUP_MAX_SCANS && a.n > 0) {
+        if (a.chunk == SCH) k_pshf_setup<SCH><<<chunks, FTH, 0, stream>>>(a);
+        else k_pshf_setup<FCH><<<chunks, FTH, 0, stream>>>(a);
+    } else {
+        a.mmpart = nullptr;
+        k_psh_meta<<<1, 1024, 0, stream>>>(a);
+        if (a.n == 0) return hipGetLastError();
+        k_pshf_minmax<<<chunks, FTH, 0, stream>>>(a);
+    }
+    if (a.chunk == SCH) return launch_steps<SCH, 1024>(a, chunks, stream);
+    return chunks <= cus ? launch_steps<FCH, 1024>(a, chunks, stream) : launch_steps<FCH, 512>(a, chunks, stream);
 }
 
 }  // namespace f3d

@@ -250,6 +250,20 @@ def test_bucketize_small_and_ragged_sizes(n):
         check_bucketize(c, None, 0.05, 64, 4, hash)
 
 
+@pytest.mark.parametrize("hash", HASHES)
+def test_bucketize_half_chunks_on_the_one_launch_per_step_path(hash):
+    # batches small enough for chunks of 1024 points: scans around a chunk, empty ones, one past the last chunk (256) and one past
+    # the largest count matrix, most points left over (their rank runs on over chunks and buckets of odd capacity) or hardly any
+    rng = np.random.default_rng(37)
+    for sizes in ([1023, 0, 1025, 1024, 2049, 1, 9000, 0], [65536], [261119], [262144], [65537, 3]):
+        bo = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+        cap = 128 if max(sizes) < 10000 else 2048 if max(sizes) > 70000 else 128      # 65536 points in 2048 buckets
+        for cloud in (lambda k: clustered_cloud(rng, k), lambda k: rng.random((k, 3)) * 4.0):
+            c = np.concatenate([cloud(int(k)) for k in sizes if k]).astype(np.float32)
+            for n_probes in (6, 0):
+                check_bucketize(c, bo, 0.05, cap, 4, hash, n_probes, max_scan_points=max(sizes), schedule="steps" if max(sizes) < 65537 or cap > 128 else "auto")
+
+
 def test_bucketize_widest_count_rows_on_the_one_launch_per_step_path():
     # 2048 buckets in one scan of 64 chunks: the largest LDS footprint of the step kernel (above the 64 KB default)
     rng = np.random.default_rng(28)
