@@ -27,6 +27,7 @@ constexpr int FW = FTH / 64; // waves
 constexpr int FKMAX = 2048;           // most buckets per scan on this path
 constexpr long long FMATMAX = 131072; // most (chunks of a scan) x (buckets of a scan)
 constexpr int SCHUNKS = 256;          // most chunks of SCH points
+constexpr uint32_t KEY_WAIT = KEY_PLACED - 1;   // no contender's: a key ends below 2^(11 + LR_BITS)
 constexpr int CFGW = (int)(sizeof(ScanCfg) / 4);
 static_assert(sizeof(ScanCfg) <= 128 && sizeof(ScanCfg) % 4 == 0, "the workspace reserves 128 bytes per scan");
 
@@ -225,8 +226,11 @@ __global__ __launch_bounds__(FTH) void k_pshf_setup(PshArgs a)
 // larger than the GPU, 1024 threads (two points each: every phase of the step is half as long) when it is not, 1024 and 1024
 // (one point each) when the count rows stay few enough.
 // LAST (r = n_probes + 1) settles the last probe and recycles in the same launch: the r-th leftover of a scan takes the r-th
-// free slot (buckets ascending, slots ascending). The count rows that settle a step also say how many of the earlier
-// chunks' contenders it turns away, so nobody has to count leftovers in a launch of their own (a pass over one room of 200000
+// free slot (buckets ascending, slots ascending).
+// A point whose probe meets a full bucket is no contender: it waits for the next step (KEY_WAIT) unranked, and groups of 64 without
+// a contender, most of them on surfaces, go past the ranks. (The bucketing of 914601 points in eight scans 122 -> 114 us, of 457295 in
+// four 92 -> 89.) The count rows that settle a step also say how many of the earlier
+// chunks' contenders it turns away, and with those that waited all along (`left`) that is every leftover, so nobody has to count leftovers in a launch of their own (a pass over one room of 200000
 // points 333 -> 322 us, the canonical order of 457295 points 249 -> 239).
 template <int CH, int TH, bool LAST>
 __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32_t* __restrict__ mat_prev,
@@ -298,7 +302,7 @@ __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32
     // lanes to a bank. The whole bucketing of 200000 points in one scan 103 -> 94 us, of 457295 in four 102 -> 91.
     const int G = (((K + 1) >> 1) + 3) >> 2;        // column groups in use (<= 256)
     const int nseg = TH / G, seg = tid / G, g = tid - seg * G;
-    int tl[8], pl[8], cntv[KPT_];
+    int tl[8], pl[8], cntv[KPT_], waited = 0;
 #pragma unroll
     for (int e = 0; e < 8; ++e) { tl[e] = 0; pl[e] = 0; }
     if (r > 0) {
@@ -336,6 +340,8 @@ __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32
         }
 #pragma unroll
         for (int j = 0; j < KPT_; ++j) cntv[j] = (tid + j * TH < K) ? a.cnt[kb0 + tid + j * TH] : 0;
+        if (LAST)
+            for (int c = tid; c < lc; c += TH) waited += a.left[ci.c0 + c];
     }
 
     // ---- LDS set-up while the loads fly
@@ -367,8 +373,12 @@ __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32
             const int k = tid + j * TH;
             if (k < K) {
                 const int base = cntv[j];
-                if (!LAST && lc == 0) a.cnt_next[kb0 + k] = min(base + tot[of(k)], k == K - 1 ? cfg.lastcap : a.S);
-                if (!LAST) pre[of(k)] += base;
+                if (!LAST) {
+                    const int cap = k == K - 1 ? cfg.lastcap : a.S, filled = min(base + tot[of(k)], cap);
+                    if (lc == 0) a.cnt_next[kb0 + k] = filled;
+                    tot[of(k)] = cap - filled;      // the room for step r
+                    pre[of(k)] += base;
+                }
             }
         }
         __syncthreads();
@@ -379,7 +389,7 @@ __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32
         // earlier chunks that found no room
         int* const fill = reinterpret_cast<int*>(wh);
         int* const freepre = tot;
-        int carry = 0, turned = 0;
+        int carry = 0, turned = waited;
 #pragma unroll
         for (int j = 0; j < KPT_; ++j) {
             if (j * TH < K) {
@@ -408,7 +418,7 @@ __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32
         for (int s = 0; s < PPT; ++s) {
             const int i = ci.begin + wave * (CH / NW) + s * 64 + lane;
             bool left = i < ci.end && kwv[s] != KEY_PLACED;
-            if (left) {
+            if (left && kwv[s] != KEY_WAIT) {
                 const int hp = (int)(kwv[s] >> LR_BITS);
                 const int rank = pre[of(hp)] + (int)(kwv[s] & ((1u << LR_BITS) - 1));
                 if (rank < (hp == K - 1 ? cfg.lastcap : a.S)) {
@@ -462,7 +472,7 @@ __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32
     const int keybits = max(1, 32 - __clz(max(K - 1, 1)));
     int hh[PPT], wl[PPT];
     bool act[PPT];
-    int nplaced = 0;
+    int nplaced = 0, nwait = 0;
     // accept what fits from step r-1, hash what is left for step r
 #pragma unroll
     for (int s = 0; s < PPT; ++s) {
@@ -473,7 +483,7 @@ __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32
             const uint32_t kv = kwv[s];
             if (kv == KEY_PLACED) {
                 active = false;
-            } else {
+            } else if (kv != KEY_WAIT) {
                 const int hp = (int)(kv >> LR_BITS), lr = (int)(kv & ((1u << LR_BITS) - 1));
                 const int rank = pre[of(hp)] + lr;
                 const int cap = (hp == K - 1) ? cfg.lastcap : a.S;
@@ -493,6 +503,11 @@ __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32
             int z = voxel_of(cz[s], cfg.mn[2], a.inv_voxel);
             if (r > 0) probe_voxel(a, r, cfg, x, y, z);
             h = hash_bucket(a.hash, x, y, z, cfg);
+            if (r > 0 && tot[of(h)] == 0) {
+                if (kwv[s] != KEY_WAIT) a.key[i] = KEY_WAIT;
+                active = false;
+                ++nwait;
+            }
         }
         act[s] = active;
         hh[s] = h;
@@ -502,8 +517,12 @@ __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32
     for (int s = 0; s < PPT; ++s) {
         const int h = hh[s];
         const bool active = act[s];
-        const unsigned long long m = match_key(h, active, keybits);
         int old = 0;
+        if (__builtin_amdgcn_ballot_w64(active) == 0ull) {
+            hh[s] = -1;
+            continue;
+        }
+        const unsigned long long m = match_key(h, active, keybits);
         if (active) {
             const int leader = __ffsll((long long)m) - 1;
             const int before = bits_below(m);
@@ -543,11 +562,13 @@ __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32
         }
     }
     if (r > 0) {
-        for (int d = 32; d >= 1; d >>= 1) nplaced += __shfl_xor(nplaced, d, 64);
-        if (lane == 0 && nplaced) atomicAdd(&placed_ct, nplaced);
+        int n2 = nplaced | (nwait << 16);     // a chunk has at most 2048 points
+        for (int d = 32; d >= 1; d >>= 1) n2 += __shfl_xor(n2, d, 64);
+        if (lane == 0 && n2) atomicAdd(&placed_ct, n2);
         __syncthreads();
-        if (tid == 0 && placed_ct) atomicAdd(&a.round_count[r - 1], placed_ct);
+        if (tid == 0 && (placed_ct & 0xFFFF)) atomicAdd(&a.round_count[r - 1], placed_ct & 0xFFFF);
     }
+    if (r == a.n_probes && tid == 0) a.left[chunk] = placed_ct >> 16;
 }
 
 }  // namespace
