@@ -225,13 +225,14 @@ __global__ __launch_bounds__(FTH) void k_pshf_setup(PshArgs a)
 // TH threads rank the CH points of a chunk: 512 and 2048 (four points each, two workgroups per CU) when the grid is
 // larger than the GPU, 1024 threads (two points each: every phase of the step is half as long) when it is not, 1024 and 1024
 // (one point each) when the count rows stay few enough.
+// A point whose probe meets a full bucket is no contender: it waits for the next step (KEY_WAIT) unranked, and groups of 64
+// without a contender, most of them on surfaces, go past the ranks. (The bucketing of 914601 points in eight scans took 122 us
+// without that and takes 114, of 457295 in four 92 and 89.)
 // LAST (r = n_probes + 1) settles the last probe and recycles in the same launch: the r-th leftover of a scan takes the r-th
-// free slot (buckets ascending, slots ascending).
-// A point whose probe meets a full bucket is no contender: it waits for the next step (KEY_WAIT) unranked, and groups of 64 without
-// a contender, most of them on surfaces, go past the ranks. (The bucketing of 914601 points in eight scans 122 -> 114 us, of 457295 in
-// four 92 -> 89.) The count rows that settle a step also say how many of the earlier
-// chunks' contenders it turns away, and with those that waited all along (`left`) that is every leftover, so nobody has to count leftovers in a launch of their own (a pass over one room of 200000
-// points 333 -> 322 us, the canonical order of 457295 points 249 -> 239).
+// free slot (buckets ascending, slots ascending). The count rows that settle a step also say how many of the earlier chunks'
+// contenders it turns away, and with those that waited all along (`left`) that is every leftover before this chunk, so nobody has
+// to count them in a launch of its own (a forward pass over a room of 200000 points 334 -> 322 us, the canonical order of
+// 457295 points 250 -> 239).
 template <int CH, int TH, bool LAST>
 __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32_t* __restrict__ mat_prev,
                                                    uint32_t* __restrict__ mat_cur)
@@ -298,8 +299,8 @@ __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32
     }
     // Count rows of step r-1, 16 bytes (8 buckets) per load: thread (g, seg) sums column group g over
     // rows seg, seg+nseg, ... in registers; the row segments are joined in LDS afterwards.
-    // This was the longest part of a step: the counts unpacked one by one (28 instructions a load, 12 now) and joined in words eight apart, sixteen
-    // lanes to a bank. The whole bucketing of 200000 points in one scan 103 -> 94 us, of 457295 in four 102 -> 91.
+    // This was the longest part of a step: counts unpacked one by one (28 instructions a load, 12 now) and joined in words eight
+    // apart, sixteen lanes to a bank. The whole bucketing of 200000 points in one scan 103 -> 94 us, of 457295 in four 102 -> 91.
     const int G = (((K + 1) >> 1) + 3) >> 2;        // column groups in use (<= 256)
     const int nseg = TH / G, seg = tid / G, g = tid - seg * G;
     int tl[8], pl[8], cntv[KPT_], waited = 0;

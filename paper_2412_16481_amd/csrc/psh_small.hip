@@ -13,9 +13,9 @@
 // nothing else.
 //
 // Bound: instruction issue and two barriers per step on ONE compute unit, not memory: about 7 ns per point of a sensor sweep, 4 of
-// a cube. That is where the line to the other paths lies. One scan, us here against the launch-per-step path: 1500 points 23
-// (70-75), 4096 31-32 (77-82), 6000 45-79 (76-84), 8192 47-71 (78-84); 16 384 points took 159-198 against 87-109 and are not
-// served. Batches above 4096 points that the one-workgroup-per-scan path takes stay there (100 scans of 8000: 55 against 62,
+// a cube. That is where the line to the other paths lies. One scan, us here against the launch-per-step path: 4500 points
+// 39-63 (58-70), 6000 43-73 (61-70), 8192 47-79 (61-69; only sensor sweeps are above it here); 16 384 points took 159-198 against
+// 87-109 and are not served. Batches above 4096 points that the one-workgroup-per-scan path takes stay there (100 scans of 8000: 55 against 62,
 // 600 of them 140 against 178). Walking every point left in every step, 4096 points took 42-52, 600 scans of 4000 115 (96 now).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
