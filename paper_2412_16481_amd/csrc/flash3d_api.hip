@@ -57,6 +57,7 @@ int static_scratch(char** out)
 struct Plan {
     int S;
     int kcap;
+    int fast_chunk;   // points per chunk where one launch per step is taken
     long long max_scan_points;
     long long max_buckets;
     long long chunks;
@@ -109,7 +110,8 @@ bool wants_scans(int64_t n, int32_t n_scans, const f3d_params* p, long long max_
     return t_scans < t_spread;
 }
 
-void make_plan(int64_t n, int32_t n_scans, const f3d_params* p, Plan* pl)
+// half: room for chunks of half the size on the path with one launch per step (see psh_fast_chunk)
+void make_plan(int64_t n, int32_t n_scans, const f3d_params* p, Plan* pl, bool half = true)
 {
     pl->S = p->bucket_cap / p->scope_buckets;
     long long msp = p->max_scan_points > 0 ? p->max_scan_points : n;
@@ -120,7 +122,8 @@ void make_plan(int64_t n, int32_t n_scans, const f3d_params* p, Plan* pl)
     pl->kcap = (int)kcap;
     pl->max_buckets = n / pl->S + n_scans;
     pl->chunks = n / f3d::PSH_CHUNK + n_scans;
-    const long long fast_chunks = n / f3d::psh_fast_chunk(n, n_scans, msp, pl->kcap) + n_scans;
+    pl->fast_chunk = f3d::psh_fast_chunk(n, n_scans, msp, pl->kcap, half);
+    const long long fast_chunks = half ? f3d::psh_fast_most_chunks(n, n_scans) : f3d::psh_fast_chunks(n, n_scans);
     size_t at = 0;
     auto take = [&](size_t bytes) { size_t o = at; at = align_up(at + bytes, 256); return o; };
     pl->o_status = take(16);
@@ -160,6 +163,14 @@ void make_plan(int64_t n, int32_t n_scans, const f3d_params* p, Plan* pl)
         pl->o_lvox1 = take((size_t)n * 8);
     }
     pl->bytes = at;
+}
+
+// The plan for a workspace of `bytes`: one that does not hold the chunks of half the size (at most 15 KB more) does without.
+bool plan_for(size_t bytes, int64_t n, int32_t n_scans, const f3d_params* p, Plan* pl)
+{
+    make_plan(n, n_scans, p, pl);
+    if (pl->bytes > bytes) make_plan(n, n_scans, p, pl, false);
+    return pl->bytes <= bytes;
 }
 
 __global__ void k_unpermute16(const uint4* __restrict__ src, const int32_t* __restrict__ perm, long long n, int vec_per_row,
@@ -253,6 +264,7 @@ static int bucketize_on(const Plan& pl, char* ws, const float* coords, const int
     a.probe_seed = p->probe_seed;
     for (int i = 0; i < 3 * F3D_MAX_PROBES; ++i) a.probe_table[i] = p->probe_table[i];
     a.kcap = pl.kcap;
+    a.chunk = pl.fast_chunk;
     a.max_scan_points = pl.max_scan_points;
     a.max_buckets = (int)pl.max_buckets;
     a.perm = perm;
@@ -328,8 +340,7 @@ int f3d_psh_bucketize(const float* coords, const int32_t* batch_offsets, int64_t
     if (!workspace) return F3D_ERR_INVALID_ARG;
     if ((uintptr_t)workspace & 255) return F3D_ERR_BAD_ALIGNMENT;
     Plan pl;
-    make_plan(n, n_scans, p, &pl);
-    if (workspace_bytes < pl.bytes) return F3D_ERR_WORKSPACE_TOO_SMALL;
+    if (!plan_for(workspace_bytes, n, n_scans, p, &pl)) return F3D_ERR_WORKSPACE_TOO_SMALL;
     return bucketize_on(pl, (char*)workspace, coords, batch_offsets, n, n_scans, p, perm, inv_perm, offsets, scan_bucket_start,
                         placed_per_round, stream);
 }
@@ -342,8 +353,7 @@ int f3d_psh_bucketize_static(const float* coords, const int32_t* batch_offsets, 
                                         placed_per_round);
     if (rc != F3D_OK) return rc;
     Plan pl;
-    make_plan(n, n_scans, p, &pl);
-    if (pl.bytes > (size_t)F3D_STATIC_SCRATCH_BYTES) return F3D_ERR_SCRATCH_LIMIT;
+    if (!plan_for(F3D_STATIC_SCRATCH_BYTES, n, n_scans, p, &pl)) return F3D_ERR_SCRATCH_LIMIT;
     char* ws = nullptr;
     const int rs = static_scratch(&ws);
     if (rs != F3D_OK) return rs;

@@ -63,7 +63,10 @@ hipError_t psh_small_launch(const PshArgs& args, hipStream_t stream); // one wor
 bool psh_small_eligible(long long n, long long max_scan_points, int kcap, bool scans);   // scans: psh_scan_launch would be taken else
 bool psh_scan_eligible(int kcap);
 bool psh_fast_eligible(long long max_scan_points, int kcap);
-int psh_fast_chunk(long long n, int n_scans, long long max_scan_points, int kcap);   // points per workgroup
+// points per workgroup of psh_fast_launch (PshArgs::chunk); `half`: the workspace has psh_fast_most_chunks rows
+int psh_fast_chunk(long long n, int n_scans, long long max_scan_points, int kcap, bool half);
+long long psh_fast_chunks(long long n, int n_scans);        // most chunks without chunks of half the size
+long long psh_fast_most_chunks(long long n, int n_scans);   // with them; never falls as n or n_scans grows
 size_t psh_fast_matrix_bytes(long long chunks, int kcap);
 __global__ void k_psh_meta(PshArgs a);
 

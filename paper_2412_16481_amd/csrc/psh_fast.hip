@@ -585,10 +585,20 @@ bool psh_fast_eligible(long long max_scan_points, int kcap)
 // Against that every workgroup sums twice as many count rows, hence the limit on rows times buckets. us per bucketing with 2048 /
 // 1024 points: 9000 points 76 / 63, 60000 84 / 72, 130000 (64000 counts) 87 / 78, 2 x 100000 87 / 76; 100000 points in buckets
 // of 64 (153000 counts) 98 / 97, 200000 points (153000 counts) 94 / 100, 4 x 114000 (448 chunks) 91 / 99.
-int psh_fast_chunk(long long n, int n_scans, long long max_scan_points, int kcap)
+int psh_fast_chunk(long long n, int n_scans, long long max_scan_points, int kcap, bool half)
 {
     const long long nc = (max_scan_points + SCH - 1) / SCH;
-    return kcap <= FKMAX && n_scans <= SETUP_MAX_SCANS && n / SCH + n_scans <= SCHUNKS && nc * kcap <= FMATMAX ? SCH : FCH;
+    return half && kcap <= FKMAX && n_scans <= SETUP_MAX_SCANS && n / SCH + n_scans <= SCHUNKS && nc * kcap <= FMATMAX ? SCH : FCH;
+}
+
+// Rows of the chunk tables and of a count matrix. Whether a batch takes chunks of 1024 points depends on n, the scans and the
+// buckets, and one point more can halve its chunks: rows for the chunks of the batch itself would make a workspace that holds
+// for n points too small for fewer. There are rows for the most chunks any batch of up to so many points and scans takes.
+long long psh_fast_chunks(long long n, int n_scans) { return n / FCH + n_scans; }
+long long psh_fast_most_chunks(long long n, int n_scans)
+{
+    const long long full = psh_fast_chunks(n, n_scans), halves = n / SCH + n_scans, bounded = halves < SCHUNKS ? halves : SCHUNKS;
+    return full > bounded ? full : bounded;
 }
 
 size_t psh_fast_matrix_bytes(long long chunks, int kcap)
@@ -626,12 +636,11 @@ hipError_t launch_steps(PshArgs a, int chunks, hipStream_t stream)
 
 }  // namespace
 
-hipError_t psh_fast_launch(const PshArgs& args, hipStream_t stream)
+hipError_t psh_fast_launch(const PshArgs& args, hipStream_t stream)   // args.chunk: psh_fast_chunk
 {
     PshArgs a = args;
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 0;
-    a.chunk = psh_fast_chunk(a.n, a.n_scans, a.max_scan_points, a.kcap);
     if (a.chunk == SCH && a.n / SCH + a.n_scans > cus) a.chunk = FCH;
     const int chunks = (int)(a.n / a.chunk) + a.n_scans;  // upper bound, surplus workgroups exit
     a.n_chunks_ub = chunks;

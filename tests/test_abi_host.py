@@ -139,6 +139,28 @@ def test_max_scan_points_lifts_the_bucket_limit():
     assert f3d.workspace_bytes(10_000_000, 200, p) > 0
 
 
+@pytest.mark.parametrize("order", ["index", "canonical"])
+@pytest.mark.parametrize("cap", [64, 192, 1024, 2048])
+def test_workspace_never_shrinks_as_the_batch_grows(cap, order):
+    """A program that allocates once for its largest batch reuses the buffer for every smaller one. The sizes walk over the limits
+    of the chunks of 1024 points: 92 160 to 262 144 points, depending on buckets, scans and the largest scan. (From 48 scans on the
+    lists of the path with one workgroup per scan come and go with n; those are not looked at here.)"""
+    def size(n, n_scans, most):
+        return f3d.workspace_bytes(n, n_scans, f3d.make_params(0.05, cap, 4, max_scan_points=most, order=order))
+
+    near = [e + d for e in (92160, 131072, 185344, 215040, 255000, 261120, 262144) for d in range(-3, 4)]
+    grow = sorted(set(near) | set(range(1, 300000, 1021)))
+    for n_scans in (1, 2, 8, 47):
+        for most in (0, 20000):
+            sizes = [size(n, n_scans, most) for n in grow if (min(n, most or n) + cap // 4 - 1) // (cap // 4) <= 8192]
+            assert sizes == sorted(sizes), (n_scans, most)
+    for n in (1000, 150000, 250000):
+        sizes = [size(n, n_scans, 5000) for n_scans in range(1, 513)]
+        assert sizes == sorted(sizes), n
+        sizes = [size(n, 8, most) for most in sorted(set(m for m in near if m <= n) | set(range(1000, n, 1021))) if 4 * most <= 8192 * cap]
+        assert sizes == sorted(sizes), n
+
+
 def test_bucketize_refuses_null_and_misaligned_pointers_on_the_host():
     L = f3d.lib()
     p = f3d.make_params(0.02, 1024)

@@ -264,6 +264,25 @@ def test_bucketize_half_chunks_on_the_one_launch_per_step_path(hash):
                 check_bucketize(c, bo, 0.05, cap, 4, hash, n_probes, max_scan_points=max(sizes), schedule="steps" if max(sizes) < 65537 or cap > 128 else "auto")
 
 
+@pytest.mark.parametrize("sizes,cap,small", [([9000], 1024, 77312), ([185344], 1024, 2028544), ([262143], 2048, 2640384),
+                                             ([30000, 0, 40000, 40000, 40000], 256, 1615104)])
+def test_bucketize_takes_a_workspace_without_room_for_half_chunks(sizes, cap, small):
+    """The workspace asked for has rows for chunks of 1024 points; a buffer with room for those of 2048 (`small` bytes: 64 bytes
+    of tables and two count rows per chunk) is taken all the same, and one of 256 bytes less refused."""
+    rng = np.random.default_rng(38)
+    bo = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    c = np.concatenate([clustered_cloud(rng, k) for k in sizes if k]).astype(np.float32)
+    _, ref = check_bucketize(c, bo, 0.05, cap, 4, max_scan_points=max(sizes), schedule="steps")
+    p = f3d.make_params(0.05, cap, 4, max_scan_points=max(sizes), schedule="steps")
+    assert f3d.workspace_bytes(len(c), len(sizes), p) > small
+    ws = torch.empty(small, dtype=torch.uint8, device=DEV)
+    got = f3d.psh_bucketize(dev(c), dev(bo), p, workspace=ws)
+    assert np.array_equal(got.perm.cpu().numpy(), ref["perm"]) and np.array_equal(got.inv_perm.cpu().numpy(), ref["inv_perm"])
+    with pytest.raises(f3d.Flash3DError) as e:
+        f3d.psh_bucketize(dev(c), dev(bo), p, workspace=ws[:-256])
+    assert e.value.code == f3d.ERR_WORKSPACE_TOO_SMALL
+
+
 def test_bucketize_widest_count_rows_on_the_one_launch_per_step_path():
     # 2048 buckets in one scan of 64 chunks: the largest LDS footprint of the step kernel (above the 64 KB default)
     rng = np.random.default_rng(28)
