@@ -720,12 +720,9 @@ __global__ __launch_bounds__(PT, WPE) void k_pool(PoolArgs a)
         uint32_t o[3] = {act ? f2ord(x) : 0xFFFFFFFFu, act ? f2ord(y) : 0xFFFFFFFFu, act ? f2ord(z) : 0xFFFFFFFFu};
 #pragma unroll
         for (int ax = 0; ax < 3; ++ax) {
-            uint32_t lo = o[ax], hi = act ? o[ax] : 0u;
-            for (int d = 32; d >= 1; d >>= 1) {
-                lo = min(lo, (uint32_t)__shfl_xor((int)lo, d, 64));
-                hi = max(hi, (uint32_t)__shfl_xor((int)hi, d, 64));
-            }
-            if (lane == 0) { atomicMin(&red[ax], lo); atomicMax(&red[8 + ax], hi); }
+            uint32_t lo = o[ax];
+            for (int d = 32; d >= 1; d >>= 1) lo = min(lo, (uint32_t)__shfl_xor((int)lo, d, 64));
+            if (lane == 0) atomicMin(&red[ax], lo);
         }
     }
     __syncthreads();
@@ -873,6 +870,14 @@ __global__ __launch_bounds__(PT, WPE) void k_pool(PoolArgs a)
     const int pitch = (nopen + 7) & ~7;
     if (nleft > 0 && nopen > 0 && (long long)nleft * pitch <= (long long)a.list_cap) {
         if (tid == 0 && nopen < kp) open_list[nopen] = (uint16_t)kp;   // what list entries beyond nopen name (none if nopen = kp)
+        // the far corner of the tile: only tiles that sort need it (in every tile it cost 7 % on 60 000 scans of three points)
+        const float far[3] = {act ? px[tid] : mnx, act ? py[tid] : mny, act ? pz[tid] : mnz};
+#pragma unroll
+        for (int ax = 0; ax < 3; ++ax) {
+            uint32_t hi = f2ord(far[ax]);
+            for (int d = 32; d >= 1; d >>= 1) hi = max(hi, (uint32_t)__shfl_xor((int)hi, d, 64));
+            if (lane == 0) atomicMax(&red[8 + ax], hi);
+        }
         __syncthreads();
         // the pattern of the tile's squared diagonal bounds that of every distance in it (rounding is monotone)
         const unsigned int top = __float_as_uint(dist2(ord2f(red[8]) - mnx, ord2f(red[9]) - mny, ord2f(red[10]) - mnz));
