@@ -61,11 +61,13 @@ __global__ __launch_bounds__(1024) void k_pool_meta(PoolArgs a)
 {
     __shared__ int lds[17];
     __shared__ int bad;
+    __shared__ int spread[2];                            // some scan of these 1024 has many tiles, by parity of the pass
     __shared__ int first_tile[1024];
     __shared__ int3 scan_rows[1024];
     const int tid = threadIdx.x;
     if (tid == 0) {
         bad = 0;
+        spread[0] = spread[1] = -1;
         *a.tile_counter = 0;
     }
     __syncthreads();
@@ -88,28 +90,36 @@ __global__ __launch_bounds__(1024) void k_pool_meta(PoolArgs a)
                 rows = (tiles - 1) * per_full + (last + a.rho - 1) / a.rho;
             }
         }
+        int* const many = &spread[(base >> 10) & 1];
+        if (tiles > 4) *many = base;
         int ttot, otot;
         const int tpre = block_excl_scan(tiles, &ttot, lds);
         const int opre = block_excl_scan(rows, &otot, lds);
-        if (b < a.n_scans) {
-            a.pooled_offsets[b] = ocarry + opre;
-        }
-        // Rows of the tile table: a thread takes every 1024th and finds its scan, so that a scan of hundreds of tiles is not
-        // one thread's loop (200 000 points in one scan: 20 -> 5 us).
-        first_tile[tid] = tpre;                          // at the threads without a scan: ttot
-        scan_rows[tid] = make_int3(p0, nb, ocarry + opre);
-        __syncthreads();
-        for (int t = tid; t < ttot && tcarry + t < a.n_tiles_ub; t += 1024) {
-            int lo = 0, hi = 1024;                       // the last scan that begins at or before t (those without tiles come first)
-            while (hi - lo > 1) {
-                const int mid = (lo + hi) >> 1;
-                if (first_tile[mid] <= t) lo = mid; else hi = mid;
+        if (b < a.n_scans) a.pooled_offsets[b] = ocarry + opre;
+        // Rows of the tile table. Short scans: every thread writes its own scan's. With a longer one a thread takes every 1024th
+        // row and finds its scan, so that a scan of hundreds of tiles is not one thread's loop (200 000 points in one scan: 20 -> 5
+        // us; the search and its two barriers for 60 000 scans of three points: 128 -> 179).
+        if (*many != base) {
+            for (int t = 0; t < tiles && tcarry + tpre + t < a.n_tiles_ub; ++t) {
+                const int r0 = p0 + t * a.tile;
+                a.tile_info[tcarry + tpre + t] = make_int4(r0, min(a.tile, p0 + nb - r0), ocarry + opre + t * per_full, b);
             }
-            const int3 sc = scan_rows[lo];
-            const int k = t - first_tile[lo], r0 = sc.x + k * a.tile;
-            a.tile_info[tcarry + t] = make_int4(r0, min(a.tile, sc.x + sc.y - r0), sc.z + k * per_full, base + lo);
+        } else {
+            first_tile[tid] = tpre;                      // at the threads without a scan: ttot
+            scan_rows[tid] = make_int3(p0, nb, ocarry + opre);
+            __syncthreads();
+            for (int t = tid; t < ttot && tcarry + t < a.n_tiles_ub; t += 1024) {
+                int lo = 0, hi = 1024;                   // the last scan that begins at or before t (those without tiles come first)
+                while (hi - lo > 1) {
+                    const int mid = (lo + hi) >> 1;
+                    if (first_tile[mid] <= t) lo = mid; else hi = mid;
+                }
+                const int3 sc = scan_rows[lo];
+                const int k = t - first_tile[lo], r0 = sc.x + k * a.tile;
+                a.tile_info[tcarry + t] = make_int4(r0, min(a.tile, sc.x + sc.y - r0), sc.z + k * per_full, base + lo);
+            }
+            __syncthreads();
         }
-        __syncthreads();
         tcarry += ttot;
         ocarry += otot;
     }

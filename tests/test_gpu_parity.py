@@ -1356,6 +1356,20 @@ def test_pool_candidates_over_many_octaves_of_distance(octaves):
         check_pool(c, None, feat, bo, 1024, rho, voxel, "zorder_div", "max")
 
 
+@pytest.mark.parametrize("at", [0, 1023, 1024, 2500])
+def test_pool_many_short_scans_around_a_long_one(at):
+    """The tile table is written 1024 scans at a time: those of short scans (at most four tiles) by the scan's own thread, those
+    beside a longer one by all threads. 2600 scans, some empty, one of 5 or 9 tiles at the ends and edges of the 1024."""
+    rng = np.random.default_rng(48)
+    for long in (5 * 64, 4 * 64 + 1, 4 * 64, 9 * 64 - 1):
+        sizes = rng.integers(0, 9, 2600)
+        sizes[at] = long
+        bo = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+        c = rng.random((int(bo[-1]), 3)).astype(np.float32)
+        feat = wl.f32_to_bf16_bits(rng.standard_normal((len(c), 8)).astype(np.float32))
+        check_pool(c, None, feat, bo, 64, 2, 0.1, "zorder_div", "max")
+
+
 def test_pool_empty_input_and_bad_offsets():
     z = np.zeros((0, 3), np.float32)
     got = f3d.inbucket_pool(dev(z), None, dev(np.zeros((0, 8), np.uint16), torch.bfloat16), None, 1024, 2, 0.1)
