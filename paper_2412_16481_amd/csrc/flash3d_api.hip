@@ -292,7 +292,7 @@ static int bucketize_on(const Plan& pl, char* ws, const float* coords, const int
     int schedule = p->schedule;
     if (schedule == F3D_SCHEDULE_SCANS && !pl.scans) return F3D_ERR_UNSUPPORTED;
     // scans whose points fit the registers of a workgroup (see psh_small.hip)
-    const bool small = schedule == F3D_SCHEDULE_AUTO && f3d::psh_small_eligible(n, pl.max_scan_points, pl.kcap, pl.scans);
+    const bool small = schedule == F3D_SCHEDULE_AUTO && f3d::psh_small_eligible(n, pl.max_scan_points, pl.kcap, p->n_probes, pl.scans);
     if (pl.scans) schedule = F3D_SCHEDULE_SCANS;
     if (schedule == F3D_SCHEDULE_AUTO) schedule = fast_ok ? F3D_SCHEDULE_STEPS : F3D_SCHEDULE_GENERAL;
     if (schedule == F3D_SCHEDULE_STEPS && !fast_ok) return F3D_ERR_UNSUPPORTED;

@@ -60,7 +60,7 @@ hipError_t psh_fast_launch(const PshArgs& args, hipStream_t stream);  // small c
 hipError_t psh_scan_launch(const PshArgs& args, int32_t* left_idx, int32_t* surv_pos, unsigned long long* voxels,
                            unsigned long long* surv_hash, hipStream_t stream);    // one workgroup per scan: batches of many scans
 hipError_t psh_small_launch(const PshArgs& args, hipStream_t stream); // one workgroup per scan, points in registers
-bool psh_small_eligible(long long n, long long max_scan_points, int kcap, bool scans);   // scans: psh_scan_launch would be taken else
+bool psh_small_eligible(long long n, long long max_scan_points, int kcap, int n_probes, bool scans);   // scans: psh_scan_launch would be taken else
 bool psh_scan_eligible(int kcap);
 bool psh_fast_eligible(long long max_scan_points, int kcap);
 // points per workgroup of psh_fast_launch (PshArgs::chunk); `half`: the workspace has psh_fast_most_chunks rows

@@ -172,11 +172,39 @@ def test_bucketize_small_scans_eight_points_per_thread(hash):
     rng = np.random.default_rng(36)
     for n in (4097, 5000, 8191, 8192, 8193):
         check_bucketize(clustered_cloud(rng, n), None, 0.05, 64 if n <= 8192 else 128, 4, hash, n_probes=(n % 7))
-        check_bucketize((rng.random((n, 3)) * 4.0).astype(np.float32), None, 0.0005, 256, 4, hash, probe_mode="seeded", probe_seed=3)
+        for probe_mode in ("seeded", "axes"):     # codes of more than 30 bits
+            check_bucketize((rng.random((n, 3)) * 4.0).astype(np.float32), None, 0.0005, 256, 4, hash, probe_mode=probe_mode, probe_seed=3)
     check_bucketize((rng.random((8192, 3)) * 4.0).astype(np.float32), None, 0.05, 32, 2, hash)    # buckets of 16 rows, 512 of them
     bo = np.array([0, 8192, 8192, 8193, 12289, 20000, 25121], dtype=np.int32)
     c = np.concatenate([clustered_cloud(rng, int(k), float(i)) for i, k in enumerate(np.diff(bo)) if k])
     check_bucketize(c, bo, 0.05, 128, 4, hash, max_scan_points=8192)
+
+
+@pytest.mark.parametrize("hash", HASHES)
+def test_bucketize_small_scans_every_width_and_number_of_probes(hash):
+    # one to eight groups of 64 per wave, at both ends of each and on both sides of the line to the other path (4096 points and 682
+    # more per probe); few points left (they change waves) and most of them
+    rng = np.random.default_rng(39)
+    for n in (1024, 1025, 2048, 2049, 3072, 3073, 4096, 5120, 5121, 6144, 6145, 7168, 7169, 8192):
+        for c in (clustered_cloud(rng, n), (rng.random((n, 3)) * 4.0).astype(np.float32)):
+            check_bucketize(c, None, 0.05, 128, 4, hash)
+    for n_probes in range(6):
+        for n in (4096 + n_probes * 2048 // 3, 4097 + n_probes * 2048 // 3):
+            check_bucketize(clustered_cloud(rng, n), None, 0.05, 128, 4, hash, n_probes)
+            check_bucketize((rng.random((n, 3)) * 4.0).astype(np.float32), None, 0.05, 512, 4, hash, n_probes)
+
+
+@pytest.mark.parametrize("per_bucket,edge", [(1600, 4096 // 6), (3200, 6144 // 6), (5120, 8192 // 6)])
+def test_bucketize_small_scans_at_the_edge_of_few_points_left(per_bucket, edge):
+    # all but three points in one voxel: its bucket takes `per_bucket`, `edge` are left and change waves, one more and they stay.
+    # Probes over the whole box reach the other bucket and place some of them
+    table = [[0, 0, 0], [9, 0, 0], [0, 9, 0], [9, 9, 9], [3, 0, 7], [-1, -1, -1]]
+    for left in (edge - 1, edge, edge + 1):
+        c = np.full((per_bucket + left, 3), 0.5, dtype=np.float32)
+        c[[7, 1000, 1500]] = [[9.5, 9.5, 9.5], [9.5, 0.5, 0.5], [0.5, 9.5, 0.5]]
+        for hash in HASHES:
+            check_bucketize(c, None, 1.0, 4 * per_bucket, 4, hash, probe_mode="table", probe_table=table)
+            check_bucketize(c, None, 1.0, 4 * per_bucket, 4, hash)
 
 
 @pytest.mark.parametrize("hash", HASHES)
