@@ -230,13 +230,17 @@ __global__ __launch_bounds__(STH, WPE) void k_pshs_scan(PshArgs a, int32_t* left
         auto probe_all = [&](auto narrow_tag) __attribute__((always_inline)) {
             constexpr bool NARROW = decltype(narrow_tag)::value;
             const int* room = roomb[cur];
-            for (int pos0 = l0; pos0 < l1; pos0 += 64 * SU) {
-                const int entries = min(l1 - pos0, 64 * SU);
-                unsigned long long v[SU], hs[SU];
-                int i[SU];
-                bool any[SU];
+            auto look_up = [&](auto groups, int pos0) __attribute__((always_inline)) {
+                constexpr int G = decltype(groups)::value;
+                const int entries = min(l1 - pos0, 64 * G);
+                // with 64 registers the probes' fields, kept over the loop, spill (118 registers: 300 sweeps of 20000 points 302 -> 329 us;
+                // read again each time 232)
+                if (HASH == 3 && WPE == 8) asm volatile("" ::: "memory");
+                unsigned long long v[G], hs[G];
+                int i[G];
+                bool any[G];
 #pragma unroll
-                for (int s = 0; s < SU; ++s) {
+                for (int s = 0; s < G; ++s) {
                     const uint32_t e = (uint32_t)(pos0 + min(s * 64 + lane, entries - 1));
                     i[s] = left_idx[e];
                     v[s] = NARROW ? reinterpret_cast<const uint32_t*>(voxels)[e] : voxels[e];
@@ -248,7 +252,7 @@ __global__ __launch_bounds__(STH, WPE) void k_pshs_scan(PshArgs a, int32_t* left
                     if (r > a.n_probes) break;
                     const ZProbe zp = zps[HASH == 3 ? r - 1 : 0];
 #pragma unroll
-                    for (int s = 0; s < SU; ++s) {
+                    for (int s = 0; s < G; ++s) {
                         int h;
                         if (NARROW) {
                             h = zdiv30(zprobe30((uint32_t)v[s], (uint32_t)zp.mask, (uint32_t)zp.step, (uint32_t)zp.lim, (uint32_t)zp.vmax, (r - 1) & 1), cfg);
@@ -265,7 +269,7 @@ __global__ __launch_bounds__(STH, WPE) void k_pshs_scan(PshArgs a, int32_t* left
                     }
                 }
 #pragma unroll
-                for (int s = 0; s < SU; ++s) {
+                for (int s = 0; s < G; ++s) {
                     const bool go = any[s] && s * 64 + lane < entries;
                     const unsigned long long m = __builtin_amdgcn_ballot_w64(go);
                     if (go) {
@@ -276,7 +280,14 @@ __global__ __launch_bounds__(STH, WPE) void k_pshs_scan(PshArgs a, int32_t* left
                     }
                     nsurv += __popcll(m);
                 }
-            }
+            };
+            // Blocks, and the last groups one by one: a wave with a few points left would hash three empty groups beside them (100 scans
+            // of 9000 points, Z-order-mod: 77 -> 63 us with that and with the steps ended when the last survivor is placed). Probes
+            // that are arithmetic on the code are cheap enough for a block of two or three groups.
+            constexpr int ONE_BY_ONE = HASH == 3 ? 1 : SU - 1;
+            int pos0 = l0;
+            for (; l1 - pos0 > 64 * ONE_BY_ONE; pos0 += 64 * SU) look_up(std::integral_constant<int, SU>{}, pos0);
+            for (; pos0 < l1; pos0 += 64) look_up(std::integral_constant<int, 1>{}, pos0);
         };
         if (HASH == 3 && narrow) probe_all(std::true_type{});
         else probe_all(std::false_type{});
@@ -300,6 +311,7 @@ __global__ __launch_bounds__(STH, WPE) void k_pshs_scan(PshArgs a, int32_t* left
                     }
                 }
                 __syncthreads();
+                if (s_surv == 0) break;               // uniform: changed again behind the second barrier only
                 join_waves<true>(tid, K, cnt, room, roomb[cur ^ 1]);
                 __syncthreads();
                 int got = 0;
@@ -337,7 +349,10 @@ __global__ __launch_bounds__(STH, WPE) void k_pshs_scan(PshArgs a, int32_t* left
                     }
                 }
                 for (int k = lane; k < K; k += 64) mine[k] = 0u;
-                if (lane == 0 && got) atomicAdd(&s_round[r], got);
+                if (lane == 0 && got) {
+                    atomicAdd(&s_round[r], got);
+                    atomicSub(&s_surv, got);
+                }
                 nplaced += got;
                 cur ^= 1;
             }
