@@ -18,10 +18,13 @@
 // Bound: HBM, mostly the writes. The workgroups of an XCD keep more output rows open (6 MB at 256 channels) than its L2
 // holds, so a line that is written in two halves a tile apart leaves L2 half full: pairs of 32-column blocks are stored
 // together, whole lines per instruction (914601 rows, 256 -> 3 x 256: WRITE_SIZE 1.60 -> 1.37 GB = what there is to write).
-// The stores are non-temporal: nothing here reads a result again, and kept in L2 the lines only push out x, W and the residual
-// (both maps of a layer, us: 100000 rows of 128 channels 53.5 -> 41.0, 400000 of 64 77.5 -> 62.5, 200000 of 256 214 -> 194, 914601 of
-// 256 847 -> 820; with an attention pass between them, which reads the results, 0 to 7 % less in all). Loads of x or the
-// residual marked the same way cost 14 and 8 % more: both are read 16 bytes of a line at a time.
+// Results of 4 MB and more are stored non-temporally: kept in L2 their lines only push out x, W and the residual (both maps of a layer,
+// us: 100000 rows of 128 channels 53.5 -> 41.0, 400000 of 64 77.5 -> 62.5, 200000 of 256 214 -> 194, 914601 of 256 847 -> 820).
+// Smaller ones are still in L2 when the attention reads them. The q, k, v map with the attention behind it, ordinary / non-temporal
+// stores, us: 3 MB of results (8000 rows of 64, 4000 of 128, 2000 of 256) 11.0 / 11.2, 12.5 / 13.0, 15.8 / 16.0; 6 MB (16000,
+// 8000, 4000) 13.3 / 13.4, 16.3 / 15.4, 20.5 / 19.6; 19 MB (50000 of 64) 28.9 / 27.3; 300 MB (200000 of 256) 238 / 232. Between
+// 40 and 160 MB the pair alone takes 1 to 6 % longer (100000 rows of 256 113 / 120), the whole layer with its output map
+// 3 % less to 1 % more. Loads of x or the residual marked the same way cost 14 and 8 % more: both are read 16 bytes of a line at a time.
 // Measured at 900000 rows with ordinary stores, LayerNorm + q, k, v map / output map with residual: 256 channels 636 -> 530 / 292 -> 242 us, 128
 // 253 -> 213 / 133 -> 111, 64 128 -> 89 / 46 -> 43. A third resident tile and 256 rows per workgroup were no faster.
 #include <hip/hip_runtime.h>
@@ -65,7 +68,7 @@ struct Tile {
 };
 
 // LN: LayerNorm in front of the map; RES: a residual is added behind it
-template <int CI, bool LN, bool RES>
+template <int CI, bool LN, bool RES, bool STREAMED>   // STREAMED: results past the caches
 __global__ __launch_bounds__(LTH, 3) void k_ln_linear(LinearArgs a)
 {
     using T = Tile<CI>;
@@ -269,7 +272,11 @@ __global__ __launch_bounds__(LTH, 3) void k_ln_linear(LinearArgs a)
                 for (int k = 0; k < 4; ++k) {
                     const uint4 y = sy[wave][yget + 64 * k];
                     const u32x4 yv = {y.x, y.y, y.z, y.w};
-                    if (yrow[k] >= 0) __builtin_nontemporal_store(yv, reinterpret_cast<u32x4*>(ob + (size_t)yrow[k] * per_out));
+                    if (yrow[k] >= 0) {
+                        u32x4* const to = reinterpret_cast<u32x4*>(ob + (size_t)yrow[k] * per_out);
+                        if (STREAMED) __builtin_nontemporal_store(yv, to);
+                        else *to = yv;
+                    }
                 }
             }
         }
@@ -285,6 +292,9 @@ __global__ __launch_bounds__(LTH, 3) void k_ln_linear(LinearArgs a)
     }
 }
 
+// Results of this size and more are stored past the caches (see above)
+constexpr size_t STREAMED_BYTES = (size_t)4 << 20;
+
 // an output tensor shares memory with x
 bool in_place(const LinearArgs& a)
 {
@@ -296,8 +306,8 @@ bool in_place(const LinearArgs& a)
     return false;
 }
 
-template <int CI, bool LN, bool RES>
-hipError_t launch_one(const LinearArgs& a, hipStream_t stream)
+template <int CI, bool LN, bool RES, bool STREAMED>
+hipError_t launch_form(const LinearArgs& a, hipStream_t stream)
 {
     const unsigned blocks = (unsigned)((a.n + LBM - 1) / LBM);
     if (blocks == 0) return hipSuccess;
@@ -310,11 +320,17 @@ hipError_t launch_one(const LinearArgs& a, hipStream_t stream)
     const size_t lds = (size_t)a.c_out * 4 + (size_t)a.c_out / 16 * sizeof(uint16_t*);
     // tiles and results in static LDS, 32 or 48 KB: from 3000 columns or so on the sum passes what a kernel gets unasked
     if (2 * Tile<CI>::BYTES + LNW * 4096 + lds > 60000) {
-        const hipError_t e = hipFuncSetAttribute((const void*)k_ln_linear<CI, LN, RES>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        const hipError_t e = hipFuncSetAttribute((const void*)k_ln_linear<CI, LN, RES, STREAMED>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    k_ln_linear<CI, LN, RES><<<dim3(blocks, split), LTH, lds, stream>>>(a);
+    k_ln_linear<CI, LN, RES, STREAMED><<<dim3(blocks, split), LTH, lds, stream>>>(a);
     return hipGetLastError();
+}
+
+template <int CI, bool LN, bool RES>
+hipError_t launch_one(const LinearArgs& a, hipStream_t stream)
+{
+    return (size_t)a.n * a.c_out * 2 >= STREAMED_BYTES ? launch_form<CI, LN, RES, true>(a, stream) : launch_form<CI, LN, RES, false>(a, stream);
 }
 
 template <int CI>

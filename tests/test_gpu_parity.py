@@ -1489,6 +1489,16 @@ def test_ln_linear_row_and_column_splits(c_in, c_out, n_outs):
     check_ln_linear(65536 + 25, c_in, c_out, n_outs, rng, ln=True, gather=True, statistical=False)
 
 
+@pytest.mark.parametrize("c", [64, 128, 256])
+def test_ln_linear_stored_through_and_past_the_caches(c):
+    # results of 4 MB (and more) are stored past the caches: the last size below and the first one at it, both forms of the store
+    rng = np.random.default_rng(600 + c)
+    for c_out, n_outs, ln in ((3 * c, 3, True), (c, 1, False)):
+        edge = -(-(4 << 20) // (2 * c_out))
+        for n in (edge - 1, edge):
+            check_ln_linear(n, c, c_out, n_outs, rng, ln=ln, with_res=not ln, gather=ln, scatter=not ln)
+
+
 @pytest.mark.parametrize("c_out,n_outs", [(3648, 3), (4096, 1), (4096, 4)])
 @pytest.mark.parametrize("c_in", [64, 128, 256])
 def test_ln_linear_most_output_columns(c_in, c_out, n_outs):
