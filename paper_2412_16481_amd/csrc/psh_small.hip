@@ -163,35 +163,64 @@ __global__ __launch_bounds__(STH) void k_pshs_small(PshArgs a)
 #pragma unroll
         for (int s = 0; s < G; ++s) hh[s0 + s] |= rank[s] << 16;
     };
-    if (w0 < nb) {
-        // no more groups than there are: a scan of up to 1024 points has one
-        if (grp == 1) rank_groups(std::integral_constant<int, 1>{}, 0);
-        else if (grp == 2) rank_groups(std::integral_constant<int, 2>{}, 0);
-        else if (grp == 3) rank_groups(std::integral_constant<int, 3>{}, 0);
-        else rank_groups(std::integral_constant<int, 4>{}, 0);
-        if constexpr (PPT > 4) {
-            if (grp == 5) rank_groups(std::integral_constant<int, 1>{}, 4);
-            else if (grp == 6) rank_groups(std::integral_constant<int, 2>{}, 4);
-        }
-        if constexpr (PPT > 6) {
-            if (grp == 7) rank_groups(std::integral_constant<int, 3>{}, 4);
-            else if (grp == 8) rank_groups(std::integral_constant<int, 4>{}, 4);
-        }
-    }
-    __syncthreads();
-    join_waves<true>(tid, K, cnt, roomb[0], roomb[1]);
-    __syncthreads();
+    if (PPT == 4 && grp == 4) {
+        // Counted by adds, and ranked behind the join: with all four groups full the ranks wait less there (a forward pass over 4096
+        // points 43.7 -> 43.0 us). With fewer groups the ranks go before the join (600 scans of 300 points 42 -> 39).
 #pragma unroll
-    for (int s = 0; s < PPT; ++s) {
-        if (s >= grp || w0 + 64 * s >= nb) continue;
-        const int h = hh[s] & 0xFFFF, rank = (int)mine[h] + (hh[s] >> 16);
-        const bool act = i0 + 64 * s < nb, fits = rank < (h == K - 1 ? cfg.lastcap : a.S);
-        if (act && fits) {
-            const int i = p0 + i0 + 64 * s, dst = p0 + h * a.S + rank;
-            a.inv_perm[(uint32_t)i] = dst;
-            a.perm[(uint32_t)dst] = i;
+        for (int s = 0; s < PPT; ++s)
+            if (i0 + 64 * s < nb) atomicAdd(&mine[hh[s]], 1u);
+        __syncthreads();
+        join_waves<true>(tid, K, cnt, roomb[0], roomb[1]);
+        __syncthreads();
+        int h[PPT], rank[PPT];
+        bool act[PPT];
+#pragma unroll
+        for (int s = 0; s < PPT; ++s) {
+            h[s] = hh[s];
+            act[s] = i0 + 64 * s < nb;
         }
-        left |= act && !fits ? 1u << s : 0u;
+        wave_ranks<PPT>(h, act, keybits, mine, rank);
+#pragma unroll
+        for (int s = 0; s < PPT; ++s) {
+            const bool fits = rank[s] < (h[s] == K - 1 ? cfg.lastcap : a.S);
+            if (act[s] && fits) {
+                const int i = p0 + i0 + 64 * s, dst = p0 + h[s] * a.S + rank[s];
+                a.inv_perm[(uint32_t)i] = dst;
+                a.perm[(uint32_t)dst] = i;
+            }
+            left |= act[s] && !fits ? 1u << s : 0u;
+        }
+    } else {
+        if (w0 < nb) {
+            // no more groups than there are: a scan of up to 1024 points has one
+            if (grp == 1) rank_groups(std::integral_constant<int, 1>{}, 0);
+            else if (grp == 2) rank_groups(std::integral_constant<int, 2>{}, 0);
+            else if (grp == 3) rank_groups(std::integral_constant<int, 3>{}, 0);
+            else rank_groups(std::integral_constant<int, 4>{}, 0);
+            if constexpr (PPT > 4) {
+                if (grp == 5) rank_groups(std::integral_constant<int, 1>{}, 4);
+                else if (grp == 6) rank_groups(std::integral_constant<int, 2>{}, 4);
+            }
+            if constexpr (PPT > 6) {
+                if (grp == 7) rank_groups(std::integral_constant<int, 3>{}, 4);
+                else if (grp == 8) rank_groups(std::integral_constant<int, 4>{}, 4);
+            }
+        }
+        __syncthreads();
+        join_waves<true>(tid, K, cnt, roomb[0], roomb[1]);
+        __syncthreads();
+#pragma unroll
+        for (int s = 0; s < PPT; ++s) {
+            if (s >= grp || w0 + 64 * s >= nb) continue;
+            const int h = hh[s] & 0xFFFF, rank = (int)mine[h] + (hh[s] >> 16);
+            const bool act = i0 + 64 * s < nb, fits = rank < (h == K - 1 ? cfg.lastcap : a.S);
+            if (act && fits) {
+                const int i = p0 + i0 + 64 * s, dst = p0 + h * a.S + rank;
+                a.inv_perm[(uint32_t)i] = dst;
+                a.perm[(uint32_t)dst] = i;
+            }
+            left |= act && !fits ? 1u << s : 0u;
+        }
     }
     for (int k = lane; k < K; k += 64) mine[k] = 0u;
     int n_left = 0;                                   // points of this wave that are not placed
