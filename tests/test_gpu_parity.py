@@ -233,6 +233,29 @@ def test_bucketize_quotients_at_bucket_boundaries(schedule):
         check_bucketize(c, None, 0.25, cap, 4, "zorder_div", schedule=schedule)
 
 
+def compact3(code):
+    """Every third bit of the codes: one axis of a Z-order code of up to 60 bits."""
+    return sum(((code >> np.uint64(3 * k)) & np.uint64(1)) << np.uint64(k) for k in range(20)).astype(np.int64)
+
+
+@pytest.mark.parametrize("bits", [10, 12, 20])
+@pytest.mark.parametrize("schedule,n", [("auto", 4000), ("auto", 8000), ("scans", 16000), ("steps", 32000), ("general", 130000)])
+def test_bucketize_quotients_beside_multiples_of_other_divisors(schedule, n, bits):
+    # Z-order-div over a voxel box of 2^bits per axis with 250 to 8125 buckets: the divisor is no power of two, so its reciprocal is
+    # rounded. Codes one below, at and one above its multiples, up to 30 bits (the 32-bit form), 36 and 60 (the conversion to
+    # binary32 rounds too), and random ones; buckets of 16 rows, so that a point in the wrong one moves others
+    rng = np.random.default_rng(40)
+    K = n // 16
+    D = (2 ** (3 * bits) - 1) // K + 1
+    assert D & (D - 1)
+    near = np.array([k * D + d for k in range(1, K) for d in (-1, 0, 1)], dtype=np.uint64)
+    ends = np.array([0, 2 ** (3 * bits) - 1], dtype=np.uint64)          # the corners of the box
+    code = rng.permutation(np.concatenate([near, near, ends, rng.integers(0, 2 ** (3 * bits), n - 2 * len(near) - 2, dtype=np.uint64)]))
+    c = np.stack([compact3(code >> np.uint64(a)) for a in range(3)], axis=1) + 0.5      # exact in binary32
+    for n_probes in (0, 6):
+        check_bucketize(c.astype(np.float32), None, 1.0, 64, 4, "zorder_div", n_probes, schedule=schedule)
+
+
 @pytest.mark.parametrize("hash", HASHES)
 def test_bucketize_small_scans_in_registers(hash):
     # scans that fit one workgroup's registers: around a wave, a workgroup, and one past the last (another path); clustered
@@ -280,10 +303,11 @@ def test_bucketize_small_and_ragged_sizes(n):
 
 @pytest.mark.parametrize("hash", HASHES)
 def test_bucketize_half_chunks_on_the_one_launch_per_step_path(hash):
-    # batches small enough for chunks of 1024 points: scans around a chunk, empty ones, one past the last chunk (256) and one past
-    # the largest count matrix, most points left over (their rank runs on over chunks and buckets of odd capacity) or hardly any
+    # batches small enough for chunks of 1024 points: scans around a chunk, empty ones, the most chunks (256 with 262143 points, the
+    # largest count matrix as well) and the first size past them, most points left over (their rank runs on over chunks and
+    # buckets of odd capacity) or hardly any
     rng = np.random.default_rng(37)
-    for sizes in ([1023, 0, 1025, 1024, 2049, 1, 9000, 0], [65536], [261119], [262144], [65537, 3]):
+    for sizes in ([1023, 0, 1025, 1024, 2049, 1, 9000, 0], [65536], [261119], [262143], [262144], [65537, 3]):
         bo = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
         cap = 128 if max(sizes) < 10000 else 2048 if max(sizes) > 70000 else 128      # 65536 points in 2048 buckets
         for cloud in (lambda k: clustered_cloud(rng, k), lambda k: rng.random((k, 3)) * 4.0):
