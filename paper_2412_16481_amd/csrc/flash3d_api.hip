@@ -66,9 +66,10 @@ struct Plan {
     size_t o_status, o_p0, o_c0, o_mm, o_cnt, o_cnt2, o_hist, o_key, o_left, o_leftpre, o_freepre, o_inv, o_rc, o_cfg, o_done, o_ci, o_mmpart;
     // canonical order only
     size_t o_obox, o_okeys, o_oidx0, o_oidx1, o_ocoords, o_operm;
-    // one workgroup per scan only: the two lists of points still unplaced (index, packed voxel)
+    // one workgroup per scan only: the points the direct step leaves (number in the scan, voxel), and of those the ones a probe
+    // can place (position in the first list, packed bucket numbers of the probes; their number in the scan is kept in `key`)
     bool scans;
-    size_t o_lidx0, o_lidx1, o_lvox0, o_lvox1;
+    size_t o_left_idx, o_surv_pos, o_voxels, o_surv_hash;
 };
 
 int check_params(int64_t n, int32_t n_scans, const f3d_params* p)
@@ -157,10 +158,10 @@ void make_plan(int64_t n, int32_t n_scans, const f3d_params* p, Plan* pl, bool h
     }
     pl->scans = wants_scans(n, n_scans, p, pl->max_scan_points, pl->kcap);
     if (pl->scans) {
-        pl->o_lidx0 = take((size_t)n * 4);
-        pl->o_lidx1 = take((size_t)n * 4);
-        pl->o_lvox0 = take((size_t)n * 8);
-        pl->o_lvox1 = take((size_t)n * 8);
+        pl->o_left_idx = take((size_t)n * 4);
+        pl->o_surv_pos = take((size_t)n * 4);
+        pl->o_voxels = take((size_t)n * 8);
+        pl->o_surv_hash = take((size_t)n * 8);
     }
     pl->bytes = at;
 }
@@ -321,8 +322,8 @@ static int bucketize_on(const Plan& pl, char* ws, const float* coords, const int
     if (small)
         e = f3d::psh_small_launch(a, (hipStream_t)stream);
     else if (schedule == F3D_SCHEDULE_SCANS)
-        e = f3d::psh_scan_launch(a, (int32_t*)(ws + pl.o_lidx0), (int32_t*)(ws + pl.o_lidx1), (unsigned long long*)(ws + pl.o_lvox0),
-                                 (unsigned long long*)(ws + pl.o_lvox1), (hipStream_t)stream);
+        e = f3d::psh_scan_launch(a, (int32_t*)(ws + pl.o_left_idx), (int32_t*)(ws + pl.o_surv_pos), (unsigned long long*)(ws + pl.o_voxels),
+                                 (unsigned long long*)(ws + pl.o_surv_hash), (hipStream_t)stream);
     else
         e = schedule == F3D_SCHEDULE_GENERAL ? f3d::psh_launch(a, (hipStream_t)stream) : f3d::psh_fast_launch(a, (hipStream_t)stream);
     if (e == hipSuccess && order)

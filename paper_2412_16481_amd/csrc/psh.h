@@ -43,8 +43,9 @@ struct PshArgs {
     int32_t* cnt;      // [max_buckets] fill level of every bucket
     int32_t* cnt_next;
     int32_t* hist;     // [chunks][kcap]
-    uint32_t* key;     // [n] per point: (bucket << 12 | rank inside chunk) or KEY_PLACED
-    int32_t* left;     // [chunks] leftovers per chunk
+    uint32_t* key;     // [n] per point: (bucket << 12 | rank inside chunk), KEY_PLACED, or on the path with one launch per step KEY_WAIT (left, and
+                       // no contender of the last step: its probe met a full bucket); one workgroup per scan: a list of point numbers
+    int32_t* left;     // [chunks] leftovers per chunk (one launch per step: only those waiting when the last probe step ranks)
     int32_t* leftpre;  // [chunks]
     int32_t* freepre;  // [max_buckets]
     void* cfg;         // [n_scans] per-scan hash settings (fast path)

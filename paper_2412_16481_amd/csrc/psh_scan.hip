@@ -33,9 +33,9 @@ namespace f3d {
 
 namespace {
 
-constexpr int SKMAX = 1024;        // most buckets per scan on this path (ten bits in a list entry; LDS: 76 bytes per bucket)
+constexpr int SKMAX = 1024;        // most buckets per scan on this path (ten bits in a list entry; LDS: 72 bytes per bucket)
 
-// dynamic LDS, in 32-bit words: cnt[SNW][K] room[2][K] spare[K]
+// dynamic LDS, in 32-bit words: cnt[SNW][K] room[2][K] spare[SNW]
 // The hash function is a template parameter: the kernel holds many scan-wide values in scalar registers, and the
 // branches between four hash functions cost enough of them to spill.
 // WPE = waves per SIMD the kernel is compiled for: 4 (128 registers, one workgroup per compute unit) or 8 (64
