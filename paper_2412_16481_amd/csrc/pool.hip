@@ -388,7 +388,7 @@ __device__ __forceinline__ int lanes_out_of_order(const unsigned int (&key)[NPL]
 // `list` rows have `pitch` entries (a multiple of 8, >= nopen), each four times an id.
 // Bound: the vector ALU. Pooling 914 601 points of sensor sweeps took 2254 us (825 million vector instructions) with a network
 // of moves, minima, maxima and selects, the full keys every time and candidates read eight words apart (all in the same
-// banks), 1654 (594) with the network as it is, and 1550 to 1300 (540 to 340) with the previous row's order to start from.
+// banks), 1654 (594) with the network as it is, and 1320 (358) with the previous row's order to start from.
 constexpr unsigned int DIST_MAX = 0x7FFDFFu;   // distances beyond; the 512 prefixes above are for entries without a sub-bucket
 template <int NPL>
 __device__ __forceinline__ void sort_choices(int nleft, int nopen, int pitch, unsigned int base, const uint16_t* left_list, const float* px,
@@ -640,16 +640,16 @@ __device__ __forceinline__ void rounds_of_two(int nleft, int pitch, int kp, cons
         if (__builtin_amdgcn_ballot_w64(contend) == 0ull) break;
         int* const w = reinterpret_cast<int*>(reinterpret_cast<char*>(win + par * kp) + c);
         if (contend) atomicMin(w, tid);
-        __builtin_amdgcn_wave_barrier();
-        const int lowest = contend ? *reinterpret_cast<volatile int*>(w) : -1;
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_sync();
+        const int lowest = contend ? *w : -1;
+        wave_lds_sync();
         if (contend) *reinterpret_cast<int*>(reinterpret_cast<char*>(stamp) + c) = -round;
         if (contend && lowest == tid) {
             rsub[orig] = (uint16_t)(c >> 2);
             walking = false;
             *w = 0x7FFFFFFF;
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_sync();
     }
 }
 

@@ -70,6 +70,15 @@ struct ScanCfg {
     int wide;               // some voxel coordinate of the scan needs more than 11 bits
 };
 
+// Behind this, lanes see what other lanes of their wave wrote to LDS before it. The hardware keeps a wave's LDS operations in
+// order; this keeps the compiler's.
+__device__ __forceinline__ void wave_lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 __device__ __forceinline__ int voxel_of(float c, float mn, float inv)
 {
     // three separate binary32 operations: subtract, multiply, floor. No product feeds a sum here, so there is nothing

@@ -326,11 +326,11 @@ __global__ __launch_bounds__(STH) void k_pshs_small(PshArgs a)
                     if (on) list[at + bits_below(m)] = get(s);
                     at += __popcll(m);
                 }
-                __builtin_amdgcn_wave_barrier();
+                wave_lds_sync();
 #pragma unroll
                 for (int s = 0; s < PPT; ++s)
                     if (64 * s < n) put(s, list[min(64 * s + lane, n - 1)]);
-                __builtin_amdgcn_wave_barrier();
+                wave_lds_sync();
             };
             auto close_up = [&](uint32_t from, int n) __attribute__((always_inline)) -> uint32_t {
                 uint32_t lo[PPT], to = 0;
