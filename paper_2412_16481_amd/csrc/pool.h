@@ -37,6 +37,7 @@ struct PoolArgs {
     uint16_t* lists;               // workspace: [n_slots][list_cap] sorted choices of the rows left, per workgroup
     size_t list_cap;
     int n_slots;                   // workgroups of the pooling kernel
+    int near_cap;                  // entries of the choice lists that fit into LDS (rho = 2; set by pool_launch)
 };
 
 hipError_t pool_launch(const PoolArgs& a, hipStream_t stream);

@@ -15,6 +15,7 @@
 
 #include "pool.h"
 #include "psh_common.h"
+#include <type_traits>
 
 
 namespace f3d {
@@ -393,13 +394,24 @@ constexpr unsigned int DIST_MAX = 0x7FFDFFu;   // distances beyond; the 512 pref
 template <int NPL>
 __device__ __forceinline__ void sort_choices(int nleft, int nopen, int pitch, unsigned int base, const uint16_t* left_list, const float* px,
                                              const float* py, const float* pz, const float4* o4, const uint16_t* open_list,
-                                             uint16_t* list)
+                                             uint16_t* list, int* taken)
 {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     unsigned int k32[NPL] = {};                          // the previous row's list, entries without a sub-bucket last
-    const int run = (nleft + PW - 1) / PW, p_begin = wave * run, p_end = min(p_begin + run, nleft);
+    // Five eighths of the rows are dealt out beforehand, the rest as the waves come for more: a row through the network takes three
+    // times as long as one that starts from the previous order (a room of 200 000: 365 -> 353 us, sensor sweeps 1236 -> 1220).
+    const int dealt = nleft * 5 / (8 * PW);
+    int p_begin = wave * dealt, p_end = p_begin + dealt;
     int misses = 2;                                      // rows in a row whose list was not nearly the previous one's
-    for (int p = p_begin; p < p_end; ++p) {
+    for (int p = p_begin;; ++p) {
+        if (p >= p_end) {
+            int t = 0;
+            if (lane == 0) t = atomicAdd(taken, 4);
+            p = p_begin = PW * dealt + __builtin_amdgcn_readfirstlane(t);
+            if (p >= nleft) break;
+            p_end = min(p + 4, nleft);
+            misses = 2;
+        }
         const bool ordered = misses < 2 || (p != p_begin && (p & 7) == 0);
         const int id = left_list[p];
         const float qx = px[id], qy = py[id], qz = pz[id];
@@ -445,9 +457,9 @@ __device__ __forceinline__ void sort_choices(int nleft, int nopen, int pitch, un
 #pragma unroll
             for (int r = 0; r < NPL; ++r) k32[r] = (unsigned int)key[r];
         }
-        unsigned int sid[NPL];   // four times the id: the byte offset of the sub-bucket's fill level. Entries beyond nopen: open_list[nopen]
+        unsigned int sid[NPL];   // what the rounds look up, see k_pool. Entries beyond nopen: open_list[nopen]
 #pragma unroll
-        for (int r = 0; r < NPL; ++r) sid[r] = 4u * (unsigned int)open_list[min((int)(k32[r] & 511u), nopen)];
+        for (int r = 0; r < NPL; ++r) sid[r] = (unsigned int)open_list[min((int)(k32[r] & 511u), nopen)];
         if (lane * NPL < pitch) {
             uint16_t* dst = list + (size_t)p * pitch + lane * NPL;
             if (NPL == 8) {
@@ -526,87 +538,119 @@ __device__ __forceinline__ bool join_passes(bool contend, int c, int tid, int rh
     return joined;
 }
 
+// Which of a chunk's eight entries are open: bit j for entry j. All eight reads are under way before the first is waited for.
+__device__ __forceinline__ unsigned int chunk_open(const uint4& c, const uint8_t* open)
+{
+    const unsigned int w[4] = {c.x, c.y, c.z, c.w};
+    unsigned int f[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) f[j] = open[(j & 1) ? w[j >> 1] >> 16 : w[j >> 1] & 0xFFFFu];
+    __builtin_amdgcn_sched_barrier(0);
+    return ((((f[7] << 1) | f[6]) << 2 | (f[5] << 1) | f[4]) << 4) | (((f[3] << 1) | f[2]) << 2) | (f[1] << 1) | f[0];
+}
+
 // The rounds for rho = 2. An open sub-bucket holds one row and has room for one: whoever contends for it knows that it
-// is closed after this round, without waiting for the winner. The contenders themselves mark it (with the round's number, so
-// that a search of the same round still sees it open), and a round needs one barrier instead of two. stamp[c]: OPEN while
-// open, minus the round in which it closed, 1 if it was full before the rounds; open in round t means stamp[c] < 1 - t.
-// Thread t speaks for the t-th row still walking, so that the lowest thread is the lowest row. Rows leave one or two per
+// is closed after this round, without waiting for the winner. The contenders themselves close it, and a round needs one
+// barrier. What is open is a byte each, held twice: round t looks up copy t & 1 and closes in the other one, and in the first a
+// round later, when nobody looks at it any more.
+// Thread t speaks for the t-th row still walking, so that the lowest thread is the lowest row. Of the lanes of a wave that
+// contend for what its first contender contends for only that one takes part in the minimum: in a dense cluster that is most
+// of them, and an LDS minimum takes its lanes one after the other where they meet. Rows leave one or two per
 // round: every 32 rounds they are closed up when fewer waves would hold them, and when one wave holds them all it goes on
-// alone, without barriers. A row looks up the eight entries of its chunk (16 bytes of its list) together: their reads overlap,
-// and the sign of stamp - threshold is shifted into a mask. (A chunk is read when it is entered; with the next one already on its
-// way to LDS the pooling of a room of 200 000 took 351 us instead of 333.)
-// Bound: the chain of LDS reads, one LDS minimum and a barrier per round. One room of
-// 200 000, a tile per compute unit: 360 us with all rows' waves kept to the end and shifts and selects for the mask, 333 now.
-constexpr int STAMP_OPEN = -(1 << 30);
-__device__ __forceinline__ void rounds_of_two(int nleft, int pitch, int kp, const uint16_t* lists, int* stamp, int* win, uint16_t* rsub,
-                                              uint32_t* moved, int* wave_rows, int* any3)
+// alone, without barriers. A row looks up the eight entries of its chunk (16 bytes of its list) together, and has the chunk
+// behind it in registers already. As soon as what is left of the lists, rows still walking times sub-buckets still open,
+// fits `near_cap` entries of LDS, it moves there.
+// Bound: the instructions of a round, one after the other in a few waves, and its two or three LDS round trips. Pooling a room of
+// 200 000 points (a tile per compute unit) / 914 601 points of sensor sweeps took 340 / 1313 us with words instead of bytes, every
+// contender in the minimum, the next chunk read when entered and the lists always in memory, and 310 / 1143 with this and the rows
+// of the sort dealt out as they are now (bits instead of bytes 388 / 1330 where that was 357 / 1322: more arithmetic per entry).
+__device__ __forceinline__ const uint8_t* rounds_of_two(int nleft, int nopen, int pitch, int kp, const uint16_t* lists, uint8_t* flags, int* win,
+                                                         uint16_t* rsub, uint32_t* moved, int* wave_rows, uint16_t* near, int near_cap)
 {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int chunks = pitch >> 3;
-    int orig = tid, idx = 0, at = 0;        // the row's place among those left at the start; next entry; chunk in `cur`
+    const int size = kp + 1;                // of a copy: sub-bucket kp is never open
+    int chunks = pitch >> 3, near_pitch = 0;
+    int orig = tid, place = 0;              // the row's number among those left at the start; its list in `near`
+    int at = 0;                             // chunk in `cur`, and which of its entries may still be open
+    unsigned int valid = 0xFFu;
     bool walking = tid < nleft;
-    uint4 cur = make_uint4(0, 0, 0, 0);
-    const uint4* mine = nullptr;
-    auto load_row = [&]() __attribute__((always_inline)) {
-        mine = reinterpret_cast<const uint4*>(lists + (size_t)orig * pitch);
-        at = idx >> 3;
-        cur = mine[at];
+    uint4 cur = make_uint4(0, 0, 0, 0), nxt = cur;
+    auto chunk = [&](auto near_tag, int i) __attribute__((always_inline)) -> uint4 {
+        if constexpr (decltype(near_tag)::value) return *reinterpret_cast<const uint4*>(near + place * near_pitch + 8 * i);
+        else return *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(lists) + (uint32_t)(2 * orig * pitch + 16 * i));
     };
-    if (walking) load_row();
-    // The first sub-bucket of the row's list that has room in this round, as its byte offset.
-    auto search = [&](int thr, int& c) __attribute__((always_inline)) -> bool {
+    auto load_row = [&](auto near_tag, int idx) __attribute__((always_inline)) {
+        at = min(idx >> 3, chunks - 1);
+        valid = idx < 8 * chunks ? 0xFFu & (0xFFu << (idx & 7)) : 0u;
+        cur = chunk(near_tag, at);
+        nxt = chunk(near_tag, min(at + 1, chunks - 1));
+    };
+    if (walking) load_row(std::false_type{}, 0);
+    auto advance = [&](auto near_tag) __attribute__((always_inline)) {
+        ++at;
+        valid = at < chunks ? 0xFFu : 0u;
+        cur = nxt;
+        nxt = chunk(near_tag, min(at + 1, chunks - 1));
+    };
+    // The first sub-bucket of the row's list that is open. Whoever gets it, it is closed from the next round on: where the chunk
+    // has no other open entry the row goes on to the next one at once.
+    auto search = [&](auto near_tag, const uint8_t* open_now, unsigned int& e) __attribute__((always_inline)) -> bool {
         if (!walking) return false;
         for (;;) {
-            const unsigned int w[4] = {cur.x, cur.y, cur.z, cur.w};
-            int level[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const unsigned int eo = (j & 1) ? w[j >> 1] >> 16 : w[j >> 1] & 0xFFFFu;
-                level[j] = *reinterpret_cast<const int*>(reinterpret_cast<const char*>(stamp) + eo);
-            }
-            __builtin_amdgcn_sched_barrier(0);   // all eight reads are under way before the first is waited for
-            unsigned int room = 0;
-#pragma unroll
-            for (int j = 7; j >= 0; --j) room = __builtin_amdgcn_alignbit(room, (unsigned int)(level[j] - thr), 31);
-            room &= 0xFFu << (idx & 7);          // entries before idx are behind
-            if (room) {
-                const int j = __builtin_ctz(room);
-                idx = (idx & ~7) + j;
-                c = chunk_entry(cur, j);
+            const unsigned int open = chunk_open(cur, open_now) & valid;
+            if (open) {
+                e = (unsigned int)chunk_entry(cur, __builtin_ctz(open));
+                valid = open & (open - 1u);
+                if (valid == 0u) advance(near_tag);
                 return true;
             }
-            if (++at >= chunks) { walking = false; return false; }   // cannot happen: the rows left and the rooms are equally many
-            idx = at << 3;
-            cur = mine[at];
+            if (at + 1 >= chunks) { walking = false; return false; }   // cannot happen: there is room for every row left
+            advance(near_tag);
         }
     };
-    int round = 0, par = 0, r3 = 0, waves = (nleft + 63) >> 6;
-    bool done = false;
-    while (!done && waves > 1) {
+    // lanes that speak for what they contend for: all but those that meet the wave's first contender
+    auto speaks = [&](bool contend, unsigned int e, unsigned long long m) __attribute__((always_inline)) -> bool {
+        const int first = (int)__builtin_ctzll(m | (1ull << 63));
+        return contend && (lane == first || e != (unsigned int)__builtin_amdgcn_readlane((int)e, first));
+    };
+    int waves = (nleft + 63) >> 6, round = 0;
+    auto batch = [&](auto near_tag) __attribute__((always_inline)) {
+        unsigned int e = 0, e_before = 0;
+        bool contend = search(near_tag, flags + (round & 1) * size, e), sent_before = false;
         for (int k = 0; k < 32; ++k, ++round) {
-            if (tid == 0) any3[r3 == 2 ? 0 : r3 + 1] = 0;
-            int c = 0;
-            const bool contend = search(1 - round, c);
-            int* const w = reinterpret_cast<int*>(reinterpret_cast<char*>(win + par * kp) + c);
-            if (contend) {
+            uint8_t* const later = flags + ((round & 1) ^ 1) * size;
+            const bool sent = speaks(contend, e, __builtin_amdgcn_ballot_w64(contend));
+            int* const w = win + (round & 1) * kp + e;
+            if (sent_before) later[e_before] = 0;
+            if (sent) {
                 atomicMin(w, tid);
-                *reinterpret_cast<int*>(reinterpret_cast<char*>(stamp) + c) = -round;
-                any3[r3] = 1;
+                later[e] = 0;
             }
             lds_barrier();
-            const int lowest = contend ? *w : -1;
-            const int seen = __builtin_amdgcn_readfirstlane(any3[r3]);   // did any row contend? (the same answer for every thread)
-            if (contend && lowest == tid) {
-                rsub[orig] = (uint16_t)(c >> 2);
+            const int lowest = sent ? *w : -1;
+            unsigned int e_next = 0;
+            const bool more = k < 31 && search(near_tag, later, e_next);   // a row looks a round ahead, not across a closing up
+            if (sent && lowest == tid) {
+                rsub[orig] = (uint16_t)e;
                 walking = false;
-                *w = 0x7FFFFFFF;                  // next written two rounds from here, a barrier in between
+                *w = 0x7FFFFFFF;              // next written two rounds from here, a barrier in between
             }
-            par ^= 1;
-            r3 = r3 == 2 ? 0 : r3 + 1;
-            if (!seen) { done = true; break; }
+            sent_before = sent;
+            e_before = e;
+            contend = more && walking;
+            e = e_next;
         }
-        if (done) break;
+        if (sent_before) (flags + ((round & 1) ^ 1) * size)[e_before] = 0;   // the copy of the last round, which nobody looks at now
+    };
+    while (waves > 1) {
+        if (wave >= waves) {
+            for (int k = 0; k < 32; ++k, ++round) lds_barrier();
+        } else if (near_pitch) {
+            batch(std::true_type{});
+        } else {
+            batch(std::false_type{});
+        }
         const unsigned long long m = __builtin_amdgcn_ballot_w64(walking);
         if (lane == 0) wave_rows[wave] = __popcll(m);
         __syncthreads();
@@ -618,39 +662,77 @@ __device__ __forceinline__ void rounds_of_two(int nleft, int pitch, int kp, cons
             total += n;
         }
         total = __builtin_amdgcn_readfirstlane(total);
+        const int open_now = nopen - (nleft - total), fits = (open_now + 7) & ~7;
+        const bool go_near = near_pitch == 0 && total * fits <= near_cap;
         const int fewer = (total + 63) >> 6;
-        if (fewer < waves) {                      // the same for every thread
+        if (fewer < waves || go_near) {           // the same for every thread
             waves = fewer;
-            if (walking) moved[before + bits_below(m)] = (uint32_t)orig | ((uint32_t)idx << 16);
+            if (walking) moved[before + bits_below(m)] = (uint32_t)orig | ((uint32_t)place << 10) | ((uint32_t)(8 * at + (int)__builtin_ctz(valid | 0x100u)) << 20);
             __syncthreads();
+            if (go_near) {
+                // a wave takes a row: its list, eight entries per lane, without the closed ones
+                const uint8_t* const open_mask = flags + (round & 1) * size;
+                for (int r = wave; r < total; r += PW) {
+                    const uint4* src = reinterpret_cast<const uint4*>(lists + (size_t)(moved[r] & 1023u) * pitch);
+                    const uint4 c = src[min(lane, chunks - 1)];
+                    const unsigned int open = lane < chunks ? chunk_open(c, open_mask) : 0u;
+                    const int count = __popc(open);
+                    int to = 0;                   // open entries of the lanes before
+#pragma unroll
+                    for (int b = 0; b < 4; ++b) to += bits_below(__builtin_amdgcn_ballot_w64((count >> b) & 1)) << b;
+                    uint16_t* const dst = near + r * fits;
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        if ((open >> j) & 1u) dst[to] = (uint16_t)chunk_entry(c, j);
+                        to += (int)((open >> j) & 1u);
+                    }
+                    if (open_now + lane < fits) dst[open_now + lane] = (uint16_t)kp;   // never open
+                }
+                __syncthreads();
+                near_pitch = fits;
+                chunks = fits >> 3;
+            }
             walking = tid < total;
             if (walking) {
                 const uint32_t r = moved[tid];
-                orig = (int)(r & 0xFFFFu);
-                idx = (int)(r >> 16);
-                load_row();
+                orig = (int)(r & 1023u);
+                place = go_near ? tid : (int)((r >> 10) & 1023u);
+                const int idx = go_near ? 0 : (int)(r >> 20);
+                if (near_pitch) load_row(std::true_type{}, idx);
+                else load_row(std::false_type{}, idx);
             }
         }
         __syncthreads();                          // wave_rows is written again
     }
-    if (done || wave != 0) return;
-    for (;; ++round) {                            // one wave: its LDS operations are in order
-        int c = 0;
-        const bool contend = search(1 - round, c);
-        if (__builtin_amdgcn_ballot_w64(contend) == 0ull) break;
-        int* const w = reinterpret_cast<int*>(reinterpret_cast<char*>(win + par * kp) + c);
-        if (contend) atomicMin(w, tid);
-        wave_lds_sync();
-        const int lowest = contend ? *w : -1;
-        wave_lds_sync();
-        if (contend) *reinterpret_cast<int*>(reinterpret_cast<char*>(stamp) + c) = -round;
-        if (contend && lowest == tid) {
-            rsub[orig] = (uint16_t)(c >> 2);
-            walking = false;
-            *w = 0x7FFFFFFF;
+    uint8_t* const open = flags + (round & 1) * size;
+    auto alone = [&](auto near_tag) __attribute__((always_inline)) {   // one wave: its LDS operations are in order
+        for (;;) {
+            unsigned int e = 0;
+            const bool contend = search(near_tag, open, e);
+            const unsigned long long m = __builtin_amdgcn_ballot_w64(contend);
+            if (m == 0ull) break;
+            const bool sent = speaks(contend, e, m);
+            int* const w = win + e;
+            if (sent) {
+                atomicMin(w, tid);
+                open[e] = 0;
+            }
+            wave_lds_sync();
+            const int lowest = sent ? *w : -1;
+            wave_lds_sync();
+            if (sent && lowest == tid) {
+                rsub[orig] = (uint16_t)e;
+                walking = false;
+                *w = 0x7FFFFFFF;
+            }
+            wave_lds_sync();
         }
-        wave_lds_sync();
+    };
+    if (wave == 0) {
+        if (near_pitch) alone(std::true_type{});
+        else alone(std::false_type{});
     }
+    return open;
 }
 
 // dynamic LDS, kp = a.kp: px,py,pz [PT] floats | o4 [kp] float4 (x, y, z, -) | fill [kp] ints | win [2][kp] ints |
@@ -671,10 +753,9 @@ __global__ __launch_bounds__(PT, WPE) void k_pool(PoolArgs a)
     __shared__ uint32_t red[11];
     __shared__ ScanCfg cfg;
     __shared__ int next_tile;
-    __shared__ int rows_left;
+    __shared__ int rows_left, rows_taken;
     __shared__ int more[2];
     __shared__ int any[2];
-    __shared__ int any3[3];
     const int rho = a.rho, kp = a.kp;
     const int tid = threadIdx.x, lane = tid & 63;
     float* px = reinterpret_cast<float*>(smem);
@@ -724,7 +805,7 @@ __global__ __launch_bounds__(PT, WPE) void k_pool(PoolArgs a)
         win[k] = 0x7FFFFFFF;
         win[kp + k] = 0x7FFFFFFF;
     }
-    if (tid == 0) { more[0] = 0; more[1] = 0; any[0] = 0; any[1] = 0; any3[0] = 0; any3[1] = 0; any3[2] = 0; }
+    if (tid == 0) { more[0] = 0; more[1] = 0; any[0] = 0; any[1] = 0; }
     __syncthreads();
     {
         uint32_t o[3] = {act ? f2ord(x) : 0xFFFFFFFFu, act ? f2ord(y) : 0xFFFFFFFFu, act ? f2ord(z) : 0xFFFFFFFFu};
@@ -879,7 +960,13 @@ __global__ __launch_bounds__(PT, WPE) void k_pool(PoolArgs a)
     }
     const int pitch = (nopen + 7) & ~7;
     if (nleft > 0 && nopen > 0 && (long long)nleft * pitch <= (long long)a.list_cap) {
-        if (tid == 0 && nopen < kp) open_list[nopen] = (uint16_t)kp;   // what list entries beyond nopen name (none if nopen = kp)
+        // From here on the open list holds what the lists hold: the sub-bucket, for rho other than 2 its fill level's
+        // byte offset. List entries beyond nopen name sub-bucket kp, which is never open (there are none if nopen = kp).
+        if (tid <= nopen && tid < kp) {
+            const unsigned int id = tid < nopen ? open_list[tid] : (unsigned int)kp;
+            open_list[tid] = (uint16_t)(rho == 2 ? id : 4u * id);
+        }
+        if (tid == 0) rows_taken = 0;
         // the far corner of the tile: only tiles that sort need it (in every tile it cost 7 % on 60 000 scans of three points)
         const float far[3] = {act ? px[tid] : mnx, act ? py[tid] : mny, act ? pz[tid] : mnz};
 #pragma unroll
@@ -893,21 +980,23 @@ __global__ __launch_bounds__(PT, WPE) void k_pool(PoolArgs a)
         const unsigned int top = __float_as_uint(dist2(ord2f(red[8]) - mnx, ord2f(red[9]) - mny, ord2f(red[10]) - mnz));
         const unsigned int base = __builtin_elementwise_sub_sat(top, DIST_MAX << 4);
         if (nopen <= 128)
-            sort_choices<2>(nleft, nopen, pitch, base, left_list, px, py, pz, o4, open_list, my_lists);
+            sort_choices<2>(nleft, nopen, pitch, base, left_list, px, py, pz, o4, open_list, my_lists, &rows_taken);
         else if (nopen <= 256)
-            sort_choices<4>(nleft, nopen, pitch, base, left_list, px, py, pz, o4, open_list, my_lists);
+            sort_choices<4>(nleft, nopen, pitch, base, left_list, px, py, pz, o4, open_list, my_lists, &rows_taken);
         else
-            sort_choices<8>(nleft, nopen, pitch, base, left_list, px, py, pz, o4, open_list, my_lists);
+            sort_choices<8>(nleft, nopen, pitch, base, left_list, px, py, pz, o4, open_list, my_lists, &rows_taken);
         __threadfence_block();   // the lists are read by other waves of this workgroup
         __syncthreads();
         if (rho == 2) {
-            int* stamp = reinterpret_cast<int*>(o4);   // [kp + 1]; the candidates' positions are not needed after the sort
-            for (int k = tid; k <= kp; k += PT) stamp[k] = k < M && fill[k] < 2 ? STAMP_OPEN : 1;   // stamp[kp] is what entries beyond nopen name
+            uint8_t* const flags = reinterpret_cast<uint8_t*>(o4);   // [2][kp + 1]; the candidates' positions are not needed after the sort
+            for (int k = tid; k <= kp; k += PT) flags[k] = flags[kp + 1 + k] = k < M && fill[k] < 2;
             __syncthreads();
-            rounds_of_two(nleft, pitch, kp, my_lists, stamp, win, rsub, reinterpret_cast<uint32_t*>(wcnt), lds, any3);
+            // ranking by key is over: its counters make room for the rows' closing up, [kp] words, and the near lists
+            const uint8_t* const still = rounds_of_two(nleft, nopen, pitch, kp, my_lists, flags, win, rsub, reinterpret_cast<uint32_t*>(wcnt), lds,
+                                                        wcnt + 2 * kp, a.near_cap);
             __syncthreads();
             for (int k = tid; k < M; k += PT)          // the sub-buckets closed in the rounds are full
-                if (stamp[k] != STAMP_OPEN && stamp[k] <= 0) fill[k] = 2;
+                if (!still[k]) fill[k] = 2;
             if (left) rslot[lpos] = 1;
         } else {
             // Thread t now speaks for the t-th row left: row order is kept. It walks its list in chunks of eight entries
@@ -1034,6 +1123,8 @@ __global__ __launch_bounds__(PT, WPE) void k_pool(PoolArgs a)
   }   // next tile
 }
 
+constexpr size_t POOL_STATIC_LDS = 1024;   // more than the kernel's static shared variables
+
 size_t pool_lds_bytes(int kp)
 {
     const size_t wcnt = (size_t)PW * kp * 2;   // kp >= 64, so this is at least PT entries
@@ -1043,14 +1134,21 @@ size_t pool_lds_bytes(int kp)
 
 }  // namespace
 
-hipError_t pool_launch(const PoolArgs& a, hipStream_t stream)
+hipError_t pool_launch(const PoolArgs& args, hipStream_t stream)
 {
+    PoolArgs a = args;
     k_pool_meta<<<1, 1024, 0, stream>>>(a);
     if (a.n == 0) return hipGetLastError();
-    const size_t lds = pool_lds_bytes(a.kp);
+    size_t lds = pool_lds_bytes(a.kp);
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 0;
     const bool two = cus > 0 && a.n_tiles_ub > cus && 2 * lds <= 160 * 1024;
+    if (a.rho == 2) {
+        // what LDS is left beside one or two workgroups holds the lists of the last rows (POOL_STATIC_LDS: the kernel's own variables)
+        const size_t most = (two ? 80 : 128) * 1024 - POOL_STATIC_LDS, all = pool_list_entries(a.tile) * 2;
+        if (lds < most) lds += (most - lds < all ? most - lds : all) & ~(size_t)15;
+        a.near_cap = (int)((lds - pool_lds_bytes(a.kp)) / 2) + (PW - 2) * a.kp;
+    }
     if (lds > 60000) {
         const hipError_t e = two ? hipFuncSetAttribute((const void*)k_pool<8>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)
                                  : hipFuncSetAttribute((const void*)k_pool<4>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

@@ -1422,6 +1422,21 @@ def test_pool_many_short_scans_around_a_long_one(at):
         check_pool(c, None, feat, bo, 64, 2, 0.1, "zorder_div", "max")
 
 
+@pytest.mark.parametrize("tiles", [3, 300])
+@pytest.mark.parametrize("tile", [66, 130, 134, 262, 518, 1022, 1024])
+def test_pool_pairs_where_most_rows_are_left_to_the_rounds(tile, tiles):
+    """Capacity 2, half of every tile one point, the rest spread out: about half of the tile's rows are left to the rounds and a few
+    join in each. Around 64 rows left one wave goes on alone, around 130 (few tiles: one workgroup per compute unit, more LDS) or
+    more the lists that remain move to LDS."""
+    rng = np.random.default_rng(50 + tile)
+    n = tiles * tile - 3
+    c = (rng.random((n, 3)) * 8).astype(np.float32)
+    c[(np.arange(n) % tile) % 2 == 1] = 4.0
+    feat = wl.f32_to_bf16_bits(rng.standard_normal((n, 8)).astype(np.float32))
+    ref = check_pool(c, None, feat, None, tile, 2, 0.01, "zorder_div", "max")
+    assert ref["step_of"].max() >= 10
+
+
 def test_pool_empty_input_and_bad_offsets():
     z = np.zeros((0, 3), np.float32)
     got = f3d.inbucket_pool(dev(z), None, dev(np.zeros((0, 8), np.uint16), torch.bfloat16), None, 1024, 2, 0.1)
