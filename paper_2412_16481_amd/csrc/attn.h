@@ -5,6 +5,24 @@
 
 namespace f3d {
 
+// How to divide a non-negative int by a value the launch knows: a shift (powers of two), else the upper half of a product
+// where that is exact for every dividend in question, else (magic 0) an ordinary division.
+struct Divide {
+    uint32_t magic;
+    int shift;      // -1: not a power of two
+};
+inline Divide make_divide(int d, long long most)   // dividends 0 .. most
+{
+    Divide r{0, -1};
+    if (d > 0 && (d & (d - 1)) == 0) {
+        r.shift = 0;
+        while ((1 << r.shift) < d) ++r.shift;
+    } else if (most * d < (1ll << 32)) {
+        r.magic = (uint32_t)((1ull << 32) / (unsigned)d + 1);   // more than 2^32/d by less than one: off by less than most/2^32 < 1/d
+    }
+    return r;
+}
+
 struct AttnArgs {
     const uint16_t* q;
     const uint16_t* k;
@@ -29,6 +47,7 @@ struct AttnArgs {
     int n_slots;  // scope slots over all scans (upper bound, surplus workgroups exit)
     int qblocks;  // query blocks per scope = ceil(bucket_cap / attn_block_rows(...))
     int extra;    // spare slots per scan: 2 (plain, shift) or stride + 1
+    Divide by_m, by_t, by_mt, by_h, by_blocks;   // buckets per scope, stride, their product, heads, row blocks of a scope
     int f16;      // 0: q, k, v, out are bfloat16; 1: binary16 (forward only)
 };
 

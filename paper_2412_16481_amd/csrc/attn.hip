@@ -119,52 +119,20 @@ __global__ __launch_bounds__(256, 3) void k_attn(AttnArgs a)
     constexpr int BM = 128 * QT;           // query rows per workgroup
 
     __shared__ __attribute__((aligned(1024))) unsigned char smem[L::TOTAL];
-    __shared__ int seg_row0[MAXSEG];
-    __shared__ int seg_pre[MAXSEG + 1];
-    __shared__ int s_nseg;
+    __shared__ int s_row0[4][MAXSEG], s_pre[4][MAXSEG + 1];   // of each wave
     const uint32_t sK = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)smem;   // LDS byte addresses
     const uint32_t sV = sK + NBUF * L::KBUF;
-
-    // ---- which (scope, head, query block) is this workgroup: consecutive ids stay on one XCD
-    const int total = gridDim.x;  // multiple of 8
-    const int w = blockIdx.x;
-    const int u = (w & 7) * (total >> 3) + (w >> 3);
-    const int qb = u % a.qblocks;
-    const int head = (u / a.qblocks) % a.H;
-    const int slot = u / (a.qblocks * a.H);
-    if (slot >= a.n_slots) return;
-    if (a.sbs[a.n_scans] <= 0) return;
-    const int b = find_slot_scan(a.sbs, a.n_scans, a.m, a.extra, slot);
-    const int g = slot - (a.sbs[b] / a.m + a.extra * b);
-    const int kb0 = a.sbs[b], K = a.sbs[b + 1] - kb0;
-    if (K <= 0) return;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, hf = lane >> 5;
-
-    // ---- rows of the scope: up to m segments (one bucket each; plain/shifted scopes are one run)
-    if (tid == 0) build_segments(a, g, kb0, K, seg_row0, seg_pre, &s_nseg);
-    __syncthreads();
-    const int nseg = s_nseg;
-    if (nseg == 0) return;
-    const int ng = seg_pre[nseg];         // rows in this scope
-    if (qb * BM >= ng) return;
-
-    // Up to four segments (the usual scope of four buckets) are kept in scalar registers as (first position,
-    // row minus position) pairs, so mapping a position to its row is a few compares and no LDS traffic.
-    constexpr int BIG = 0x7FFFFFFF;
-    const int d0 = __builtin_amdgcn_readfirstlane(seg_row0[0]);
-    const int p1 = __builtin_amdgcn_readfirstlane(nseg > 1 ? seg_pre[1] : BIG);
-    const int p2 = __builtin_amdgcn_readfirstlane(nseg > 2 ? seg_pre[2] : BIG);
-    const int p3 = __builtin_amdgcn_readfirstlane(nseg > 3 ? seg_pre[3] : BIG);
-    const int d1 = __builtin_amdgcn_readfirstlane(nseg > 1 ? seg_row0[1] - seg_pre[1] : 0);
-    const int d2 = __builtin_amdgcn_readfirstlane(nseg > 2 ? seg_row0[2] - seg_pre[2] : 0);
-    const int d3 = __builtin_amdgcn_readfirstlane(nseg > 3 ? seg_row0[3] - seg_pre[3] : 0);
-    const SegMap sm{nseg, d0, d1, d2, d3, p1, p2, p3};
-    auto seg_row = [sm](int x) __attribute__((always_inline)) -> int {
-        return seg_row_of(sm, seg_pre, seg_row0, x);
-    };
+    int slot, head, qb, ng;               // ng: rows in this scope
+    SegMap sm;
+    block_of_grid(a, a.qblocks, slot, head, qb);
+    int* const seg_row0 = s_row0[wave];
+    int* const seg_pre = s_pre[wave];
+    if (slot >= a.n_slots || !scope_of_slot(a, slot, seg_row0, seg_pre, ng, sm) || qb * BM >= ng) return;
+    auto seg_row = [&](int x) __attribute__((always_inline)) -> int { return seg_row_of(sm, seg_pre, seg_row0, x); };
 
     const size_t hoff = (size_t)head * D;
     const uint32_t row_bytes = (uint32_t)a.C * 2u;

@@ -46,37 +46,11 @@ struct ScopeCtx {
 };
 
 template <int BM>
-__device__ __forceinline__ bool scope_of_block(const AttnArgs& a, int blocks_per_scope, int* seg_row0, int* seg_pre, int* s_nseg,
-                                               ScopeCtx& c)
+__device__ __forceinline__ bool scope_of_block(const AttnArgs& a, int blocks_per_scope, int* seg_row0, int* seg_pre, ScopeCtx& c)
 {
-    const int total = gridDim.x;  // multiple of 8; consecutive ids stay on one XCD
-    const int w = blockIdx.x;
-    const int u = (w & 7) * (total >> 3) + (w >> 3);
-    c.blk = u % blocks_per_scope;
-    c.head = (u / blocks_per_scope) % a.H;
-    const int slot = u / (blocks_per_scope * a.H);
-    if (slot >= a.n_slots) return false;
-    if (a.sbs[a.n_scans] <= 0) return false;
-    const int b = find_slot_scan(a.sbs, a.n_scans, a.m, a.extra, slot);
-    const int g = slot - (a.sbs[b] / a.m + a.extra * b);
-    const int kb0 = a.sbs[b], K = a.sbs[b + 1] - kb0;
-    if (K <= 0) return false;
-    if (threadIdx.x == 0) build_segments(a, g, kb0, K, seg_row0, seg_pre, s_nseg);
-    __syncthreads();
-    const int nseg = *s_nseg;
-    if (nseg == 0) return false;
-    c.ng = seg_pre[nseg];
-    if (c.blk * BM >= c.ng) return false;
-    constexpr int BIG = 0x7FFFFFFF;
-    c.sm.nseg = nseg;
-    c.sm.d0 = __builtin_amdgcn_readfirstlane(seg_row0[0]);
-    c.sm.p1 = __builtin_amdgcn_readfirstlane(nseg > 1 ? seg_pre[1] : BIG);
-    c.sm.p2 = __builtin_amdgcn_readfirstlane(nseg > 2 ? seg_pre[2] : BIG);
-    c.sm.p3 = __builtin_amdgcn_readfirstlane(nseg > 3 ? seg_pre[3] : BIG);
-    c.sm.d1 = __builtin_amdgcn_readfirstlane(nseg > 1 ? seg_row0[1] - seg_pre[1] : 0);
-    c.sm.d2 = __builtin_amdgcn_readfirstlane(nseg > 2 ? seg_row0[2] - seg_pre[2] : 0);
-    c.sm.d3 = __builtin_amdgcn_readfirstlane(nseg > 3 ? seg_row0[3] - seg_pre[3] : 0);
-    return true;
+    int slot;
+    block_of_grid(a, blocks_per_scope, slot, c.head, c.blk);
+    return slot < a.n_slots && scope_of_slot(a, slot, seg_row0, seg_pre, c.ng, c.sm) && c.blk * BM < c.ng;
 }
 
 // bf16 fragment times a scalar, split into a bf16 head and a bf16 remainder (x*c = hi + lo up to 2^-17 relative)
@@ -208,16 +182,16 @@ __global__ __launch_bounds__(256, AHEAD ? 2 : 3) void k_attn_bwd_dq(AttnBwdArgs 
     constexpr int NC = L::NC, KS = D / 16, LPW = L::LPW, SR = L::ROWS;
     constexpr int BM = 128 * QT;                      // query rows per workgroup
     __shared__ __attribute__((aligned(1024))) unsigned char smem[L::NBUF * 2 * L::BUF];   // K stages, then V stages
-    __shared__ int seg_row0[MAXSEG];
-    __shared__ int seg_pre[MAXSEG + 1];
-    __shared__ int s_nseg;
+    __shared__ int s_row0[4][MAXSEG], s_pre[4][MAXSEG + 1];                               // of each wave
     const AttnArgs& a = b.f;
-    ScopeCtx sc;
-    if (!scope_of_block<BM>(a, a.qblocks, seg_row0, seg_pre, &s_nseg, sc)) return;
-    const int ng = sc.ng, head = sc.head;
-    const SegMap sm = sc.sm;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int* const seg_row0 = s_row0[wave];
+    int* const seg_pre = s_pre[wave];
+    ScopeCtx sc;
+    if (!scope_of_block<BM>(a, a.qblocks, seg_row0, seg_pre, sc)) return;
+    const int ng = sc.ng, head = sc.head;
+    const SegMap sm = sc.sm;
     const int l32 = lane & 31, hf = lane >> 5;
     const size_t hoff = (size_t)head * D;
     const uint32_t row_bytes = (uint32_t)a.C * 2u;
@@ -486,16 +460,16 @@ __global__ __launch_bounds__(256, AHEAD ? 2 : 3) void k_attn_bwd_dkdv(AttnBwdArg
     constexpr int BM = 128 * KTW;                     // key rows per workgroup
     __shared__ __attribute__((aligned(1024))) unsigned char smem[L::NBUF * 2 * L::BUF];   // Q stages, then dO stages
     __shared__ uint2 sx[L::NBUF * SR];                // per staged row {lse hi, lo, D hi, lo}, see split_pairs
-    __shared__ int seg_row0[MAXSEG];
-    __shared__ int seg_pre[MAXSEG + 1];
-    __shared__ int s_nseg;
+    __shared__ int s_row0[4][MAXSEG], s_pre[4][MAXSEG + 1];                               // of each wave
     const AttnArgs& a = b.f;
-    ScopeCtx sc;
-    if (!scope_of_block<BM>(a, b.kblocks, seg_row0, seg_pre, &s_nseg, sc)) return;
-    const int ng = sc.ng, head = sc.head;
-    const SegMap sm = sc.sm;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int* const seg_row0 = s_row0[wave];
+    int* const seg_pre = s_pre[wave];
+    ScopeCtx sc;
+    if (!scope_of_block<BM>(a, b.kblocks, seg_row0, seg_pre, sc)) return;
+    const int ng = sc.ng, head = sc.head;
+    const SegMap sm = sc.sm;
     const int l32 = lane & 31, hf = lane >> 5;
     const size_t hoff = (size_t)head * D;
     const uint32_t row_bytes = (uint32_t)a.C * 2u;

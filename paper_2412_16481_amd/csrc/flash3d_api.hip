@@ -406,9 +406,22 @@ static int fill_attn_args(f3d::AttnArgs& a, const void* q, const void* k, const 
         a.q_pow2 = ldexpf(1.0f, e - 1);
     }
     a.extra = mode == F3D_STRIDE ? stride + 1 : 2;
+    a.by_m = f3d::make_divide(scope_buckets, max_buckets);
+    if (mode == F3D_STRIDE) {
+        a.by_t = f3d::make_divide(stride, max_buckets + 1);      // scopes of a scan: no more than its buckets
+        a.by_mt = f3d::make_divide(scope_buckets * stride, max_buckets);
+    }
     *scale_out = scale;
     *slots_out = max_buckets / scope_buckets + (long long)a.extra * n_scans + 1;
     return F3D_OK;
+}
+
+// once the number of workgroups is known
+static void set_divides(f3d::AttnArgs& a)
+{
+    const long long scopes = (long long)a.n_slots * a.H + 8;     // the grid is rounded up to a multiple of 8
+    a.by_blocks = f3d::make_divide(a.qblocks, scopes * a.qblocks + 8);
+    a.by_h = f3d::make_divide(a.H, scopes);
 }
 
 static int attn_forward(int f16, const void* q, const void* k, const void* v, const int32_t* perm, const int32_t* offsets,
@@ -437,6 +450,7 @@ static int attn_forward(int f16, const void* q, const void* k, const void* v, co
     a.qblocks = (bucket_cap + bm - 1) / bm;
     if (slots * heads * a.qblocks > 2000000000ll) return F3D_ERR_UNSUPPORTED;
     a.n_slots = (int)slots;
+    set_divides(a);
     (void)hipGetLastError();
     const hipError_t e = f3d::attn_launch(a, head_dim, bm, (hipStream_t)stream);
     return e == hipSuccess ? F3D_OK : hip_fail(e);
@@ -531,6 +545,7 @@ int f3d_bucket_swin_attn_bwd(const void* q, const void* k, const void* v, const 
     b.kblocks = (bucket_cap + 128 * b.tiles - 1) / (128 * b.tiles);
     b.f.qblocks = b.kblocks;
     b.f.n_slots = (int)slots;
+    set_divides(b.f);
     (void)hipGetLastError();
     const hipError_t e = f3d::attn_bwd_launch(b, head_dim, (hipStream_t)stream);
     return e == hipSuccess ? F3D_OK : hip_fail(e);
