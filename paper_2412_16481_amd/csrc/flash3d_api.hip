@@ -307,6 +307,10 @@ static int bucketize_on(const Plan& pl, char* ws, const float* coords, const int
         o.n = (int)n;
         o.n_scans = n_scans;
         o.inv_voxel = a.inv_voxel;
+        o.max_scan_points = pl.max_scan_points;
+        // the bucketing that follows writes its own over these: 32 bytes per chunk of 2048 points each
+        o.tile_info = a.chunk_info;
+        o.tile_box = a.mmpart;
         o.box = (uint32_t*)(ws + pl.o_obox);
         o.keys = (unsigned long long*)(ws + pl.o_okeys);
         o.idx[0] = (int32_t*)(ws + pl.o_oidx0);

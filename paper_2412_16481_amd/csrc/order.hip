@@ -4,16 +4,19 @@
 // which they are stored. It is done by sorting the points once by that key and running the index-ordered bucketing on
 // the sorted copy; the result is mapped back through the sort order.
 //
-// The sort is a merge sort on whole keys (112 + 63 bits in three 64-bit words), carrying only the point index: one kernel
-// builds the keys and sorts tiles of 2048 positions in LDS, then one kernel per doubling of the sorted length merges
-// pairs of runs, a workgroup per 2048 positions of the result. A comparison almost always ends at the first word, which
-// holds the scan and the upper 48 bits of the code. The cost does not depend on how the points fall into voxels.
+// The sort is a merge sort on whole keys (scan, code, x, y, z packed into three 64-bit words), carrying only the point index: one kernel
+// cuts the scans into tiles of 2048 positions and takes the tiles' bounding boxes, one builds the keys and sorts the tiles in LDS, then
+// one kernel per doubling of the sorted length merges pairs of runs, a workgroup per tile of the result. Runs never reach over the
+// end of a scan, so there are as many merges as the longest scan needs. (Batches of more than 512 scans are sorted as one run of
+// positions, the scan in front of the key.) The cost does not depend on how the points fall into voxels.
 //
 // Bound: launches and latency (a merge launch is a chain of a search, two dependent loads and a search in LDS: 10 us at
-// 457295 points, the tiles 32 us). A radix sort on 8-bit digits takes 21 passes over these keys, each with its own count,
-// scan and scatter, whatever n is. A whole canonical bucketing took 248 us at 1500 points, 521 us at 457295 and 3.44 ms at
-// 4 million with such a sort, and took 64 us, 249 us and 1.62 ms with this one (229 us at
-// 457295 points since the bucketing that follows takes 89).
+// 457295 points, the tiles 27 us). A radix sort on 8-bit digits takes 21 passes over these keys, each with its own count,
+// scan and scatter, whatever n is. A whole canonical bucketing, us: with such a sort / with runs over scan ends, minima by atomics and the
+// code in the upper 63 bits of the key whatever its size / now: 457295 points in four scans 521 / 224 / 191, 900000 in eight - / 299 / 255,
+// 500000 in 100 - / 213 / 132, 60000 in 300 - / 129 / 70, one scan of 200000 - / 211 / 204, of 4 million 3440 / 3212 / 3189, of 1500
+// 248 / 58.7 / 57.6. Tiles of 4096 take one merge less and one workgroup per compute unit: 457295 points 1 us less, one scan of
+// 1500 12 more, of 200000 16 more.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -26,14 +29,122 @@ namespace {
 
 constexpr int OT = 256;          // threads per workgroup
 constexpr int OE = 2048;         // positions per tile
-constexpr int OST = 512;         // threads that sort or merge a tile
+constexpr int OST = 512;        // threads that sort or merge a tile
 constexpr int OPT = OE / OST;    // results per thread
+
+constexpr int OSCANS = OST;      // most scans that are sorted each by itself
+
+// Where tile t of a batch of up to OSCANS scans lies: tiles never straddle scans. Written by k_order_set, with the bounding box of the
+// tile's points (ordered ints, minimum xyz at [0..2], maximum at [4..6]) beside it.
+struct TileInfo {
+    int first, count;   // positions
+    int p0, len;        // of the scan
+    int t0, tiles;      // first tile of the scan and how many it has
+    int scan, ok;
+};
+static_assert(sizeof(TileInfo) == 32, "the workspace has 32 bytes per tile");
+
+__device__ __forceinline__ TileInfo tile_of(const OrderArgs& a, int t)
+{
+    if (a.n_scans > 1 && a.n_scans <= OSCANS) return reinterpret_cast<const TileInfo*>(a.tile_info)[t];
+    // one scan, or (the keys begin with the scan) one run of positions over all
+    const int first = t * OE;
+    return TileInfo{first, min(OE, a.n - first), 0, a.n, 0, (a.n + OE - 1) / OE, 0, first < a.n};
+}
 
 __device__ __forceinline__ int scan_of(const OrderArgs& a, int p)
 {
     return a.batch_offsets ? find_scan(a.batch_offsets, a.n_scans, p) : 0;
 }
 
+// Batches of up to OSCANS scans: one workgroup per tile finds its place (a prefix over the scans), writes it down, and the
+// bounding box of its points, without atomics. Offsets that are not those of a batch leave no tiles: what follows does nothing, and
+// the bucketing flags them.
+__global__ __launch_bounds__(OST) void k_order_set(OrderArgs a)
+{
+    __shared__ TileInfo s_info;
+    __shared__ uint32_t red[8];
+    __shared__ int lds17[17];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int t = blockIdx.x, ns = a.n_scans;
+    if (ns == 1) {
+        if (tid == 0) s_info = tile_of(a, t);
+    } else {
+        // thread i looks at scan i; the first wave alone where it holds them all
+        int p0 = 0, nb = 0;
+        bool good = true;
+        if (tid < ns) {
+            p0 = a.batch_offsets ? a.batch_offsets[tid] : tid == 0 ? 0 : a.n;
+            const int p1 = a.batch_offsets ? a.batch_offsets[tid + 1] : a.n;
+            const long long d = (long long)p1 - p0;
+            good = d >= 0 && d <= a.max_scan_points && p0 >= 0 && p1 <= a.n && (tid > 0 || p0 == 0) && (tid < ns - 1 || p1 == a.n);
+            nb = good ? (int)d : 0;
+        }
+        const int tiles = (nb + OE - 1) / OE;
+        int t0, total, bad;
+        if (ns <= 64) {
+            const int last = wave_incl_scan(tiles, lane);
+            t0 = last - tiles;
+            total = __shfl(last, 63, 64);
+            bad = __builtin_amdgcn_ballot_w64(!good) != 0ull;
+        } else {
+            t0 = block_excl_scan(tiles, &total, lds17);
+            bad = __syncthreads_or(!good);
+        }
+        if (tid == 0) s_info.ok = 0;
+        if (ns > 64) __syncthreads();
+        if (t0 <= t && t < t0 + tiles && !bad && tid < ns) {      // this thread's scan has the tile
+            TileInfo f;
+            f.scan = tid;
+            f.t0 = t0;
+            f.tiles = tiles;
+            f.p0 = p0;
+            f.len = nb;
+            f.first = p0 + (t - t0) * OE;
+            f.count = min(OE, p0 + nb - f.first);
+            f.ok = 1;
+            s_info = f;
+            reinterpret_cast<TileInfo*>(a.tile_info)[t] = f;
+        }
+        if (tid == 0 && (bad || t >= total)) reinterpret_cast<TileInfo*>(a.tile_info)[t].ok = 0;
+    }
+    if (tid < 3) {
+        red[tid] = 0xFFFFFFFFu;
+        red[4 + tid] = 0u;
+    }
+    __syncthreads();
+    if (!s_info.ok) return;
+    const float* src = a.coords + (size_t)s_info.first * 3;
+    const int nf = s_info.count * 3;
+    uint32_t mn[3] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu}, mx[3] = {0u, 0u, 0u};
+    float v[3 * OPT];
+#pragma unroll
+    for (int j = 0; j < 3 * OPT; ++j) {          // all loads in flight together; past the end: the axis' first value again
+        const int f = tid + j * OST;
+        v[j] = src[f < nf ? f : f % 3];
+    }
+#pragma unroll
+    for (int j = 0; j < 3 * OPT; ++j) {
+        const uint32_t o = f2ord(v[j]);
+        const int ax = (tid + j * OST) % 3;
+#pragma unroll
+        for (int x = 0; x < 3; ++x)
+            if (ax == x) { mn[x] = min(mn[x], o); mx[x] = max(mx[x], o); }
+    }
+#pragma unroll
+    for (int x = 0; x < 3; ++x) {
+        uint32_t lo = mn[x], hi = mx[x];
+        for (int d = 32; d >= 1; d >>= 1) {
+            lo = min(lo, (uint32_t)__shfl_xor((int)lo, d, 64));
+            hi = max(hi, (uint32_t)__shfl_xor((int)hi, d, 64));
+        }
+        if (lane == 0) { atomicMin(&red[x], lo); atomicMax(&red[4 + x], hi); }
+    }
+    __syncthreads();
+    if (tid < 8) a.tile_box[t * 8 + tid] = red[(tid & 3) < 3 ? tid : 0];
+}
+
+// Batches of more scans: their minima by atomics.
 __global__ __launch_bounds__(OT) void k_order_init(OrderArgs a)
 {
     const int i = blockIdx.x * OT + threadIdx.x;
@@ -110,10 +221,19 @@ __global__ __launch_bounds__(OT) void k_order_box(OrderArgs a)
     if (tid < 3) atomicMin(&a.box[b_first * 4 + tid], red[tid]);
 }
 
-// key of a point: {scan:16 code:63 x:32 y:32 z:32} from the top of the first word down, zero-padded at the end
+// Key of a point: scan (16 bits), code, x, y, z (32 bits each), from the top of the first word down, zero-padded at the end. The code
+// takes as many bits as the scan's largest (63 in batches of many scans): what stands in front of x is then nearly always
+// in the first word, and some of x too, and a comparison seldom looks at the second.
 struct OrderKey {
     unsigned long long a, b, c;
 };
+
+__device__ __forceinline__ OrderKey make_key(int scan, uint64_t code, int bits, uint32_t x, uint32_t y, uint32_t z)
+{
+    const uint64_t u = ((uint64_t)x << 32) | y, w = (uint64_t)z << 32;
+    const uint64_t h0 = (code << (64 - bits)) | (u >> bits), h1 = (u << (64 - bits)) | (w >> bits), h2 = w << (64 - bits);   // 0 < bits < 64
+    return OrderKey{((uint64_t)(uint32_t)scan << 48) | (h0 >> 16), (h0 << 48) | (h1 >> 16), (h1 << 48) | (h2 >> 16)};
+}
 
 // A tile of keys in LDS.
 struct KeyTile {
@@ -133,34 +253,63 @@ __device__ __forceinline__ bool key_less(const KeyTile& k, int i, int j)
 }
 
 // Keys of the points (also to `keys`, 24 bytes per point) and the sorted order of every tile of OE positions.
+template <bool FEW>   // a batch of up to OSCANS scans
 __global__ __launch_bounds__(OST) void k_order_tiles(OrderArgs a)
 {
     __shared__ KeyTile k;
     __shared__ uint16_t ord[2][OE];
+    __shared__ uint32_t box[8];
     const int tid = threadIdx.x;
-    const long long first = (long long)blockIdx.x * OE;
+    const TileInfo ti = tile_of(a, blockIdx.x);
+    if (!ti.ok) return;
+    if (FEW && tid < 64) {                            // the boxes of the scan's tiles
+        uint32_t lo[3] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu}, hi[3] = {0u, 0u, 0u};
+        for (int t = tid; t < ti.tiles; t += 64) {
+            const uint32_t* b = a.tile_box + (size_t)(ti.t0 + t) * 8;
+#pragma unroll
+            for (int x = 0; x < 3; ++x) { lo[x] = min(lo[x], b[x]); hi[x] = max(hi[x], b[4 + x]); }
+        }
+#pragma unroll
+        for (int x = 0; x < 3; ++x) {
+            for (int d = 32; d >= 1; d >>= 1) {
+                lo[x] = min(lo[x], (uint32_t)__shfl_xor((int)lo[x], d, 64));
+                hi[x] = max(hi[x], (uint32_t)__shfl_xor((int)hi[x], d, 64));
+            }
+            if (tid == 0) { box[x] = lo[x]; box[4 + x] = hi[x]; }
+        }
+    }
+    float c[OPT][3];
+#pragma unroll
+    for (int u = 0; u < OPT; ++u) {
+        const int e = min(u * OST + tid, ti.count - 1);
+#pragma unroll
+        for (int x = 0; x < 3; ++x) c[u][x] = a.coords[(size_t)(ti.first + e) * 3 + x];
+    }
+    int bits = 63;
+    if (FEW) {                                        // of the largest code: that of the far corner of the box
+        __syncthreads();
+        bits = 1;
+#pragma unroll
+        for (int x = 0; x < 3; ++x) {
+            const float far = ord2f(box[4 + x]);
+            const int v = far == far ? voxel_of(far, ord2f(box[x]), a.inv_voxel) : F3D_VOXEL_MAX;   // a NaN says nothing of the others
+            if (v > 0) bits = max(bits, 3 * (31 - __clz(v)) + x + 1);
+        }
+    }
 #pragma unroll
     for (int u = 0; u < OPT; ++u) {
         const int e = u * OST + tid;
-        const long long p = first + e;
         OrderKey key = {~0ull, ~0ull, ~0ull};         // past the end: behind every point (a scan index is below 65535)
-        if (p < a.n) {
-            const int b = scan_of(a, (int)p);
+        if (e < ti.count) {
+            const size_t p = (size_t)(ti.first + e);
+            const int b = FEW ? ti.scan : scan_of(a, (int)p);
             int v[3];
-            uint32_t o[3];
 #pragma unroll
-            for (int t = 0; t < 3; ++t) {
-                const float c = a.coords[(size_t)p * 3 + t];
-                o[t] = f2ord(c);
-                v[t] = voxel_of(c, ord2f(a.box[b * 4 + t]), a.inv_voxel);
-            }
-            const uint64_t code = morton3(v[0], v[1], v[2]);
-            key.a = ((unsigned long long)(uint32_t)b << 48) | (code >> 15);
-            key.b = ((code & 0x7FFFull) << 49) | ((unsigned long long)o[0] << 17) | (o[1] >> 15);
-            key.c = ((unsigned long long)o[1] << 49) | ((unsigned long long)o[2] << 17);
-            a.keys[3 * (size_t)p] = key.a;
-            a.keys[3 * (size_t)p + 1] = key.b;
-            a.keys[3 * (size_t)p + 2] = key.c;
+            for (int x = 0; x < 3; ++x) v[x] = voxel_of(c[u][x], ord2f(FEW ? box[x] : a.box[b * 4 + x]), a.inv_voxel);
+            key = make_key(b, morton3(v[0], v[1], v[2]), bits, f2ord(c[u][0]), f2ord(c[u][1]), f2ord(c[u][2]));
+            a.keys[3 * p] = key.a;
+            a.keys[3 * p + 1] = key.b;
+            a.keys[3 * p + 2] = key.c;
         }
         k.a[e] = key.a;
         k.b[e] = key.b;
@@ -206,7 +355,7 @@ __global__ __launch_bounds__(OST) void k_order_tiles(OrderArgs a)
 #pragma unroll
     for (int u = 0; u < OPT; ++u) {
         const int e = u * OST + tid;
-        if (first + e < a.n) a.idx[0][first + e] = (int)first + ord[cur][e];
+        if (e < ti.count) a.idx[0][ti.first + e] = ti.first + ord[cur][e];
     }
 }
 
@@ -223,23 +372,35 @@ __device__ __forceinline__ bool before(const OrderKey& x, const OrderKey& y)
     return x.c <= y.c;
 }
 
-// Merges the sorted runs [base, base + run) and [base + run, base + 2 run) of src into dst, one workgroup per OE results.
-__global__ __launch_bounds__(OST) void k_order_merge(const int32_t* __restrict__ src, int32_t* __restrict__ dst,
-                                                     const unsigned long long* __restrict__ keys, int n, long long run)
+// Merges the sorted runs [base, base + run) and [base + run, base + 2 run) of a scan's (of all) positions of src into dst, one
+// workgroup per tile of results.
+__global__ __launch_bounds__(OST) void k_order_merge(OrderArgs a, const int32_t* __restrict__ src_all, int32_t* __restrict__ dst_all, int run)
 {
     __shared__ KeyTile k;
     __shared__ int32_t idx[OE];
     __shared__ int split[2];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const long long out0 = (long long)blockIdx.x * OE;
-    const int count = (int)min((long long)OE, (long long)n - out0);
-    const long long base = out0 / (2 * run) * (2 * run);
-    const int na = (int)min(run, (long long)n - base), nb = (int)max(0ll, min(run, (long long)n - base - run));
+    const TileInfo ti = tile_of(a, blockIdx.x);
+    if (!ti.ok) return;
+    const unsigned long long* __restrict__ keys = a.keys;
+    const int32_t* __restrict__ src = src_all + ti.p0;
+    int32_t* __restrict__ dst = dst_all + ti.p0;
+    const int out0 = ti.first - ti.p0, count = ti.count;
+    const int base = (int)((long long)out0 / (2ll * run) * (2ll * run));
+    const int na = min(run, ti.len - base), nb = max(0, min(run, ti.len - base - run));
     const int32_t *ra = src + base, *rb = src + base + run;      // rb is only read when nb > 0
+    if (nb == 0) {                                    // the last run has no partner yet
+#pragma unroll
+        for (int u = 0; u < OPT; ++u) {
+            const int e = u * OST + tid;
+            if (e < count) dst[out0 + e] = src[out0 + e];
+        }
+        return;
+    }
     if (wave < 2) {
         // how many of the first d results come from the first run: 64 places tried at once, d = where this workgroup's
         // results start (wave 0) and end (wave 1)
-        const int d = (int)(out0 - base) + (wave ? count : 0);
+        const int d = out0 - base + (wave ? count : 0);
         int lo = max(0, d - nb), hi = min(d, na);
         while (lo < hi) {
             const int step = (hi - lo + 63) >> 6;
@@ -254,7 +415,7 @@ __global__ __launch_bounds__(OST) void k_order_merge(const int32_t* __restrict__
         if (lane == 0) split[wave] = lo;
     }
     __syncthreads();
-    const int a0 = split[0], la = split[1] - a0, b0 = (int)(out0 - base) - a0, lb = count - la;
+    const int a0 = split[0], la = split[1] - a0, b0 = out0 - base - a0, lb = count - la;
 #pragma unroll
     for (int u = 0; u < OPT; ++u) {
         const int e = u * OST + tid;
@@ -316,15 +477,22 @@ hipError_t order_launch(const OrderArgs& a, const int32_t** order_out, hipStream
 {
     *order_out = a.idx[0];
     if (a.n <= 0) return hipSuccess;
-    const int tiles = (a.n + OE - 1) / OE;
+    const bool few = a.n_scans <= OSCANS;
+    const int tiles = few ? a.n / OE + a.n_scans : (a.n + OE - 1) / OE;
     const int blocks = (a.n + OT - 1) / OT;
-    k_order_init<<<(a.n_scans * 4 + OT - 1) / OT, OT, 0, stream>>>(a);
-    k_order_box<<<(a.n + OB - 1) / OB, OT, 0, stream>>>(a);
-    k_order_tiles<<<tiles, OST, 0, stream>>>(a);
+    if (few) {
+        k_order_set<<<tiles, OST, 0, stream>>>(a);
+        k_order_tiles<true><<<tiles, OST, 0, stream>>>(a);
+    } else {
+        k_order_init<<<(a.n_scans * 4 + OT - 1) / OT, OT, 0, stream>>>(a);
+        k_order_box<<<(a.n + OB - 1) / OB, OT, 0, stream>>>(a);
+        k_order_tiles<false><<<tiles, OST, 0, stream>>>(a);
+    }
     const int32_t* src = a.idx[0];
     int cur = 1;
-    for (long long run = OE; run < a.n; run *= 2) {
-        k_order_merge<<<tiles, OST, 0, stream>>>(src, a.idx[cur], a.keys, a.n, run);
+    const long long longest = few && a.max_scan_points < a.n ? a.max_scan_points : a.n;
+    for (long long run = OE; run < longest; run *= 2) {
+        k_order_merge<<<tiles, OST, 0, stream>>>(a, src, a.idx[cur], (int)run);
         src = a.idx[cur];
         cur ^= 1;
     }
