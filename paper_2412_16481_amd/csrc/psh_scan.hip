@@ -18,10 +18,14 @@
 // (a full bucket standing in for the probes that found none). The probe steps walk that list, 0 to 30 % of the points on
 // most inputs and hashes, instead of all points left (45 % after the direct step on uniform cubes, 90 % on sensor sweeps).
 //
-// Bound: instruction issue on one compute unit per scan, then the waits for the survivors' list in the probe steps (it is read
-// twice per step). us per call before (every point left walked in every step) and now: 128 scans of 131 072 points in
-// buckets of 256, 1170 and 497; 300 of 40 000 in buckets of 128, 629 and 339; 64 sensor sweeps of 30 000 in buckets of 64,
-// 484 and 252; 100 of 60 000, Z-order-mod, 334 and 210; 200 of 20 000, XOR-div, 138 and 88.
+// The count pass of a probe step reads the list; the contenders it finds, a quarter of the survivors and fewer from step to step, go on
+// a queue in LDS, bucket and number, and only those are ranked. What the queue does not hold is read from the list again.
+//
+// Bound: instruction issue on one compute unit per scan. us per call with every point left walked in every step / with every survivor
+// ranked in every step / now: 128 scans of 131 072 points in buckets of 256, 1170 / 501 / 453; 300 of 40 000 in buckets of 128, 629 /
+// 360 / 332; 64 sensor sweeps of 30 000 in buckets of 64, 484 / 253 / 236; 100 of 60 000, Z-order-mod, 334 / 167 / 165; 200 of
+// 20 000, XOR-div, 138 / 87 / 82; 600 of 20 000 in buckets of 128, - / 296 / 269. (The survivors that have a row as bits in LDS
+// instead of marks in the list: 4 to 15 us more with one workgroup per compute unit.)
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -33,9 +37,10 @@ namespace f3d {
 
 namespace {
 
+constexpr int QUEUE_MOST = (1 << 22) - 64;   // survivors of a wave that the queue can name (22 bits beside ten for the bucket)
 constexpr int SKMAX = 1024;        // most buckets per scan on this path (ten bits in a list entry; LDS: 72 bytes per bucket)
 
-// dynamic LDS, in 32-bit words: cnt[SNW][K] room[2][K] spare[SNW]
+// dynamic LDS, in 32-bit words: cnt[SNW][K] room[2][K] spare[SNW] queue[SNW][queue_cap]
 // The hash function is a template parameter: the kernel holds many scan-wide values in scalar registers, and the
 // branches between four hash functions cost enough of them to spill.
 // WPE = waves per SIMD the kernel is compiled for: 4 (128 registers, one workgroup per compute unit) or 8 (64
@@ -43,7 +48,7 @@ constexpr int SKMAX = 1024;        // most buckets per scan on this path (ten bi
 // workgroup fills the issue slots the first leaves at its barriers).
 template <int HASH, int WPE>
 __global__ __launch_bounds__(STH, WPE) void k_pshs_scan(PshArgs a, int32_t* left_idx, int32_t* surv_pos, unsigned long long* voxels,
-                                                   unsigned long long* surv_hash)
+                                                   unsigned long long* surv_hash, int queue_cap)
 {
     // Groups of 64 a wave handles per iteration, all their loads in flight together: stores and loads are waited for in order,
     // so a load an iteration ahead would wait for the stores of this one all the same; more work per wait hides it.
@@ -57,6 +62,10 @@ __global__ __launch_bounds__(STH, WPE) void k_pshs_scan(PshArgs a, int32_t* left
     __shared__ int s_round[8];
     __shared__ int s_full, s_surv;
     __shared__ int lds17[17];
+    // Z-order codes of one axis, for coordinates of up to 11 bits (131072 points x 128 scans 491 -> 483 us: three reads for 27 instructions);
+    // with two workgroups per compute unit there is no room for it
+    constexpr bool TABLE = HASH == 3 && WPE == 4;
+    __shared__ uint32_t spread[TABLE ? 2048 : 1];
     if (a.status[0]) return;   // inconsistent batch offsets: flagged by the set-up kernel, nothing to do
     const int b = blockIdx.x;
     const int p0 = a.scan_p0[b], nb = a.scan_p0[b + 1] - p0;
@@ -68,6 +77,7 @@ __global__ __launch_bounds__(STH, WPE) void k_pshs_scan(PshArgs a, int32_t* left
     uint32_t* mine = cnt + wave * K;
     int* roomb[2] = {smem + SNW * K, smem + (SNW + 1) * K};
     int* spare = smem + (SNW + 2) * K;
+    uint32_t* queue = reinterpret_cast<uint32_t*>(spare + SNW) + wave * queue_cap;   // this wave's contenders of a probe step
     // The lists: points left by the direct step (number in the scan, voxel), and of those the survivors (position in the first
     // list, number, buckets). Every list of a scan lies in the scan's own stretch of its array.
     int32_t* const surv_idx = reinterpret_cast<int32_t*>(a.key) + p0;
@@ -110,6 +120,10 @@ __global__ __launch_bounds__(STH, WPE) void k_pshs_scan(PshArgs a, int32_t* left
         if (tid == 0) compute_cfg(a, b, red, cfg);
     }
     for (int w = tid; w < SNW * K; w += STH) cnt[w] = 0u;
+    if (TABLE) {
+        spread[tid] = spread11((uint32_t)tid);
+        spread[STH + tid] = spread11((uint32_t)(STH + tid));
+    }
     __syncthreads();
     for (int k = tid; k < K; k += STH) roomb[0][k] = 0;      // the contenders so far, in the direct step
 
@@ -139,7 +153,7 @@ __global__ __launch_bounds__(STH, WPE) void k_pshs_scan(PshArgs a, int32_t* left
                               z = voxel_of(c[s].z, cfg.mn[2], a.inv_voxel);
                     int h;
                     if (NARROW) {
-                        const uint32_t code = (uint32_t)morton3_low(x, y, z);
+                        const uint32_t code = TABLE ? spread[x & 2047] | (spread[y & 2047] << 1) | (spread[z & 2047] << 2) : (uint32_t)morton3_low(x, y, z);
                         vox[s0 + s] = code;
                         h = zdiv30(code, cfg);
                     } else if (zc) {
@@ -300,14 +314,25 @@ __global__ __launch_bounds__(STH, WPE) void k_pshs_scan(PshArgs a, int32_t* left
             for (int r = 1; r <= a.n_probes; ++r) {
                 const int sh = 10 * (r - 1);
                 const int* room = roomb[cur];
+                int nq = 0, stop = nsurv;             // contenders on the queue; survivors from here on are not
                 for (int j0 = 0; j0 < nsurv; j0 += 64 * 2 * SU) {
                     unsigned long long e[2 * SU];
 #pragma unroll
                     for (int s = 0; s < 2 * SU; ++s) e[s] = surv_hash[(uint32_t)(l0 + min(j0 + s * 64 + lane, nsurv - 1))];
 #pragma unroll
                     for (int s = 0; s < 2 * SU; ++s) {
-                        const int h = (int)(e[s] >> sh) & 1023;
-                        if (j0 + s * 64 + lane < nsurv && room[h] > 0) atomicAdd(&mine[h], 1u);
+                        const int g0 = j0 + s * 64;
+                        if (g0 >= nsurv) break;
+                        const int j = g0 + lane, h = (int)(e[s] >> sh) & 1023;
+                        const bool on = j < nsurv && room[h] > 0;
+                        if (on) atomicAdd(&mine[h], 1u);
+                        const unsigned long long m = __builtin_amdgcn_ballot_w64(on);
+                        const int more = __popcll(m);
+                        if (stop == nsurv && (nq + more > queue_cap || g0 >= QUEUE_MOST)) stop = g0;
+                        if (stop == nsurv) {
+                            if (on) queue[nq + bits_below(m)] = (uint32_t)h | ((uint32_t)j << 10);
+                            nq += more;
+                        }
                     }
                 }
                 __syncthreads();
@@ -315,39 +340,63 @@ __global__ __launch_bounds__(STH, WPE) void k_pshs_scan(PshArgs a, int32_t* left
                 join_waves<true>(tid, K, cnt, room, roomb[cur ^ 1]);
                 __syncthreads();
                 int got = 0;
-                for (int j0 = 0; j0 < nsurv; j0 += 64 * SU) {
-                    unsigned long long e[SU];
-                    int pos[SU], idx[SU];
+                // SU groups of contenders at a time, those on the queue and then the others: where they come from (under way while they
+                // are ranked), their ranks, the rows of those that fit
+                for (int q0 = 0, j0 = stop; q0 < nq || j0 < nsurv;) {
+                    bool on[SU];
+                    int hh[SU], jj[SU], dst[SU], pos[SU], idx[SU];
+                    if (q0 < nq) {
 #pragma unroll
-                    for (int s = 0; s < SU; ++s) {
-                        const uint32_t j = (uint32_t)(l0 + min(j0 + s * 64 + lane, nsurv - 1));
-                        e[s] = surv_hash[j];
-                        pos[s] = surv_pos[j];
-                        idx[s] = surv_idx[j];
+                        for (int s = 0; s < SU; ++s) {
+                            const uint32_t e = queue[min(q0 + s * 64 + lane, nq - 1)];
+                            on[s] = q0 + s * 64 + lane < nq;
+                            hh[s] = (int)(e & 1023u);
+                            jj[s] = (int)(e >> 10);
+                        }
+                        q0 += 64 * SU;
+                    } else {
+#pragma unroll
+                        for (int s = 0; s < SU; ++s) {
+                            jj[s] = min(j0 + s * 64 + lane, nsurv - 1);
+                            hh[s] = (int)(surv_hash[(uint32_t)(l0 + jj[s])] >> sh) & 1023;
+                            on[s] = j0 + s * 64 + lane < nsurv && room[hh[s]] > 0;
+                        }
+                        j0 += 64 * SU;
                     }
 #pragma unroll
                     for (int s = 0; s < SU; ++s) {
-                        const int j = j0 + s * 64 + lane;
-                        const int h[1] = {(int)(e[s] >> sh) & 1023};
-                        const int f = room[h[0]];
-                        const bool act[1] = {j < nsurv && f > 0};
+                        if (__builtin_amdgcn_ballot_w64(on[s]) == 0ull) continue;
+                        pos[s] = surv_pos[(uint32_t)(l0 + jj[s])];
+                        idx[s] = surv_idx[(uint32_t)(l0 + jj[s])];
+                    }
+#pragma unroll
+                    for (int s = 0; s < SU; ++s) {
+                        const bool act[1] = {on[s]};
+                        on[s] = false;
                         if (__builtin_amdgcn_ballot_w64(act[0]) == 0ull) continue;
+                        const int h[1] = {hh[s]}, f = room[h[0]];
                         int rank[1];
                         wave_ranks<1>(h, act, keybits, mine, rank);
-                        const bool ok = act[0] && rank[0] < f;
-                        if (ok) {
-                            const int dst = p0 + h[0] * a.S + (h[0] == K - 1 ? cfg.lastcap : a.S) - f + rank[0];
-                            a.inv_perm[(uint32_t)(p0 + idx[s])] = dst;
-                            a.perm[(uint32_t)dst] = p0 + idx[s];
+                        on[s] = act[0] && rank[0] < f;
+                        dst[s] = p0 + h[0] * a.S + (h[0] == K - 1 ? cfg.lastcap : a.S) - f + rank[0];
+                    }
+#pragma unroll
+                    for (int s = 0; s < SU; ++s) {
+                        const unsigned long long m = __builtin_amdgcn_ballot_w64(on[s]);
+                        if (m == 0ull) continue;
+                        got += __popcll(m);
+                        if (on[s]) {
+                            a.inv_perm[(uint32_t)(p0 + idx[s])] = dst[s];
+                            a.perm[(uint32_t)dst[s]] = p0 + idx[s];
                             left_idx[(uint32_t)pos[s]] = -1;
                             // from now on it contends for a bucket without room
                             unsigned long long gone = 0ull;
                             for (int t = 0; t < NPROBE; ++t) gone |= all_full << (10 * t);
-                            surv_hash[(uint32_t)(l0 + j)] = gone;
+                            surv_hash[(uint32_t)(l0 + jj[s])] = gone;
                         }
-                        got += __popcll(__builtin_amdgcn_ballot_w64(ok));
                     }
                 }
+                if (got) __threadfence_block();       // another lane of the wave may read the buckets of a survivor next
                 for (int k = lane; k < K; k += 64) mine[k] = 0u;
                 if (lane == 0 && got) {
                     atomicAdd(&s_round[r], got);
@@ -442,10 +491,14 @@ hipError_t psh_scan_launch(const PshArgs& args, int32_t* left_idx, int32_t* surv
     a.meta_light = 1;   // the scan's own workgroup writes its bucket offsets
     k_psh_meta<<<1, 1024, 0, stream>>>(a);
     if (a.n == 0) return hipGetLastError();
-    const size_t lds = ((size_t)(SNW + 2) * a.kcap + SNW) * 4;
+    size_t lds = ((size_t)(SNW + 2) * a.kcap + SNW) * 4;
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 0;
     const bool two = cus > 0 && a.n_scans > cus && 2 * lds <= 150 * 1024;
+    // The queues get what LDS is left beside one or two workgroups, but no more than the points of a wave.
+    const size_t most = (two ? 75 : 150) * 1024, room = lds < most ? (most - lds) / (SNW * 4) : 0, all = (size_t)(a.max_scan_points / SNW) + 64;
+    const int queue_cap = (int)(room < all ? room : all);
+    lds += (size_t)SNW * queue_cap * 4;
     const void* fn[8] = {(const void*)k_pshs_scan<0, 4>, (const void*)k_pshs_scan<1, 4>, (const void*)k_pshs_scan<2, 4>,
                          (const void*)k_pshs_scan<3, 4>, (const void*)k_pshs_scan<0, 8>, (const void*)k_pshs_scan<1, 8>,
                          (const void*)k_pshs_scan<2, 8>, (const void*)k_pshs_scan<3, 8>};
@@ -455,14 +508,14 @@ hipError_t psh_scan_launch(const PshArgs& args, int32_t* left_idx, int32_t* surv
         if (e != hipSuccess) return e;
     }
     switch (which) {
-        case 0: k_pshs_scan<0, 4><<<a.n_scans, STH, lds, stream>>>(a, left_idx, surv_pos, voxels, surv_hash); break;
-        case 1: k_pshs_scan<1, 4><<<a.n_scans, STH, lds, stream>>>(a, left_idx, surv_pos, voxels, surv_hash); break;
-        case 2: k_pshs_scan<2, 4><<<a.n_scans, STH, lds, stream>>>(a, left_idx, surv_pos, voxels, surv_hash); break;
-        case 3: k_pshs_scan<3, 4><<<a.n_scans, STH, lds, stream>>>(a, left_idx, surv_pos, voxels, surv_hash); break;
-        case 4: k_pshs_scan<0, 8><<<a.n_scans, STH, lds, stream>>>(a, left_idx, surv_pos, voxels, surv_hash); break;
-        case 5: k_pshs_scan<1, 8><<<a.n_scans, STH, lds, stream>>>(a, left_idx, surv_pos, voxels, surv_hash); break;
-        case 6: k_pshs_scan<2, 8><<<a.n_scans, STH, lds, stream>>>(a, left_idx, surv_pos, voxels, surv_hash); break;
-        default: k_pshs_scan<3, 8><<<a.n_scans, STH, lds, stream>>>(a, left_idx, surv_pos, voxels, surv_hash); break;
+        case 0: k_pshs_scan<0, 4><<<a.n_scans, STH, lds, stream>>>(a, left_idx, surv_pos, voxels, surv_hash, queue_cap); break;
+        case 1: k_pshs_scan<1, 4><<<a.n_scans, STH, lds, stream>>>(a, left_idx, surv_pos, voxels, surv_hash, queue_cap); break;
+        case 2: k_pshs_scan<2, 4><<<a.n_scans, STH, lds, stream>>>(a, left_idx, surv_pos, voxels, surv_hash, queue_cap); break;
+        case 3: k_pshs_scan<3, 4><<<a.n_scans, STH, lds, stream>>>(a, left_idx, surv_pos, voxels, surv_hash, queue_cap); break;
+        case 4: k_pshs_scan<0, 8><<<a.n_scans, STH, lds, stream>>>(a, left_idx, surv_pos, voxels, surv_hash, queue_cap); break;
+        case 5: k_pshs_scan<1, 8><<<a.n_scans, STH, lds, stream>>>(a, left_idx, surv_pos, voxels, surv_hash, queue_cap); break;
+        case 6: k_pshs_scan<2, 8><<<a.n_scans, STH, lds, stream>>>(a, left_idx, surv_pos, voxels, surv_hash, queue_cap); break;
+        default: k_pshs_scan<3, 8><<<a.n_scans, STH, lds, stream>>>(a, left_idx, surv_pos, voxels, surv_hash, queue_cap); break;
     }
     return hipGetLastError();
 }

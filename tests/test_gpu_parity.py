@@ -454,6 +454,20 @@ def test_bucketize_canonical_order_many_scans_with_empty_ones():
     check_bucketize(c, bo, 0.05, 64, 4, "zorder_div", order="canonical")
 
 
+@pytest.mark.parametrize("hash", ["zorder_div", "xor_div"])
+@pytest.mark.parametrize("n_scans,points,cap", [(60, 20_000, 1024), (60, 40_000, 256), (300, 16_300, 64), (300, 5000, 64), (49, 1025, 128)])
+def test_bucketize_scans_with_more_contenders_than_a_queue_holds(n_scans, points, cap, hash):
+    """One workgroup per scan: the contenders of a probe step are queued in what LDS the counters of the buckets leave. Room for all
+    of them, for 50 per wave (1019 buckets, two workgroups per compute unit) and sizes between; Z-order-div uses its table of codes
+    with one workgroup per compute unit and not with two."""
+    rng = np.random.default_rng(70 + n_scans)
+    sizes = rng.integers(points * 9 // 10, points + 1, n_scans)
+    bo = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    c = (rng.random((int(bo[-1]), 3)) * 20).astype(np.float32)
+    c[::3] = (c[::3] * 0.05 + 3.0).astype(np.float32)      # a dense corner that overflows into its neighbours
+    check_bucketize(c, bo, 0.05, cap, 4, hash, max_scan_points=int(sizes.max()), schedule="scans")
+
+
 @pytest.mark.parametrize("n_scans", [2, 63, 64, 65, 511, 512, 513])
 def test_bucketize_canonical_order_sorts_every_scan_by_itself(n_scans):
     """Tiles of the sort never reach over the end of a scan: scans of no, one and two tiles and one point around that, scans of more
