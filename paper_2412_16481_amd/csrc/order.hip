@@ -83,7 +83,7 @@ __global__ __launch_bounds__(OST) void k_order_set(OrderArgs a)
         const int tiles = (nb + OE - 1) / OE;
         int t0, total, bad;
         if (ns <= 64) {
-            const int last = wave_incl_scan(tiles, lane);
+            const int last = wave_incl_scan(tiles);
             t0 = last - tiles;
             total = __shfl(last, 63, 64);
             bad = __builtin_amdgcn_ballot_w64(!good) != 0ull;
@@ -134,10 +134,8 @@ __global__ __launch_bounds__(OST) void k_order_set(OrderArgs a)
 #pragma unroll
     for (int x = 0; x < 3; ++x) {
         uint32_t lo = mn[x], hi = mx[x];
-        for (int d = 32; d >= 1; d >>= 1) {
-            lo = min(lo, (uint32_t)__shfl_xor((int)lo, d, 64));
-            hi = max(hi, (uint32_t)__shfl_xor((int)hi, d, 64));
-        }
+        lo = wave_min(lo);
+        hi = wave_max(hi);
         if (lane == 0) { atomicMin(&red[x], lo); atomicMax(&red[4 + x], hi); }
     }
     __syncthreads();
@@ -271,10 +269,8 @@ __global__ __launch_bounds__(OST) void k_order_tiles(OrderArgs a)
         }
 #pragma unroll
         for (int x = 0; x < 3; ++x) {
-            for (int d = 32; d >= 1; d >>= 1) {
-                lo[x] = min(lo[x], (uint32_t)__shfl_xor((int)lo[x], d, 64));
-                hi[x] = max(hi[x], (uint32_t)__shfl_xor((int)hi[x], d, 64));
-            }
+            lo[x] = wave_min(lo[x]);
+            hi[x] = wave_max(hi[x]);
             if (tid == 0) { box[x] = lo[x]; box[4 + x] = hi[x]; }
         }
     }

@@ -812,7 +812,7 @@ __global__ __launch_bounds__(PT, WPE) void k_pool(PoolArgs a)
 #pragma unroll
         for (int ax = 0; ax < 3; ++ax) {
             uint32_t lo = o[ax];
-            for (int d = 32; d >= 1; d >>= 1) lo = min(lo, (uint32_t)__shfl_xor((int)lo, d, 64));
+            lo = wave_min(lo);
             if (lane == 0) atomicMin(&red[ax], lo);
         }
     }
@@ -829,7 +829,7 @@ __global__ __launch_bounds__(PT, WPE) void k_pool(PoolArgs a)
 #pragma unroll
         for (int ax = 0; ax < 3; ++ax) {
             int hi = v[ax];
-            for (int d = 32; d >= 1; d >>= 1) hi = max(hi, __shfl_xor(hi, d, 64));
+            hi = (int)wave_max((uint32_t)hi);
             if (lane == 0) atomicMax(&red[4 + ax], (uint32_t)hi);
         }
     }
@@ -972,7 +972,7 @@ __global__ __launch_bounds__(PT, WPE) void k_pool(PoolArgs a)
 #pragma unroll
         for (int ax = 0; ax < 3; ++ax) {
             uint32_t hi = f2ord(far[ax]);
-            for (int d = 32; d >= 1; d >>= 1) hi = max(hi, (uint32_t)__shfl_xor((int)hi, d, 64));
+            hi = wave_max(hi);
             if (lane == 0) atomicMax(&red[8 + ax], hi);
         }
         __syncthreads();

@@ -130,10 +130,8 @@ __global__ __launch_bounds__(PSH_THREADS) void k_psh_minmax(PshArgs a)
 #pragma unroll
     for (int t = 0; t < 3; ++t) {
         uint32_t lo = mn[t], hi = mx[t];
-        for (int d = 32; d >= 1; d >>= 1) {
-            lo = min(lo, (uint32_t)__shfl_xor((int)lo, d, 64));
-            hi = max(hi, (uint32_t)__shfl_xor((int)hi, d, 64));
-        }
+        lo = wave_min(lo);
+        hi = wave_max(hi);
         if ((threadIdx.x & 63) == 0) { atomicMin(&red[t], lo); atomicMax(&red[4 + t], hi); }
     }
     __syncthreads();
@@ -253,7 +251,7 @@ __global__ __launch_bounds__(PSH_THREADS) void k_psh_step(PshArgs a, int r)
         }
     }
     if (r > 0) {
-        for (int d = 32; d >= 1; d >>= 1) nplaced += __shfl_xor(nplaced, d, 64);
+        nplaced = wave_sum(nplaced);
         if (lane == 0 && nplaced) atomicAdd(&placed_ct, nplaced);
         __syncthreads();
         if (tid == 0 && placed_ct) atomicAdd(&a.round_count[r - 1], placed_ct);
@@ -360,7 +358,7 @@ __global__ __launch_bounds__(PSH_THREADS) void k_psh_recycle_place(PshArgs a)
     }
     // one atomic per workgroup: per-wave atomics of thousands of workgroups on one counter queue up
     __shared__ int s_mine;
-    for (int d = 32; d >= 1; d >>= 1) mine += __shfl_xor(mine, d, 64);
+    mine = wave_sum(mine);
     if (threadIdx.x == 0) s_mine = 0;
     __syncthreads();
     if ((threadIdx.x & 63) == 0 && mine) atomicAdd(&s_mine, mine);

@@ -81,10 +81,8 @@ __global__ __launch_bounds__(FTH) void k_pshf_minmax(PshArgs a)
 #pragma unroll
     for (int t = 0; t < 3; ++t) {
         uint32_t lo = mn[t], hi = mx[t];
-        for (int d = 32; d >= 1; d >>= 1) {
-            lo = min(lo, (uint32_t)__shfl_xor((int)lo, d, 64));
-            hi = max(hi, (uint32_t)__shfl_xor((int)hi, d, 64));
-        }
+        lo = wave_min(lo);
+        hi = wave_max(hi);
         if ((threadIdx.x & 63) == 0) { atomicMin(&red[t], lo); atomicMax(&red[4 + t], hi); }
     }
     __syncthreads();
@@ -127,7 +125,7 @@ __global__ __launch_bounds__(FTH) void k_pshf_setup(PshArgs a)
             }
         }
         const bool bad = __builtin_amdgcn_ballot_w64(!ok) != 0ull;
-        const int kin = wave_incl_scan(K, lane), cin = wave_incl_scan(c, lane);
+        const int kin = wave_incl_scan(K), cin = wave_incl_scan(c);
         if (lane < ns) {
             s_p0[lane] = p0;
             s_kb0[lane] = kin - K;
@@ -206,10 +204,8 @@ __global__ __launch_bounds__(FTH) void k_pshf_setup(PshArgs a)
 #pragma unroll
     for (int t = 0; t < 3; ++t) {
         uint32_t lo = mn[t], hi = mx[t];
-        for (int d = 32; d >= 1; d >>= 1) {
-            lo = min(lo, (uint32_t)__shfl_xor((int)lo, d, 64));
-            hi = max(hi, (uint32_t)__shfl_xor((int)hi, d, 64));
-        }
+        lo = wave_min(lo);
+        hi = wave_max(hi);
         if (lane == 0) { atomicMin(&red[t], lo); atomicMax(&red[4 + t], hi); }
     }
     __syncthreads();
@@ -268,10 +264,8 @@ __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32
                 }
 #pragma unroll
                 for (int ax = 0; ax < 3; ++ax) {
-                    for (int d = 32; d >= 1; d >>= 1) {
-                        lo[ax] = min(lo[ax], (uint32_t)__shfl_xor((int)lo[ax], d, 64));
-                        hi[ax] = max(hi[ax], (uint32_t)__shfl_xor((int)hi[ax], d, 64));
-                    }
+                    lo[ax] = wave_min(lo[ax]);
+                    hi[ax] = wave_max(hi[ax]);
                     box[ax] = lo[ax];
                     box[4 + ax] = hi[ax];
                 }
@@ -410,7 +404,7 @@ __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32
                 carry += t2;
             }
         }
-        for (int d = 32; d >= 1; d >>= 1) turned += __shfl_xor(turned, d, 64);
+        turned = wave_sum(turned);
         if (lane == 0 && turned) atomicAdd(&left_before, turned);
         __syncthreads();
         unsigned long long rest[PPT];
@@ -458,10 +452,8 @@ __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32
             at += __popcll(rest[s]);
         }
         // one atomic per workgroup: hundreds of waves adding to the same counter queue up behind each other
-        for (int d = 32; d >= 1; d >>= 1) {
-            nplaced += __shfl_xor(nplaced, d, 64);
-            nrec += __shfl_xor(nrec, d, 64);
-        }
+        nplaced = wave_sum(nplaced);
+        nrec = wave_sum(nrec);
         if (lane == 0 && nplaced) atomicAdd(&placed_ct, nplaced);
         if (lane == 0 && nrec) atomicAdd(&recycled_ct, nrec);
         __syncthreads();
@@ -564,7 +556,7 @@ __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32
     }
     if (r > 0) {
         int n2 = nplaced | (nwait << 16);     // a chunk has at most 2048 points
-        for (int d = 32; d >= 1; d >>= 1) n2 += __shfl_xor(n2, d, 64);
+        n2 = wave_sum(n2);
         if (lane == 0 && n2) atomicAdd(&placed_ct, n2);
         __syncthreads();
         if (tid == 0 && (placed_ct & 0xFFFF)) atomicAdd(&a.round_count[r - 1], placed_ct & 0xFFFF);

@@ -110,10 +110,8 @@ __global__ __launch_bounds__(STH, WPE) void k_pshs_scan(PshArgs a, int32_t* left
 #pragma unroll
         for (int t = 0; t < 3; ++t) {
             uint32_t lo = mn[t], hi = mx[t];
-            for (int d = 32; d >= 1; d >>= 1) {
-                lo = min(lo, (uint32_t)__shfl_xor((int)lo, d, 64));
-                hi = max(hi, (uint32_t)__shfl_xor((int)hi, d, 64));
-            }
+            lo = wave_min(lo);
+            hi = wave_max(hi);
             if (lane == 0) { atomicMin(&red[t], lo); atomicMax(&red[4 + t], hi); }
         }
         __syncthreads();

@@ -108,10 +108,8 @@ __global__ __launch_bounds__(STH) void k_pshs_small(PshArgs a)
         }
 #pragma unroll
         for (int t = 0; t < 3; ++t) {
-            for (int d = 32; d >= 1; d >>= 1) {
-                mn[t] = min(mn[t], (uint32_t)__shfl_xor((int)mn[t], d, 64));
-                mx[t] = max(mx[t], (uint32_t)__shfl_xor((int)mx[t], d, 64));
-            }
+            mn[t] = wave_min(mn[t]);
+            mx[t] = wave_max(mx[t]);
             if (lane == 0) {
                 atomicMin(&red[t], mn[t]);
                 atomicMax(&red[4 + t], mx[t]);
