@@ -454,6 +454,18 @@ def test_bucketize_canonical_order_many_scans_with_empty_ones():
     check_bucketize(c, bo, 0.05, 64, 4, "zorder_div", order="canonical")
 
 
+@pytest.mark.parametrize("n,scans,cap", [(9000, 1, 4096), (9000, 1, 128), (30_000, 1, 512), (60_000, 1, 256), (120_000, 1, 1024), (150_000, 1, 512),
+                                         (200_000, 1, 1024), (300_000, 1, 2048), (800_000, 8, 1024), (400_000, 20, 2048)])
+def test_bucketize_steps_with_few_and_many_count_rows_per_thread(n, scans, cap):
+    """One launch per step: a thread sums up to 4, 7 or 10 count rows at a time, in one or several goes, and threads without a row do
+    not join. From 1 to 13 rows a thread, more threads than rows and column groups from 2 to 147."""
+    rng = np.random.default_rng(n + cap)
+    bo = np.round(np.linspace(0, n, scans + 1)).astype(np.int32)
+    c = (rng.random((n, 3)) * 12).astype(np.float32)
+    c[::2] = (c[::2] * 0.1).astype(np.float32)
+    check_bucketize(c, bo, 0.05, cap, 4, "zorder_div", max_scan_points=int(np.diff(bo).max()), schedule="steps")
+
+
 @pytest.mark.parametrize("hash", ["zorder_div", "xor_div"])
 @pytest.mark.parametrize("n_scans,points,cap", [(60, 20_000, 1024), (60, 40_000, 256), (300, 16_300, 64), (300, 5000, 64), (49, 1025, 128)])
 def test_bucketize_scans_with_more_contenders_than_a_queue_holds(n_scans, points, cap, hash):
