@@ -91,9 +91,8 @@ __global__ __launch_bounds__(OST) void k_order_set(OrderArgs a)
             t0 = block_excl_scan(tiles, &total, lds17);
             bad = __syncthreads_or(!good);
         }
-        if (tid == 0) s_info.ok = 0;
-        if (ns > 64) __syncthreads();
-        if (t0 <= t && t < t0 + tiles && !bad && tid < ns) {      // this thread's scan has the tile
+        // One thread writes s_info: the one whose scan has the tile, thread 0 where there is none.
+        if (t0 <= t && t < t0 + tiles && !bad && tid < ns) {
             TileInfo f;
             f.scan = tid;
             f.t0 = t0;
@@ -106,7 +105,10 @@ __global__ __launch_bounds__(OST) void k_order_set(OrderArgs a)
             s_info = f;
             reinterpret_cast<TileInfo*>(a.tile_info)[t] = f;
         }
-        if (tid == 0 && (bad || t >= total)) reinterpret_cast<TileInfo*>(a.tile_info)[t].ok = 0;
+        if (tid == 0 && (bad || t >= total)) {
+            s_info.ok = 0;
+            reinterpret_cast<TileInfo*>(a.tile_info)[t].ok = 0;
+        }
     }
     if (tid < 3) {
         red[tid] = 0xFFFFFFFFu;

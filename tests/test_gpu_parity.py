@@ -499,6 +499,31 @@ def test_bucketize_canonical_order_sorts_every_scan_by_itself(n_scans):
     assert np.array_equal(np.sort(got.perm.cpu().numpy()), np.arange(len(c)))
 
 
+@pytest.mark.parametrize("n_scans", [2, 64, 65])
+def test_bucketize_canonical_order_in_a_workspace_of_another_batch(n_scans):
+    """Every tile of the sort writes its place and its bounding box, or that there is no such tile, before either is read: in one workspace
+    a batch of many tiles far away, one of bad offsets, one of few tiles, and bytes that are no boxes."""
+    rng = np.random.default_rng(80 + n_scans)
+    far = np.linspace(0, 40_000, n_scans + 1).astype(np.int32)
+    near = np.zeros(n_scans + 1, np.int32)
+    near[n_scans // 2 + 1:] = 3000
+    near[-1] = 7001
+    p = f3d.make_params(0.05, 256, order="canonical")
+    ws = torch.empty(f3d.workspace_bytes(40_000, n_scans, p), dtype=torch.uint8, device="cuda")
+    c = clustered_cloud(rng, 7001)
+    ref = oracle.bucketize(c, near, 0.05, 64, "zorder_div", order="canonical")
+    for before in ("far", "bad", 0, 255):
+        if before == "far":
+            f3d.psh_bucketize(dev(clustered_cloud(rng, 40_000, -90.0)), dev(far), p, workspace=ws)
+        elif before == "bad":
+            bad = f3d.psh_bucketize(dev(c), dev(near + 1), p, workspace=ws)
+            assert int(bad.scan_bucket_start[-1]) == -1
+        else:
+            ws.fill_(before)
+        got = f3d.psh_bucketize(dev(c), dev(near), p, workspace=ws)
+        assert np.array_equal(got.perm.cpu().numpy(), ref["perm"]), before
+
+
 @pytest.mark.parametrize("probe_mode", ["axes", "seeded"])
 def test_bucketize_canonical_order_is_equivariant_to_input_order_on_the_gpu(probe_mode):
     rng = np.random.default_rng(32)
