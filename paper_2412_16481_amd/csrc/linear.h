@@ -6,6 +6,7 @@
 namespace f3d {
 
 constexpr int LIN_MAX_OUTS = 4;
+constexpr int LIN_MAX_COLUMNS = 4096;
 
 struct LinearArgs {
     const uint16_t* x;        // bf16 [n, c_in]

@@ -31,6 +31,7 @@
 #include <stdint.h>
 
 #include "attn_common.h"
+#include "launch.h"
 #include "linear.h"
 
 namespace f3d {
@@ -306,6 +307,8 @@ bool in_place(const LinearArgs& a)
     return false;
 }
 
+constexpr size_t linear_lds_bytes(int c_out) { return (size_t)c_out * 4 + (size_t)c_out / 16 * sizeof(uint16_t*); }
+
 template <int CI, bool LN, bool RES, bool STREAMED>
 hipError_t launch_form(const LinearArgs& a, hipStream_t stream)
 {
@@ -317,10 +320,10 @@ hipError_t launch_form(const LinearArgs& a, hipStream_t stream)
     // rows holds them in registers before its first store, a second one would read what the first has stored.
     const unsigned units = (unsigned)(a.c_out / 64);
     const unsigned split = blocks >= 512 || in_place(a) ? 1u : (512u / blocks < units ? 512u / blocks : units);
-    const size_t lds = (size_t)a.c_out * 4 + (size_t)a.c_out / 16 * sizeof(uint16_t*);
+    const size_t lds = linear_lds_bytes(a.c_out);
     // tiles and results in static LDS, 32 or 48 KB: from 3000 columns or so on the sum passes what a kernel gets unasked
     if (2 * Tile<CI>::BYTES + LNW * 4096 + lds > 60000) {
-        const hipError_t e = hipFuncSetAttribute((const void*)k_ln_linear<CI, LN, RES, STREAMED>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        const hipError_t e = allow_lds((const void*)k_ln_linear<CI, LN, RES, STREAMED>, linear_lds_bytes(LIN_MAX_COLUMNS));
         if (e != hipSuccess) return e;
     }
     k_ln_linear<CI, LN, RES, STREAMED><<<dim3(blocks, split), LTH, lds, stream>>>(a);

@@ -13,6 +13,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "launch.h"
 #include "pool.h"
 #include "psh_common.h"
 #include <type_traits>
@@ -1142,16 +1143,16 @@ hipError_t pool_launch(const PoolArgs& args, hipStream_t stream)
     size_t lds = pool_lds_bytes(a.kp);
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 0;
-    const bool two = cus > 0 && a.n_tiles_ub > cus && 2 * lds <= 160 * 1024;
+    const bool two = cus > 0 && a.n_tiles_ub > cus && 2 * (lds + POOL_STATIC_LDS) <= 160 * 1024;
+    const size_t most = (two ? 80 : 128) * 1024 - POOL_STATIC_LDS;
     if (a.rho == 2) {
         // what LDS is left beside one or two workgroups holds the lists of the last rows (POOL_STATIC_LDS: the kernel's own variables)
-        const size_t most = (two ? 80 : 128) * 1024 - POOL_STATIC_LDS, all = pool_list_entries(a.tile) * 2;
+        const size_t all = pool_list_entries(a.tile) * 2;
         if (lds < most) lds += (most - lds < all ? most - lds : all) & ~(size_t)15;
         a.near_cap = (int)((lds - pool_lds_bytes(a.kp)) / 2) + (PW - 2) * a.kp;
     }
     if (lds > 60000) {
-        const hipError_t e = two ? hipFuncSetAttribute((const void*)k_pool<8>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)
-                                 : hipFuncSetAttribute((const void*)k_pool<4>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        const hipError_t e = allow_lds(two ? (const void*)k_pool<8> : (const void*)k_pool<4>, most);
         if (e != hipSuccess) return e;
     }
     if (two) {

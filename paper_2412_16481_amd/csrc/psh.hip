@@ -14,6 +14,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "flash3d.h"
+#include "launch.h"
 #include "psh_common.h"
 
 namespace f3d {
@@ -367,6 +369,8 @@ __global__ __launch_bounds__(PSH_THREADS) void k_psh_recycle_place(PshArgs a)
 }
 
 // ------------------------------------------------------------------------------------------------
+static constexpr size_t step_lds_bytes(int kcap) { return (size_t)kcap * 4 + (size_t)PSH_WAVES * ((kcap + 1) / 2) * 4; }
+
 hipError_t psh_launch(const PshArgs& args, hipStream_t stream)
 {
     PshArgs a = args;
@@ -376,9 +380,9 @@ hipError_t psh_launch(const PshArgs& args, hipStream_t stream)
     if (a.n == 0) return hipGetLastError();
     const int chunks = (int)(a.n / PSH_CHUNK) + a.n_scans;  // upper bound, surplus workgroups exit
     k_psh_minmax<<<chunks, PSH_THREADS, 0, stream>>>(a);
-    const size_t lds = (size_t)a.kcap * 4 + (size_t)PSH_WAVES * ((a.kcap + 1) / 2) * 4;
+    const size_t lds = step_lds_bytes(a.kcap);
     if (lds > 60000) {
-        const hipError_t e = hipFuncSetAttribute((const void*)k_psh_step, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        const hipError_t e = allow_lds((const void*)k_psh_step, step_lds_bytes(F3D_MAX_SCAN_BUCKETS));
         if (e != hipSuccess) return e;
     }
     const dim3 cgrid((a.kcap + 63) / 64, a.n_scans);

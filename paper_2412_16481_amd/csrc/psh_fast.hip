@@ -15,6 +15,7 @@
 
 #include <type_traits>
 
+#include "launch.h"
 #include "psh_common.h"
 
 namespace f3d {
@@ -609,14 +610,16 @@ size_t psh_fast_matrix_bytes(long long chunks, int kcap)
 
 namespace {
 
+inline size_t step_lds_bytes(int threads, int kcap) { return (size_t)group_pitch(kcap) * 64 + (size_t)(threads / 64) * row_pitch(kcap) * 4; }
+
 template <int CH, int TH>
 hipError_t launch_steps(PshArgs a, int chunks, hipStream_t stream)
 {
     const int kwp = row_pitch(a.kcap);
-    const size_t lds = (size_t)group_pitch(a.kcap) * 64 + (size_t)(TH / 64) * kwp * 4;
+    const size_t lds = step_lds_bytes(TH, a.kcap);
     if (lds > 60000) {
         for (const void* fn : {(const void*)k_pshf_step<CH, TH, false>, (const void*)k_pshf_step<CH, TH, true>}) {
-            const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            const hipError_t e = allow_lds(fn, step_lds_bytes(TH, FKMAX));
             if (e != hipSuccess) return e;
         }
     }

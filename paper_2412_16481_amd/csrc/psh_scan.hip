@@ -31,6 +31,7 @@
 
 #include <type_traits>
 
+#include "launch.h"
 #include "psh_block.h"
 
 namespace f3d {
@@ -502,7 +503,7 @@ hipError_t psh_scan_launch(const PshArgs& args, int32_t* left_idx, int32_t* surv
                          (const void*)k_pshs_scan<2, 8>, (const void*)k_pshs_scan<3, 8>};
     const int which = (a.hash & 3) + (two ? 4 : 0);
     if (lds > 60000) {
-        const hipError_t e = hipFuncSetAttribute(fn[which], hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        const hipError_t e = allow_lds(fn[which], most);
         if (e != hipSuccess) return e;
     }
     switch (which) {

@@ -23,6 +23,7 @@
 
 #include <type_traits>
 
+#include "launch.h"
 #include "psh_block.h"
 
 namespace f3d {
@@ -503,11 +504,13 @@ __global__ __launch_bounds__(STH) void k_pshs_small(PshArgs a)
     }
 }
 
+constexpr size_t small_lds_bytes(int ppt, int kcap) { return ((size_t)(SNW + 2) * kcap + (size_t)ppt * STH / 32 + (size_t)ppt * STH) * 4; }
+
 template <int PPT>
 hipError_t launch_small(const PshArgs& a, hipStream_t stream)
 {
-    const size_t lds = ((size_t)(SNW + 2) * a.kcap + (size_t)PPT * STH / 32 + (size_t)PPT * STH) * 4;
-    const hipError_t e = hipFuncSetAttribute((const void*)k_pshs_small<PPT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    const size_t lds = small_lds_bytes(PPT, a.kcap);
+    const hipError_t e = allow_lds((const void*)k_pshs_small<PPT>, small_lds_bytes(PPT, MKMAX));
     if (e != hipSuccess) return e;
     k_pshs_small<PPT><<<a.n_scans, STH, lds, stream>>>(a);
     return hipGetLastError();

@@ -5,6 +5,7 @@ import os
 import re
 import shutil
 import subprocess
+import sys
 
 import pytest
 
@@ -59,6 +60,82 @@ def test_every_load_into_lds_waits_for_the_write_of_m0(tmp_path):
                 assert not re.match(r"s_\w+ m0\b", before), f"{part.name}: {before}; {line}"
             before = line or before
     assert loads > 0
+
+
+RECORDING_RUNTIME = r"""
+// stands in for the HIP runtime on a machine without a GPU: says what LDS a kernel is allowed and what every launch asks for
+#include <stddef.h>
+#include <stdio.h>
+typedef struct { unsigned x, y, z; } dim3;
+static size_t lds;
+int hipFuncSetAttribute(const void* f, int attr, int value) { fprintf(stderr, "allow %p %d %d\n", f, attr, value); return 0; }
+int hipLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t bytes, void* s) { fprintf(stderr, "launch %p %zu\n", f, bytes); return 0; }
+int __hipPushCallConfiguration(dim3 g, dim3 b, size_t bytes, void* s) { lds = bytes; return 0; }
+int __hipPopCallConfiguration(dim3* g, dim3* b, size_t* bytes, void** s)
+{
+    const dim3 one = {1, 1, 1};
+    *g = one; *b = one; *bytes = lds; *s = 0;
+    return 0;
+}
+int hipGetDevice(int* d) { *d = 0; return 0; }
+int hipDeviceGetAttribute(int* v, int attr, int d) { *v = 256; return 0; }
+int hipGetLastError(void) { return 0; }
+void** __hipRegisterFatBinary(const void* data) { static void* h; return &h; }
+void __hipRegisterFunction(void** m, const void* f, char* d, const char* n, unsigned l, void* t, void* b, void* bd, void* gd, int* w) {}
+void __hipRegisterVar(void** m, void* v, char* h, char* d, int e, size_t size, int c, int g) {}
+void __hipUnregisterFatBinary(void** m) {}
+"""
+
+CALLS_OF_MANY_SIZES = """
+import ctypes, sys
+from ctypes import byref, c_float, c_int32, c_int64, c_size_t, c_void_p
+ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+import paper_2412_16481_amd as f3d
+L = ctypes.CDLL(f3d.LIB_PATH)
+at, big = c_void_p(0x10000), c_size_t(1 << 40)     # never followed: nothing is launched
+def bucketize(n, scans, most, cap, hash="zorder_div", schedule="auto"):
+    p = f3d.make_params(0.05, cap, hash=hash, max_scan_points=most, schedule=schedule)
+    return L.f3d_psh_bucketize(at, None, c_int64(n), scans, byref(p), at, None, at, at, None, at, big, None)
+def pool(n, tile, rho):
+    return L.f3d_inbucket_pool(at, None, at, None, c_int64(n), 1, 8, tile, rho, c_float(0.1), 3, 0, at, None, None, at, at, big, None)
+def linear(c_in, c_out):
+    return L.f3d_ln_linear(at, None, None, None, c_float(0), at, None, None, c_int64(100), c_in, c_out, (c_void_p * 1)(0x10000), 1, None, None)
+rc = []
+for n in (3000, 3000000):
+    for tile in (66, 256, 640, 1024):
+        rc += [pool(n, tile, rho) for rho in (1, 2, 4)]
+for hash in ("xor_mod", "xor_div", "zorder_mod", "zorder_div"):
+    for scans in (60, 600):
+        rc += [bucketize(scans * most, scans, most, cap, hash, "scans") for most in (900, 5000, 50000) for cap in (256, 1024) if 4 * most <= 1024 * cap]
+rc += [bucketize(n, 1, n, cap) for n in (500, 3000, 5000, 8000) for cap in (64, 1024)]
+rc += [bucketize(n, 1, n, cap, schedule="steps") for n in (3000, 30000, 200000) for cap in (64, 256, 1024) if 4 * n <= 2048 * cap and n * n // cap < 1 << 25]
+rc += [bucketize(n, 1, n, cap, schedule="general") for n in (30000, 500000) for cap in (256, 1024)]
+rc += [linear(c_in, c_out) for c_in in (64, 128, 256) for c_out in (64, 3648, 4096)]
+print("codes", *rc)
+"""
+
+
+def test_lds_allowed_to_a_kernel_is_the_same_in_every_call(tmp_path):
+    """How much dynamic LDS a kernel may be launched with is a setting of the kernel, shared by all threads of the process. If a call
+    set it to what it needs itself, a smaller call of another thread could lower it between that setting and the launch."""
+    cc = shutil.which("gcc") or shutil.which("cc")
+    if cc is None:
+        pytest.skip("no C compiler here")
+    (tmp_path / "hip.c").write_text(RECORDING_RUNTIME)
+    (tmp_path / "calls.py").write_text(CALLS_OF_MANY_SIZES)
+    subprocess.run([cc, "-shared", "-fPIC", "-w", "-fno-builtin", "-o", tmp_path / "hip.so", tmp_path / "hip.c"], check=True)
+    run = subprocess.run([sys.executable, tmp_path / "calls.py", tmp_path / "hip.so"], cwd=ROOT, env={**os.environ, "PYTHONPATH": ROOT},
+                         capture_output=True, text=True)
+    assert run.returncode == 0, run.stderr
+    allowed, launches = {}, 0
+    assert set(run.stdout.split()) == {"codes", "0"}
+    for word in (line.split() for line in run.stderr.splitlines()):
+        if word[0] == "allow":
+            assert allowed.setdefault(word[1], word[2:]) == word[2:], "set to two values"
+        elif word[0] == "launch":
+            assert int(word[2]) <= int(allowed.get(word[1], [0, 65536])[1])
+            launches += 1
+    assert len(allowed) >= 18 and launches > 100     # pooling 2, one workgroup per scan 8, small scans 3, a launch per step 2, general 1, linear 2
 
 
 def test_params_default_and_sizes():

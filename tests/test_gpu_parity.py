@@ -5,6 +5,8 @@ counts must match bit for bit. Attention is compared element by element within m
 (bf16 inputs and outputs, fp32 accumulation on the GPU; binary64 in the oracle); at the full
 benchmark sizes the comparison runs on sampled query rows, each computed in full by the oracle.
 """
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -1756,6 +1758,41 @@ def test_calls_on_two_streams_do_not_share_state():
         for bk, out in results[j]:
             assert torch.equal(bk.perm, alone.perm) and torch.equal(bk.offsets, alone.offsets)
             assert torch.equal(out.view(torch.int16), out_alone.view(torch.int16))
+
+
+def test_calls_of_two_threads_with_different_sizes():
+    """Two threads, each on a stream of its own, call the kernels that take as much LDS as a call's sizes need, with different sizes: each
+    gets what it gets alone."""
+    rng = np.random.default_rng(90)
+    jobs = []
+    for tile, sizes in ((1024, [30_000] * 60), (256, [3000] * 49)):
+        n = sum(sizes)
+        coords, bo = dev(clustered_cloud(rng, n)), dev(np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32))
+        feat = torch.randn(n, 8, device=DEV).bfloat16()
+        p = f3d.make_params(0.05, 256, max_scan_points=max(sizes), schedule="scans")
+
+        def call(coords=coords, bo=bo, feat=feat, p=p, tile=tile):
+            bk = f3d.psh_bucketize(coords, bo, p)
+            return bk.perm, f3d.inbucket_pool(coords, bk.perm, feat, bo, tile, 2, 0.1)
+        jobs.append((call, call(), [], torch.cuda.Stream()))
+    torch.cuda.synchronize()
+
+    def work(call, alone, got, stream):
+        with torch.cuda.stream(stream):
+            for _ in range(8):
+                got.append(call())
+            stream.synchronize()
+    threads = [threading.Thread(target=work, args=job) for job in jobs]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for call, (perm, pooled), got, stream in jobs:
+        rows = int(pooled.pooled_offsets[-1])
+        assert len(got) == 8
+        for perm2, pooled2 in got:
+            assert torch.equal(perm2, perm) and torch.equal(pooled2.sub_of, pooled.sub_of)
+            assert torch.equal(pooled2.feat[:rows].view(torch.int16), pooled.feat[:rows].view(torch.int16))
 
 
 def test_binding_refuses_wrong_shapes_and_types_on_the_device():
