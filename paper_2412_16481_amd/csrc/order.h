@@ -16,6 +16,7 @@ struct OrderArgs {
     long long max_scan_points;
     int4* tile_info;            // [tiles][2], tiles = n / 2048 + n_scans (batches of up to 512 scans): place of every tile of the sort
     uint32_t* tile_box;         // [tiles][8]: bounding box of its points
+    int joined;                 // set by order_launch: the first tile of a scan has the box of the whole scan
     uint32_t* box;      // [n_scans][4] per-scan minimum as ordered ints (word 3 unused)
     unsigned long long* keys;  // [n][3] sort keys
     int32_t* idx[2];    // [n] each: ping-pong buffers of the sort

@@ -33,6 +33,10 @@ constexpr int OST = 512;        // threads that sort or merge a tile
 constexpr int OPT = OE / OST;    // results per thread
 
 constexpr int OSCANS = OST;      // most scans that are sorted each by itself
+// Longer scans have their boxes joined once (k_order_join); in others every tile joins them for itself, which is quadratic in the
+// tiles. us of a whole canonical bucketing of one scan without / with that launch: 300 000 points 331 / 333, 1 million 661 / 662, 2 million
+// 1234 / 1227, 16 million 14 750 / 14 300, 48 million 61 180 / 56 640.
+constexpr long long OJOIN = 768 * OE;
 
 // Where tile t of a batch of up to OSCANS scans lies: tiles never straddle scans. Written by k_order_set, with the bounding box of the
 // tile's points (ordered ints, minimum xyz at [0..2], maximum at [4..6]) beside it.
@@ -142,6 +146,31 @@ __global__ __launch_bounds__(OST) void k_order_set(OrderArgs a)
     }
     __syncthreads();
     if (tid < 8) a.tile_box[t * 8 + tid] = red[(tid & 3) < 3 ? tid : 0];
+}
+
+// Scans of many tiles: the workgroup of the first joins the boxes of all of them in place of its own.
+__global__ __launch_bounds__(OST) void k_order_join(OrderArgs a)
+{
+    __shared__ uint32_t red[8];
+    const int tid = threadIdx.x;
+    const TileInfo ti = tile_of(a, blockIdx.x);
+    if (!ti.ok || (int)blockIdx.x != ti.t0) return;
+    if (tid < 8) red[tid] = tid < 4 ? 0xFFFFFFFFu : 0u;
+    __syncthreads();
+    uint32_t* const boxes = a.tile_box + (size_t)ti.t0 * 8;
+    uint32_t lo[3] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu}, hi[3] = {0u, 0u, 0u};
+    for (int t = tid; t < ti.tiles; t += OST) {
+#pragma unroll
+        for (int x = 0; x < 3; ++x) { lo[x] = min(lo[x], boxes[(size_t)t * 8 + x]); hi[x] = max(hi[x], boxes[(size_t)t * 8 + 4 + x]); }
+    }
+#pragma unroll
+    for (int x = 0; x < 3; ++x) {
+        lo[x] = wave_min(lo[x]);
+        hi[x] = wave_max(hi[x]);
+        if ((tid & 63) == 0) { atomicMin(&red[x], lo[x]); atomicMax(&red[4 + x], hi[x]); }
+    }
+    __syncthreads();                                  // every box has been read
+    if (tid < 8) boxes[tid] = red[tid];
 }
 
 // Batches of more scans: their minima by atomics.
@@ -264,7 +293,7 @@ __global__ __launch_bounds__(OST) void k_order_tiles(OrderArgs a)
     if (!ti.ok) return;
     if (FEW && tid < 64) {                            // the boxes of the scan's tiles
         uint32_t lo[3] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu}, hi[3] = {0u, 0u, 0u};
-        for (int t = tid; t < ti.tiles; t += 64) {
+        for (int t = tid; t < (a.joined ? 1 : ti.tiles); t += 64) {
             const uint32_t* b = a.tile_box + (size_t)(ti.t0 + t) * 8;
 #pragma unroll
             for (int x = 0; x < 3; ++x) { lo[x] = min(lo[x], b[x]); hi[x] = max(hi[x], b[4 + x]); }
@@ -471,15 +500,19 @@ __global__ __launch_bounds__(OT) void k_order_compose(const int32_t* __restrict_
 
 }  // namespace
 
-hipError_t order_launch(const OrderArgs& a, const int32_t** order_out, hipStream_t stream)
+hipError_t order_launch(const OrderArgs& args, const int32_t** order_out, hipStream_t stream)
 {
+    OrderArgs a = args;
     *order_out = a.idx[0];
     if (a.n <= 0) return hipSuccess;
     const bool few = a.n_scans <= OSCANS;
     const int tiles = few ? a.n / OE + a.n_scans : (a.n + OE - 1) / OE;
     const int blocks = (a.n + OT - 1) / OT;
+    const long long longest = few && a.max_scan_points < a.n ? a.max_scan_points : a.n;
     if (few) {
         k_order_set<<<tiles, OST, 0, stream>>>(a);
+        a.joined = longest > OJOIN;
+        if (a.joined) k_order_join<<<a.n_scans == 1 ? 1 : tiles, OST, 0, stream>>>(a);
         k_order_tiles<true><<<tiles, OST, 0, stream>>>(a);
     } else {
         k_order_init<<<(a.n_scans * 4 + OT - 1) / OT, OT, 0, stream>>>(a);
@@ -488,7 +521,6 @@ hipError_t order_launch(const OrderArgs& a, const int32_t** order_out, hipStream
     }
     const int32_t* src = a.idx[0];
     int cur = 1;
-    const long long longest = few && a.max_scan_points < a.n ? a.max_scan_points : a.n;
     for (long long run = OE; run < longest; run *= 2) {
         k_order_merge<<<tiles, OST, 0, stream>>>(a, src, a.idx[cur], (int)run);
         src = a.idx[cur];

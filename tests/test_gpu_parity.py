@@ -501,6 +501,18 @@ def test_bucketize_canonical_order_sorts_every_scan_by_itself(n_scans):
     assert np.array_equal(np.sort(got.perm.cpu().numpy()), np.arange(len(c)))
 
 
+@pytest.mark.parametrize("sizes", [[768 * 2048], [768 * 2048 + 1], [3000, 768 * 2048 + 1, 1, 0, 50_000]])
+def test_bucketize_canonical_order_of_scans_around_the_length_whose_boxes_are_joined_once(sizes):
+    rng = np.random.default_rng(sizes[0])
+    bo = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    c = (rng.random((int(bo[-1]), 3)) * 30 - 15).astype(np.float32)
+    for b, size in enumerate(sizes):
+        if size > 3000:      # the corners of the box in tiles far apart
+            c[bo[b] + size - 2] = (-20 - b, 14, 3)
+            c[bo[b] + 2500] = (3, -18 - b, 22)
+    check_bucketize(c, bo, 0.05, 2048, 4, "zorder_div", order="canonical", max_scan_points=max(sizes))
+
+
 @pytest.mark.parametrize("n_scans", [2, 64, 65])
 def test_bucketize_canonical_order_in_a_workspace_of_another_batch(n_scans):
     """Every tile of the sort writes its place and its bounding box, or that there is no such tile, before either is read: in one workspace
