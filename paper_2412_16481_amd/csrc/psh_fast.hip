@@ -300,7 +300,8 @@ __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32
     // apart, sixteen lanes to a bank. The whole bucketing of 200000 points in one scan 103 -> 94 us, of 457295 in four 102 -> 91. With twelve
     // rows a thread whatever there are, most threads added up zeros: as many as are likely to be there, and threads without a row out
     // of the joining, 200000 points 89.3 -> 88.2 us, 457295 83 -> 77.5, 914601 in eight 108 -> 106, one scan of 9000 58.5 -> 54.8 (joining
-    // without a branch per word, but by all threads: 73.9).
+    // without a branch per word, but by all threads: 73.9). Eleven and twelve rows in two goes of ten are no faster than with twelve for
+    // all: 215000 points 97.9 us, 93.9 in one go.
     const int G = (((K + 1) >> 1) + 3) >> 2;        // column groups in use (<= 256)
     const int nseg = TH / G, seg = tid / G, g = tid - seg * G;
     int tl[8], pl[8], cntv[KPT_], waited = 0;
@@ -343,6 +344,7 @@ __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32
         if (seg < min(nseg, nc)) {
             if (nc <= 4 * nseg) sum_rows(std::integral_constant<int, 4>{});
             else if (nc <= 7 * nseg) sum_rows(std::integral_constant<int, 7>{});
+            else if (nc > 10 * nseg && nc <= 12 * nseg) sum_rows(std::integral_constant<int, 12>{});
             else sum_rows(std::integral_constant<int, 10>{});
         }
 #pragma unroll

@@ -457,9 +457,10 @@ def test_bucketize_canonical_order_many_scans_with_empty_ones():
 
 
 @pytest.mark.parametrize("n,scans,cap", [(9000, 1, 4096), (9000, 1, 128), (30_000, 1, 512), (60_000, 1, 256), (120_000, 1, 1024), (150_000, 1, 512),
-                                         (200_000, 1, 1024), (300_000, 1, 2048), (800_000, 8, 1024), (400_000, 20, 2048)])
+                                         (200_000, 1, 1024), (206_000, 1, 1024), (215_000, 1, 1024), (224_000, 1, 1024), (300_000, 1, 2048), (800_000, 8, 1024),
+                                         (400_000, 20, 2048)])
 def test_bucketize_steps_with_few_and_many_count_rows_per_thread(n, scans, cap):
-    """One launch per step: a thread sums up to 4, 7 or 10 count rows at a time, in one or several goes, and threads without a row do
+    """One launch per step: a thread sums up to 4, 7, 10 or 12 count rows at a time, in one or several goes, and threads without a row do
     not join. From 1 to 13 rows a thread, more threads than rows and column groups from 2 to 147."""
     rng = np.random.default_rng(n + cap)
     bo = np.round(np.linspace(0, n, scans + 1)).astype(np.int32)
