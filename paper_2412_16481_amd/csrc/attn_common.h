@@ -113,15 +113,22 @@ __device__ __forceinline__ int row_sums(int v)
 }
 
 // The rows of scope slot `slot`: `ng` of them in `sm.nseg` runs, one for plain and shifted scopes, up to m (one bucket each)
-// for strided ones. False if the slot has none. Every wave works this out for itself, from two loads that depend on each
-// other: lane i looks at scan i, then at run i. (One thread walking through the scans and the buckets, a load at a time, and a
-// barrier behind it: a strided pass over 914601 points x 8 heads x 32 1425 -> 1405 us, a room of 200000 x 4 x 16 107.5 -> 106.8.)
+// for strided ones. False if the slot has none. Every wave works this out for itself, from two groups of loads the second of
+// which depends on the first. Where the addresses are the same for all lanes and few (one scan, up to four runs) they are scalar
+// loads, which come back sooner than a lane's; else lane i looks at scan i, then at run i.
+// Bound: those two waits, in front of everything else a workgroup does. us with one thread walking through scans and buckets and a
+// barrier behind it / a lane per scan and run always / now, 8 heads x 32: 200000 points, scope 256, strided 127 / 131 / 124; scope
+// 128, backward 138 / 145 / 134; 100000 + 3000 points, 12 runs of 16, strided 133 / 117 / 117; 64 scans of 1000, strided 48.2 / 44.1 / 43.7.
 // `row0` and `pre` (MAXSEG and MAXSEG + 1 words of LDS, the wave's own) are written for more than four runs only.
 __device__ __forceinline__ bool scope_of_slot(const AttnArgs& a, int slot, int* row0, int* pre, int& ng, SegMap& sm)
 {
     const int lane = threadIdx.x & 63;
     int kb0, K, g;
-    if (a.n_scans < 64) {
+    if (a.n_scans == 1) {
+        kb0 = a.sbs[0];
+        K = a.sbs[1] - kb0;
+        g = slot - divide(kb0, a.m, a.by_m);
+    } else if (a.n_scans < 64) {
         // scans own disjoint slot ranges starting at sbs[b]/m + extra*b
         const int first = a.sbs[min(lane, a.n_scans)];
         const int start = divide(first, a.m, a.by_m) + a.extra * lane;
@@ -149,16 +156,39 @@ __device__ __forceinline__ bool scope_of_slot(const AttnArgs& a, int slot, int* 
         const int j0 = a.mode == 1 ? (g == 0 ? 0 : a.shift + (g - 1) * a.m) : g * a.m;
         const int j1 = min(a.mode == 1 && g == 0 ? a.shift : j0 + a.m, K);
         if (j0 >= K) return false;
-        const int at = a.offsets[kb0 + (lane == 0 ? j0 : j1)];
         sm.nseg = 1;
-        sm.d0 = __builtin_amdgcn_readlane(at, 0);
-        ng = __builtin_amdgcn_readlane(at, 1) - sm.d0;
+        sm.d0 = a.offsets[kb0 + j0];
+        ng = a.offsets[kb0 + j1] - sm.d0;
         return ng > 0;
     }
     const int t = a.stride, mt = a.m * t;
     const int full = divide(K, mt, a.by_mt), rem = K - full * mt;
     if (g >= full * t + min(rem, t)) return false;
-    const int blk = divide(g, t, a.by_t), j = blk * mt + (g - blk * t) + lane * t;
+    const int blk = divide(g, t, a.by_t), j0 = blk * mt + (g - blk * t);
+    if (a.m <= 4) {                                   // the usual scope of four buckets
+        int r0[4], r1[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {                 // all under way together
+            const int* const at = a.offsets + kb0 + min(j0 + min(i, a.m - 1) * t, K - 1);
+            r0[i] = at[0];
+            r1[i] = at[1];
+        }
+        int before[5] = {};
+        sm.nseg = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const bool has = i < a.m && j0 + i * t < K;
+            sm.nseg += has ? 1 : 0;
+            before[i + 1] = before[i] + (has ? max(r1[i] - r0[i], 0) : 0);
+        }
+        ng = before[4];
+        sm.d0 = r0[0];
+        if (sm.nseg > 1) { sm.p1 = before[1]; sm.d1 = r0[1] - before[1]; }
+        if (sm.nseg > 2) { sm.p2 = before[2]; sm.d2 = r0[2] - before[2]; }
+        if (sm.nseg > 3) { sm.p3 = before[3]; sm.d3 = r0[3] - before[3]; }
+        return ng > 0;
+    }
+    const int j = j0 + lane * t;
     const bool has = lane < a.m && j < K;
     int r0 = 0, len = 0;
     if (has) {

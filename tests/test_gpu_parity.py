@@ -739,6 +739,63 @@ def test_attention_other_scope_shapes_and_scale():
             attn_case(q, k, v, bk, ref, 2, 16, mode, True, shift=max(1, m // 2), scale=0.31)
 
 
+def scope_search_layouts():
+    """What the search for a workgroup's scope tells apart: scans up to 63 (a lane each), more (halving), one (no search), with scans
+    that have no buckets; and runs without rows, as the first, the last and between others, in up to four runs and in more."""
+    rng = np.random.default_rng(34)
+    for n_scans in (63, 64, 65, 300):
+        sizes = [list(rng.integers(1, 17, rng.choice([0, 0, 1, 3, 4, 7, 9]))) for _ in range(n_scans)]
+        sizes[n_scans // 2] = [16] * 25
+        if n_scans != 64:
+            sizes[0], sizes[-1] = [], [5, 16]
+        yield f"{n_scans} scans", sizes, 64, 4
+    for m in (2, 3, 4, 8, 16):
+        full = [[16 if (i + j) % 3 else 9 for i in range(m)] for j in range(5)]
+        holes = ({0}, {m - 1}, set(range(1, m - 1)) or {0}, set(range(m - 1)), set(range(m)))
+        one = [0 if i in hole else rows for scope, hole in zip(full, holes) for i, rows in enumerate(scope)]
+        turned = [one[j * m + i] for i in range(m) for j in range(5)]      # the same holes for a stride of five
+        yield f"runs of {m} without rows", [one + [0, 3]], 16 * m, m
+        yield f"strided runs of {m} without rows", [turned, [0] * m, [4, 0] + turned + [0]], 16 * m, m
+
+
+def short_scope_atol(v):
+    """Scopes of a few rows give results as large as the values. A weight p_i is rounded to bfloat16 (relative 2^-9) above and below the
+    fraction, which moves the result by at most 2^-9 sum p_i |v_i - o| <= 2^-8 max |v|; the result is rounded by 2^-9 max |v|."""
+    return 3 * 2.0 ** -9 * float(np.abs(wl.bf16_bits_to_f32(v)).max())
+
+
+@pytest.mark.parametrize("d", [16, 32])
+@pytest.mark.parametrize("case", range(14))
+def test_attention_forward_and_backward_find_every_scope(case, d):
+    name, sizes, cap, m = list(scope_search_layouts())[case]
+    bk, ref, n = hand_layout(sizes, cap, m)
+    rng = np.random.default_rng(35 + case)
+    q, k, v, g = (wl.f32_to_bf16_bits(rng.standard_normal((n, 2 * d)).astype(np.float32)) for _ in range(4))
+    for mode, kw in (("plain", {}), ("shift", {"shift": 1}), ("stride", {"stride": 2}), ("stride", {"stride": 5})):
+        attn_case(q, k, v, bk, ref, 2, d, mode, True, atol=short_scope_atol(v), **kw)
+        bwd_case(q, k, v, g, bk, ref, 2, d, mode, True, **kw)
+
+
+@pytest.mark.parametrize("sizes,cap,m,heads,max_buckets,mode,kw", [
+    ([[1] * 69_000, [1] * 900], 256, 16, 1, 70_000, "stride", {"stride": 4095}),        # buckets by 16 x 4095: 65 520 x 70 000
+    ([[1] * 40_000, [1] * 900], 64, 4, 1, 1_100_000, "stride", {"stride": 4095}),    # scopes by the stride: 4095 x 1 100 001
+    ([[900, 70] * 5, [333]], 256_064, 4, 2, 10_000, "shift", {"shift": 3}),             # 5 or 10 million workgroups by 1001 or 2001 a scope
+    ([[16, 3, 16] * 3, [8]], 64, 4, 4095, 1200, "plain", {}),                           # scopes by 4095 heads
+])
+def test_attention_where_dividends_are_too_large_for_a_product(sizes, cap, m, heads, max_buckets, mode, kw):
+    """Quotients in the search for a scope are the upper half of a product where largest dividend times divisor is below 2^32; in each of
+    these calls one of them is not. (The bound on the number of buckets is the caller's and may be far above what there is.)"""
+    bk, ref, n = hand_layout(sizes, cap, m)
+    offsets = torch.full((max_buckets + 1,), n, dtype=torch.int32, device=DEV)
+    offsets[:len(ref["offsets"])] = dev(ref["offsets"])
+    bk.offsets, bk.max_buckets = offsets, max_buckets
+    rng = np.random.default_rng(36)
+    q, k, v, g = (wl.f32_to_bf16_bits(rng.standard_normal((n, 16 * heads), dtype=np.float32)) for _ in range(4))
+    attn_case(q, k, v, bk, ref, heads, 16, mode, True, atol=short_scope_atol(v), **kw)
+    if n < 1000 and heads < 4095:
+        bwd_case(q, k, v, g, bk, ref, heads, 16, mode, True, **kw)
+
+
 def test_attention_large_logits_stay_finite():
     # peaked softmax: scores of order +-60 exercise the running-max rescaling
     bk, ref, n = hand_layout([[64] * 8], 256, 4)
