@@ -487,7 +487,7 @@ def test_bucketize_scans_with_more_contenders_than_a_queue_holds(n_scans, points
 def test_bucketize_canonical_order_sorts_every_scan_by_itself(n_scans):
     """Tiles of the sort never reach over the end of a scan: scans of no, one and two tiles and one point around that, scans of more
     merges than the others, up to the number of scans that are still sorted one by one and beyond it; with the largest scan known
-    and not. Codes of 3 bits to 63, and one of them beside coordinates that are no numbers."""
+    and not. Codes of 3 bits to 63."""
     rng = np.random.default_rng(60 + n_scans)
     sizes = rng.choice([0, 1, 7, 60], n_scans)
     for at, size in zip(rng.permutation(n_scans), (2048, 2049, 4096, 4097, 6145, 0)):
@@ -497,9 +497,53 @@ def test_bucketize_canonical_order_sorts_every_scan_by_itself(n_scans):
     for voxel in (0.05, 1e-6, 1e3):
         check_bucketize(c, bo, voxel, 256, 4, "zorder_div", order="canonical", max_scan_points=int(sizes.max()))
     check_bucketize(c, bo, 0.05, 256, 4, "xor_mod", order="canonical")
-    c[bo[np.argmax(sizes)] + 5] = np.nan
-    got = run_bucketize(c, bo, 0.05, 256, order="canonical")
-    assert np.array_equal(np.sort(got.perm.cpu().numpy()), np.arange(len(c)))
+
+
+def canonical_order_of(c, voxel):
+    """Places of a scan's points by (Z-order code, x, y, z, place), floats as ordered integers, a voxel that is no number as 0; and the codes."""
+    u = c.view(np.uint32)
+    o = np.where(u >> 31, ~u, u | np.uint32(0x80000000)).astype(np.uint32)
+    low = o.min(axis=0)
+    mn = np.where(low >> 31, low ^ np.uint32(0x80000000), ~low).astype(np.uint32).view(np.float32)
+    with np.errstate(invalid="ignore"):
+        f = np.floor((c - mn) * (np.float32(1) / np.float32(voxel)))
+    v = np.clip(np.nan_to_num(f, nan=0.0, posinf=2.0 ** 21, neginf=0.0), 0, 2 ** 21 - 1).astype(np.uint64)
+    code = np.zeros(len(c), np.uint64)
+    for axis in range(3):
+        for bit in range(21):
+            code |= ((v[:, axis] >> np.uint64(bit)) & np.uint64(1)) << np.uint64(3 * bit + axis)
+    return np.lexsort((np.arange(len(c)), o[:, 2], o[:, 1], o[:, 0], code)), code
+
+
+@pytest.mark.parametrize("more", [0, 510])
+def test_bucketize_canonical_order_beside_coordinates_that_are_no_numbers(more):
+    """The key holds as many bits of the code as the scan's largest needs, by the far corner of its box. A NaN there says nothing of the other
+    points, one with its sign set is the box's minimum, infinities make a box of codes at the limit. One bucket holds the scan, so that its
+    rows are the order itself. With 513 scans (`more`) the code has all its bits."""
+    rng = np.random.default_rng(95)
+    nan, minus_nan, inf = np.float32(np.nan), np.copysign(np.float32(np.nan), np.float32(-1)), np.float32(np.inf)
+    special = [[(nan, 1, 1)], [(1, minus_nan, 1)], [(1, 1, inf)], [(-inf, 1, 1), (1, 1, nan)], [(nan, minus_nan, inf), (inf, nan, -inf)], []]
+    if more:
+        special = special[:3]
+    scans = []
+    for points in special:
+        c = clustered_cloud(rng, 2500) * np.array([16, 1, 1], np.float32)
+        for at, point in zip((5, 2100), points):
+            c[at] = point
+        scans.append(c)
+    scans += [np.full((3, 3), nan, np.float32)] * 2 + [clustered_cloud(rng, 9)] * more
+    bo = np.concatenate([[0], np.cumsum([len(c) for c in scans])]).astype(np.int32)
+    assert len(scans) == (515 if more else 8)
+    got = run_bucketize(np.concatenate(scans), bo, 0.05, 4 * 4096, hash="xor_mod", order="canonical").perm.cpu().numpy()
+    for b, c in enumerate(scans):
+        order, code = canonical_order_of(c, 0.05)
+        assert np.array_equal(got[bo[b]:bo[b + 1]], bo[b] + order), b
+    # without a word for the NaN, the first scan's code would have the bits of y and z only, and its order would be another
+    order, code = canonical_order_of(scans[0], 0.05)
+    y, z = (int((scans[0][:, axis].max() - scans[0][:, axis].min()) / 0.05).bit_length() for axis in (1, 2))
+    bits = max(3 * y - 1, 3 * z)
+    assert int(code.max()).bit_length() > bits
+    assert not np.array_equal(np.argsort(code & np.uint64(2 ** bits - 1), kind="stable"), np.argsort(code, kind="stable"))
 
 
 @pytest.mark.parametrize("sizes", [[768 * 2048], [768 * 2048 + 1], [3000, 768 * 2048 + 1, 1, 0, 50_000]])
