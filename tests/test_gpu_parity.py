@@ -487,7 +487,7 @@ def test_bucketize_scans_with_more_contenders_than_a_queue_holds(n_scans, points
 def test_bucketize_canonical_order_sorts_every_scan_by_itself(n_scans):
     """Tiles of the sort never reach over the end of a scan: scans of no, one and two tiles and one point around that, scans of more
     merges than the others, up to the number of scans that are still sorted one by one and beyond it; with the largest scan known
-    and not. Codes of 3 bits to 63."""
+    and not. Codes of 3 bits to 63, and one of them beside coordinates that are no numbers (whose order itself is looked at below)."""
     rng = np.random.default_rng(60 + n_scans)
     sizes = rng.choice([0, 1, 7, 60], n_scans)
     for at, size in zip(rng.permutation(n_scans), (2048, 2049, 4096, 4097, 6145, 0)):
@@ -497,6 +497,9 @@ def test_bucketize_canonical_order_sorts_every_scan_by_itself(n_scans):
     for voxel in (0.05, 1e-6, 1e3):
         check_bucketize(c, bo, voxel, 256, 4, "zorder_div", order="canonical", max_scan_points=int(sizes.max()))
     check_bucketize(c, bo, 0.05, 256, 4, "xor_mod", order="canonical")
+    c[bo[np.argmax(sizes)] + 5] = np.nan
+    got = run_bucketize(c, bo, 0.05, 256, order="canonical")
+    assert np.array_equal(np.sort(got.perm.cpu().numpy()), np.arange(len(c)))
 
 
 def canonical_order_of(c, voxel):
