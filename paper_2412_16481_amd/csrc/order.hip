@@ -13,10 +13,13 @@
 // Bound: launches and latency (a merge launch is a chain of a search, two dependent loads and a search in LDS: 10 us at
 // 457295 points, the tiles 27 us). A radix sort on 8-bit digits takes 21 passes over these keys, each with its own count,
 // scan and scatter, whatever n is. A whole canonical bucketing, us: with such a sort / with runs over scan ends, minima by atomics and the
-// code in the upper 63 bits of the key whatever its size / now: 457295 points in four scans 521 / 224 / 191, 900000 in eight - / 299 / 255,
-// 500000 in 100 - / 213 / 132, 60000 in 300 - / 129 / 70, one scan of 200000 - / 211 / 204, of 4 million 3440 / 3212 / 3189, of 1500
-// 248 / 58.7 / 57.6. Tiles of 4096 take one merge less and one workgroup per compute unit: 457295 points 1 us less, one scan of
-// 1500 12 more, of 200000 16 more.
+// code in the upper 63 bits of the key whatever its size / now (the last two in one job; the bucketing behind the sort has become shorter
+// between them too): sensor sweeps, 457295 points in four scans 521 / 224 / 178, 914601 in eight - / 299 / 231; cubes, 500000 points in
+// 100 scans - / 212 / 128, 60000 in 300 - / 147 / 84, 4 million in eight (buckets of 1024) - / 1626 / 1273; a room of 200000 486 / 209 / 198;
+// one scan of 300 points - / 55.8 / 54.1, of 1500 248 / 58.3 / 55.1, of 4 million in buckets of 1024, where the bucketing alone takes
+// 1843, - / 3216 / 3152. (A batch of 4 million points took 3440 with the radix sort and 1620 with the first form of this one; how it was cut into
+// scans is not on record.) Tiles of 4096 take one merge less and one workgroup per compute unit: 457295 points 1 us less, one
+// scan of 1500 12 more, of 200000 16 more.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

@@ -382,12 +382,14 @@ __device__ __forceinline__ int lanes_out_of_order(const unsigned int (&key)[NPL]
 // 15 bits of mantissa it was most of them) are the full 64-bit keys worked out and settled among neighbours (if that takes
 // long, sorted outright).
 // The rows left are those of dense clusters, and rows that follow each other lie close together: the list of one is nearly
-// that of the next (on sensor sweeps no candidate moves by more than 1 to 6 places at the median, 12 on average). So only the
+// that of the next (on sensor sweeps no candidate moves by more than 1 to 6 places at the median, 12 on average). So the
 // first row of a run goes through the network; the others take the previous row's order with their own distances and
 // transpose neighbours until nothing is out of place. Where half of the lanes are out of order or twelve passes have not
-// sufficed the network sorts, and after two such rows it sorts every row but each eighth (in rooms, where what is left lies
-// scattered over the tile).
-// `list` rows have `pitch` entries (a multiple of 8, >= nopen), each four times an id.
+// sufficed the network sorts, and after two such rows in a row it sorts the rest of the run outright (in rooms, where what is left lies
+// scattered over the tile), but for the rows at multiples of eight, which try the previous order again. Runs are of two kinds: each
+// wave's part of the first five eighths of the rows, and the rest in runs of four, which begin at multiples of four and so hold no such row
+// behind their first.
+// `list` rows have `pitch` entries (a multiple of 8, >= nopen): what `open_list` holds, the ids themselves for rho = 2, else four times the id.
 // Bound: the vector ALU. Pooling 914 601 points of sensor sweeps took 2254 us (825 million vector instructions) with a network
 // of moves, minima, maxima and selects, the full keys every time and candidates read eight words apart (all in the same
 // banks), 1654 (594) with the network as it is, and 1320 (358) with the previous row's order to start from.
