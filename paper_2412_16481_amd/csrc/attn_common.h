@@ -124,8 +124,10 @@ __device__ __forceinline__ bool scope_of_slot(const AttnArgs& a, int slot, int* 
     const int lane = threadIdx.x & 63;
     int kb0, K, g;
     if (a.n_scans == 1) {
+        const int end = a.sbs[1];
         kb0 = a.sbs[0];
-        K = a.sbs[1] - kb0;
+        if (end <= 0) return false;                   // as below: flagged, or no buckets
+        K = end - kb0;
         g = slot - divide(kb0, a.m, a.by_m);
     } else if (a.n_scans < 64) {
         // scans own disjoint slot ranges starting at sbs[b]/m + extra*b

@@ -823,6 +823,19 @@ def test_attention_forward_and_backward_find_every_scope(case, d):
         bwd_case(q, k, v, g, bk, ref, 2, d, mode, True, **kw)
 
 
+@pytest.mark.parametrize("n_scans", [1, 3, 63, 64, 200])
+def test_attention_on_a_flagged_layout_writes_nothing(n_scans):
+    sizes = [[16, 16, 9]] * n_scans
+    bk, ref, n = hand_layout(sizes, 64, 4)
+    bk.scan_bucket_start[-1] = -1
+    q = torch.ones(n, 32, dtype=torch.bfloat16, device=DEV)
+    lse = torch.ones(n, 2, device=DEV)
+    for mode in ("plain", "shift", "stride"):
+        out = torch.full_like(q, 7.0)
+        f3d.bucket_swin_attn(q, q, q, bk, 2, 16, mode, out=out, lse=lse)
+        assert (out == 7.0).all() and (lse == 1.0).all(), mode
+
+
 @pytest.mark.parametrize("sizes,cap,m,heads,max_buckets,mode,kw", [
     ([[1] * 69_000, [1] * 900], 256, 16, 1, 70_000, "stride", {"stride": 4095}),        # buckets by 16 x 4095: 65 520 x 70 000
     ([[1] * 40_000, [1] * 900], 64, 4, 1, 1_100_000, "stride", {"stride": 4095}),    # scopes by the stride: 4095 x 1 100 001
