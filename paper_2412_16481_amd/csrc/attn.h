@@ -65,8 +65,16 @@ struct AttnBwdArgs {
     int ahead;              // the score products run a tile ahead (always with two tiles); 0: the form for short scopes
     int tiles;              // tiles of 32 rows a wave owns (1 or 2): queries in the dQ kernel, keys in the dK/dV kernel
     int kblocks;            // ceil(bucket_cap / (128 * tiles)): row blocks of a scope (f.qblocks is the same)
+    // one kernel for all three gradients
+    int tasks;              // scope slots x heads, rounded up to a multiple of 8
+    int done;               // tasks it takes of each eighth of them (those of an XCD); the two kernels take the others
+    int cap;                // most rows of a scope
+    float* scratch;         // workspace of scopes of several passes: [workgroups][cap][head_dim]
 };
+constexpr int ATTN_BWD_ONE_WAVES = 8;     // of a workgroup, 64 keys each
+constexpr int ATTN_BWD_ONE_ROWS = 2048;   // the longest scope it takes: 16 bytes of LDS per row
 
+hipError_t attn_bwd_one_launch(const AttnBwdArgs& a, int head_dim, int grid, hipStream_t stream);
 hipError_t attn_bwd_launch(const AttnBwdArgs& a, int head_dim, hipStream_t stream);
 
 int attn_block_rows(int head_dim, long long slots, int heads, int bucket_cap);   // query rows one workgroup covers

@@ -489,10 +489,15 @@ int f3d_bucket_swin_attn_f16(const void* q, const void* k, const void* v, const 
                         shift, stride, heads, head_dim, softmax_scale, out, out_perm, lse, stream);
 }
 
+static size_t bwd_dsum_bytes(int64_t n, int32_t heads) { return align_up((size_t)n * heads * sizeof(float), 256); }
+
 int f3d_attn_bwd_workspace_bytes(int64_t n, int32_t heads, size_t* out_bytes)
 {
     if (!out_bytes || n < 0 || heads < 1) return F3D_ERR_INVALID_ARG;
-    *out_bytes = align_up((size_t)n * heads * sizeof(float), 256);
+    // The dQ sums between the passes of one kernel for all gradients: 256 workgroups, scopes of up to 2048 rows, head_dim 32; and no more
+    // than all rows have.
+    const size_t most = (size_t)64 << 20, rows = (size_t)n * heads * 32 * sizeof(float);
+    *out_bytes = bwd_dsum_bytes(n, heads) + align_up(rows < most ? rows : most, 256);
     return F3D_OK;
 }
 
@@ -514,8 +519,7 @@ int f3d_bucket_swin_attn_bwd(const void* q, const void* k, const void* v, const 
     if (((uintptr_t)out | (uintptr_t)dout | (uintptr_t)dq | (uintptr_t)dk | (uintptr_t)dv) & 15) return F3D_ERR_BAD_ALIGNMENT;
     if (((uintptr_t)lse | (uintptr_t)grad_perm) & 3) return F3D_ERR_BAD_ALIGNMENT;
     if ((uintptr_t)workspace & 255) return F3D_ERR_BAD_ALIGNMENT;
-    size_t need = 0;
-    f3d_attn_bwd_workspace_bytes(n, heads, &need);
+    const size_t need = bwd_dsum_bytes(n, heads);     // the two kernels' share, enough for any call
     if (workspace_bytes < need) return F3D_ERR_WORKSPACE_TOO_SMALL;
     b.f.out = (uint16_t*)const_cast<void*>(out);
     b.f.lse = const_cast<float*>(lse);
@@ -547,8 +551,40 @@ int f3d_bucket_swin_attn_bwd(const void* q, const void* k, const void* v, const 
         b.tiles = 1;
     }
     b.kblocks = (bucket_cap + 128 * b.tiles - 1) / (128 * b.tiles);
-    b.f.qblocks = b.kblocks;
     b.f.n_slots = (int)slots;
+    // One kernel for all three gradients where scopes are long enough for its passes over the queries (as above) and short enough for
+    // its LDS, and no gradient takes the forward output's place at other rows (a workgroup would read rows that another has stored).
+    // It takes whole tasks, one per compute unit at a time, so what counts is how the last round of them fills the chip: up to half of one
+    // goes to the two kernels, in blocks of 128 rows. us with all tasks / with whole rounds of them / with the two kernels alone: 200000
+    // points x 4 heads x 16, 3.1 rounds, 366 / 326 / 378; 300000 x 8 x 32, 9.4 rounds, 1193 / 1186 / 1385; a round that is more
+    // than half full is taken (60000 x 8 x 32, 1.9 rounds, 246 / 302 / 277). Scope slots that short scans leave empty fill no compute unit: with
+    // more than an eighth of them empty the two kernels keep the launch (8 scans of 3000 points, 167 / 143 / 117).
+    bool elsewhere = false;
+    for (const void* grad : {dq, dk, dv})
+        elsewhere = elsewhere || (at < (uintptr_t)grad + size && (uintptr_t)grad < at + size && (at != (uintptr_t)grad || grad_perm));
+    const long long tasks = (slots * heads + 7) / 8 * 8, filled = (long long)scopes * n_scans * heads;
+    if (b.ahead && !elsewhere && bucket_cap <= f3d::ATTN_BWD_ONE_ROWS && tasks <= 2000000000ll && tasks <= filled + filled / 8 + 8) {
+        constexpr int CUS = 256;
+        const long long left = tasks % CUS, done = left <= CUS / 2 ? tasks - left : tasks;
+        const bool one_pass = bucket_cap <= 64 * f3d::ATTN_BWD_ONE_WAVES;
+        const int grid = (int)(one_pass || done < CUS ? done : CUS);
+        // a workspace with no room for the sums between passes: the two kernels need none
+        if (done > 0 && (one_pass || (workspace_bytes - need) / 4 >= (size_t)grid * bucket_cap * head_dim)) {
+            b.tasks = (int)tasks;
+            b.done = (int)(done / 8);
+            b.cap = bucket_cap;
+            b.scratch = (float*)((char*)workspace + need);
+            b.f.qblocks = 1;
+            set_divides(b.f);
+            (void)hipGetLastError();
+            const hipError_t e = f3d::attn_bwd_one_launch(b, head_dim, grid, (hipStream_t)stream);
+            if (e != hipSuccess) return hip_fail(e);
+            if (done == tasks) return F3D_OK;
+            b.tiles = 1;
+            b.kblocks = (bucket_cap + 127) / 128;
+        }
+    }
+    b.f.qblocks = b.kblocks;
     set_divides(b.f);
     (void)hipGetLastError();
     const hipError_t e = f3d::attn_bwd_launch(b, head_dim, (hipStream_t)stream);

@@ -1326,6 +1326,35 @@ def test_attention_backward_two_tiles_per_wave_ragged(d, heads):
             bwd_case(q, k, v, g, bk, ref, heads, d, mode, mode != "shift", scope_sel=sel)
 
 
+@pytest.mark.parametrize("d,heads,cap,m,scopes,tail", [
+    (32, 4, 512, 4, 36, 33),       # one pass of 512 keys, a last scope of two tiles
+    (16, 5, 928, 1, 29, 545),      # 29 tiles: the second pass begins in the middle of a stage; a last scope of 33 keys in its second pass
+    (32, 3, 1024, 8, 50, 31),      # strided scopes of eight runs, a last scope of one tile
+    (16, 4, 1024, 4, 68, 700),     # a round of tasks and a rest for the two kernels
+    (32, 5, 2048, 4, 28, 1030),    # the longest scopes: four passes, all of the LDS
+])
+def test_attention_backward_one_kernel(d, heads, cap, m, scopes, tail):
+    # launches whose scopes are computed once for all gradients, and the same call with a workspace that has no room for that
+    s = cap // m
+    bk, ref, n = hand_layout([[s] * (m * scopes + tail // s) + ([tail % s] if tail % s else [])], cap, m)
+    rng = np.random.default_rng(68)
+    q, k, v, g = (wl.f32_to_bf16_bits(rng.standard_normal((n, heads * d)).astype(np.float32)) for _ in range(4))
+    sel = np.zeros(n, dtype=np.uint8)
+    sel[[0, n // 2, n - 1]] = 1
+    ws = torch.empty((n * heads * 4 + 255) // 256 * 256, dtype=torch.uint8, device=DEV)
+    for mode in ("plain", "stride") if m == 1 else ("plain", "shift", "stride"):
+        one = bwd_case(q, k, v, g, bk, ref, heads, d, mode, mode != "shift", scope_sel=sel)
+        tq, tk, tv, tg = (dev(x, torch.bfloat16) for x in (q, k, v, g))
+        lse = torch.empty(n, heads, dtype=torch.float32, device=DEV)
+        out = f3d.bucket_swin_attn(tq, tk, tv, bk, heads, d, mode, use_perm=mode != "shift", lse=lse)
+        two = f3d.bucket_swin_attn_bwd(tq, tk, tv, out, tg, lse, bk, heads, d, mode, use_perm=mode != "shift", workspace=ws)
+        for a, b in zip(one, two):
+            # every row of both: P and dS are rounded to bf16 alike, so what differs is the order of binary32 sums and, at the edge of a
+            # rounding, single terms by 2^-8 of themselves: a few times 2^-9 of the result's scale, and the stored rounding
+            assert float((a.float() - b.float()).abs().max()) <= 2.0 ** -6 * float(b.float().abs().max())
+            assert float((a.float() - b.float()).norm()) <= 2.0 ** -9 * float(b.float().norm())
+
+
 @pytest.mark.parametrize("d,heads", [(16, 3), (32, 2)])
 def test_attention_backward_short_and_long_scopes_one_tile_per_wave(d, heads):
     # the form for short scopes (an average below 448 rows) over one to four stages with last tiles of every kind, and
