@@ -567,6 +567,11 @@ __device__ __forceinline__ unsigned int chunk_open(const uint4& c, const uint8_t
 // 200 000 points (a tile per compute unit) / 914 601 points of sensor sweeps took 340 / 1313 us with words instead of bytes, every
 // contender in the minimum, the next chunk read when entered and the lists always in memory, and 310 / 1143 with this and the rows
 // of the sort dealt out as they are now (bits instead of bytes 388 / 1330 where that was 357 / 1322: more arithmetic per entry).
+// The search is one stretch of code repeated while some lane of the wave has found nothing. As a loop that each lane leaves by itself its
+// masks took about as many scalar instructions as the look-up vector instructions: 335 / 1135 -> 320 / 1072 us (another box); who speaks
+// without branches 315 / 1037; the winner's word read together with the next look-up and not waited for in front of it 311 / 1030 (114 000
+// points of one sweep 410 -> 355). Sixteen entries at hand, so that a load is not wanted before four rounds are over: 361 / 1245; flags of
+// eight bytes, one per place in a chunk, that need no shifts: 343 / 1208, the reads meet in the banks.
 __device__ __forceinline__ const uint8_t* rounds_of_two(int nleft, int nopen, int pitch, int kp, const uint16_t* lists, uint8_t* flags, int* win,
                                                          uint16_t* rsub, uint32_t* moved, int* wave_rows, uint16_t* near, int near_cap)
 {
@@ -598,24 +603,29 @@ __device__ __forceinline__ const uint8_t* rounds_of_two(int nleft, int nopen, in
     };
     // The first sub-bucket of the row's list that is open. Whoever gets it, it is closed from the next round on: where the chunk
     // has no other open entry the row goes on to the next one at once.
+    auto look = [&](const uint8_t* open_now, unsigned int& e) __attribute__((always_inline)) -> bool {
+        const unsigned int open = chunk_open(cur, open_now) & valid;
+        e = (unsigned int)chunk_entry(cur, __builtin_ctz(open | 0x100u));
+        valid = open & (open - 1u);
+        return open != 0u;
+    };
     auto search = [&](auto near_tag, const uint8_t* open_now, unsigned int& e) __attribute__((always_inline)) -> bool {
-        if (!walking) return false;
-        for (;;) {
-            const unsigned int open = chunk_open(cur, open_now) & valid;
-            if (open) {
-                e = (unsigned int)chunk_entry(cur, __builtin_ctz(open));
-                valid = open & (open - 1u);
+        bool found = false, pending = walking;
+        do {
+            if (pending) {
+                found = look(open_now, e);
                 if (valid == 0u) advance(near_tag);
-                return true;
+                pending = !found && at < chunks;
             }
-            if (at + 1 >= chunks) { walking = false; return false; }   // cannot happen: there is room for every row left
-            advance(near_tag);
-        }
+        } while (__builtin_amdgcn_ballot_w64(pending));
+        walking = walking && found;                   // the end of the list cannot come first: there is room for every row left
+        return found;
     };
     // lanes that speak for what they contend for: all but those that meet the wave's first contender
     auto speaks = [&](bool contend, unsigned int e, unsigned long long m) __attribute__((always_inline)) -> bool {
         const int first = (int)__builtin_ctzll(m | (1ull << 63));
-        return contend && (lane == first || e != (unsigned int)__builtin_amdgcn_readlane((int)e, first));
+        const unsigned int lead = (unsigned int)__builtin_amdgcn_readlane((int)e, first);
+        return contend & ((lane == first) | (e != lead));
     };
     int waves = (nleft + 63) >> 6, round = 0;
     auto batch = [&](auto near_tag) __attribute__((always_inline)) {
@@ -631,7 +641,7 @@ __device__ __forceinline__ const uint8_t* rounds_of_two(int nleft, int nopen, in
                 later[e] = 0;
             }
             lds_barrier();
-            const int lowest = sent ? *w : -1;
+            const int lowest = *w;                // of the others' too: under way with the reads of the search, not in front of them
             unsigned int e_next = 0;
             const bool more = k < 31 && search(near_tag, later, e_next);   // a row looks a round ahead, not across a closing up
             if (sent && lowest == tid) {
