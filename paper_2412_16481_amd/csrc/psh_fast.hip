@@ -242,8 +242,13 @@ __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32
     __shared__ int placed_ct, recycled_ct, left_before;
     __shared__ int lds17[17];
     const int chunk = blockIdx.x;
-    const ChunkInfo ci = load_chunk(a, chunk);
-    if (ci.b < 0 || a.status[0]) return;
+    // One scan: its chunks follow from what the launch knows, and nothing waits for the table (a scan's points are all n, so its buckets are
+    // kcap; where the offsets say otherwise the status does too, which is looked at behind the loads). us per bucketing, with the table and the
+    // status waited for in front: 20000 points 60 -> 56, 130000 72.7 -> 68, 200000 89.8 -> 86.6; 457295 in four scans 78.6 -> 77.
+    const ChunkInfo ci = a.n_scans == 1 ? ChunkInfo{chunk * CH < a.n ? 0 : -1, chunk, (a.n + CH - 1) / CH, chunk * CH, min(chunk * CH + CH, a.n), 0, a.kcap, 0}
+                                        : load_chunk(a, chunk);
+    const int bad = a.status[0];
+    if (ci.b < 0) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int K = ci.K, kb0 = ci.kb0, lc = ci.lc, nc = ci.nc;
     const int kwp = row_pitch(a.kcap);
@@ -353,6 +358,7 @@ __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32
             for (int c = tid; c < lc; c += TH) waited += a.left[ci.c0 + c];
     }
 
+    if (bad) return;
     // ---- LDS set-up while the loads fly
     for (int w = (r > 0 ? 0 : 4 * gp) + tid; w < 4 * gp + NW * (kwp >> 2); w += TH) reinterpret_cast<int4*>(smem)[w] = make_int4(0, 0, 0, 0);
     if (tid == 0) placed_ct = recycled_ct = left_before = 0;

@@ -66,6 +66,25 @@ def test_bucketize_matches_oracle_on_workloads(name, hash):
     check_bucketize(w.coords, w.batch_offsets, w.voxel_size, w.bucket_cap, w.scope_buckets, hash)
 
 
+@pytest.mark.parametrize("n", [1, 1023, 1024, 2049, 9000, 70001, 262145])
+def test_bucketize_one_scan_with_a_launch_per_step(n):
+    # one scan's chunks (of 1024 and of 2048 points) follow from the launch; offsets that say otherwise are flagged and nothing is written
+    rng = np.random.default_rng(17)
+    pts = (rng.random((n, 3)) * [9.0, 7.0, 2.0]).astype(np.float32)
+    cap = 1024 if n < 200_000 else 2048
+    for bo, most in ((None, 0), (np.array([0, n], dtype=np.int32), 0), (None, 2 * n)):
+        check_bucketize(pts, bo, 0.05, cap, schedule="steps", max_scan_points=most)
+    p = f3d.make_params(0.05, cap, 4, schedule="steps")
+    for bo in ([0, n - 1], [1, n], [0, n + 1]):
+        bk = f3d.psh_bucketize(dev(pts), dev(np.array(bo, dtype=np.int32)), p)
+        bk.perm.fill_(-7)
+        bk.inv_perm.fill_(-7)
+        f3d.psh_bucketize(dev(pts), dev(np.array(bo, dtype=np.int32)), p, out=bk)
+        torch.cuda.synchronize()
+        assert int(bk.scan_bucket_start[-1]) == -1
+        assert bool((bk.perm == -7).all()) and bool((bk.inv_perm == -7).all())
+
+
 @pytest.mark.parametrize("n", [1, 2, 2047, 2048, 2049, 4096, 4097, 6145, 8193, 12289])
 def test_bucketize_canonical_order_at_sort_tile_edges(n):
     # sizes around the sort's tiles and runs (an odd run without a partner among them), a lattice with many equal points
