@@ -568,7 +568,7 @@ __device__ __forceinline__ unsigned int chunk_open(const uint4& c, const uint8_t
 // contender in the minimum, the next chunk read when entered and the lists always in memory, and 310 / 1143 with this and the rows
 // of the sort dealt out as they are now (bits instead of bytes 388 / 1330 where that was 357 / 1322: more arithmetic per entry).
 // The search is one stretch of code repeated while some lane of the wave has found nothing. As a loop that each lane leaves by itself its
-// masks took about as many scalar instructions as the look-up vector instructions: 335 / 1135 -> 320 / 1072 us (another box); who speaks
+// masks took about as many scalar instructions as the look-up vector instructions: 335 / 1135 -> 320 / 1072 us (another card); who speaks
 // without branches 315 / 1037; the winner's word read together with the next look-up and not waited for in front of it 311 / 1030 (114 000
 // points of one sweep 410 -> 355). Sixteen entries at hand, so that a load is not wanted before four rounds are over: 361 / 1245; flags of
 // eight bytes, one per place in a chunk, that need no shifts: 343 / 1208, the reads meet in the banks.
