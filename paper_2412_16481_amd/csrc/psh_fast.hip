@@ -243,9 +243,10 @@ __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32
     __shared__ int lds17[17];
     const int chunk = blockIdx.x;
     // One scan: its chunks follow from what the launch knows, and nothing waits for the table (a scan's points are all n, so its buckets are
-    // kcap; where the offsets say otherwise the status does too, which is looked at behind the loads). us per bucketing, with the table and the
+    // kcap; where the offsets say otherwise the status does too, which is looked at behind the loads; a bound below n is refused in any case,
+    // and n then says nothing about how many rows there are to sum). us per bucketing, with the table and the
     // status waited for in front: 20000 points 60 -> 56, 130000 72.7 -> 68, 200000 89.8 -> 86.6; 457295 in four scans 78.6 -> 77.
-    const ChunkInfo ci = a.n_scans == 1 ? ChunkInfo{chunk * CH < a.n ? 0 : -1, chunk, (a.n + CH - 1) / CH, chunk * CH, min(chunk * CH + CH, a.n), 0, a.kcap, 0}
+    const ChunkInfo ci = a.n_scans == 1 && a.max_scan_points >= a.n ? ChunkInfo{chunk * CH < a.n ? 0 : -1, chunk, (a.n + CH - 1) / CH, chunk * CH, min(chunk * CH + CH, a.n), 0, a.kcap, 0}
                                         : load_chunk(a, chunk);
     const int bad = a.status[0];
     if (ci.b < 0) return;
