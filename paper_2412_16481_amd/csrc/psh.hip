@@ -73,7 +73,12 @@ __global__ __launch_bounds__(1024) void k_psh_meta(PshArgs a)
     if (tid < 8) a.round_count[tid] = 0;
     __threadfence_block();   // the scan tables just written are read below by other threads (the barrier alone orders LDS)
     __syncthreads();
-    if (isbad) return;
+    if (isbad) {
+        // no row of the chunk table names a chunk: the steps read it, and load by what it says, before they look at the status
+        if (a.chunk_info)
+            for (int c = tid; c < a.n_chunks_ub; c += 1024) a.chunk_info[2 * c] = make_int4(-1, 0, 0, 0);
+        return;
+    }
     // first row of every bucket (buckets are full except the last of a scan) and the chunk table (everything a
     // workgroup needs to find its points, in one load). With up to three scans the whole workgroup walks each scan; with more,
     // that loop is a chain of dependent loads (a batch may hold hundreds of scans): then a wave takes a scan.

@@ -248,7 +248,7 @@ __global__ __launch_bounds__(TH) void k_pshf_step(PshArgs a, int r, const uint32
     // status waited for in front: 20000 points 60 -> 56, 130000 72.7 -> 68, 200000 89.8 -> 86.6; 457295 in four scans 78.6 -> 77.
     const ChunkInfo ci = a.n_scans == 1 && a.max_scan_points >= a.n ? ChunkInfo{chunk * CH < a.n ? 0 : -1, chunk, (a.n + CH - 1) / CH, chunk * CH, min(chunk * CH + CH, a.n), 0, a.kcap, 0}
                                         : load_chunk(a, chunk);
-    const int bad = a.status[0];
+    const int bad = a.status[0];                    // looked at behind the loads: in a flagged call the table names no chunk
     if (ci.b < 0) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int K = ci.K, kb0 = ci.kb0, lc = ci.lc, nc = ci.nc;

@@ -87,6 +87,35 @@ def test_bucketize_one_scan_with_a_launch_per_step(n):
         assert bool((bk.perm == -7).all()) and bool((bk.inv_perm == -7).all())
 
 
+@pytest.mark.parametrize("order", ["index", "canonical"])
+@pytest.mark.parametrize("n_scans", [64, 65, 200])
+def test_bucketize_many_scans_with_a_launch_per_step_flags_bad_offsets(n_scans, order):
+    # the steps load what the chunk table names before they look at the status: the set-up (one kernel up to 64 scans, another for more)
+    # names no chunk in a flagged call. A row of the table is 32 bytes and begins with its scan, -1 for none.
+    n = 9001
+    pts = (np.random.default_rng(18).random((n, 3)) * [9.0, 7.0, 2.0]).astype(np.float32)
+    good = np.linspace(0, n, n_scans + 1).astype(np.int32)
+    check_bucketize(pts, good, 0.05, 64, schedule="steps", order=order)
+    back, early, late, above = good.copy(), good.copy(), good + 1, good.copy()
+    back[[n_scans // 2, n_scans // 2 + 1]] = back[[n_scans // 2 + 1, n_scans // 2]]
+    early[-1] = n - 1
+    most = int(np.diff(good).max())
+    for bo, bound in ((back, 0), (early, 0), (late, 0), (above, most - 1)):
+        p = f3d.make_params(0.05, 64, 4, schedule="steps", order=order, max_scan_points=bound)
+        ws = torch.zeros(f3d.workspace_bytes(n, n_scans, p), dtype=torch.uint8, device=DEV)
+        bk = f3d.psh_bucketize(dev(pts), dev(good), f3d.make_params(0.05, 64, 4, schedule="steps"))
+        for t in (bk.perm, bk.inv_perm):
+            t.fill_(-7)
+        f3d.psh_bucketize(dev(pts), dev(bo), p, ws, out=bk)
+        torch.cuda.synchronize()
+        assert int(bk.scan_bucket_start[-1]) == -1
+        assert bool((bk.perm == -7).all()) and bool((bk.inv_perm == -7).all())
+        none = (ws[:ws.numel() // 32 * 32].view(torch.int32).reshape(-1, 8)[:, 0] == -1).cpu().numpy()
+        ends = np.flatnonzero(np.diff(np.concatenate([[0], none.astype(np.int8), [0]])))
+        # longer than the run of empty bounding boxes, one per scan, which look the same
+        assert int(np.diff(ends)[::2].max()) >= n // 2048 + n_scans
+
+
 @pytest.mark.parametrize("n", [1, 2, 2047, 2048, 2049, 4096, 4097, 6145, 8193, 12289])
 def test_bucketize_canonical_order_at_sort_tile_edges(n):
     # sizes around the sort's tiles and runs (an odd run without a partner among them), a lattice with many equal points
