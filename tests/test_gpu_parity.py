@@ -1405,6 +1405,39 @@ def test_attention_backward_one_kernel(d, heads, cap, m, scopes, tail):
             assert float((a.float() - b.float()).norm()) <= 2.0 ** -9 * float(b.float().norm())
 
 
+def one_kernel_share(n, heads, run, size):
+    """Share of the rows and heads whose gradients one kernel computes in run(workspace): only the two kernels keep D, the workspace's
+    first n x heads words."""
+    ws = torch.full((size,), 255, dtype=torch.uint8, device=DEV)
+    run(ws)
+    return float((ws[:n * heads * 4].view(torch.int32) == -1).float().mean())
+
+
+@pytest.mark.parametrize("d,heads,cap,tasks,share", [
+    # tasks: scopes and spare scope slots times heads; faster, and taken, by
+    (32, 8, 640, 408, 0),      # the two kernels: a second pass of 128 keys
+    (16, 8, 1280, 408, 0),     # ... a third pass of 256 keys
+    (16, 4, 2048, 192, 0),     # ... a round of four passes that is three quarters full
+    (32, 4, 1536, 152, 0),
+    (32, 8, 1024, 360, 0),     # ... at head_dim 32, a round and a rest of 104
+    (32, 8, 512, 600, 0),      # ... at head_dim 32, one pass, more than two rounds
+    (32, 8, 512, 288, 0),      # ... at head_dim 32, one pass, a round and a rest
+    (32, 8, 512, 480, 1),      # the one kernel: two rounds of one pass
+    (16, 8, 512, 288, 0.9),    # a round of them, the rest of 32 by the two
+    (16, 8, 832, 216, 1),      # the one kernel: a second pass of 320 keys
+    (16, 4, 2048, 200, 1),     # ... a round of four passes
+    (32, 8, 1024, 344, 0.76),  # a round of them, the rest of 88 by the two
+])
+def test_attention_backward_kernels_by_size(d, heads, cap, tasks, share):
+    bk, _, n = hand_layout([[cap // 4] * (4 * (tasks // heads - 3) - 1) + [5]], cap, 4)
+    q, k, v, g = (torch.randn(n, heads * d, device=DEV).to(torch.bfloat16) for _ in range(4))
+    lse = torch.empty(n, heads, dtype=torch.float32, device=DEV)
+    out = f3d.bucket_swin_attn(q, k, v, bk, heads, d, "plain", lse=lse)
+    got = one_kernel_share(n, heads, lambda ws: f3d.bucket_swin_attn_bwd(q, k, v, out, g, lse, bk, heads, d, "plain", workspace=ws),
+                           n * heads * 4 + 512 + (64 << 20))
+    assert abs(got - share) <= 0.03, got
+
+
 @pytest.mark.parametrize("d,heads", [(16, 3), (32, 2)])
 def test_attention_backward_short_and_long_scopes_one_tile_per_wave(d, heads):
     # the form for short scopes (an average below 448 rows) over one to four stages with last tiles of every kind, and
