@@ -243,8 +243,8 @@ int f3d_bucket_swin_attn_f16(const void *q, const void *k, const void *v, const 
  *               was read from; with grad_perm it is stored at row grad_perm[p] instead (passing perm returns the
  *               gradients in the input order of the points)
  *   grad_perm   NULL or [n] int32, a permutation
- *   workspace   >= f3d_attn_bwd_workspace_bytes(n, heads), 256-byte aligned; n * heads floats, rounded up to 256 bytes, are
- *               taken too, by a slower form where scopes are longer than 512 rows
+ *   workspace   >= f3d_attn_bwd_workspace_bytes(n, heads), 256-byte aligned: enough for the fastest form of any call; n * heads floats,
+ *               rounded up to 256 bytes, are taken too, by a slower form where scopes are longer than 512 rows
  * In place: one of dq, dk, dv may be out (which is then lost); they overlap nothing else.
  * Arithmetic: bf16 operands, fp32 accumulation; P and dS are rounded to bf16 before the second products.
  */

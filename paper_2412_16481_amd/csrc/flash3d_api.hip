@@ -489,15 +489,22 @@ int f3d_bucket_swin_attn_f16(const void* q, const void* k, const void* v, const 
                         shift, stride, heads, head_dim, softmax_scale, out, out_perm, lse, stream);
 }
 
+// The backward's dispatch: scopes are long from so many rows on, and a round of its workgroups is one per compute unit of the chip. Neither the
+// device nor a partition of it is asked: the split, and with it the last bits of a gradient, is the same on all of them.
+constexpr int BWD_LONG_ROWS = 448, BWD_CUS = 256;
+
 static size_t bwd_dsum_bytes(int64_t n, int32_t heads) { return align_up((size_t)n * heads * sizeof(float), 256); }
 
 int f3d_attn_bwd_workspace_bytes(int64_t n, int32_t heads, size_t* out_bytes)
 {
     if (!out_bytes || n < 0 || heads < 1) return F3D_ERR_INVALID_ARG;
-    // The dQ sums between the passes of one kernel for all gradients: 256 workgroups, scopes of up to 2048 rows, head_dim 32; and no more
-    // than all rows have.
-    const size_t most = (size_t)64 << 20, rows = (size_t)n * heads * 32 * sizeof(float);
-    *out_bytes = bwd_dsum_bytes(n, heads) + align_up(rows < most ? rows : most, 256);
+    // The dQ sums between the passes of one kernel for all gradients: a strip of a scope's rows, up to 2048 of head_dim 32, for every workgroup.
+    // What a call needs follows from more than n and heads, so this is the most that any can: it takes the kernel only with scopes of
+    // BWD_LONG_ROWS rows on average, which is scan / scopes >= BWD_LONG_ROWS with scan = ceil(n / n_scans) and makes them fewer than
+    // n / (BWD_LONG_ROWS - 1), for up to an eighth and 8 more tasks than scopes times heads, and for more than half a round of tasks.
+    const size_t strip = (size_t)f3d::ATTN_BWD_ONE_ROWS * 32 * sizeof(float), filled = (size_t)n * heads / (BWD_LONG_ROWS - 1);
+    const size_t tasks = (filled + filled / 8 + 8) / 8 * 8, strips = tasks <= BWD_CUS / 2 ? 0 : tasks < BWD_CUS ? tasks : BWD_CUS;
+    *out_bytes = bwd_dsum_bytes(n, heads) + strips * strip;
     return F3D_OK;
 }
 
@@ -546,7 +553,7 @@ int f3d_bucket_swin_attn_bwd(const void* q, const void* k, const void* v, const 
     const int64_t scan = (n + n_scans - 1) / n_scans, buckets = (scan * scope_buckets + bucket_cap - 1) / bucket_cap;
     const int64_t round = (int64_t)scope_buckets * stride, rest = mode == F3D_STRIDE ? buckets % round : 0;
     const int64_t scopes = mode == F3D_STRIDE ? buckets / round * stride + (rest < stride ? rest : stride) : (buckets + scope_buckets - 1) / scope_buckets;
-    if (scan / scopes < 448 || (b.tiles == 2 && head_dim == 16 && scan < 2 * (int64_t)bucket_cap)) {
+    if (scan / scopes < BWD_LONG_ROWS || (b.tiles == 2 && head_dim == 16 && scan < 2 * (int64_t)bucket_cap)) {
         b.ahead = 0;
         b.tiles = 1;
     }
@@ -573,7 +580,7 @@ int f3d_bucket_swin_attn_bwd(const void* q, const void* k, const void* v, const 
         elsewhere = elsewhere || (at < (uintptr_t)grad + size && (uintptr_t)grad < at + size && (at != (uintptr_t)grad || grad_perm));
     const long long tasks = (slots * heads + 7) / 8 * 8, filled = (long long)scopes * n_scans * heads;
     if (b.ahead && !elsewhere && bucket_cap <= f3d::ATTN_BWD_ONE_ROWS && tasks <= 2000000000ll && tasks <= filled + filled / 8 + 8) {
-        constexpr int CUS = 256, KB = 64 * f3d::ATTN_BWD_ONE_WAVES;
+        constexpr int CUS = BWD_CUS, KB = 64 * f3d::ATTN_BWD_ONE_WAVES;
         const int passes = (bucket_cap + KB - 1) / KB;
         const bool one_pass = passes == 1;
         const long long left = tasks % CUS;

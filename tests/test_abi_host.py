@@ -296,6 +296,32 @@ def test_error_strings():
     assert f3d.error_string(-99) == "unknown error code"
 
 
+def test_backward_workspace_has_room_for_the_sums_of_every_workgroup():
+    # the most a call can want beside n x heads floats for D: a strip of bucket_cap x head_dim floats for each of up to 256 tasks (scopes and spare
+    # scope slots times heads, in eights), where scopes hold 448 rows or more on average and at most an eighth of the slots, and 8, is spare
+    size, seen = ctypes.c_size_t(0), 0
+    for heads in (1, 2, 3, 4, 5, 8, 16):
+        for scans in (1, 2, 3, 8, 40):
+            for n in sorted({int(scans * 448 * 1.13 ** e) for e in range(52)}):
+                for cap in (520, 1024, 1500, 2048):
+                    for stride in (0, 1, 2, 7, 16):     # 0: plain
+                        scan, m = -(-n // scans), 4
+                        buckets = -(-scan * m // cap)
+                        rest = buckets % (m * stride) if stride else 0
+                        scopes = buckets // (m * stride) * stride + min(rest, stride) if stride else -(-buckets // m)
+                        slots = (n * m // cap + scans) // m + (stride + 1 if stride else 2) * scans + 1
+                        tasks, filled = -(-slots * heads // 8) * 8, scopes * scans * heads
+                        if scan // scopes < 448 or tasks <= 128 or tasks > filled + filled // 8 + 8:
+                            continue
+                        assert f3d.lib().f3d_attn_bwd_workspace_bytes(n, heads, ctypes.byref(size)) == 0
+                        assert size.value >= (4 * n * heads + 255) // 256 * 256 + min(tasks, 256) * cap * 32 * 4, (n, heads, scans, cap, stride)
+                        seen += 1
+    assert seen > 1000
+    for n, heads, room in ((50000, 1, 0), (1 << 20, 8, 64 << 20)):   # none below a half round of tasks; a strip per compute unit at most
+        assert f3d.lib().f3d_attn_bwd_workspace_bytes(n, heads, ctypes.byref(size)) == 0
+        assert size.value == (4 * n * heads + 255) // 256 * 256 + room
+
+
 def test_product_package_never_touches_the_oracle():
     pkg = os.path.join(ROOT, "paper_2412_16481_amd")
     for dirpath, _, files in os.walk(pkg):

@@ -5,6 +5,7 @@ counts must match bit for bit. Attention is compared element by element within m
 (bf16 inputs and outputs, fp32 accumulation on the GPU; binary64 in the oracle); at the full
 benchmark sizes the comparison runs on sampled query rows, each computed in full by the oracle.
 """
+import ctypes
 import threading
 
 import numpy as np
@@ -1435,6 +1436,19 @@ def test_attention_backward_kernels_by_size(d, heads, cap, tasks, share):
     out = f3d.bucket_swin_attn(q, k, v, bk, heads, d, "plain", lse=lse)
     got = one_kernel_share(n, heads, lambda ws: f3d.bucket_swin_attn_bwd(q, k, v, out, g, lse, bk, heads, d, "plain", workspace=ws),
                            n * heads * 4 + 512 + (64 << 20))
+    assert abs(got - share) <= 0.03, got
+
+
+@pytest.mark.parametrize("n,heads,cap,share", [(14700, 8, 1024, 1), (25000, 8, 1024, 1), (32500, 8, 1024, 0.94), (50000, 4, 1024, 1), (100000, 4, 2048, 1)])
+def test_attention_backward_one_kernel_has_room_in_the_workspace_the_library_asks_for(n, heads, cap, share):
+    # a round of tasks or less, head_dim 32: there are more workgroups, each with a strip of sums between its passes, than scopes
+    bk, _, n = hand_layout([[cap // 4] * (4 * n // cap) + [n % (cap // 4)]], cap, 4)
+    q, k, v, g = (torch.randn(n, heads * 32, device=DEV).to(torch.bfloat16) for _ in range(4))
+    lse = torch.empty(n, heads, dtype=torch.float32, device=DEV)
+    out = f3d.bucket_swin_attn(q, k, v, bk, heads, 32, "plain", lse=lse)
+    size = ctypes.c_size_t(0)
+    assert f3d.lib().f3d_attn_bwd_workspace_bytes(n, heads, ctypes.byref(size)) == 0
+    got = one_kernel_share(n, heads, lambda ws: f3d.bucket_swin_attn_bwd(q, k, v, out, g, lse, bk, heads, 32, "plain", workspace=ws), size.value)
     assert abs(got - share) <= 0.03, got
 
 
