@@ -567,19 +567,21 @@ int f3d_bucket_swin_attn_bwd(const void* q, const void* k, const void* v, const 
     // It takes whole tasks, one per compute unit at a time, so what counts is how the last round of them fills the chip: up to half of one
     // goes to the two kernels, in blocks of 128 rows. us with all tasks / with whole rounds of them / with the two kernels alone: 200000
     // points x 4 heads x 16, 3.1 rounds, 366 / 326 / 378; 300000 x 8 x 32, 9.4 rounds, 1193 / 1186 / 1385; a round that is more
-    // than half full is taken (60000 x 8 x 32, 1.9 rounds, 246 / 302 / 277). The two kernels keep
+    // than half full is taken (60000 x 8 x 32, 1.9 rounds, 246 / 302 / 277). The two kernels keep (us, they / this one)
     //   a single round of scopes of three or four passes that is not more than three quarters full (152 tasks of 2048 rows: 273 / 304, head_dim 32
     //   333 / 386; 1536 rows 167 / 176, 206 / 226; but 200 tasks of 2048 373 / 311, 455 / 396);
-    //   at head_dim 32 what is one round and a rest of more than three eighths (368 tasks of 1024 rows: 209 / 214; 328: 204 / 192);
-    //   at head_dim 32 scopes of one pass but for one or two rounds that the kernel takes whole: there a task's set-up weighs most (tasks
-    //   of 512 rows, 832 of them 139 / 142, 1504 252 / 270; but 216 56 / 39, 480 88 / 78).
-    // Scope slots that short scans leave empty fill no compute unit: with more than an eighth of them empty the two kernels keep the
-    // launch (8 scans of 3000 points, 167 / 143 / 117).
+    //   at head_dim 32 one to three rounds and a rest of between a quarter and five eighths of one, which costs them half a round and this one a
+    //   whole round or two launches (344 tasks of 1536 rows 399 / 419, 408 of 2048 754 / 791, 904 of 1024 502 / 524; but 328 of 1024 204 / 192);
+    //   scopes of one pass, where a task's set-up weighs most, but for up to two rounds (head_dim 16: six) with no rest (tasks of 512 rows, 832 of
+    //   them 139 / 142, 1504 252 / 270; but 216 56 / 39, 480 88 / 78; head_dim 16, 344 52 / 54, 816 94 / 100, 3168 406 / 434).
+    // Scope slots that short scans leave empty fill no compute unit, and all but one of eight XCDs have their full share of tasks still: with
+    // more than a tenth of them empty, an eighth in a single round, the two kernels keep the launch (8 scans of 3000 points, 167 / 143 /
+    // 117; 8 of 27360 points x 3 heads x 16, scopes of 1920, 566 / 588 with 40 of 400 tasks empty).
     bool elsewhere = false;
     for (const void* grad : {dq, dk, dv})
         elsewhere = elsewhere || (at < (uintptr_t)grad + size && (uintptr_t)grad < at + size && (at != (uintptr_t)grad || grad_perm));
     const long long tasks = (slots * heads + 7) / 8 * 8, filled = (long long)scopes * n_scans * heads;
-    if (b.ahead && !elsewhere && bucket_cap <= f3d::ATTN_BWD_ONE_ROWS && tasks <= 2000000000ll && tasks <= filled + filled / 8 + 8) {
+    if (b.ahead && !elsewhere && bucket_cap <= f3d::ATTN_BWD_ONE_ROWS && tasks <= 2000000000ll && tasks <= filled + (tasks <= BWD_CUS ? filled / 8 + 8 : filled / 10)) {
         constexpr int CUS = BWD_CUS, KB = 64 * f3d::ATTN_BWD_ONE_WAVES;
         const int passes = (bucket_cap + KB - 1) / KB;
         const bool one_pass = passes == 1;
@@ -587,8 +589,8 @@ int f3d_bucket_swin_attn_bwd(const void* q, const void* k, const void* v, const 
         long long done = left <= CUS / 2 ? tasks - left : tasks;
         if ((bucket_cap - 1) % KB < KB / 2) done = 0;
         if (passes > 2 && tasks <= CUS * 3 / 4) done = 0;
-        if (head_dim == 32 && !one_pass && done == CUS && left > CUS * 3 / 8) done = 0;
-        if (head_dim == 32 && one_pass && (done < tasks || tasks > 2 * CUS)) done = 0;
+        if (head_dim == 32 && !one_pass && tasks > CUS && tasks < 4 * CUS && left > CUS / 4 && left <= CUS * 5 / 8) done = 0;
+        if (one_pass && (done < tasks || tasks > (head_dim == 32 ? 2 : 6) * CUS)) done = 0;
         const int grid = (int)(one_pass || done < CUS ? done : CUS);
         // a workspace with no room for the sums between passes: the two kernels need none
         if (done > 0 && (one_pass || (workspace_bytes - need) / 4 >= (size_t)grid * bucket_cap * head_dim)) {

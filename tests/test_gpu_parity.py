@@ -1420,14 +1420,18 @@ def one_kernel_share(n, heads, run, size):
     (16, 8, 1280, 408, 0),     # ... a third pass of 256 keys
     (16, 4, 2048, 192, 0),     # ... a round of four passes that is three quarters full
     (32, 4, 1536, 152, 0),
-    (32, 8, 1024, 360, 0),     # ... at head_dim 32, a round and a rest of 104
+    (32, 8, 1024, 328, 0),     # ... at head_dim 32, a round and a rest of 72
+    (32, 4, 1024, 928, 0),     # ... at head_dim 32, three rounds and a rest of 160
     (32, 8, 512, 600, 0),      # ... at head_dim 32, one pass, more than two rounds
-    (32, 8, 512, 288, 0),      # ... at head_dim 32, one pass, a round and a rest
+    (32, 8, 512, 288, 0),      # ... one pass, a round and a rest
+    (16, 8, 512, 288, 0),
+    (16, 8, 512, 1720, 0),     # ... at head_dim 16, one pass, more than six rounds
     (32, 8, 512, 480, 1),      # the one kernel: two rounds of one pass
-    (16, 8, 512, 288, 0.9),    # a round of them, the rest of 32 by the two
-    (16, 8, 832, 216, 1),      # the one kernel: a second pass of 320 keys
+    (16, 8, 512, 1000, 1),     # ... four rounds at head_dim 16
+    (16, 8, 832, 216, 1),      # ... a second pass of 320 keys
     (16, 4, 2048, 200, 1),     # ... a round of four passes
-    (32, 8, 1024, 344, 0.76),  # a round of them, the rest of 88 by the two
+    (32, 4, 1024, 936, 1),     # ... the fourth round with 168 tasks
+    (32, 8, 1024, 320, 0.8),   # a round of them, the rest of 64 by the two
 ])
 def test_attention_backward_kernels_by_size(d, heads, cap, tasks, share):
     bk, _, n = hand_layout([[cap // 4] * (4 * (tasks // heads - 3) - 1) + [5]], cap, 4)
