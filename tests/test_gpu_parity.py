@@ -1377,14 +1377,28 @@ def test_attention_backward_two_tiles_per_wave_ragged(d, heads):
             bwd_case(q, k, v, g, bk, ref, heads, d, mode, mode != "shift", scope_sel=sel)
 
 
-@pytest.mark.parametrize("d,heads,cap,m,scopes,tail", [
-    (32, 4, 512, 4, 36, 33),       # one pass of 512 keys, a last scope of two tiles
-    (16, 5, 928, 1, 29, 545),      # 29 tiles: the second pass begins in the middle of a stage; a last scope of 33 keys in its second pass
-    (32, 3, 1024, 8, 50, 31),      # strided scopes of eight runs, a last scope of one tile
-    (16, 4, 1024, 4, 68, 700),     # a round of tasks and a rest for the two kernels
-    (32, 5, 2048, 4, 28, 1030),    # the longest scopes: four passes, all of the LDS
+def one_kernel_share(n, heads, run, size):
+    """Share of the rows and heads whose gradients one kernel computes in run(workspace): only the two kernels keep D, the workspace's
+    first n x heads words."""
+    ws = torch.full((size,), 255, dtype=torch.uint8, device=DEV)
+    run(ws)
+    return float((ws[:n * heads * 4].view(torch.int32) == -1).float().mean())
+
+
+def bwd_workspace_bytes(n, heads):
+    size = ctypes.c_size_t(0)
+    assert f3d.lib().f3d_attn_bwd_workspace_bytes(n, heads, ctypes.byref(size)) == 0
+    return size.value
+
+
+@pytest.mark.parametrize("d,heads,cap,m,scopes,tail,share", [
+    (32, 4, 512, 4, 36, 33, 1),       # one pass of 512 keys, a last scope of two tiles
+    (16, 5, 928, 1, 29, 545, 1),      # 29 tiles: the second pass begins in the middle of a stage; a last scope of 33 keys in its second pass
+    (32, 3, 1024, 8, 50, 31, 1),      # strided scopes of eight runs, a last scope of one tile
+    (16, 4, 1024, 4, 68, 700, 0.9),   # a round of tasks and a rest for the two kernels
+    (32, 5, 2048, 4, 37, 1030, 1),    # the longest scopes: four passes, all of the LDS
 ])
-def test_attention_backward_one_kernel(d, heads, cap, m, scopes, tail):
+def test_attention_backward_one_kernel(d, heads, cap, m, scopes, tail, share):
     # launches whose scopes are computed once for all gradients, and the same call with a workspace that has no room for that
     s = cap // m
     bk, ref, n = hand_layout([[s] * (m * scopes + tail // s) + ([tail % s] if tail % s else [])], cap, m)
@@ -1394,11 +1408,18 @@ def test_attention_backward_one_kernel(d, heads, cap, m, scopes, tail):
     sel[[0, n // 2, n - 1]] = 1
     ws = torch.empty((n * heads * 4 + 255) // 256 * 256, dtype=torch.uint8, device=DEV)
     for mode in ("plain", "stride") if m == 1 else ("plain", "shift", "stride"):
-        one = bwd_case(q, k, v, g, bk, ref, heads, d, mode, mode != "shift", scope_sel=sel)
+        perm = mode != "shift"
+        one = bwd_case(q, k, v, g, bk, ref, heads, d, mode, perm, scope_sel=sel)
         tq, tk, tv, tg = (dev(x, torch.bfloat16) for x in (q, k, v, g))
         lse = torch.empty(n, heads, dtype=torch.float32, device=DEV)
-        out = f3d.bucket_swin_attn(tq, tk, tv, bk, heads, d, mode, use_perm=mode != "shift", lse=lse)
-        two = f3d.bucket_swin_attn_bwd(tq, tk, tv, out, tg, lse, bk, heads, d, mode, use_perm=mode != "shift", workspace=ws)
+        out = f3d.bucket_swin_attn(tq, tk, tv, bk, heads, d, mode, use_perm=perm, lse=lse)
+
+        def again(w):
+            for a, b in zip(one, f3d.bucket_swin_attn_bwd(tq, tk, tv, out, tg, lse, bk, heads, d, mode, use_perm=perm, workspace=w)):
+                assert torch.equal(a, b)
+
+        assert abs(one_kernel_share(n, heads, again, bwd_workspace_bytes(n, heads)) - share) <= 0.03
+        two = f3d.bucket_swin_attn_bwd(tq, tk, tv, out, tg, lse, bk, heads, d, mode, use_perm=perm, workspace=ws)
         for a, b in zip(one, two):
             # every row of both: P and dS are rounded to bf16 alike, so what differs is the order of binary32 sums and, at the edge of a
             # rounding, single terms by 2^-8 of themselves: a few times 2^-9 of the result's scale, and the stored rounding
@@ -1406,12 +1427,81 @@ def test_attention_backward_one_kernel(d, heads, cap, m, scopes, tail):
             assert float((a.float() - b.float()).norm()) <= 2.0 ** -9 * float(b.float().norm())
 
 
-def one_kernel_share(n, heads, run, size):
-    """Share of the rows and heads whose gradients one kernel computes in run(workspace): only the two kernels keep D, the workspace's
-    first n x heads words."""
-    ws = torch.full((size,), 255, dtype=torch.uint8, device=DEV)
-    run(ws)
-    return float((ws[:n * heads * 4].view(torch.int32) == -1).float().mean())
+@pytest.mark.parametrize("d,heads,cap,scopes,share", [
+    (16, 4, 512, 100, 1),       # one pass
+    (16, 4, 1024, 69, 0.9),     # two, and a rest for the two kernels
+    (32, 3, 1024, 60, 1),
+    (32, 5, 2048, 38, 1),       # four
+])
+def test_attention_backward_one_kernel_stores_elsewhere(d, heads, cap, scopes, share):
+    # gradients in the input order of the points are the same rows, moved; one that takes the forward output's place is the same too (D is read
+    # before anything is stored, and of a rest the two kernels read rows of other scopes or heads); at rows of another order the two kernels do all
+    bk, _, n = hand_layout([[cap // 4] * (4 * scopes - 2) + [cap // 8 + 1]], cap, 4)
+    rng = np.random.default_rng(69)
+    q, k, v, g = (dev(wl.f32_to_bf16_bits(rng.standard_normal((n, heads * d)).astype(np.float32)), torch.bfloat16) for _ in range(4))
+    lse = torch.empty(n, heads, dtype=torch.float32, device=DEV)
+    perm, size = bk.perm.data_ptr(), bwd_workspace_bytes(n, heads)
+    for mode in ("plain", "stride"):
+        out = f3d.bucket_swin_attn(q, k, v, bk, heads, d, mode, lse=lse)
+        want = f3d.bucket_swin_attn_bwd(q, k, v, out, g, lse, bk, heads, d, mode)
+
+        def moved(ws):
+            for a, b in zip(want, f3d.bucket_swin_attn_bwd(q, k, v, out, g, lse, bk, heads, d, mode, original_order=True, workspace=ws)):
+                assert torch.equal(f3d.unpermute(a, bk.perm), b)
+
+        assert abs(one_kernel_share(n, heads, moved, size) - share) <= 0.03
+        for which in range(3):
+            for original_order in (False, True):
+                def in_place(ws):
+                    o = out.clone()
+                    grads = [o if i == which else torch.empty_like(q) for i in range(3)]
+                    rc = f3d.lib().f3d_bucket_swin_attn_bwd(
+                        q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), g.data_ptr(), lse.data_ptr(), perm, bk.offsets.data_ptr(),
+                        bk.scan_bucket_start.data_ptr(), n, bk.n_scans, bk.max_buckets, bk.bucket_cap, bk.scope_buckets, f3d.MODES[mode], 2, 2,
+                        heads, d, 0.0, *(t.data_ptr() for t in grads), perm if original_order else None, ws.data_ptr(), ws.numel(),
+                        torch.cuda.current_stream().cuda_stream)
+                    assert rc == 0
+                    for a, b in zip(grads, want):
+                        if original_order:
+                            b = f3d.unpermute(b, bk.perm)
+                            assert float((a.float() - b.float()).abs().max()) <= 2.0 ** -6 * float(b.float().abs().max())
+                            assert float((a.float() - b.float()).norm()) <= 2.0 ** -9 * float(b.float().norm())
+                        else:
+                            assert torch.equal(a, b)
+
+                assert abs(one_kernel_share(n, heads, in_place, size) - (0 if original_order else share)) <= 0.03
+
+
+@pytest.mark.parametrize("d,heads,share", [(16, 4, 0.86), (32, 3, 1)])
+def test_attention_backward_one_kernel_batches(d, heads, share):
+    # several scans of different length whose last scopes are short: sharp softmaxes, and q and k whose products pass the largest binary32
+    # (see test_attention_products_beyond_binary32_with_finite_scores)
+    sizes = [[256] * 260 + [1], [256] * 187 + [33], [256] * 110 + [188]]
+    bk, ref, n = hand_layout(sizes, 1024, 4)
+    rng = np.random.default_rng(70)
+    q, k, v, g = (wl.f32_to_bf16_bits((rng.standard_normal((n, heads * d)) * s).astype(np.float32)) for s in (3.0, 3.0, 1.0, 1.0))
+    sel = np.zeros(n, dtype=np.uint8)
+    ends = np.cumsum([sum(x) for x in sizes])
+    sel[ends - 1] = 1
+    sel[ends[0]] = sel[ends[1] + 5000] = 1
+    t = [dev(x, torch.bfloat16) for x in (q, k, v, g)]
+    lse = torch.empty(n, heads, dtype=torch.float32, device=DEV)
+    for mode in ("plain", "shift", "stride"):
+        grads = bwd_case(q, k, v, g, bk, ref, heads, d, mode, True, scope_sel=sel)
+        out = f3d.bucket_swin_attn(*t[:3], bk, heads, d, mode, lse=lse)
+
+        def again(ws):
+            for a, b in zip(grads, f3d.bucket_swin_attn_bwd(*t[:3], out, t[3], lse, bk, heads, d, mode, workspace=ws)):
+                assert torch.equal(a, b)
+
+        assert abs(one_kernel_share(n, heads, again, bwd_workspace_bytes(n, heads)) - share) <= 0.03
+        got = []
+        for up, scale in ((0.25, 1.0), (2.0 ** 61, 2.0 ** -126)):   # no gradient so small that it would be flushed
+            out = f3d.bucket_swin_attn(t[0] * up, t[1] * up, t[2], bk, heads, d, mode, softmax_scale=scale, lse=lse)
+            dq, dk, dv = f3d.bucket_swin_attn_bwd(t[0] * up, t[1] * up, t[2], out, t[3], lse, bk, heads, d, mode, softmax_scale=scale)
+            got.append((dq * up, dk * up, dv))
+        for a, b in zip(*got):
+            assert torch.isfinite(a).all() and torch.equal(a, b)
 
 
 @pytest.mark.parametrize("d,heads,cap,tasks,share", [
@@ -1450,9 +1540,8 @@ def test_attention_backward_one_kernel_has_room_in_the_workspace_the_library_ask
     q, k, v, g = (torch.randn(n, heads * 32, device=DEV).to(torch.bfloat16) for _ in range(4))
     lse = torch.empty(n, heads, dtype=torch.float32, device=DEV)
     out = f3d.bucket_swin_attn(q, k, v, bk, heads, 32, "plain", lse=lse)
-    size = ctypes.c_size_t(0)
-    assert f3d.lib().f3d_attn_bwd_workspace_bytes(n, heads, ctypes.byref(size)) == 0
-    got = one_kernel_share(n, heads, lambda ws: f3d.bucket_swin_attn_bwd(q, k, v, out, g, lse, bk, heads, 32, "plain", workspace=ws), size.value)
+    got = one_kernel_share(n, heads, lambda ws: f3d.bucket_swin_attn_bwd(q, k, v, out, g, lse, bk, heads, 32, "plain", workspace=ws),
+                           bwd_workspace_bytes(n, heads))
     assert abs(got - share) <= 0.03, got
 
 
