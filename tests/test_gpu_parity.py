@@ -1516,8 +1516,10 @@ def test_attention_backward_one_kernel_batches(d, heads, share):
     (32, 8, 512, 288, 0),      # ... one pass, a round and a rest
     (16, 8, 512, 288, 0),
     (16, 8, 512, 1720, 0),     # ... at head_dim 16, one pass, more than six rounds
+    (16, 16, 512, 6128, 0),    # ... and up to 24
     (32, 8, 512, 480, 1),      # the one kernel: two rounds of one pass
     (16, 8, 512, 1000, 1),     # ... four rounds at head_dim 16
+    (16, 16, 512, 6144, 1),    # ... 24 rounds
     (16, 8, 832, 216, 1),      # ... a second pass of 320 keys
     (16, 4, 2048, 200, 1),     # ... a round of four passes
     (32, 4, 1024, 936, 1),     # ... the fourth round with 168 tasks
