@@ -43,17 +43,23 @@ struct ScopeCtx {
     SegMap sm;
 };
 
-template <int BM>
+// REST: behind the tasks that one kernel has done already, the same number in the eighth of every XCD. A form of its own: reckoned with in every
+// launch it made the two kernels 0.3 to 0.9 % slower (0.5 us of 60, 2.5 of 500).
+template <int BM, bool REST>
 __device__ __forceinline__ bool scope_of_block(const AttnBwdArgs& b, int blocks_per_scope, int* seg_row0, int* seg_pre, ScopeCtx& c)
 {
     const AttnArgs& a = b.f;
-    // consecutive ids stay on one XCD (block_of_grid), behind the tasks of its eighth that are done already
-    const int xcd = blockIdx.x & 7, u = xcd * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
-    int x = divide(u, blocks_per_scope, a.by_blocks);
-    c.blk = u - x * blocks_per_scope;
-    x += (xcd + 1) * b.done;
-    const int slot = divide(x, a.H, a.by_h);
-    c.head = x - slot * a.H;
+    int slot;
+    if (REST) {
+        const int xcd = blockIdx.x & 7, u = xcd * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);   // as in block_of_grid
+        int x = divide(u, blocks_per_scope, a.by_blocks);
+        c.blk = u - x * blocks_per_scope;
+        x += (xcd + 1) * b.done;
+        slot = divide(x, a.H, a.by_h);
+        c.head = x - slot * a.H;
+    } else {
+        block_of_grid(a, blocks_per_scope, slot, c.head, c.blk);
+    }
     return slot < a.n_slots && scope_of_slot(a, slot, seg_row0, seg_pre, c.ng, c.sm) && c.blk * BM < c.ng;
 }
 
@@ -93,7 +99,7 @@ __global__ __launch_bounds__(256) void k_attn_bwd_d(AttnBwdArgs b)
 //   head_dim 16: the two-term query of the forward kernel with -lse as the starting accumulator (5 MFMAs per tile): there
 //                the remainder is one MFMA, half the issue time of 16 multiply-adds.
 // DF: D is there already (k_attn_bwd_d). AHEAD: the score products run a tile ahead; without, the form for short scopes
-template <int D, int QT, bool DF, bool AHEAD>
+template <int D, int QT, bool DF, bool AHEAD, bool REST = false>
 __global__ __launch_bounds__(256, AHEAD ? 2 : 3) void k_attn_bwd_dq(AttnBwdArgs b)
 {
     using L = BLay<D>;
@@ -108,7 +114,7 @@ __global__ __launch_bounds__(256, AHEAD ? 2 : 3) void k_attn_bwd_dq(AttnBwdArgs 
     int* const seg_row0 = s_row0[wave];
     int* const seg_pre = s_pre[wave];
     ScopeCtx sc;
-    if (!scope_of_block<BM>(b, a.qblocks, seg_row0, seg_pre, sc)) return;
+    if (!scope_of_block<BM, REST>(b, a.qblocks, seg_row0, seg_pre, sc)) return;
     const int ng = sc.ng, head = sc.head;
     const SegMap sm = sc.sm;
     const int l32 = lane & 31, hf = lane >> 5;
@@ -370,7 +376,7 @@ __global__ __launch_bounds__(256, AHEAD ? 2 : 3) void k_attn_bwd_dq(AttnBwdArgs 
 // The vector ALU (16 exponentials, 16 or 32 multiplies and 16 packs per tile and lane) and the matrix core (10 MFMAs at
 // head_dim 32) are both busy, so the loop runs one score tile ahead: the products of the next tile are issued between
 // the exponentials, multiplies and packs of the current one.
-template <int D, int KTW, bool AHEAD>
+template <int D, int KTW, bool AHEAD, bool REST = false>
 __global__ __launch_bounds__(256, AHEAD ? 2 : 3) void k_attn_bwd_dkdv(AttnBwdArgs b)
 {
     using L = BLay<D>;
@@ -386,7 +392,7 @@ __global__ __launch_bounds__(256, AHEAD ? 2 : 3) void k_attn_bwd_dkdv(AttnBwdArg
     int* const seg_row0 = s_row0[wave];
     int* const seg_pre = s_pre[wave];
     ScopeCtx sc;
-    if (!scope_of_block<BM>(b, b.kblocks, seg_row0, seg_pre, sc)) return;
+    if (!scope_of_block<BM, REST>(b, b.kblocks, seg_row0, seg_pre, sc)) return;
     const int ng = sc.ng, head = sc.head;
     const SegMap sm = sc.sm;
     const int l32 = lane & 31, hf = lane >> 5;
@@ -677,7 +683,7 @@ template <int D>
 hipError_t launch_d(const AttnBwdArgs& b, hipStream_t stream)
 {
     const AttnArgs& a = b.f;
-    // with tasks done already: whole ones, the same number on every XCD
+    // with tasks done already: whole ones, the same number on every XCD, of long scopes (one tile per wave, D not in front)
     const long long left = b.done ? b.tasks - 8ll * b.done : (long long)a.n_slots * a.H;
     long long total = left * a.qblocks;
     total = (total + 7) / 8 * 8;
@@ -686,14 +692,16 @@ hipError_t launch_d(const AttnBwdArgs& b, hipStream_t stream)
         if (b.tiles == 2) k_attn_bwd_dq<D, 2, true, true><<<(unsigned)total, 256, 0, stream>>>(b);
         else k_attn_bwd_dq<D, 1, true, true><<<(unsigned)total, 256, 0, stream>>>(b);
     } else if (total > 0) {
-        if (b.tiles == 2) k_attn_bwd_dq<D, 2, false, true><<<(unsigned)total, 256, 0, stream>>>(b);
+        if (b.done) k_attn_bwd_dq<D, 1, false, true, true><<<(unsigned)total, 256, 0, stream>>>(b);
+        else if (b.tiles == 2) k_attn_bwd_dq<D, 2, false, true><<<(unsigned)total, 256, 0, stream>>>(b);
         else if (b.ahead) k_attn_bwd_dq<D, 1, false, true><<<(unsigned)total, 256, 0, stream>>>(b);
         else k_attn_bwd_dq<D, 1, false, false><<<(unsigned)total, 256, 0, stream>>>(b);
     }
     total = left * b.kblocks;
     total = (total + 7) / 8 * 8;
     if (total > 0) {
-        if (b.tiles == 2) k_attn_bwd_dkdv<D, 2, true><<<(unsigned)total, 256, 0, stream>>>(b);
+        if (b.done) k_attn_bwd_dkdv<D, 1, true, true><<<(unsigned)total, 256, 0, stream>>>(b);
+        else if (b.tiles == 2) k_attn_bwd_dkdv<D, 2, true><<<(unsigned)total, 256, 0, stream>>>(b);
         else if (b.ahead) k_attn_bwd_dkdv<D, 1, true><<<(unsigned)total, 256, 0, stream>>>(b);
         else k_attn_bwd_dkdv<D, 1, false><<<(unsigned)total, 256, 0, stream>>>(b);
     }
