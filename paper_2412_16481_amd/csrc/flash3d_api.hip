@@ -572,17 +572,18 @@ int f3d_bucket_swin_attn_bwd(const void* q, const void* k, const void* v, const 
     //   333 / 386; 1536 rows 167 / 176, 206 / 226; but 200 tasks of 2048 373 / 311, 455 / 396);
     //   at head_dim 32 one to three rounds and a rest of between a quarter and five eighths of one, which costs them half a round and this one a
     //   whole round or two launches (344 tasks of 1536 rows 399 / 419, 408 of 2048 754 / 791, 904 of 1024 502 / 524; but 328 of 1024 204 / 192);
-    //   scopes of one pass, where a task's set-up weighs most, but for up to two rounds (head_dim 16: six) with no rest and, at head_dim 16, 24
-    //   rounds and more (tasks of 512 rows, 832 of them 139 / 142, 1504 252 / 270; but 216 56 / 39, 480 88 / 78; head_dim 16, 344 52 / 54, 816
-    //   94 / 100, 3168 406 / 434; but 6280 898 / 836, 14080 1946 / 1809).
-    // Scope slots that short scans leave empty fill no compute unit, and all but one of eight XCDs have their full share of tasks still: with
-    // more than a tenth of them empty, an eighth in a single round, the two kernels keep the launch (8 scans of 3000 points, 167 / 143 /
-    // 117; 8 of 27360 points x 3 heads x 16, scopes of 1920, 566 / 588 with 40 of 400 tasks empty).
+    //   scopes of one pass, where a task's set-up weighs most, but for up to two rounds (head_dim 16: six) with no rest and, at head_dim 16, one
+    //   round and a rest of a sixteenth to a quarter, and 24 rounds and more (tasks of 512 rows, 832 of them 139 / 142, 1504 252 / 270; but
+    //   216 56 / 39, 480 88 / 78; head_dim 16, 264 39 / 50, 344 52 / 54, 816 94 / 100, 3168 406 / 434; but 320 61 / 55, 6280 898 / 836, 14080
+    //   1946 / 1809);
+    //   a round that is a little more than half full where more than a tenth of the scope slots, which short scans leave empty, fill no compute
+    //   unit (8 of 27360 points x 3 heads x 16, scopes of 1920, 40 of 400 tasks empty: 566 / 588).
+    // With more than an eighth of them empty they keep every launch (8 scans of 3000 points, 167 / 143 / 117; in a single round 8 more are let pass).
     bool elsewhere = false;
     for (const void* grad : {dq, dk, dv})
         elsewhere = elsewhere || (at < (uintptr_t)grad + size && (uintptr_t)grad < at + size && (at != (uintptr_t)grad || grad_perm));
     const long long tasks = (slots * heads + 7) / 8 * 8, filled = (long long)scopes * n_scans * heads;
-    if (b.ahead && !elsewhere && bucket_cap <= f3d::ATTN_BWD_ONE_ROWS && tasks <= 2000000000ll && tasks <= filled + (tasks <= BWD_CUS ? filled / 8 + 8 : filled / 10)) {
+    if (b.ahead && !elsewhere && bucket_cap <= f3d::ATTN_BWD_ONE_ROWS && tasks <= 2000000000ll && tasks <= filled + filled / 8 + (tasks <= BWD_CUS ? 8 : 0)) {
         constexpr int CUS = BWD_CUS, KB = 64 * f3d::ATTN_BWD_ONE_WAVES;
         const int passes = (bucket_cap + KB - 1) / KB;
         const bool one_pass = passes == 1;
@@ -591,7 +592,12 @@ int f3d_bucket_swin_attn_bwd(const void* q, const void* k, const void* v, const 
         if ((bucket_cap - 1) % KB < KB / 2) done = 0;
         if (passes > 2 && tasks <= CUS * 3 / 4) done = 0;
         if (head_dim == 32 && !one_pass && tasks > CUS && tasks < 4 * CUS && left > CUS / 4 && left <= CUS * 5 / 8) done = 0;
-        if (one_pass && (done < tasks || tasks > (head_dim == 32 ? 2 : 6) * CUS) && (head_dim == 32 || tasks < 24 * CUS)) done = 0;
+        if (!one_pass && tasks > CUS && tasks > filled + filled / 10 && left >= CUS / 2 && left <= CUS * 11 / 16) done = 0;
+        if (one_pass) {
+            const bool few = done == tasks && tasks <= (head_dim == 32 ? 2 : 6) * CUS;
+            const bool rest = head_dim == 16 && done == CUS && left >= CUS / 16 && left <= CUS / 4;
+            if (!few && !rest && (head_dim == 32 || tasks < 24 * CUS)) done = 0;
+        }
         const int grid = (int)(one_pass || done < CUS ? done : CUS);
         // a workspace with no room for the sums between passes: the two kernels need none
         if (done > 0 && (one_pass || (workspace_bytes - need) / 4 >= (size_t)grid * bucket_cap * head_dim)) {

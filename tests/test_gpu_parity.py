@@ -1514,11 +1514,14 @@ def test_attention_backward_one_kernel_batches(d, heads, share):
     (32, 4, 1024, 928, 0),     # ... at head_dim 32, three rounds and a rest of 160
     (32, 8, 512, 600, 0),      # ... at head_dim 32, one pass, more than two rounds
     (32, 8, 512, 288, 0),      # ... one pass, a round and a rest
-    (16, 8, 512, 288, 0),
+    (16, 8, 512, 264, 0),      # ... at head_dim 16 of less than 16
+    (16, 8, 512, 328, 0),      # ... and of more than 64
     (16, 8, 512, 1720, 0),     # ... at head_dim 16, one pass, more than six rounds
     (16, 16, 512, 6128, 0),    # ... and up to 24
     (32, 8, 512, 480, 1),      # the one kernel: two rounds of one pass
     (16, 8, 512, 1000, 1),     # ... four rounds at head_dim 16
+    (16, 8, 512, 272, 0.94),   # ... a round, the rest of 16 by the two
+    (16, 8, 512, 320, 0.8),    # ... of 64
     (16, 16, 512, 6144, 1),    # ... 24 rounds
     (16, 8, 832, 216, 1),      # ... a second pass of 320 keys
     (16, 4, 2048, 200, 1),     # ... a round of four passes
