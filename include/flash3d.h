@@ -247,6 +247,10 @@ int f3d_bucket_swin_attn_f16(const void *q, const void *k, const void *v, const 
  *               rounded up to 256 bytes, are taken too, by a slower form where scopes are longer than 512 rows
  * In place: one of dq, dk, dv may be out (which is then lost); they overlap nothing else.
  * Arithmetic: bf16 operands, fp32 accumulation; P and dS are rounded to bf16 before the second products.
+ * Bits: the same call gives the same bits every time. There is more than one form of the kernels, alike in accuracy but not in the
+ * order of the fp32 sums nor in how the scale, lse and D enter, and what a call takes, or parts of it, follows from n, n_scans,
+ * max_buckets, bucket_cap, scope_buckets, mode, stride, heads, head_dim, workspace_bytes, and whether a gradient takes out's place
+ * with grad_perm. So a scan's gradients can differ in their last bits with the batch it is in and with the size of the workspace.
  */
 int f3d_attn_bwd_workspace_bytes(int64_t n, int32_t heads, size_t *out_bytes);
 

@@ -15,8 +15,8 @@
 //                    a lane owns 16 queries of ONE key: P and dS, packed to bf16, are the B operands of
 //                    dV^T += dO^T P and dK^T += Q^T dS.
 // Both recompute the exponentials. k_attn_bwd_one (attn_bwd_one.hip) computes each score once and takes most launches of long scopes;
-// these two take short scopes, small launches, scopes of more than 2048 rows, gradients at other rows of the forward output, and what that
-// kernel leaves of a last round of tasks.
+// these two take short scopes, small launches, scopes of more than 2048 rows, gradients at other rows of the forward output, what that
+// kernel leaves of a last round of tasks, and the launches that they are faster at (the rule and its figures: f3d_bucket_swin_attn_bwd).
 //
 // Bound: power and issue. On 914601 points x 8 heads x 32 (scopes of 1024) the dK/dV kernel kept the matrix core busy
 // 61 % and the vector ALU 58 % of the cycles while the clock fell to 1.69 GHz, and ran 1.1 PFLOP/s of MFMAs (an 8192^3

@@ -14,7 +14,7 @@
 // What comes per step (32 queries) beside it is spread so that of a SIMD's two waves one goes on computing: the upper half of the waves
 // loads the stages in the middle of a step, the lower half adds up dQ behind its barrier (both behind the barrier: 914601 points x 8 heads x 32
 // 5.30 ms for the whole training pass instead of 5.11). MFMAs stand about 28 cycles of vector work apart (in the compiler's order 5.14 ms
-// instead of 4.99).
+// instead of 4.99; each pair from one card, cards differ by 5 %).
 // Backward pass, us, two kernels / this one, scopes of 1024: 200000 points x 4 heads x 16 378 / 326, x 16 heads 1453 / 1184; 401111 x 8 x 16
 // 1442 / 1172 (scopes of 512 833 / 740, of 2048 2711 / 2428); 300000 x 8 x 32 1385 / 1186, 60000 x 8 x 32 277 / 243. Workgroups of four
 // waves, two per compute unit, at head_dim 16: 1181 for the 1172, 3135 for the 2439 of scopes of 2048 (twice the passes).
@@ -44,7 +44,8 @@ struct OLay {
     static constexpr int NBLK = 2 * BUF / 1024;       // 1 KB blocks of a stage: Q, then dO
     static constexpr int LPW = NBLK / (W / 2);        // of which a wave of the upper half loads so many
     static constexpr int KB = 64 * W;                 // keys per pass over the queries
-    // one wave's share of the dQ of a query tile: binary32, rows 16 bytes apart from each other's banks (the last needs no gap)
+    // One wave's share of the dQ of a query tile: binary32, rows 16 bytes apart from each other's banks (the last needs no gap). Of the writes,
+    // a piece of every row, no two lanes meet; of the reads in add_up, whole rows, the first and the last row of sixteen lanes meet in one piece.
     static constexpr int PROW = D * 4 + 16, PART = 32 * PROW - 16;
     static constexpr int DS = 2 * 2048;               // a wave's two dS tiles
     static constexpr int AT_G = NBUF * BUF, AT_PART = 2 * NBUF * BUF, AT_DS = AT_PART + 2 * W * PART, AT_X = AT_DS + W * DS;

@@ -641,7 +641,9 @@ __device__ __forceinline__ const uint8_t* rounds_of_two(int nleft, int nopen, in
                 later[e] = 0;
             }
             lds_barrier();
-            const int lowest = *w;                // of the others' too: under way with the reads of the search, not in front of them
+            // Of the others' too: under way with the reads of the search, not in front of them. A lane that contends for nothing has some e up
+            // to kp: at most one word past `win`, in what lies behind it in LDS, and looks at nothing it read.
+            const int lowest = *w;
             unsigned int e_next = 0;
             const bool more = k < 31 && search(near_tag, later, e_next);   // a row looks a round ahead, not across a closing up
             if (sent && lowest == tid) {
